@@ -301,15 +301,18 @@ int oases_op_gemm(int op, int epi, int M, int N, int K, const void *A, int lda, 
  * any M, N the GEMM accepts; no forward SwiGLU epilogue; also over 2 or 4 k slices of whole stages, 202128256 and
  * 204128256, K % (64 * slices) == 0); the 256x256 kernel takes one slice only.  W = 3 names the eight-wave forms of
  * the same tiles (two waves per SIMD that alternate between loading and multiplying): 301256256, 301128256, 302128256,
- * 304128256, on the shapes of their W = 2 counterparts; 301128256 gives bit for bit what 201128256 gives.  The W = 2 and
- * W = 3 kernels address an operand with 32-bit byte offsets: oases_op_gemm launches them only if rows x leading
+ * 304128256, on the shapes of their W = 2 counterparts; 301128256 gives bit for bit what 201128256 gives.  W = 4 names the
+ * small-tile kernels 64x64 and 64x128 (401064064, 401064128; direct-to-LDS loads, waves split k, any shape the GEMM
+ * accepts, up to 16 slices of whole 64-wide stages; the forward SwiGLU epilogue on 64x128 only).  The W >= 2
+ * kernels address an operand with 32-bit byte offsets: oases_op_gemm launches them only if rows x leading
  * dimension x 2 bytes of A and of B stay under 2 GiB (the staged kernel of the same tile otherwise), and
  * oases_op_gemm_forced returns EINVAL for them on larger operands.
  * Host only; used to group per-operator timings by kernel. */
 int oases_op_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace_bytes);
 /* oases_op_gemm on the instantiation `variant` names (encoding above) instead of the one the library would choose:
  * for tests and tuning sweeps.  EINVAL if no such instantiation exists (block tiles 256x256, 128x256, 256x128,
- * 128x128; W = 1 only with the rectangular ones; W = 2, 3 only as x01256256, x01128256, x02128256 or x04128256 on shapes they fit; 1..8 slices), if the slices do not fit K (every slice needs at least
+ * 128x128; W = 1 only with the rectangular ones; W = 2, 3 only as x01256256, x01128256, x02128256 or x04128256 on shapes they fit, W = 4 as 4SS064064 or 4SS064128; 1..8
+ * slices, W = 4: 1..16), if the slices do not fit K (every slice needs at least
  * one k column) or if the workspace is smaller than slices*M*N*4 bytes.  Results of different variants differ only
  * by the fp32 summation order. */
 int oases_op_gemm_forced(int variant, int op, int epi, int M, int N, int K, const void *A, int lda,
@@ -327,7 +330,8 @@ int oases_op_gemm_tn_pair(int K, int M0, int N0, const void *A0, int lda0, const
                           int ldc0, int M1, int N1, const void *A1, int lda1, const void *B1, int ldb1, void *C1,
                           int ldc1, void *stream);
 /* Host only: 1 if the library issues two such weight gradients as one launch (both fit whole 128x256 tiles, more than 128
- * tiles together, and fewer rounds of 256 workgroups together than apart), else 0. */
+ * tiles together, fewer rounds of 256 workgroups together than apart, and not so few rows K that the small-tile kernel is
+ * chosen for both), else 0. */
 int oases_op_gemm_tn_pair_wins(int K, int M0, int N0, int M1, int N1);
 /* Bytes of split-K scratch that oases_forward / oases_backward set aside inside the workspace. */
 size_t oases_gemm_workspace_bytes(const oases_handle *h);

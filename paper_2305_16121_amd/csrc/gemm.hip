@@ -135,6 +135,62 @@ __device__ __forceinline__ float silu_grad_f(float z) { const float sg = fast_si
 // instruction-group hints for the machine scheduler (kinds: 0x8 MFMA, 0x20 VMEM read, 0x100 LDS read, 0x200 LDS write)
 #define SGB(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
 
+// What the epilogue of four consecutive elements C[row][col .. col+3] reads besides the accumulator: bias (f), the old value
+// of C (f), pre-activations (a; SwiGLU gradient: gate a, up b).
+struct EpiOperands {
+  f32x4 f;
+  u32x2 a, b;
+};
+template <int EPI>
+__device__ __forceinline__ EpiOperands epi_load(const GemmArgs& g, int row, int col) {
+  EpiOperands o;
+  if constexpr (EPI == EPI_BIAS_BF16 || EPI == EPI_BIAS_GELU) o.f = *reinterpret_cast<const f32x4*>(g.bias + col);
+  if constexpr (EPI == EPI_ACC_F32) o.f = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.C) + (size_t)row * g.ldc + col);
+  if constexpr (EPI == EPI_DGELU) o.a = *reinterpret_cast<const u32x2*>(g.aux + (size_t)row * g.ldaux + col);
+  if constexpr (EPI == EPI_DSWIGLU) {
+    // gate and up pre-activations of 32 columns sit in blocks side by side in aux ([gate 32 | up 32] per block)
+    const uint16_t* p = g.aux + (size_t)row * g.ldaux + (size_t)col + (col & ~31);
+    o.a = *reinterpret_cast<const u32x2*>(p);
+    o.b = *reinterpret_cast<const u32x2*>(p + 32);
+  }
+  return o;
+}
+template <int EPI>
+__device__ __forceinline__ void epi_apply(const GemmArgs& g, int row, int col, f32x4 v, const EpiOperands& o) {
+  const size_t at = (size_t)row * g.ldc + col;
+  if constexpr (EPI == EPI_F32 || EPI == EPI_ACC_F32) {
+    if constexpr (EPI == EPI_ACC_F32) v = o.f + v;
+    *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + at) = v;
+  } else if constexpr (EPI == EPI_DSWIGLU) {
+    // the accumulator holds dF for 4 columns of f; the gradients of gate and up go to C in the block layout of aux
+    float dg[4], du[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float ge = bf16_bits_to_f32((e & 1) ? o.a[e >> 1] >> 16 : o.a[e >> 1] & 0xffffu);
+      const float ue = bf16_bits_to_f32((e & 1) ? o.b[e >> 1] >> 16 : o.b[e >> 1] & 0xffffu);
+      dg[e] = v[e] * ue * silu_grad_f(ge);
+      du[e] = v[e] * silu_f(ge);
+    }
+    uint16_t* cp = reinterpret_cast<uint16_t*>(g.C) + at + (col & ~31);
+    *reinterpret_cast<u32x2*>(cp) = u32x2{pack_bf16x2(dg[0], dg[1]), pack_bf16x2(dg[2], dg[3])};
+    *reinterpret_cast<u32x2*>(cp + 32) = u32x2{pack_bf16x2(du[0], du[1]), pack_bf16x2(du[2], du[3])};
+  } else {
+    if constexpr (EPI == EPI_BIAS_BF16 || EPI == EPI_BIAS_GELU) v += o.f;
+    if constexpr (EPI == EPI_BIAS_GELU) {
+      *reinterpret_cast<u32x2*>(g.aux + (size_t)row * g.ldaux + col) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+#pragma unroll
+      for (int e = 0; e < 4; e++) v[e] = gelu_tanh(v[e]);
+    }
+    if constexpr (EPI == EPI_DGELU) {
+      v[0] *= gelu_tanh_grad(bf16_bits_to_f32(o.a[0] & 0xffffu));
+      v[1] *= gelu_tanh_grad(bf16_bits_to_f32(o.a[0] >> 16));
+      v[2] *= gelu_tanh_grad(bf16_bits_to_f32(o.a[1] & 0xffffu));
+      v[3] *= gelu_tanh_grad(bf16_bits_to_f32(o.a[1] >> 16));
+    }
+    *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + at) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+  }
+}
+
 // Epilogue of one 32 x 32 accumulator tile whose first element is C[row0][col0].  Transposed accumulator (every epilogue
 // but the plain fp32 store): element e is C[row][col + (e&3)] with row = row0 + (lane & 31), col = col0 + 8 (e>>2) +
 // 4 (lane>>5), so a lane owns 4 consecutive columns.
@@ -160,67 +216,32 @@ __device__ __forceinline__ void epilogue_tile(const GemmArgs& g, int row0, int c
   for (int q = 0; q < 4; q++) {
     const int col = col0 + 8 * q + 4 * (lane >> 5);
     if (!FULL && col >= g.N) continue;
-    f32x4 v = {a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
-    const size_t o = (size_t)row * g.ldc + col;
-    if (EPI == EPI_DSWIGLU) {
-      // the accumulator holds dF for 4 columns of f; gate and up pre-activations of those columns sit in 32-column
-      // blocks side by side in aux ([gate 32 | up 32] per block), and so do their gradients in C
-      const size_t cg = (size_t)col + (col & ~31);
-      const u32x2 gt = *reinterpret_cast<const u32x2*>(g.aux + (size_t)row * g.ldaux + cg);
-      const u32x2 up = *reinterpret_cast<const u32x2*>(g.aux + (size_t)row * g.ldaux + cg + 32);
-      float dg[4], du[4];
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        const float ge = bf16_bits_to_f32((e & 1) ? gt[e >> 1] >> 16 : gt[e >> 1] & 0xffffu);
-        const float ue = bf16_bits_to_f32((e & 1) ? up[e >> 1] >> 16 : up[e >> 1] & 0xffffu);
-        dg[e] = v[e] * ue * silu_grad_f(ge);
-        du[e] = v[e] * silu_f(ge);
-      }
-      uint16_t* cp = reinterpret_cast<uint16_t*>(g.C) + (size_t)row * g.ldc + cg;
-      *reinterpret_cast<u32x2*>(cp) = u32x2{pack_bf16x2(dg[0], dg[1]), pack_bf16x2(dg[2], dg[3])};
-      *reinterpret_cast<u32x2*>(cp + 32) = u32x2{pack_bf16x2(du[0], du[1]), pack_bf16x2(du[2], du[3])};
-    } else if (EPI == EPI_F32) {
-      *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + o) = v;
-    } else if (EPI == EPI_ACC_F32) {
-      f32x4* p = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + o);
-      *p = *p + v;
-    } else {
-      uint16_t* cp = reinterpret_cast<uint16_t*>(g.C) + o;
-      if (EPI == EPI_BIAS_BF16 || EPI == EPI_BIAS_GELU) v += *reinterpret_cast<const f32x4*>(g.bias + col);
-      if (EPI == EPI_BIAS_GELU) {
-        *reinterpret_cast<u32x2*>(g.aux + (size_t)row * g.ldaux + col) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-#pragma unroll
-        for (int e = 0; e < 4; e++) v[e] = gelu_tanh(v[e]);
-      } else if (EPI == EPI_DGELU) {
-        u32x2 x = *reinterpret_cast<const u32x2*>(g.aux + (size_t)row * g.ldaux + col);
-        v[0] *= gelu_tanh_grad(bf16_bits_to_f32(x[0] & 0xffffu));
-        v[1] *= gelu_tanh_grad(bf16_bits_to_f32(x[0] >> 16));
-        v[2] *= gelu_tanh_grad(bf16_bits_to_f32(x[1] & 0xffffu));
-        v[3] *= gelu_tanh_grad(bf16_bits_to_f32(x[1] >> 16));
-      }
-      *reinterpret_cast<u32x2*>(cp) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-    }
+    epi_apply<EPI>(g, row, col, f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]}, epi_load<EPI>(g, row, col));
   }
 }
 
 // SwiGLU: two neighbouring accumulator tiles, gate (first column col0 of the interleaved [gate 32 | up 32] layout) and up,
 // hold the same 32 columns of f, element for element
+// one lane's part: gate columns cg .. cg+3 of the interleaved [gate 32 | up 32] layout, columns cf .. cf+3 of f
+__device__ __forceinline__ void epi_swiglu(const GemmArgs& g, int row, int cg, int cf, const f32x4& gate, const f32x4& up) {
+  uint16_t* ap = g.aux + (size_t)row * g.ldaux + cg;
+  *reinterpret_cast<u32x2*>(ap) = u32x2{pack_bf16x2(gate[0], gate[1]), pack_bf16x2(gate[2], gate[3])};
+  *reinterpret_cast<u32x2*>(ap + 32) = u32x2{pack_bf16x2(up[0], up[1]), pack_bf16x2(up[2], up[3])};
+  float f[4];
+#pragma unroll
+  for (int e = 0; e < 4; e++) f[e] = silu_f(gate[e]) * up[e];
+  *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + (size_t)row * g.ldc + cf) = u32x2{pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3])};
+}
 template <bool FULL>
 __device__ __forceinline__ void epilogue_tile_swiglu(const GemmArgs& g, int row0, int col0, int lane, const f32x16& ag, const f32x16& au) {
   const int row = row0 + (lane & 31);
   if (!FULL && row >= g.M) return;
 #pragma unroll
   for (int q = 0; q < 4; q++) {
-    const int cg = col0 + 8 * q + 4 * (lane >> 5);  // gate column in the interleaved [gate 32 | up 32] layout
-    if (!FULL && cg >= g.N) continue;
-    const int cf = col0 / 2 + 8 * q + 4 * (lane >> 5);
-    uint16_t* ap = g.aux + (size_t)row * g.ldaux + cg;
-    *reinterpret_cast<u32x2*>(ap) = u32x2{pack_bf16x2(ag[4 * q], ag[4 * q + 1]), pack_bf16x2(ag[4 * q + 2], ag[4 * q + 3])};
-    *reinterpret_cast<u32x2*>(ap + 32) = u32x2{pack_bf16x2(au[4 * q], au[4 * q + 1]), pack_bf16x2(au[4 * q + 2], au[4 * q + 3])};
-    float f[4];
-#pragma unroll
-    for (int e = 0; e < 4; e++) f[e] = silu_f(ag[4 * q + e]) * au[4 * q + e];
-    *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + (size_t)row * g.ldc + cf) = u32x2{pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3])};
+    const int c = 8 * q + 4 * (lane >> 5);
+    if (!FULL && col0 + c >= g.N) continue;
+    epi_swiglu(g, row, col0 + c, col0 / 2 + c, f32x4{ag[4 * q], ag[4 * q + 1], ag[4 * q + 2], ag[4 * q + 3]},
+               f32x4{au[4 * q], au[4 * q + 1], au[4 * q + 2], au[4 * q + 3]});
   }
 }
 
@@ -1203,6 +1224,266 @@ __global__ __launch_bounds__(512) void gemm_pp_pair_kernel(GemmArgs g0, GemmArgs
   else pp_tile<128, false, false, EPI_ACC_F32, true>(g1, blockIdx.x - first, lds);
 }
 
+// =================================================================================================
+// Small tiles: 64 x 64 (TN = 1) and 64 x 128 (TN = 2), for launches that the large tiles would leave short of workgroups or
+// that are a chain of memory latencies rather than MFMA work.  Eight waves: 2 x 2 parts of 32 x 32 TN elements, times two
+// k halves -- a wave multiplies two of the four 16-wide k steps of a 64-wide stage, and the two partial sums of a part
+// meet once, through LDS, after the loop (a k half has its own accumulator, so the order of the additions is the same for
+// every shape).  Tiles come by direct-to-LDS buffer loads into NS stages, so NS-1 tiles are in flight: with K of a few
+// hundred the whole k extent is requested before the first MFMA, and the launch pays one memory latency instead of one
+// per tile.  The stages take 80 KB (64 x 64, five) and 72 KB (64 x 128, three): two workgroups share a CU.  What the epilogue reads (bias, old C, pre-activations) is
+// requested first of all and has arrived by the time it is needed.  One barrier per tile:
+//   tile kt has landed when at most PER x (younger tiles in flight) of the wave's loads are outstanding; the barrier makes
+//   all waves' parts of it visible and also says that every wave is done with tile kt-1 (its fragments were waited for
+//   before its MFMAs), whose stage then takes tile kt+NS-1.
+// Any M, N, K that are multiples of 8: rows and columns beyond an operand are fetched from valid memory and never stored;
+// k beyond K in the last tile is fetched from k = 0 and replaced by zeros in the fragments.
+// Layouts of the operand tiles: k-major [R][64] as in the 128 x 256 kernel; row-indexed [64][R] with chunk c of k row kr at
+// slot c ^ 4 (kr%4) for R = 128 (256-byte k rows: four of them share all banks) and c ^ 4 ((kr/2)%2) for R = 64 (128-byte k
+// rows: every second one does).
+//   What bounds it: LDS bandwidth when the chip is full (48 KB resp. 72 KB read and written per stage, 0.16 / 0.24 us at 128
+// bytes per clock; measured 0.22 / 0.33 us per stage and workgroup), one memory latency plus some 3 us of launch and drain
+// otherwise.  Measured in microseconds, register-staged kernels before -> this one: NN bias 256 x 768 x 512 9.5 -> 4.4,
+// NT dGeLU 256 x 1024 x 512 12.5 -> 4.8, NN bias+GeLU 200 x 2048 x 1024 18.6 -> 6.8, NT dSwiGLU 1024 x 704 x 1024 21.4 -> 8.1,
+// NN bias+GeLU 2048 x 1024 x 1024 18.0 -> 11.2, TN 1024 x 512 x 512 10.0 -> 4.8, NT bf16 4096 x 512 x 2048 22.9 -> 13.9, NN fp32
+// 64 x 12288 x 1536 23.1 -> 9.2.  Five stages against three or nine for 64 x 64 and three against six for 64 x 128: within
+// 5 % of each other or better; 128 x 128 tiles on the same scheme (four stages): slower on every shape that these two win.
+// =================================================================================================
+constexpr int BKS = 64;
+template <int R>
+__device__ __forceinline__ int st_swizzle(int kr) { return R == 64 ? 4 * ((kr >> 1) & 1) : 4 * (kr & 3); }
+// byte offset from the operand of the 16 bytes that a lane fetches in DMA instruction q of a tile that starts at row r0
+// (k tile 0), and the lane's k within the tile
+template <bool KC, int R>
+__device__ __forceinline__ uint32_t st_src(int ld, int r0, int q, int lane, int extent, int* k) {
+  if (KC) {
+    const int row = 8 * q + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
+    *k = chunk * 8;
+    return ((uint32_t)min(r0 + row, extent - 1) * ld + chunk * 8) * 2u;
+  }
+  constexpr int CPR = R / 8, KPI = 64 / CPR;
+  const int kr = KPI * q + lane / CPR, cc = (lane % CPR) ^ st_swizzle<R>(kr);
+  int col = r0 + cc * 8;
+  if (col >= extent) col = 0;
+  *k = kr;
+  return ((uint32_t)kr * ld + col) * 2u;
+}
+// fragments of k step KK (of the wave's two) of T 32-row parts
+template <bool KC, int R, int T, int KK>
+__device__ __forceinline__ void st_read_frags(u32x4 (&f)[T], uint32_t base, const uint32_t* off) {
+  if constexpr (KC) {
+    f[0] = lds_read_b128<0>(base + off[KK]);
+    if constexpr (T > 1) f[1] = lds_read_b128<4096>(base + off[KK]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < T; i++) {
+      const u32x2 lo = lds_read_tr16_b64<KK * 16 * 2 * R>(base + off[i]);
+      const u32x2 hi = lds_read_tr16_b64<KK * 16 * 2 * R + 4 * 2 * R>(base + off[i]);
+      f[i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+    }
+  }
+}
+template <bool KC, int R, int T>
+__device__ __forceinline__ void st_frag_offsets(uint32_t (&off)[2], int R0, int wk, int lane) {
+  if (KC) {  // off[kk]: k step kk of the wave's half (fragment i adds 32 rows = 4096 bytes)
+#pragma unroll
+    for (int kk = 0; kk < 2; kk++) {
+      const int row = R0 + (lane & 31), chunk = 4 * wk + 2 * kk + (lane >> 5);
+      off[kk] = (uint32_t)(row * 128 + 16 * (chunk ^ ((row >> 1) & 7)));
+    }
+  } else {  // off[i]: fragment i
+    const int krow = 32 * wk + 8 * (lane >> 5) + ((lane & 15) >> 2);
+#pragma unroll
+    for (int i = 0; i < T; i++) {
+      const int col = R0 + 32 * i + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+      off[i] = (uint32_t)(krow * (2 * R) + (((col >> 3) ^ st_swizzle<R>(krow)) << 4) + (col & 7) * 2);
+    }
+  }
+}
+__device__ __forceinline__ void st_wait_frags(u32x4 (&a)[2][1], u32x4 (&b)[2][1]) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0][0]), "+v"(a[1][0]), "+v"(b[0][0]), "+v"(b[1][0]));
+}
+__device__ __forceinline__ void st_wait_frags(u32x4 (&a)[2][1], u32x4 (&b)[2][2]) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0][0]), "+v"(a[1][0]), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
+}
+
+template <int TN, int NS, bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(512) void gemm_st_kernel(GemmArgs g) {  // g: by value, adjusted per k slice
+  constexpr int BM = 64, BN = 64 * TN;
+  constexpr int kOpA = BM * BKS * 2, kStage = (BM + BN) * BKS * 2;
+  constexpr int PER_A = 1, PER_B = TN, PER = PER_A + PER_B;  // direct-to-LDS instructions of a wave per stage
+  constexpr int kExchange = 8 * TN * 2 * 64 * 16;                       // half of every wave's accumulator
+  static_assert(EPI != EPI_SWIGLU || TN == 2, "gate and up columns of a block must belong to one wave");
+  __shared__ __attribute__((aligned(1024))) char lds[NS * kStage > kExchange ? NS * kStage : kExchange];
+  int pid = blockIdx.x;
+  if (g.ksplit > 1) {  // this workgroup's k range (k_per: a whole number of stages) and fp32 partial-result plane
+    const int T = g.tiles_m * g.tiles_n, slice = pid / T, k0 = slice * g.k_per;
+    pid -= slice * T;
+    g.A += A_KC ? (size_t)k0 : (size_t)k0 * g.lda;
+    g.B += B_KC ? (size_t)k0 : (size_t)k0 * g.ldb;
+    g.K = min(g.K - k0, g.k_per);
+    g.C = reinterpret_cast<float*>(g.C) + (size_t)slice * g.M * g.ldc;
+  }
+  int tile_m, tile_n;
+  tile_of_workgroup(pid, g.tiles_m, g.tiles_n, tile_m, tile_n);
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+  const int row0 = m0 + wm * 32, col0 = n0 + wn * 32 * TN;
+  const int nk = (g.K + BKS - 1) / BKS, ktail = g.K % BKS;
+
+  // operands of the epilogue.  A wave finishes quarters 2 wk and 2 wk + 1 of its accumulator tiles (quarter q of a
+  // transposed accumulator: columns 8 q + 4 (lane/32) ..+3 of row lane%32)
+  EpiOperands pre[TN][2];
+  if constexpr (EPI != EPI_F32 && EPI != EPI_SWIGLU) {
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int q = 0; q < 2; q++)
+        pre[j][q] = epi_load<EPI>(g, min(row0 + (lane & 31), g.M - 1), min(col0 + 32 * j + 8 * (2 * wk + q) + 4 * (lane >> 5), g.N - 4));
+  }
+
+  const __amdgpu_buffer_rsrc_t rsA = operand_rsrc(g.A), rsB = operand_rsrc(g.B);
+  uint32_t srcB[PER_B];
+  int kA, kB[PER_B];
+  const uint32_t srcA = st_src<A_KC, BM>(g.lda, m0, wave, lane, g.M, &kA);
+#pragma unroll
+  for (int j = 0; j < PER_B; j++) srcB[j] = st_src<B_KC, BN>(g.ldb, n0, PER_B * wave + j, lane, g.N, &kB[j]);
+  const uint32_t unitA = A_KC ? 2u : 2u * g.lda, unitB = B_KC ? 2u : 2u * g.ldb;  // one k further
+  auto issue = [&](int t, int stage) {
+    char* st = lds + stage * kStage;
+    const uint32_t tA = (uint32_t)t * BKS * unitA, tB = (uint32_t)t * BKS * unitB;
+    if (ktail && t == nk - 1) {  // k >= K: fetched from k = 0 of the same row / column (valid memory, zeroed later)
+      dma16(rsA, kA < ktail ? srcA + tA : srcA - kA * unitA, 0, st + wave * 1024);
+#pragma unroll
+      for (int j = 0; j < PER_B; j++) dma16(rsB, kB[j] < ktail ? srcB[j] + tB : srcB[j] - kB[j] * unitB, 0, st + kOpA + (PER_B * wave + j) * 1024);
+    } else {
+      dma16(rsA, srcA, tA, st + wave * 1024);
+#pragma unroll
+      for (int j = 0; j < PER_B; j++) dma16(rsB, srcB[j], tB, st + kOpA + (PER_B * wave + j) * 1024);
+    }
+  };
+  uint32_t offA[2], offB[2];
+  st_frag_offsets<A_KC, BM, 1>(offA, wm * 32, wk, lane);
+  st_frag_offsets<B_KC, BN, TN>(offB, wn * 32 * TN, wk, lane);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(OASES_LDS char*)lds;
+
+  f32x16 acc[TN];
+#pragma unroll
+  for (int j = 0; j < TN; j++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[j][e] = 0.f;
+
+#pragma unroll
+  for (int t = 0; t < NS - 1; t++)
+    if (t < nk) issue(t, t);
+
+  u32x4 fa[2][1], fb[2][TN];
+  int stage = 0;
+  // one tile; YOUNG: tiles behind it that may still be in flight (compile-time, for the wait); steady: tile kt+NS-1 exists
+  auto iteration = [&](auto young_c, auto steady_c, int kt) {
+    constexpr int Y = PER * decltype(young_c)::value;
+    constexpr bool STEADY = decltype(steady_c)::value;
+    __builtin_amdgcn_s_waitcnt(((Y >> 4) << 14) | (Y & 15) | (7 << 4) | (15 << 8));  // vmcnt(Y)
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    if (STEADY) issue(kt + NS - 1, stage == 0 ? NS - 1 : stage - 1);
+    const uint32_t st = lds0 + (uint32_t)stage * kStage;
+    st_read_frags<A_KC, BM, 1, 0>(fa[0], st, offA);
+    st_read_frags<B_KC, BN, TN, 0>(fb[0], st + kOpA, offB);
+    st_read_frags<A_KC, BM, 1, 1>(fa[1], st, offA);
+    st_read_frags<B_KC, BN, TN, 1>(fb[1], st + kOpA, offB);
+    st_wait_frags(fa, fb);
+    __builtin_amdgcn_sched_barrier(0);
+    if (!STEADY && decltype(young_c)::value == 0 && ktail) {  // last tile: k beyond K counts as zero in both operands
+#pragma unroll
+      for (int kk = 0; kk < 2; kk++)
+        if (32 * wk + 16 * kk + 8 * (lane >> 5) >= ktail) {
+          fa[kk][0] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+          for (int j = 0; j < TN; j++) fb[kk][j] = u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+#pragma unroll
+    for (int kk = 0; kk < 2; kk++)
+#pragma unroll
+      for (int j = 0; j < TN; j++) {
+        const bf16x8 a = __builtin_bit_cast(bf16x8, fa[kk][0]), b = __builtin_bit_cast(bf16x8, fb[kk][j]);
+        if constexpr (EPI == EPI_F32) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[j], 0, 0, 0);
+        else acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[j], 0, 0, 0);
+      }
+    stage = stage == NS - 1 ? 0 : stage + 1;
+  };
+  int kt = 0;
+  for (; kt + NS - 1 < nk; kt++) iteration(std::integral_constant<int, NS - 2>{}, std::true_type{}, kt);
+  // drain: the tile with r tiles behind it, r = NS-2 .. 0
+  auto drain = [&](auto self, auto r_c) {
+    constexpr int R = decltype(r_c)::value;
+    if (nk > R) iteration(r_c, std::false_type{}, nk - 1 - R);
+    if constexpr (R > 0) self(self, std::integral_constant<int, R - 1>{});
+  };
+  drain(drain, std::integral_constant<int, NS - 2>{});
+
+  // The two k halves of a part: each wave hands the quarters that the other one finishes over through LDS and adds what it
+  // receives to its own (two terms: the order of the addition does not matter)
+  f32x4* xch = reinterpret_cast<f32x4*>(lds);
+  __syncthreads();  // every wave has its last fragments in registers, and all direct-to-LDS loads have landed
+  auto hand_over = [&](auto half_c) {
+    constexpr int E = 8 * decltype(half_c)::value;
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int q = 0; q < 2; q++)
+        xch[((wave * TN + j) * 2 + q) * 64 + lane] = f32x4{acc[j][E + 4 * q], acc[j][E + 4 * q + 1], acc[j][E + 4 * q + 2], acc[j][E + 4 * q + 3]};
+  };
+  if (wk == 0) hand_over(std::integral_constant<int, 1>{}); else hand_over(std::integral_constant<int, 0>{});
+  __syncthreads();
+  auto finish = [&](auto half_c, auto full_c) {
+    constexpr int H = decltype(half_c)::value;
+    constexpr bool FULL = decltype(full_c)::value;
+    f32x4 v[TN][2];
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int q = 0; q < 2; q++) {
+        v[j][q] = xch[(((wave ^ 4) * TN + j) * 2 + q) * 64 + lane];
+#pragma unroll
+        for (int e = 0; e < 4; e++) v[j][q][e] += acc[j][8 * H + 4 * q + e];
+      }
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      const int c = 8 * (2 * H + q) + 4 * (lane >> 5);
+      if constexpr (EPI == EPI_F32) {  // plain accumulator: element e of the quarter is C[row0 + c + e][column lane%32 of the tile]
+#pragma unroll
+        for (int j = 0; j < TN; j++) {
+          const int col = col0 + 32 * j + (lane & 31), row = row0 + c;
+          if (!FULL && col >= g.N) continue;
+          float* p = reinterpret_cast<float*>(g.C) + (size_t)row * g.ldc + col;
+#pragma unroll
+          for (int e = 0; e < 4; e++)
+            if (FULL || row + e < g.M) p[(size_t)e * g.ldc] = v[j][q][e];
+        }
+      } else {
+        const int row = row0 + (lane & 31);
+        if (!FULL && row >= g.M) continue;
+        if constexpr (EPI == EPI_SWIGLU) {
+          if (FULL || col0 + c < g.N) epi_swiglu(g, row, col0 + c, col0 / 2 + c, v[0][q], v[1][q]);
+        } else {
+#pragma unroll
+          for (int j = 0; j < TN; j++)
+            if (FULL || col0 + 32 * j + c < g.N) epi_apply<EPI>(g, row, col0 + 32 * j + c, v[j][q], pre[j][q]);
+        }
+      }
+    }
+  };
+  const bool full = m0 + BM <= g.M && n0 + BN <= g.N;
+  using H0 = std::integral_constant<int, 0>;
+  using H1 = std::integral_constant<int, 1>;
+  if (full) { if (wk == 0) finish(H0{}, std::true_type{}); else finish(H1{}, std::true_type{}); }
+  else { if (wk == 0) finish(H0{}, std::false_type{}); else finish(H1{}, std::false_type{}); }
+}
+
 // split-K second pass: C = epilogue(sum over slices of the fp32 partial planes), slices added in index order
 template <int EPI>
 __global__ __launch_bounds__(256) void splitk_fixup_kernel(const float* __restrict__ part, int S, GemmArgs g) {
@@ -1213,28 +1494,7 @@ __global__ __launch_bounds__(256) void splitk_fixup_kernel(const float* __restri
   const size_t plane = (size_t)g.M * g.N;
   f32x4 v = *reinterpret_cast<const f32x4*>(part + (size_t)row * g.N + col);
   for (int s2 = 1; s2 < S; s2++) v += *reinterpret_cast<const f32x4*>(part + s2 * plane + (size_t)row * g.N + col);
-  const size_t o = (size_t)row * g.ldc + col;
-  if (EPI == EPI_F32) {
-    *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + o) = v;
-  } else if (EPI == EPI_ACC_F32) {
-    f32x4* p = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + o);
-    *p = *p + v;
-  } else {
-    uint16_t* cp = reinterpret_cast<uint16_t*>(g.C) + o;
-    if (EPI == EPI_BIAS_BF16 || EPI == EPI_BIAS_GELU) v += *reinterpret_cast<const f32x4*>(g.bias + col);
-    if (EPI == EPI_BIAS_GELU) {
-      *reinterpret_cast<u32x2*>(g.aux + (size_t)row * g.ldaux + col) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-#pragma unroll
-      for (int e = 0; e < 4; e++) v[e] = gelu_tanh(v[e]);
-    } else if (EPI == EPI_DGELU) {
-      u32x2 a = *reinterpret_cast<const u32x2*>(g.aux + (size_t)row * g.ldaux + col);
-      v[0] *= gelu_tanh_grad(bf16_bits_to_f32(a[0] & 0xffffu));
-      v[1] *= gelu_tanh_grad(bf16_bits_to_f32(a[0] >> 16));
-      v[2] *= gelu_tanh_grad(bf16_bits_to_f32(a[1] & 0xffffu));
-      v[3] *= gelu_tanh_grad(bf16_bits_to_f32(a[1] >> 16));
-    }
-    *reinterpret_cast<u32x2*>(cp) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-  }
+  epi_apply<EPI>(g, row, col, v, epi_load<EPI>(g, row, col));
 }
 
 template <int BM, int BN, int WGM, int WGN, int WGK, bool A_KC, bool B_KC, int EPI>
@@ -1266,10 +1526,41 @@ int launch_one(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
   return 0;
 }
 
+inline int st_k_per(int K, int slices) { return ((K + slices - 1) / slices + BKS - 1) / BKS * BKS; }  // k of one slice
+
+template <int TN, int NS, bool A_KC, bool B_KC, int EPI>
+int launch_small(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
+  GemmArgs g = g0;
+  g.tiles_m = (g.M + 63) / 64;
+  g.tiles_n = (g.N + 64 * TN - 1) / (64 * TN);
+  if (ksplit <= 1) {
+    hipLaunchKernelGGL((gemm_st_kernel<TN, NS, A_KC, B_KC, EPI>), dim3(g.tiles_m * g.tiles_n), dim3(512), 0, s, g);
+    OASES_LAUNCH_CHECK("gemm_st_kernel");
+    return 0;
+  }
+  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_DSWIGLU) {
+    set_error("gemm: the SwiGLU epilogues do not run over k slices");
+    return OASES_EINVAL;
+  } else {
+    if (!ws) { set_error("gemm: split-K chosen without a workspace"); return OASES_ENULL; }
+    GemmArgs p = g;
+    p.ksplit = ksplit;
+    p.k_per = st_k_per(g.K, ksplit);
+    p.C = ws;
+    p.ldc = g.N;
+    hipLaunchKernelGGL((gemm_st_kernel<TN, NS, A_KC, B_KC, EPI_F32>), dim3(g.tiles_m * g.tiles_n * ksplit), dim3(512), 0, s, p);
+    OASES_LAUNCH_CHECK("gemm_st_kernel (split-K)");
+    const long n4 = (long)g.M * (g.N / 4);
+    hipLaunchKernelGGL((splitk_fixup_kernel<EPI>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, ws, ksplit, g);
+    OASES_LAUNCH_CHECK("splitk_fixup_kernel");
+    return 0;
+  }
+}
+
 // Tile and split-K choice by a small time model.  Bigger tiles run closer to the MFMA rate (fewer LDS bytes per flop)
 // but a launch only uses the chip well if its workgroup count is near a multiple of the 256 CUs; splitting K multiplies
 // the workgroup count at the price of a second pass over fp32 partial planes.  Rates measured on this part.
-struct TileChoice { int bm, bn, ksplit; bool wave_ksplit; bool dtl = false; bool pp = false; };  // pp: the eight-wave kernel of a direct-to-LDS tile shape
+struct TileChoice { int bm, bn, ksplit; bool wave_ksplit; bool dtl = false; bool pp = false; bool st = false; };  // st: the small-tile kernel; pp: the eight-wave kernel of a direct-to-LDS tile shape
 // per kind of contraction (0: NN, 1: NT, 2: TN, 3: NN with the bias+GeLU epilogue): whether the rectangular tiles
 // split k between waves, and the sustained rates of the four block tiles
 // Shapes the direct-to-LDS kernels cover, per kind of contraction (0, 3: NN, 1: NT, 2: TN): whole k tiles; in the
@@ -1286,7 +1577,7 @@ bool dtl_rect_whole(int M, int N, int K) { return M % 128 == 0 && N % 256 == 0 &
 struct KindTable { bool wave_ksplit; float r256x256, r128x256, r256x128, r128x128; };
 const KindTable g_kinds[4] = {{true, 1200.f, 1080.f, 960.f, 740.f}, {true, 1200.f, 1080.f, 960.f, 740.f},
                         {true, 1200.f, 1080.f, 960.f, 740.f}, {false, 1200.f, 1080.f, 900.f, 740.f}};
-TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes) {
+TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes) {
   const KindTable& kt = g_kinds[kind];
   const struct { int bm, bn; float tflops; } cand[] = {{256, 256, kt.r256x256}, {128, 256, kt.r128x256}, {256, 128, kt.r256x128}, {128, 128, kt.r128x128}};
   TileChoice best{128, 128, 1, kt.wave_ksplit};
@@ -1321,9 +1612,45 @@ TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes) {
   return best;
 }
 
+// Small tiles against the choice above, by the same kind of model (measured on this part): a launch costs 2.9 us, a
+// workgroup 0.225 us (64 x 64) or 0.335 us (64 x 128) per 64-wide stage of its slice, two workgroups on a CU take turns at the
+// LDS, so the busiest CU's workgroups add up; the output moves at 4 TB/s (3.1 TB/s with the large tiles, one workgroup per
+// CU: nothing covers the latency of its read-modify-write); k slices cost a second launch and their planes.  The
+// eight-wave kernels run better than the model on long k, so they give way only to a tenth less; the register-staged ones
+// wait out two more memory latencies, 2 us, before the first product.  Both sides measured,
+// us, large tile -> small: 4096 x 1536 x 2048 NN bias 31.6 -> 34.8 (stays large), 1024 x 3072 x 8192 56.2 -> 71.6 (stays
+// large), 4096 x 512 x 4096 NT 29.8 -> 22.9, 1024 x 1024 x 4096 TN 21.4 -> 16.9, 64 x 4608 x 12288 NN 53.5 -> 34.8,
+// 6144 x 12288 x 128 TN 195 -> 152.  Slices of 8192 k and more stay with the large tiles.
+TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes) {
+  const TileChoice large = pick_large_tile(kind, epi, M, N, K, ws_bytes);
+  const KindTable& kt = g_kinds[kind];
+  const double out = (double)M * N * (epi == EPI_F32 ? 4.0 : kind == 2 ? 8.0 : epi == EPI_SWIGLU ? 3.0 : epi == EPI_DSWIGLU ? 8.0 : epi == EPI_BIAS_GELU || epi == EPI_DGELU ? 4.0 : 2.0);
+  auto slices = [&](int S) { return S > 1 ? 3.2e-6 + 2.0 * S * M * N * 4.0 / 6.0e12 : 0.0; };
+  const double rate = large.bm == 256 && large.bn == 256 ? kt.r256x256 : large.bm == 256 ? kt.r256x128 : large.bn == 256 ? kt.r128x256 : kt.r128x128;
+  const long wgs = (long)((M + large.bm - 1) / large.bm) * ((N + large.bn - 1) / large.bn) * large.ksplit;
+  double best_t = (double)((wgs + 255) / 256) * (2.0 * large.bm * large.bn * ((double)K / large.ksplit) + 3.0e6) / (rate * 1e12 / 256.0) + out / 3.1e12 +
+                  slices(large.ksplit);
+  if (large.pp) best_t *= 0.9; else best_t += 2.0e-6;
+  TileChoice best = large;
+  for (int bn = epi == EPI_SWIGLU ? 128 : 64; bn <= 128; bn += 64)
+    for (int S = 1; S <= 16; S *= 2) {
+      const int k_per = st_k_per(K, S);
+      if (S > 1 && ((size_t)S * M * N * 4 > ws_bytes || k_per < 2 * BKS || (long)(S - 1) * k_per >= K)) break;
+      if (k_per >= 8192) continue;
+      const long per_cu = ((long)((M + 63) / 64) * ((N + bn - 1) / bn) * S + 255) / 256;
+      const double t = 2.9e-6 + (double)per_cu * ((k_per + BKS - 1) / BKS) * (bn == 64 ? 0.225e-6 : 0.335e-6) + out / 4.0e12 + slices(S);
+      if (t < best_t) {
+        best_t = t;
+        best = TileChoice{64, bn, S, true};
+        best.st = true;
+      }
+    }
+  return best;
+}
+
 int encode_variant(const TileChoice& t) {
   const bool rect = t.bm != t.bn;
-  return (t.dtl ? (t.pp ? 300000000 : 200000000) : rect && t.wave_ksplit ? 100000000 : 0) + t.ksplit * 1000000 + t.bm * 1000 + t.bn;
+  return (t.st ? 400000000 : t.dtl ? (t.pp ? 300000000 : 200000000) : rect && t.wave_ksplit ? 100000000 : 0) + t.ksplit * 1000000 + t.bm * 1000 + t.bn;
 }
 // variant -> TileChoice; false if no such instantiation exists or the k slices do not fit the problem / workspace
 bool decode_variant(int variant, int kind, int M, int N, int K, size_t ws_bytes, TileChoice* t) {
@@ -1338,6 +1665,14 @@ bool decode_variant(int variant, int kind, int M, int N, int K, size_t ws_bytes,
   if ((wk == 2 || wk == 3) && bm == 128 && bn == 256 && (S == 2 || S == 4)) {  // the 128 x 256 kernels over k slices of whole stages
     if (K % (S * BKR) || !dtl_rect_fits(kind, M, N, K / S) || (size_t)S * M * N * 4 > ws_bytes) return false;
     *t = TileChoice{128, 256, S, true, true, wk == 3};
+    return true;
+  }
+  if (wk >= 4) {  // small tiles; k slices of whole stages that all start inside K
+    const bool tile = bm == 64 && (bn == 64 || bn == 128);
+    if (wk > 4 || !tile || S < 1 || S > 16) return false;
+    if (S > 1 && ((size_t)S * M * N * 4 > ws_bytes || (long)(S - 1) * st_k_per(K, S) >= K)) return false;
+    *t = TileChoice{bm, bn, S, true};
+    t->st = true;
     return true;
   }
   if (wk > 1 || !(square || rect) || (wk == 1 && !rect) || S < 1 || S > 8) return false;
@@ -1363,7 +1698,10 @@ int launch_shape(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_varia
     t = pick_tile(kind, EPI, pinned ? choice_rows : g.M, g.N, g.K, ws ? ws_bytes : 0);
     if (pinned && t.dtl && t.bm == 256 && !dtl_fits(kind, g.M, g.N, g.K)) t.dtl = t.pp = false;
     const int rows = pinned ? choice_rows : g.M;
-    if (t.dtl && !(gemm_span_fits(A_KC ? rows : g.K, g.lda) && gemm_span_fits(B_KC ? g.N : g.K, g.ldb))) t.dtl = t.pp = false;
+    if ((t.dtl || t.st) && !(gemm_span_fits(A_KC ? rows : g.K, g.lda) && gemm_span_fits(B_KC ? g.N : g.K, g.ldb))) {
+      if (t.st) t = pick_large_tile(kind, EPI, rows, g.N, g.K, ws ? ws_bytes : 0);
+      t.dtl = t.pp = false;
+    }
 #ifdef OASES_GEMM_TUNE_HOOK
     {  // tuning aid (not compiled into the library): OASES_GEMM_TUNE="kind:epi:M:N:K=variant;..." overrides the choice
       static const char* tune = getenv("OASES_GEMM_TUNE");
@@ -1379,8 +1717,14 @@ int launch_shape(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_varia
   } else if (!decode_variant(forced_variant, kind, g.M, g.N, g.K, ws ? ws_bytes : 0, &t)) {
     set_error("gemm: variant %d does not exist or does not fit M=%d N=%d K=%d with %zu workspace bytes", forced_variant, g.M, g.N, g.K, ws ? ws_bytes : (size_t)0);
     return OASES_EINVAL;
-  } else if (t.dtl && !(gemm_span_fits(A_KC ? g.M : g.K, g.lda) && gemm_span_fits(B_KC ? g.N : g.K, g.ldb))) {
+  } else if ((t.dtl || t.st) && !(gemm_span_fits(A_KC ? g.M : g.K, g.lda) && gemm_span_fits(B_KC ? g.N : g.K, g.ldb))) {
     set_error("gemm: variant %d (direct-to-LDS) needs operands that span less than 2 GiB (lda=%d ldb=%d)", forced_variant, g.lda, g.ldb);
+    return OASES_EINVAL;
+  }
+  if (t.st) {
+    if (t.bn == 128) return launch_small<2, 3, A_KC, B_KC, EPI>(g, t.ksplit, ws, s);
+    if constexpr (EPI != EPI_SWIGLU) return launch_small<1, 5, A_KC, B_KC, EPI>(g, t.ksplit, ws, s);
+    set_error("gemm: the 64x64 kernel has no SwiGLU epilogue");
     return OASES_EINVAL;
   }
   if (t.dtl && t.pp) {
@@ -1516,6 +1860,8 @@ int launch_gemm_tn(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_var
 
 bool gemm_tn_pair_wins(int K, int M0, int N0, int M1, int N1) {
   if (M0 <= 0 || N0 <= 0 || M1 <= 0 || N1 <= 0 || !dtl_rect_whole(M0, N0, K) || !dtl_rect_whole(M1, N1, K)) return false;
+  // few rows: what counts is the traffic of the gradients, which small tiles move faster (see pick_tile)
+  if (pick_tile(2, EPI_ACC_F32, M0, N0, K, 0).st && pick_tile(2, EPI_ACC_F32, M1, N1, K, 0).st) return false;
   const long t0 = (long)(M0 / 128) * (N0 / 256), t1 = (long)(M1 / 128) * (N1 / 256);
   // enough tiles to be worth whole 128 x 256 tiles at all, and fewer rounds of 256 workgroups together than apart
   return t0 + t1 > 128 && (t0 + t1 + 255) / 256 < (t0 + 255) / 256 + (t1 + 255) / 256;
