@@ -85,7 +85,8 @@ enum { OASES_ARCH_GPT = 0, OASES_ARCH_LLAMA = 1, OASES_ARCH_BERT = 2 };
 
 enum {
   OASES_FLAG_SERIALISE = 1, /* enqueue everything on stream_compute only (same results) */
-  OASES_FLAG_PROFILE = 2,   /* bracket every operator with timing events, see oases_profile_read */
+  OASES_FLAG_PROFILE = 2,   /* execute the schedule operator by operator and sub-batch by sub-batch, each operator bracketed
+                               by timing events, see oases_profile_read */
   OASES_FLAG_RECOMPUTE = 4, /* fine-grained recomputation (paper Sec. IV-B): keep only the input of each computation
                                sequence (x, x1) per layer, rebuild u, qkv, attention output, LSE, v2, pre, f inside
                                oases_backward with the forward kernels -- never a reduction point -- interleaved with
@@ -98,7 +99,7 @@ enum {
                                splitting the batch leaves the results unchanged); bias and LayerNorm-parameter gradients,
                                which are summed over row groups of a sub-batch, still differ in the last bits.  Default
                                (flag clear): each launch takes the kernel that is fastest for its own shape, and results
-                               for different n_sub agree to fp32 summation order only */
+                               for different n_sub agree to fp32 summation order (and what a bf16 rounding makes of it) */
 };
 
 typedef struct oases_handle oases_handle; /* opaque; holds host metadata and HIP events only */
@@ -133,10 +134,15 @@ void oases_destroy(oases_handle *h);
 size_t oases_workspace_bytes(const oases_handle *h);
 
 /* Forward of all layers under Alg. 1 "At Forward": for each computation sequence, sub-batch after
- * sub-batch; after each row-parallel GEMM the reduction point of that sub-batch is started on
+ * sub-batch; after each row-parallel GEMM the reduction point of that sub-batch belongs to
  * stream_comm (adds the peer sum, then the fused bias+dropout+residual(+LayerNorm) that consumes it)
  * while stream_compute goes on with the next sub-batch.  w: [n_layers]; peers: [n_layers] or NULL.
- * x [M,h] fp32 in, y [M,h] fp32 out (y may not alias x). */
+ * x [M,h] fp32 in, y [M,h] fp32 out (y may not alias x).
+ * The peer sums are inputs, so within one call there is no transfer that a sub-batch could hide: the kernels take all
+ * sub-batches together (in the fewest parts whose GEMM operands span less than 2 GiB) and run on stream_compute.
+ * stream_comm keeps its place in the order: what is enqueued on it before the call precedes the first reduction point,
+ * what is enqueued on it afterwards follows the whole call.  With OASES_FLAG_PROFILE every operator runs by itself, per
+ * sub-batch and on the stream that the schedule gives it.  The same holds for oases_backward. */
 int oases_forward(oases_handle *h, const oases_weights *w, const void *x, void *y,
                   const oases_peer_sums *peers, void *workspace, size_t workspace_bytes,
                   void *stream_compute, void *stream_comm);
@@ -156,7 +162,7 @@ int oases_backward(oases_handle *h, const oases_weights *w, const void *x, const
  * time: each rank (its own handle, weights and workspace) runs a segment up to its reduction point, the caller forms
  * y = sum_i x_i over the ranks' partials (the AllReduce of Sec. IV-B, whose input gradient is its output gradient, Eq. (1))
  * and hands the sum to every rank's next segment.  A segment runs the operators of ONE layer for ALL sub-batches, in the
- * order of oases_schedule_dump, on one stream.
+ * order and over the parts of the rows of the whole pass, on one stream.
  *   forward  segment 0: [LN1 (first layer), QKV, attention, projection]              ends in   Z1_r  (fwd_attn point)
  *            segment 1: [bias+dropout+residual+LN2 on Z1, FC1+GeLU, FC2]             Z1 in,    ends in Z2_r (fwd_ffn point)
  *            segment 2: [bias+dropout+residual on Z2 (+ LN1 of the next layer)]      Z2 in,    writes the layer output

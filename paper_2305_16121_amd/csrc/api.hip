@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -111,7 +112,11 @@ struct oases_handle {
   bool llama;    // OASES_ARCH_LLAMA: RMSNorm, rotary embedding, SwiGLU, no biases
   bool bert;     // OASES_ARCH_BERT: post-LayerNorm
   float eps, theta;
-  std::vector<Op> fwd, bwd;
+  std::vector<Op> fwd, bwd;    // the schedule: one operator per sub-batch, two streams
+  // What a pass executes (see pass_sub_batches): the same operator sequences over xn groups of consecutive sub-batches of
+  // xMs rows each, on one stream
+  int xn, xMs;
+  std::vector<Op> xfwd, xbwd;
   int n_events;
   std::vector<hipEvent_t> events;  // created on first use
   std::vector<hipEvent_t> prof[2];  // OASES_FLAG_PROFILE: start/stop event per operator of each pass
@@ -120,7 +125,7 @@ struct oases_handle {
   size_t layer_bytes, shared_off, scratch_comm_off, scratch_compute_off, gemm_ws_off, gemm_ws_bytes, total_bytes;
   // arena of partial rows of the backward pass's column reductions, per layer: five slots (see ColsumSlot)
   size_t colsum_off, colsum_layer_bytes, colsum_slot_off[5];
-  int colsum_groups_sub, colsum_groups_all;  // row groups of a reduction over a sub-batch's rows / over all M rows
+  int colsum_groups_sub, colsum_groups_all;  // row groups of a reduction over xMs rows / over all M rows
 };
 
 namespace oases {
@@ -169,12 +174,12 @@ static bool plan_workspace(oases_handle* H) {
   size_t wide = 3 * hp > fw ? 3 * hp : fw;
   tot += align_up((size_t)kColPartials * wide * 4);
   // Partial rows of the column reductions of a backward pass, kept until its single second-stage launch.  Slots of a
-  // layer: three reduction-point kernels with up to three output arrays each, laid out [array][sub-batch][group][h], and
+  // layer: three reduction-point kernels with up to three output arrays each, laid out [array][part of the rows][group][h], and
   // the two bias sums over all rows [group][columns].
   {
-    H->colsum_groups_sub = colsum_groups(H->Ms);
+    H->colsum_groups_sub = colsum_groups(H->xMs);
     H->colsum_groups_all = colsum_groups(H->M);
-    const size_t tri = align_up((size_t)3 * H->n * H->colsum_groups_sub * h * 4);
+    const size_t tri = align_up((size_t)3 * H->xn * H->colsum_groups_sub * h * 4);
     size_t o = 0;
     for (int k = 0; k < 3; k++) { H->colsum_slot_off[k] = o; o += tri; }
     H->colsum_slot_off[3] = o; o += align_up((size_t)H->colsum_groups_all * fw * 4);
@@ -184,9 +189,9 @@ static bool plan_workspace(oases_handle* H) {
     tot += o * H->L;
   }
   // split-K partial planes: up to 8 fp32 copies of the widest GEMM output of the layer
-  const size_t Ms = H->Ms;
-  size_t mn = Ms * h;
-  for (size_t v : {Ms * 3 * hp, Ms * fw, fw * h, h * 3 * hp, hp * h}) mn = v > mn ? v : mn;
+  const size_t rows = H->xMs;
+  size_t mn = rows * h;
+  for (size_t v : {rows * 3 * hp, rows * fw, fw * h, h * 3 * hp, hp * h}) mn = v > mn ? v : mn;
   H->gemm_ws_off = tot;
   H->gemm_ws_bytes = 8 * mn * 4 < kSplitKWorkspaceBytes ? 8 * mn * 4 : kSplitKWorkspaceBytes;
   tot += align_up(H->gemm_ws_bytes);
@@ -209,9 +214,7 @@ static int ev_id(const oases_handle* H, int layer, int point, int sub, int kind)
 // Alg. 1 "At Forward": walk the operator sequence; at every communication operator start it for the
 // current sub-batch and switch to the next sub-batch, rewinding to the start of the computation
 // sequence; advance past the communication operator once every sub-batch has been through.
-static void build_forward(oases_handle* H) {
-  auto& ops = H->fwd;
-  const int n = H->n;
+static void build_forward(const oases_handle* H, int n, std::vector<Op>& ops) {
   if (H->llama) ops.push_back(Op{F_ROPE_TABLE, 0, -1, 0, -1, -1});
   for (int l = 0; l < H->L; l++) {
     for (int j = 0; j < n; j++) {
@@ -238,11 +241,10 @@ static void build_forward(oases_handle* H) {
 // on the communication stream) fill in.  No reduction depends on a weight gradient, and a weight gradient sums
 // over token rows, so the weight-gradient GEMMs of all sub-batches of a block are merged into one contraction
 // over all M rows and issued behind the last sub-batch's reduction start, under which they run.
-static void build_backward(oases_handle* H) {
-  auto& ops = H->bwd;
-  const int n = H->n, L = H->L;
+static void build_backward(const oases_handle* H, int n, std::vector<Op>& ops) {
+  const int L = H->L;
   const bool recompute = H->cfg.flags & OASES_FLAG_RECOMPUTE;
-  const bool chunks = H->n > H->b;  // sub-batches are parts of a sequence: attention of a chunk reads earlier chunks' K/V
+  const bool chunks = n > H->b;  // sub-batches are parts of a sequence: attention of a chunk reads earlier chunks' K/V
   for (int j = n - 1; j >= 0; j--) ops.push_back(Op{B_BDR2, L - 1, j, 1, -1, ev_id(H, L - 1, 1, j, 1)});
   for (int l = L - 1; l >= 0; l--) {
     for (int j = n - 1; j >= 0; j--) {
@@ -292,6 +294,27 @@ static void build_backward(oases_handle* H) {
   for (int j = n - 1; j >= 0; j--) ops.push_back(Op{JOIN, 0, j, 0, ev_id(H, 0, 3, j, 1), -1});
   // every first stage of a column reduction has run (both streams are joined): one launch adds up all partial rows
   ops.push_back(Op{B_COLSUMS, 0, -1, 0, -1, -1});
+}
+
+// Parts of the rows that a pass works through one after the other.  A sub-batch of the schedule stands for a piece of work
+// under which another piece's reduction travels; inside one call nothing travels (the peer sums are inputs), so walking
+// the sub-batches one at a time only shortens every launch, reads the weights n times and, with the consumers of the
+// reductions on a second stream, waits for an event at every reduction point.  Measured per training step, us, two streams
+// with n_sub sub-batches -> one stream with n_sub -> one stream with one part: h 512 (512 tokens, n_sub 2) 336 -> 177 -> 118, h 1024
+// ragged (600 tokens, n_sub 3, three layers) 1475 -> 1025 -> 490, h 2048 (8192) 1383 -> 1397 -> 1256, h 4096 (8192) 2218 -> 2160
+// -> 2072, h 8192 in chunks (4096, n_sub 4) 3897 -> 3719 -> 3069, h 12288 (128) 1352 -> 1369 -> 1073; also two parts of the four chunks
+// (3247) lose against one.  So all sub-batches go together, as long as every GEMM operand of a part spans less
+// than 2 GiB, which is what the direct-to-LDS kernels address; beyond that, the fewest parts that do (groups of
+// consecutive sub-batches, so whole sequences or equal chunks of one again).  A handle with OASES_FLAG_PROFILE executes the schedule as it stands:
+// what it is asked for is the time of every operator of every sub-batch.
+static int pass_sub_batches(const oases_handle* H) {
+  if (H->cfg.flags & OASES_FLAG_PROFILE) return H->n;
+  const int widest = std::max({H->h, 3 * H->hp, H->fw});
+  for (int x = 1; x < H->n; x++) {
+    if (H->n % x || (x <= H->b ? H->b % x : x % H->b)) continue;
+    if (gemm_span_fits(H->M / x, widest)) return x;
+  }
+  return H->n;
 }
 
 static int check_ptrs(const void* const* p, int n, const char* who) {
@@ -346,8 +369,8 @@ static T* wsp(const Run& R, TensorId id, int layer) {  // offsets were resolved 
 static int run_op(const Run& R, const Op& op) {
   const oases_handle* H = R.H;
   const int l = op.layer, j = op.sub, h = H->h, hp = H->hp, fp = H->fp, L = H->L;
-  const int Ms = j < 0 ? H->M : H->Ms;              // sub = -1: all rows (merged weight gradients)
-  const size_t r0 = j < 0 ? 0 : (size_t)j * Ms;     // first token row of the sub-batch
+  const int Ms = j < 0 ? H->M : H->xMs;             // sub = -1: all rows (merged weight gradients)
+  const size_t r0 = j < 0 ? 0 : (size_t)j * Ms;     // first token row of the part
   hipStream_t s = R.st[op.stream];
   const oases_weights& W = R.w[l];
   const oases_peer_sums* P = R.peers ? &R.peers[l] : nullptr;
@@ -379,8 +402,8 @@ static int run_op(const Run& R, const Op& op) {
     if (slot < 3) {
       const int g = H->colsum_groups_sub;
       sink.first_row = j * g;
-      sink.rows_total = H->n * g;
-      sink.kstride = (size_t)H->n * g * h;
+      sink.rows_total = H->xn * g;
+      sink.kstride = (size_t)H->xn * g * h;
       cs_scratch = base + (size_t)sink.first_row * h;
     } else {
       sink.first_row = 0;
@@ -595,20 +618,68 @@ static int run_op(const Run& R, const Op& op) {
   return OASES_EINVAL;
 }
 
-static int run_ops(const Run& R, const std::vector<Op>& ops) {
+static int capturing(hipStream_t s, bool* yes) {
+  *yes = false;
+  if (!s) return 0;  // the null stream cannot be captured
+  hipStreamCaptureStatus st;
+  OASES_HIP(hipStreamIsCapturing(s, &st));
+  *yes = st != hipStreamCaptureStatusNone;
+  return 0;
+}
+
+// The pass on stream_compute.  Both streams see the order that the schedule gives them: the first operator that belongs to
+// stream_comm waits for what the caller has enqueued there (peer sums written on that stream, or a reader of y still at
+// work), and work enqueued on stream_comm afterwards follows the whole pass.
+static int run_pass(const Run& R, const std::vector<Op>& ops) {
+  oases_handle* H = R.H;
+  const bool two = !(H->cfg.flags & OASES_FLAG_SERIALISE) && R.st[0] != R.st[1];
+  hipEvent_t before = nullptr, after = nullptr;
+  bool captured = false;
+  if (two) {
+    int rc = ensure_events(H);
+    if (rc) return rc;
+    before = H->events[0];
+    after = H->events[1];
+    bool c0, c1;
+    if ((rc = capturing(R.st[0], &c0)) || (rc = capturing(R.st[1], &c1))) return rc;
+    captured = c0 || c1;
+    if (captured) {  // stream_comm joins the capture of stream_compute (the two in different captures: an error from HIP)
+      OASES_HIP(hipEventRecord(after, R.st[0]));
+      OASES_HIP(hipStreamWaitEvent(R.st[1], after, 0));
+    }
+    OASES_HIP(hipEventRecord(before, R.st[1]));
+  }
+  bool waited = !two;
+  for (const Op& op0 : ops) {
+    if (op0.kind == JOIN) continue;
+    if (op0.stream == 1 && !waited) {
+      OASES_HIP(hipStreamWaitEvent(R.st[0], before, 0));
+      waited = true;
+    }
+    Op op = op0;
+    op.stream = 0;
+    const int rc = run_op(R, op);
+    if (rc) return rc;
+  }
+  if (two) {
+    OASES_HIP(hipEventRecord(after, R.st[0]));
+    OASES_HIP(hipStreamWaitEvent(R.st[1], after, 0));
+  }
+  return 0;
+}
+
+// OASES_FLAG_PROFILE: the schedule operator by operator, on its two streams, each operator between two timing events
+static int run_schedule(const Run& R, const std::vector<Op>& ops, int pass) {
   oases_handle* H = R.H;
   const bool serial = (H->cfg.flags & OASES_FLAG_SERIALISE) || R.st[0] == R.st[1];
   if (!serial) {
     int rc = ensure_events(H);
     if (rc) return rc;
-  }
-  if (!serial) {  // everything already enqueued on stream_compute (inputs) precedes the work on stream_comm
+    // everything already enqueued on stream_compute (inputs) precedes the work on stream_comm
     OASES_HIP(hipEventRecord(H->events[H->n_events - 1], R.st[0]));
     OASES_HIP(hipStreamWaitEvent(R.st[1], H->events[H->n_events - 1], 0));
   }
-  const bool profile = H->cfg.flags & OASES_FLAG_PROFILE;
-  const int pass = &ops == &H->bwd;
-  if (profile && H->prof[pass].empty()) {
+  if (H->prof[pass].empty()) {
     H->prof[pass].resize(2 * ops.size());
     for (auto& e : H->prof[pass]) {
       hipError_t err = hipEventCreate(&e);
@@ -623,15 +694,21 @@ static int run_ops(const Run& R, const std::vector<Op>& ops) {
     Op op = op0;
     if (serial) op.stream = 0;
     if (!serial && op.wait >= 0) OASES_HIP(hipStreamWaitEvent(R.st[op.stream], H->events[op.wait], 0));
-    if (profile) OASES_HIP(hipEventRecord(H->prof[pass][2 * i], R.st[op.stream]));
+    OASES_HIP(hipEventRecord(H->prof[pass][2 * i], R.st[op.stream]));
     int rc = run_op(R, op);
     if (rc) return rc;
-    if (profile) OASES_HIP(hipEventRecord(H->prof[pass][2 * i + 1], R.st[op.stream]));
+    OASES_HIP(hipEventRecord(H->prof[pass][2 * i + 1], R.st[op.stream]));
     if (!serial && op.record >= 0) OASES_HIP(hipEventRecord(H->events[op.record], R.st[op.stream]));
     i++;
   }
-  if (profile) H->prof_ran[pass] = true;
+  H->prof_ran[pass] = true;
   return 0;
+}
+
+static int run_ops(const Run& R, bool backward) {
+  const oases_handle* H = R.H;
+  if (H->cfg.flags & OASES_FLAG_PROFILE) return run_schedule(R, backward ? H->bwd : H->fwd, backward);
+  return run_pass(R, backward ? H->xbwd : H->xfwd);
 }
 
 }  // namespace oases
@@ -687,10 +764,16 @@ int oases_create(const oases_layer_cfg* c, oases_handle** out) {
   H->fw = llama ? 2 * H->fp : H->fp;
   H->eps = c->ln_eps > 0.f ? c->ln_eps : 1e-5f;
   H->theta = c->rope_theta > 0.f ? c->rope_theta : 10000.f;
-  H->n_events = H->L * 4 * H->n * 2 + 1;  // + the fork event that orders stream_comm behind stream_compute
+  H->xn = pass_sub_batches(H);
+  H->xMs = H->M / H->xn;
+  // executing the schedule itself: two per layer, reduction point and sub-batch, and the fork event that orders stream_comm
+  // behind stream_compute
+  H->n_events = c->flags & OASES_FLAG_PROFILE ? H->L * 4 * H->n * 2 + 1 : 2;
   if (!plan_workspace(H)) { delete H; set_error("oases_create: internal error (workspace plan)"); return OASES_EINVAL; }
-  build_forward(H);
-  build_backward(H);
+  build_forward(H, H->n, H->fwd);
+  build_backward(H, H->n, H->bwd);
+  build_forward(H, H->xn, H->xfwd);
+  build_backward(H, H->xn, H->xbwd);
   *out = H;
   return 0;
 }
@@ -777,7 +860,7 @@ int oases_forward(oases_handle* H, const oases_weights* w, const void* x, void* 
   if ((rc = check_weights(H, w))) return rc;
   Run R{H, w, nullptr, peers, (char*)workspace, (const float*)x, (float*)y, nullptr, nullptr,
         {(hipStream_t)stream_compute, (hipStream_t)stream_comm}};
-  return run_ops(R, H->fwd);
+  return run_ops(R, false);
 }
 
 int oases_backward(oases_handle* H, const oases_weights* w, const void* x, const void* dy, void* dx, const oases_grads* g,
@@ -799,7 +882,7 @@ int oases_backward(oases_handle* H, const oases_weights* w, const void* x, const
   R.defer_colsums = true;
   R.jobs = &jobs;
   R.n_jobs = &n_jobs;
-  return run_ops(R, H->bwd);
+  return run_ops(R, true);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -828,8 +911,7 @@ static int segment_of(int kind, bool backward) {
   }
 }
 
-// the operators of (layer, segment) in schedule order on one stream: that order is a valid serial order of the pass
-// (it is what OASES_FLAG_SERIALISE runs), and every operator of a segment depends only on operators of the same segment
+// the operators of (layer, segment) on one stream, in the order and over the row parts of the whole pass; every operator of a segment depends only on operators of the same segment
 // before it and on earlier segments
 static int run_segment(Run& R, bool backward, int layer, int segment, void* partial_out, const void* reduced_in) {
   oases_handle* H = R.H;
@@ -848,7 +930,7 @@ static int run_segment(Run& R, bool backward, int layer, int segment, void* part
   if (produces >= 0) R.partial_out[produces] = (float*)partial_out;
   if (consumes >= 0) R.reduced_in[consumes] = (const float*)reduced_in;
   R.st[1] = R.st[0];
-  for (const Op& op0 : backward ? H->bwd : H->fwd) {
+  for (const Op& op0 : backward ? H->xbwd : H->xfwd) {
     if (op0.layer != layer || segment_of(op0.kind, backward) != segment) continue;
     if (op0.kind == F_ROPE_TABLE && layer != 0) continue;
     Op op = op0;

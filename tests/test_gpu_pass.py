@@ -1,0 +1,73 @@
+"""What a pass executes -- all sub-batches together, on the compute stream -- against the schedule executed operator by operator
+(OASES_FLAG_PROFILE), and the place of the communication stream in the order of the caller's work."""
+import pytest
+import torch
+
+import synth_inputs as si
+from tests import layer_harness as LH
+from tests.util import rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("name,n_sub", [("C1", 2), ("C2", 2), ("C2", 16)])   # 16 > batch: sub-batches are chunks of a sequence
+@pytest.mark.parametrize("recompute", [False, True])
+def test_pass_agrees_with_the_schedule_operator_by_operator(name, n_sub, recompute):
+    from paper_2305_16121_amd import binding as B
+    cfg = si.CONFIGS[name]
+    layers, x, dy = LH.make_inputs(cfg)
+    flags = B.FLAG_RECOMPUTE if recompute else 0
+    a = LH.gpu_rank_run(cfg, 0, layers, x, dy, n_sub=n_sub, flags=flags)
+    b = LH.gpu_rank_run(cfg, 0, layers, x, dy, n_sub=n_sub, flags=flags | B.FLAG_PROFILE)
+    # the bounds of the sub-batch count test: fp32 summation order, and a bf16 rounding downstream that falls the other way
+    assert rel_err(a["y"], b["y"]) < 5e-3 and rel_err(a["dx"], b["dx"]) < 1e-2
+    for l in range(cfg["n_layers"]):
+        for k in LH.GPU_PARAMS:
+            assert rel_err(a["grads"][l][k], b["grads"][l][k]) < LH.GRAD_TOL, (l, k)
+
+
+def test_communication_stream_keeps_its_place_in_the_order():
+    """Peer sums and dy written on stream_comm just before the calls are seen by them, and work enqueued on stream_comm behind
+    a call sees its outputs, without any synchronisation by the caller."""
+    from paper_2305_16121_amd import binding as B
+    cfg = si.CONFIGS["C1"]
+    layers, x, dy = LH.make_inputs(cfg)
+    W = [B.pack_rank_params(si.shard_layer_params(p, cfg, 0)) for p in layers]
+    H = B.Handle(B.make_cfg(cfg, rank=0, seed=3))
+    ws = torch.empty(H.workspace_bytes, dtype=torch.uint8, device="cuda")
+    xd, dyd = torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda()
+    points = ("fwd_attn", "fwd_ffn", "bwd_ffn", "bwd_attn")
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    values = [{k: torch.randn(xd.shape, generator=gen, device="cuda") for k in points} for _ in layers]
+    busy = torch.randn(2048, 2048, device="cuda")
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def step(late):
+        y, dx = torch.full_like(xd, float("nan")), torch.full_like(xd, float("nan"))
+        peers = [{k: torch.zeros_like(v) if late else v for k, v in p.items()} for p in values]
+        dyl = torch.zeros_like(dyd) if late else dyd
+        G = [B.zero_grads_like(w) for w in W]
+        seen = {}
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s2):
+            if late:                       # some milliseconds of work, then the inputs of the reduction points
+                t = busy
+                for _ in range(20):
+                    t = (t @ busy) * 1e-2
+                for p, v in zip(peers, values):
+                    for k in points:
+                        p[k].copy_(v[k])
+            H.forward(W, xd, y, ws, peers=peers, s_compute=s1, s_comm=s2)
+            seen["y"] = y.clone()
+            if late:
+                dyl.copy_(dyd)
+            H.backward(W, xd, dyl, dx, G, ws, peers=peers, s_compute=s1, s_comm=s2)
+            seen["dx"] = dx.clone()
+            seen.update({f"{l}.{k}": g.clone() for l, d in enumerate(G) for k, g in d.items()})
+        torch.cuda.synchronize()
+        return seen
+
+    ref, got = step(False), step(True)
+    for k, v in ref.items():
+        assert bool(torch.isfinite(v).all()) and torch.equal(v, got[k]), k
+    H.close()
