@@ -1,7 +1,7 @@
 // HBM-bound kernels of the layer: LayerNorm forward/backward, the fused
 // reduction-point + bias + dropout + residual (+ LayerNorm) step, dropout backward, and the
 // two-stage (deterministic) column reductions that give bias / LayerNorm-parameter gradients.
-// One 256-thread workgroup walks whole rows with 16-byte accesses; a row stays in registers
+// A wave or a workgroup walks whole rows with 16-byte accesses; a row stays in registers
 // between its reduction and its write, so every tensor is read once and written once.
 #include "common.h"
 
@@ -48,57 +48,84 @@ __global__ __launch_bounds__(NT) void dropout_mask_kernel(uint8_t* mask, DropCfg
 }
 
 // ------------------------------------------------------------------------------------------------
+// The row kernels below give a row to T threads: a wave (T = 64: no barrier in the reduction; what bounds a short row is the
+// latency of load, reduction and store, and a workgroup of waves has that many rows under way), or a whole workgroup of 256 or
+// 1024 threads (wide rows).  All loads of a row are requested before the first is used: chunks beyond the row are fetched
+// from its last chunk and counted as zero, so that no branch comes between the loads (with one load behind another's
+// branch a row of 12288 paid its memory latency twelve times).
+// chunk at byte offset `off` of a row: uniform row address in scalar registers, 32-bit lane offset
+__device__ __forceinline__ f32x4 row_load4(const float* row, uint32_t off) {
+  return *reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(row) + off);
+}
+template <int T>
+__device__ __forceinline__ uint32_t chunk_off(int tid, int i, int nc) { return 16u * (uint32_t)min(tid + i * T, nc - 1); }
+// wave of the workgroup, uniform
+__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
+
+template <int T>
+__device__ __forceinline__ void row_sum2(float& a, float& b, float* red) {
+  if constexpr (T == 64) {
+    a = wave_sum(a);
+    b = wave_sum(b);
+  } else {
+    block_sum2<T / 64>(a, b, red);
+  }
+}
+
 // xo = xin + keep * (part + peer + bias) * scale   (if part != nullptr; else the row is xin itself; bias may be NULL)
 // ln_out = gamma * (xo - mu) * rstd + beta          (if ln_out != nullptr; bf16), the same in fp32 to ln_f32 if given
 // RMS: ln_out = gamma * xo * rstd with rstd = 1/sqrt(mean(xo^2) + eps) (RMSNorm: no mean, no beta, mu_out unused)
-template <int NC, bool RMS>
-__global__ __launch_bounds__(NT) void bdr_ln_kernel(const float* __restrict__ part, const float* __restrict__ peer,
+template <int NC, int T, bool RMS>
+__global__ __launch_bounds__(T) void bdr_ln_kernel(const float* __restrict__ part, const float* __restrict__ peer,
                                                     const float* __restrict__ bias, const float* __restrict__ xin,
                                                     float* __restrict__ xo, const float* __restrict__ gamma,
                                                     const float* __restrict__ beta, uint16_t* __restrict__ ln_out,
                                                     float* __restrict__ mu_out, float* __restrict__ rstd_out, int h,
                                                     float eps, DropCfg d, int64_t row0, float* __restrict__ ln_f32) {
-  __shared__ float red[8];
+  __shared__ float red[2 * (T / 64)];
   const int row = blockIdx.x, tid = threadIdx.x;
   const int nc = h >> 2;
   const size_t base = (size_t)row * h;
-  f32x4 v[NC];
-  // mean and variance in ONE reduction: moments of (x - shift) with shift = first element of the row that is
-  // normalised (a value within a few standard deviations of the mean, so E[d^2] - E[d]^2 does not cancel).  Every
-  // thread rebuilds that element itself, so the statistics are the same function of the row whether the row was
-  // just produced here (fused reduction point) or is read back later (LayerNorm alone, recomputation).
-  float shift = RMS ? 0.f : xin[base];
-  if (!RMS && part) {
-    float z0 = part[base] + (bias ? bias[0] : 0.f);
-    if (peer) z0 += peer[base];
-    bool k0[4];
-    dropout_keep4(d, (uint64_t)(row0 + row) * h >> 2, k0);
-    if (k0[0]) shift += z0 * d.scale;
-  }
-  float s = 0.f, q = 0.f;
+  f32x4 v[NC], z[NC];
 #pragma unroll
-  for (int i = 0; i < NC; i++) {
-    const int c = tid + i * NT;
-    v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (c < nc) {
-      f32x4 x = *reinterpret_cast<const f32x4*>(xin + base + 4 * c);
-      if (part) {
-        f32x4 z = *reinterpret_cast<const f32x4*>(part + base + 4 * c);
-        if (peer) z += *reinterpret_cast<const f32x4*>(peer + base + 4 * c);
-        if (bias) z += *reinterpret_cast<const f32x4*>(bias + 4 * c);
-        bool k[4];
-        dropout_keep4(d, ((uint64_t)(row0 + row) * h >> 2) + c, k);
+  for (int i = 0; i < NC; i++) v[i] = row_load4(xin + base, chunk_off<T>(tid, i, nc));
+  if (part) {
 #pragma unroll
-        for (int j = 0; j < 4; j++) x[j] = k[j] ? x[j] + z[j] * d.scale : x[j];
-        *reinterpret_cast<f32x4*>(xo + base + 4 * c) = x;
-      }
-      v[i] = x;
+    for (int i = 0; i < NC; i++) z[i] = row_load4(part + base, chunk_off<T>(tid, i, nc));
+    if (peer)
 #pragma unroll
-      for (int j = 0; j < 4; j++) { float t = x[j] - shift; s += t; q += t * t; }
+      for (int i = 0; i < NC; i++) z[i] += row_load4(peer + base, chunk_off<T>(tid, i, nc));
+    if (bias)
+#pragma unroll
+      for (int i = 0; i < NC; i++) z[i] += row_load4(bias, chunk_off<T>(tid, i, nc));
+#pragma unroll
+    for (int i = 0; i < NC; i++) {
+      const int c = tid + i * T;
+      bool k[4];
+      dropout_keep4(d, ((uint64_t)(row0 + row) * h >> 2) + c, k);
+#pragma unroll
+      for (int j = 0; j < 4; j++) v[i][j] = k[j] ? v[i][j] + z[i][j] * d.scale : v[i][j];
+      if (c < nc) *reinterpret_cast<f32x4*>(xo + base + 4 * c) = v[i];
     }
   }
   if (!ln_out && !ln_f32) return;
-  block_sum2(s, q, red);
+  // mean and variance in ONE reduction: moments of (x - shift) with shift = first element of the row that is
+  // normalised (a value within a few standard deviations of the mean, so E[d^2] - E[d]^2 does not cancel).  That element
+  // is in the first thread's first chunk, whether the row was just produced here (fused reduction point) or is read back
+  // later (LayerNorm alone, recomputation).
+  float shift = 0.f;
+  if constexpr (!RMS) {
+    if (tid == 0) red[0] = v[0][0];
+    __syncthreads();
+    shift = red[0];  // block_sum2 starts with a barrier before it writes red
+  }
+  float s = 0.f, q = 0.f;
+#pragma unroll
+  for (int i = 0; i < NC; i++)
+    if (tid + i * T < nc)
+#pragma unroll
+      for (int j = 0; j < 4; j++) { float t = v[i][j] - shift; s += t; q += t * t; }
+  block_sum2<T / 64>(s, q, red);
   const float ms = RMS ? 0.f : s / h;
   const float mu = shift + ms;
   const float rstd = rsqrtf(fmaxf(q / h - ms * ms, 0.f) + eps);
@@ -108,7 +135,7 @@ __global__ __launch_bounds__(NT) void bdr_ln_kernel(const float* __restrict__ pa
   }
 #pragma unroll
   for (int i = 0; i < NC; i++) {
-    const int c = tid + i * NT;
+    const int c = tid + i * T;
     if (c < nc) {
       f32x4 gm = *reinterpret_cast<const f32x4*>(gamma + 4 * c);
       f32x4 bt = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -123,38 +150,63 @@ __global__ __launch_bounds__(NT) void bdr_ln_kernel(const float* __restrict__ pa
 }
 
 // ------------------------------------------------------------------------------------------------
+// Column sums of a workgroup.  T = 64: the waves of a workgroup hold sums over different rows, merged through LDS in the
+// order of the waves; otherwise a thread owns its columns and stores them.
+template <int NC, int T>
+__device__ __forceinline__ void store_colsums(const f32x4 (&acc)[NC], float* out, f32x4* lds, int nc) {
+  if constexpr (T == 64) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+#pragma unroll
+    for (int i = 0; i < NC; i++) lds[(wave * NC + i) * 64 + lane] = acc[i];
+    __syncthreads();
+    for (int c = threadIdx.x; c < nc; c += blockDim.x) {
+      f32x4 s = lds[c];
+      for (int w = 1; w < waves; w++) s += lds[w * NC * 64 + c];
+      *reinterpret_cast<f32x4*>(out + 4 * c) = s;
+    }
+    __syncthreads();
+  } else {
+#pragma unroll
+    for (int i = 0; i < NC; i++) {
+      const int c = threadIdx.x + i * T;
+      if (c < nc) *reinterpret_cast<f32x4*>(out + 4 * c) = acc[i];
+    }
+  }
+}
+// T = 64: up to 8 waves (of up to 256 registers), the rows of a workgroup dealt out to them
+constexpr int wg_max(int T) { return T == 64 ? 512 : T; }
+constexpr int colsum_lds(int NC, int T) { return T == 64 ? 8 * NC * 64 : 1; }
+
 // dz = keep * dyin * scale (bf16); partial column sums of the unrounded dz into scratch[group][h]
-template <int NC, int NT>
-__global__ __launch_bounds__(NT) void dropout_bwd_kernel(const float* __restrict__ dyin, uint16_t* __restrict__ dz,
+template <int NC, int T>
+__global__ __launch_bounds__(wg_max(T)) void dropout_bwd_kernel(const float* __restrict__ dyin, uint16_t* __restrict__ dz,
                                                          float* __restrict__ scratch, int rows, int h, DropCfg d,
                                                          int64_t row0) {
-  const int tid = threadIdx.x, nc = h >> 2;
+  __shared__ f32x4 merge[colsum_lds(NC, T)];
+  const int tid = threadIdx.x % T, nc = h >> 2;
+  const int step = gridDim.x * (T == 64 ? blockDim.x >> 6 : 1);
   f32x4 acc[NC];
 #pragma unroll
   for (int i = 0; i < NC; i++) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int row = blockIdx.x; row < rows; row += gridDim.x) {
+  for (int row = blockIdx.x + (T == 64 ? wave_index() * (int)gridDim.x : 0); row < rows; row += step) {
     const size_t base = (size_t)row * h;
+    f32x4 g[NC];
+#pragma unroll
+    for (int i = 0; i < NC; i++) g[i] = row_load4(dyin + base, chunk_off<T>(tid, i, nc));
 #pragma unroll
     for (int i = 0; i < NC; i++) {
-      const int c = tid + i * NT;
-      if (c < nc) {
-        f32x4 g = *reinterpret_cast<const f32x4*>(dyin + base + 4 * c);
-        bool k[4];
-        dropout_keep4(d, ((uint64_t)(row0 + row) * h >> 2) + c, k);
+      const int c = tid + i * T;
+      bool k[4];
+      dropout_keep4(d, ((uint64_t)(row0 + row) * h >> 2) + c, k);
 #pragma unroll
-        for (int j = 0; j < 4; j++) g[j] = k[j] ? g[j] * d.scale : 0.f;
-        store_bf16x4(dz + base + 4 * c, g[0], g[1], g[2], g[3]);
-        acc[i] += g;
+      for (int j = 0; j < 4; j++) g[i][j] = k[j] ? g[i][j] * d.scale : 0.f;
+      if (c < nc) {
+        store_bf16x4(dz + base + 4 * c, g[i][0], g[i][1], g[i][2], g[i][3]);
+        acc[i] += g[i];
       }
     }
   }
-  if (scratch) {
-#pragma unroll
-    for (int i = 0; i < NC; i++) {
-      const int c = tid + i * NT;
-      if (c < nc) *reinterpret_cast<f32x4*>(scratch + (size_t)blockIdx.x * h + 4 * c) = acc[i];
-    }
-  }
+  if (scratch) store_colsums<NC, T>(acc, scratch + (size_t)blockIdx.x * h, merge, nc);
 }
 
 // out[c] += sum over the partial rows src[g][c], g < groups, for every job of the list
@@ -199,57 +251,79 @@ __global__ __launch_bounds__(NT) void colsum_finalize_kernel(FinalizeArgs a) {
 // RMS: xhat = x * rstd, dxo = dres + rstd * (g*gamma - xhat * mean(g*gamma*xhat)), no dbeta
 // POST (post-LN layers): the residual gradient passes through the LayerNorm too: g = part + peer + dres (dres may be
 // NULL), dxo = rstd * (g*gamma - mean(g*gamma) - xhat * mean(g*gamma*xhat))
-template <int NC, int NT, bool RMS, bool POST>
-__global__ __launch_bounds__(NT) void layernorm_bwd_kernel(const float* __restrict__ part, const float* __restrict__ peer,
+// What bounds it: wide rows run at the rate of memory (8192 rows of 4096, 604 MB: 120 us); short rows were bound by the latency
+// of a row, with one row per workgroup under way.  Measured with the second stage, us, 256 threads per row -> a wave per row:
+// 512 x 512 14.6 -> 10.7, 2048 x 1024 19.6 -> 15.6, 4096 x 1024 33.9 -> 22.8; all of a row's loads at once, 128 x 12288 (also one row
+// per workgroup instead of two) 29.6 -> 18.6, 2048 x 12288 138 -> 104, 8192 x 4096 133 -> 126.
+template <int NC, int T, bool RMS, bool POST>
+__global__ __launch_bounds__(wg_max(T)) void layernorm_bwd_kernel(const float* __restrict__ part, const float* __restrict__ peer,
                                                            const float* __restrict__ dres, const float* __restrict__ x,
                                                            const float* __restrict__ mu, const float* __restrict__ rstd,
                                                            const float* __restrict__ gamma, float* __restrict__ dxo,
                                                            uint16_t* __restrict__ dz, float* __restrict__ scratch, int rows,
                                                            int h, DropCfg d, int64_t row0, int want_dbias, size_t gstride) {
-  __shared__ float red[2 * (NT / 64)];
-  const int tid = threadIdx.x, nc = h >> 2;
+  __shared__ float red[T == 64 ? 1 : 2 * (T / 64)];
+  __shared__ f32x4 merge[colsum_lds(NC, T)];
+  const int tid = threadIdx.x % T, nc = h >> 2;
+  const int step = gridDim.x * (T == 64 ? blockDim.x >> 6 : 1);
   f32x4 ag[NC], ab[NC], az[NC];
 #pragma unroll
   for (int i = 0; i < NC; i++) ag[i] = ab[i] = az[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int row = blockIdx.x; row < rows; row += gridDim.x) {
+  for (int row = blockIdx.x + (T == 64 ? wave_index() * (int)gridDim.x : 0); row < rows; row += step) {
     const size_t base = (size_t)row * h;
     const float m = RMS ? 0.f : mu[row], rs = rstd[row];
     f32x4 gg[NC], xh[NC], dr[NC];
     uint32_t kb[NC];  // keep bits of the row's dropout mask: integer work done while the row's loads are in flight
     float s1 = 0.f, s2 = 0.f;
+    auto load = [&](int i) {
+      const uint32_t c = chunk_off<T>(tid, i, nc);
+      gg[i] = row_load4(part + base, c);
+      xh[i] = row_load4(x + base, c);
+      if (!POST || dres) dr[i] = row_load4(dres + base, c);  // pre-LN: needed only after the reduction, fetched now
+      if (peer) gg[i] += row_load4(peer + base, c);
+    };
+    auto keep = [&](int i) {
+      if (!dz) return;
+      bool k[4];
+      dropout_keep4(d, ((uint64_t)(row0 + row) * h >> 2) + (tid + i * T), k);
+      kb[i] = (uint32_t)k[0] | ((uint32_t)k[1] << 1) | ((uint32_t)k[2] << 2) | ((uint32_t)k[3] << 3);
+    };
+    auto use = [&](int i, bool in) {
+      const f32x4 gm = row_load4(gamma, chunk_off<T>(tid, i, nc));
+      if (POST) gg[i] += dr[i];
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const float g = in ? gg[i][j] : 0.f;
+        xh[i][j] = in ? (xh[i][j] - m) * rs : 0.f;
+        ag[i][j] += g * xh[i][j];
+        ab[i][j] += g;
+        gg[i][j] = g * gm[j];
+        s1 += gg[i][j];
+        s2 += gg[i][j] * xh[i][j];
+      }
+    };
 #pragma unroll
     for (int i = 0; i < NC; i++) {
-      const int c = tid + i * NT;
       gg[i] = xh[i] = dr[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       kb[i] = 0u;
-      if (c < nc) {
-        f32x4 g = *reinterpret_cast<const f32x4*>(part + base + 4 * c);
-        if (peer) g += *reinterpret_cast<const f32x4*>(peer + base + 4 * c);
-        f32x4 xv = *reinterpret_cast<const f32x4*>(x + base + 4 * c);
-        if (!POST || dres) dr[i] = *reinterpret_cast<const f32x4*>(dres + base + 4 * c);   // pre-LN: needed only after the reduction, fetched now
-        if (POST) g += dr[i];
-        f32x4 gm = *reinterpret_cast<const f32x4*>(gamma + 4 * c);
-        if (dz) {
-          bool k[4];
-          dropout_keep4(d, ((uint64_t)(row0 + row) * h >> 2) + c, k);
-          kb[i] = (uint32_t)k[0] | ((uint32_t)k[1] << 1) | ((uint32_t)k[2] << 2) | ((uint32_t)k[3] << 3);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-          xh[i][j] = (xv[j] - m) * rs;
-          ag[i][j] += g[j] * xh[i][j];
-          ab[i][j] += g[j];
-          gg[i][j] = g[j] * gm[j];
-          s1 += gg[i][j];
-          s2 += gg[i][j] * xh[i][j];
-        }
-      }
     }
-    block_sum2<NT / 64>(s1, s2, red);
+    if constexpr (T == 1024 && NC > 2) {  // 128 registers a thread: a chunk at a time (all at once spills: 1024 x 16384 108 -> 174 us)
+#pragma unroll
+      for (int i = 0; i < NC; i++)
+        if (tid + i * T < nc) { load(i); keep(i); use(i, true); }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NC; i++) load(i);
+#pragma unroll
+      for (int i = 0; i < NC; i++) keep(i);
+#pragma unroll
+      for (int i = 0; i < NC; i++) use(i, tid + i * T < nc);
+    }
+    row_sum2<T>(s1, s2, red);
     const float m1 = RMS ? 0.f : s1 / h, m2 = s2 / h;
 #pragma unroll
     for (int i = 0; i < NC; i++) {
-      const int c = tid + i * NT;
+      const int c = tid + i * T;
       if (c < nc) {
         f32x4 o = POST ? f32x4{0.f, 0.f, 0.f, 0.f} : dr[i];
 #pragma unroll
@@ -264,36 +338,46 @@ __global__ __launch_bounds__(NT) void layernorm_bwd_kernel(const float* __restri
       }
     }
   }
-#pragma unroll
-  for (int i = 0; i < NC; i++) {
-    const int c = tid + i * NT;
-    if (c < nc) {
-      float* p = scratch + (size_t)blockIdx.x * h + 4 * c;
-      *reinterpret_cast<f32x4*>(p) = ag[i];
-      if (!RMS) *reinterpret_cast<f32x4*>(p + gstride) = ab[i];
-      if (dz && want_dbias) *reinterpret_cast<f32x4*>(p + 2 * gstride) = az[i];
-    }
-  }
+  float* p = scratch + (size_t)blockIdx.x * h;
+  store_colsums<NC, T>(ag, p, merge, nc);
+  if (!RMS) store_colsums<NC, T>(ab, p + gstride, merge, nc);
+  if (dz && want_dbias) store_colsums<NC, T>(az, p + 2 * gstride, merge, nc);
 }
 
 // ------------------------------------------------------------------------------------------------
-// partial column sums of a bf16 matrix; each thread owns 8 columns
+// Partial column sums of a bf16 matrix.  A lane owns 8 columns, a workgroup 512 columns; its four waves take every fourth of
+// the group's rows, four loads each in flight (8192 x 2048 with its second stage: one row after the other 13.3 us, this 10.4).
 __global__ __launch_bounds__(NT) void colsum_bf16_kernel(const uint16_t* __restrict__ a, int ld, int rows, int cols,
                                                          float* __restrict__ scratch) {
-  const int c = blockIdx.y * NT + threadIdx.x;  // 8-column chunk
-  if (c * 8 >= cols) return;
+  __shared__ f32x4 merge[4 * 2 * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int c = blockIdx.y * 64 + lane, nc = cols >> 3;  // 8-column chunk
+  const uint16_t* p = a + 8 * (size_t)min(c, nc - 1);
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int row = blockIdx.x; row < rows; row += gridDim.x) {
-    u32x4 v = *reinterpret_cast<const u32x4*>(a + (size_t)row * ld + 8 * c);
+  auto add = [&](const u32x4& v) {
 #pragma unroll
     for (int j = 0; j < 4; j++) {
       acc[2 * j] += bf16_bits_to_f32(v[j] & 0xffffu);
       acc[2 * j + 1] += bf16_bits_to_f32(v[j] >> 16);
     }
+  };
+  const int step = 4 * gridDim.x;
+  int row = blockIdx.x + wave * gridDim.x;
+  for (; row + 3 * step < rows; row += 4 * step) {
+    u32x4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = *reinterpret_cast<const u32x4*>(p + (size_t)(row + k * step) * ld);
+#pragma unroll
+    for (int k = 0; k < 4; k++) add(v[k]);
   }
-  float* p = scratch + (size_t)blockIdx.x * cols + 8 * c;
-  *reinterpret_cast<f32x4*>(p) = f32x4{acc[0], acc[1], acc[2], acc[3]};
-  *reinterpret_cast<f32x4*>(p + 4) = f32x4{acc[4], acc[5], acc[6], acc[7]};
+  for (; row < rows; row += step) add(*reinterpret_cast<const u32x4*>(p + (size_t)row * ld));
+  merge[wave * 128 + lane] = f32x4{acc[0], acc[1], acc[2], acc[3]};
+  merge[wave * 128 + 64 + lane] = f32x4{acc[4], acc[5], acc[6], acc[7]};
+  __syncthreads();
+  if (wave < 2 && c < nc) {  // wave w: the w-th four of each lane's eight columns
+    const f32x4* q = merge + wave * 64 + lane;
+    *reinterpret_cast<f32x4*>(scratch + (size_t)blockIdx.x * cols + 8 * c + 4 * wave) = (q[0] + q[128]) + (q[256] + q[384]);
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -353,54 +437,58 @@ __global__ __launch_bounds__(NT) void add3_kernel(const float* __restrict__ a, c
 }
 
 // row groups of a two-stage column reduction: about sixteen rows per group (few partial rows to write and to add up:
-// measured faster than eight), but at least one group per CU when the rows allow it, at most kColPartials groups
+// measured faster than eight), but one group per CU when the rows allow it, at most kColPartials groups
 int col_groups(int rows) {
   int g = rows / 16;
-  if (g < 256) g = rows / 2 < 256 ? rows / 2 : 256;
-  return g < 1 ? 1 : (g > kColPartials ? kColPartials : g);
-}
-
-int pick_nc(int h) {
-  const int nc = (h / 4 + NT - 1) / NT;
-  for (int c = 1; c <= 16; c *= 2)
-    if (nc <= c) return c;
-  return 0;
+  if (g < 256) g = rows < 256 ? rows : 256;
+  return g > kColPartials ? kColPartials : g;
 }
 
 bool check_h(int rows, int h, const char* who) {
-  if (rows <= 0 || h <= 0 || (h % 8) != 0 || pick_nc(h) == 0) {
+  if (rows <= 0 || h <= 0 || (h % 8) != 0 || h > 16384) {
     set_error("%s: rows=%d h=%d unsupported (h must be a multiple of 8, at most 16384)", who, rows, h);
     return false;
   }
   return true;
 }
 
-// backward kernels: 1024-thread workgroups for wide rows (more bytes in flight per row, fewer registers per thread)
+// Threads per row and 16-byte chunks per thread, from h alone, so that a row is reduced in the same order whatever rows it
+// comes with.
+#define OASES_ROW_CASE(T_, NC_, ...) { constexpr int T = T_, NC = NC_; __VA_ARGS__; break; }
+// Reduction point and LayerNorm forward (a row per workgroup): 256 threads up to h = 4096, 1024 beyond.  Both sides measured,
+// us (256 -> 1024 threads): 128 x 12288 15.3 -> 9.8, 4096 x 8192 98 -> 92, LayerNorm alone 8192 x 4096 33 -> 42.
+#define OASES_ROW_DISPATCH(H, ...)                                                   \
+  switch ((H) <= 4096 ? ((H) + 1023) / 1024 : 4 + ((H) + 4095) / 4096) {             \
+    case 1: OASES_ROW_CASE(256, 1, __VA_ARGS__)                                      \
+    case 2: OASES_ROW_CASE(256, 2, __VA_ARGS__)                                      \
+    case 3: OASES_ROW_CASE(256, 3, __VA_ARGS__)                                      \
+    case 4: OASES_ROW_CASE(256, 4, __VA_ARGS__)                                      \
+    case 6: OASES_ROW_CASE(1024, 2, __VA_ARGS__)                                     \
+    case 7: OASES_ROW_CASE(1024, 3, __VA_ARGS__)                                     \
+    default: OASES_ROW_CASE(1024, 4, __VA_ARGS__)                                    \
+  }
+// Column-reducing backward kernels: a wave up to h = 1024, 256 threads below 4096, 1024 threads from there on
 #define OASES_BWD_DISPATCH(H, ...)                                                   \
-  if ((H) >= 4096) {                                                                 \
-    constexpr int NTHR = 1024;                                                       \
-    switch (((H) / 4 + NTHR - 1) / NTHR) {                                           \
-      case 1: { constexpr int NC = 1; __VA_ARGS__; break; }                          \
-      case 2: { constexpr int NC = 2; __VA_ARGS__; break; }                          \
-      default: { constexpr int NC = 4; __VA_ARGS__; break; }                         \
-    }                                                                                \
-  } else {                                                                           \
-    constexpr int NTHR = 256;                                                        \
-    switch (pick_nc(H)) {                                                            \
-      case 1: { constexpr int NC = 1; __VA_ARGS__; break; }                          \
-      case 2: { constexpr int NC = 2; __VA_ARGS__; break; }                          \
-      default: { constexpr int NC = 4; __VA_ARGS__; break; }                         \
-    }                                                                                \
+  switch ((H) <= 1024 ? ((H) + 255) / 256 : (H) < 4096 ? 4 + ((H) + 1023) / 1024 : 8 + ((H) + 4095) / 4096) { \
+    case 1: OASES_ROW_CASE(64, 1, __VA_ARGS__)                                       \
+    case 2: OASES_ROW_CASE(64, 2, __VA_ARGS__)                                       \
+    case 3: OASES_ROW_CASE(64, 3, __VA_ARGS__)                                       \
+    case 4: OASES_ROW_CASE(64, 4, __VA_ARGS__)                                       \
+    case 6: OASES_ROW_CASE(256, 2, __VA_ARGS__)                                      \
+    case 7: OASES_ROW_CASE(256, 3, __VA_ARGS__)                                      \
+    case 8: OASES_ROW_CASE(256, 4, __VA_ARGS__)                                      \
+    case 9: OASES_ROW_CASE(1024, 1, __VA_ARGS__)                                     \
+    case 10: OASES_ROW_CASE(1024, 2, __VA_ARGS__)                                    \
+    case 11: OASES_ROW_CASE(1024, 3, __VA_ARGS__)                                    \
+    default: OASES_ROW_CASE(1024, 4, __VA_ARGS__)                                    \
   }
 
-#define OASES_NC_DISPATCH(NCV, ...)          \
-  switch (NCV) {                             \
-    case 1: { constexpr int NC = 1; __VA_ARGS__; break; }   \
-    case 2: { constexpr int NC = 2; __VA_ARGS__; break; }   \
-    case 4: { constexpr int NC = 4; __VA_ARGS__; break; }   \
-    case 8: { constexpr int NC = 8; __VA_ARGS__; break; }   \
-    default: { constexpr int NC = 16; __VA_ARGS__; break; } \
-  }
+// workgroup size of a column-reducing row kernel: a wave per row of the group (4 or 8 waves) where a row is a wave's work
+int row_threads(int T, int rows, int groups) {
+  if (T > 64) return T;
+  const int per = (rows + groups - 1) / groups;
+  return per > 4 ? 512 : 256;
+}
 
 }  // namespace
 
@@ -434,13 +522,11 @@ int launch_bdr_ln(const float* part, const float* peer, const float* bias, const
     set_error("bias_dropout_residual_ln: NULL argument");
     return OASES_ENULL;
   }
-  if (rms) {
-    OASES_NC_DISPATCH(pick_nc(h), hipLaunchKernelGGL((bdr_ln_kernel<NC, true>), dim3(rows), dim3(NT), 0, s, part, peer, bias, xin, xo,
-                                                     gamma, beta, (uint16_t*)ln_out, mu, rstd, h, eps, d, row0, ln_f32));
-  } else {
-    OASES_NC_DISPATCH(pick_nc(h), hipLaunchKernelGGL((bdr_ln_kernel<NC, false>), dim3(rows), dim3(NT), 0, s, part, peer, bias, xin, xo,
-                                                     gamma, beta, (uint16_t*)ln_out, mu, rstd, h, eps, d, row0, ln_f32));
-  }
+#define OASES_BDR_LN(RMS)                                                                                                       \
+  OASES_ROW_DISPATCH(h, hipLaunchKernelGGL((bdr_ln_kernel<NC, T, RMS>), dim3(rows), dim3(T), 0, s, part, peer, bias, xin, xo, gamma, \
+                                           beta, (uint16_t*)ln_out, mu, rstd, h, eps, d, row0, ln_f32))
+  if (rms) { OASES_BDR_LN(true); } else { OASES_BDR_LN(false); }
+#undef OASES_BDR_LN
   OASES_LAUNCH_CHECK("bdr_ln_kernel");
   return 0;
 }
@@ -484,8 +570,8 @@ int launch_dropout_bwd(const float* dyin, void* dz, float* dbias, int rows, int 
   if (!check_h(rows, h, "dropout_bwd")) return OASES_EINVAL;
   if (!dyin || !dz || (dbias && !scratch)) { set_error("dropout_bwd: NULL argument"); return OASES_ENULL; }
   const int groups = col_groups(rows);
-  OASES_BWD_DISPATCH(h, hipLaunchKernelGGL((dropout_bwd_kernel<NC, NTHR>), dim3(groups), dim3(NTHR), 0, s, dyin, (uint16_t*)dz,
-                                           dbias ? scratch : nullptr, rows, h, d, row0));
+  OASES_BWD_DISPATCH(h, hipLaunchKernelGGL((dropout_bwd_kernel<NC, T>), dim3(groups), dim3(row_threads(T, rows, groups)), 0, s, dyin,
+                                           (uint16_t*)dz, dbias ? scratch : nullptr, rows, h, d, row0));
   OASES_LAUNCH_CHECK("dropout_bwd_kernel");
   if (dbias) return finish_colsums(sink, scratch, 0, dbias, nullptr, nullptr, groups, h, s);
   return 0;
@@ -505,16 +591,12 @@ int launch_layernorm_bwd(const float* part, const float* peer, const float* dres
   const int want_dbias = dz && dbias;
   // distance between the three arrays of partial rows: behind one another for this call alone, or as the sink lays them out
   const size_t kstride = sink ? sink->kstride : (size_t)groups * h;
-  if (rms) {
-    OASES_BWD_DISPATCH(h, hipLaunchKernelGGL((layernorm_bwd_kernel<NC, NTHR, true, false>), dim3(groups), dim3(NTHR), 0, s, part, peer, dres, x,
-                                             mu, rstd, gamma, dxo, (uint16_t*)dz, scratch, rows, h, d, row0, want_dbias, kstride));
-  } else if (post) {
-    OASES_BWD_DISPATCH(h, hipLaunchKernelGGL((layernorm_bwd_kernel<NC, NTHR, false, true>), dim3(groups), dim3(NTHR), 0, s, part, peer, dres, x,
-                                             mu, rstd, gamma, dxo, (uint16_t*)dz, scratch, rows, h, d, row0, want_dbias, kstride));
-  } else {
-    OASES_BWD_DISPATCH(h, hipLaunchKernelGGL((layernorm_bwd_kernel<NC, NTHR, false, false>), dim3(groups), dim3(NTHR), 0, s, part, peer, dres, x,
-                                             mu, rstd, gamma, dxo, (uint16_t*)dz, scratch, rows, h, d, row0, want_dbias, kstride));
-  }
+#define OASES_LN_BWD(RMS, POST)                                                                                                       \
+  OASES_BWD_DISPATCH(h, hipLaunchKernelGGL((layernorm_bwd_kernel<NC, T, RMS, POST>), dim3(groups), dim3(row_threads(T, rows, groups)), \
+                                           0, s, part, peer, dres, x, mu, rstd, gamma, dxo, (uint16_t*)dz, scratch, rows, h, d, row0,   \
+                                           want_dbias, kstride))
+  if (rms) { OASES_LN_BWD(true, false); } else if (post) { OASES_LN_BWD(false, true); } else { OASES_LN_BWD(false, false); }
+#undef OASES_LN_BWD
   OASES_LAUNCH_CHECK("layernorm_bwd_kernel");
   return finish_colsums(sink, scratch, kstride, dgamma, rms ? nullptr : dbeta, want_dbias ? dbias : nullptr, groups, h, s);
 }
@@ -563,7 +645,7 @@ int launch_colsum_bf16(const void* a, int ld, int rows, int cols, float* out, fl
   if (!a || !out || !scratch) { set_error("colsum_bf16: NULL argument"); return OASES_ENULL; }
   if (rows <= 0 || cols <= 0 || cols % 8 || ld % 8 || ld < cols) { set_error("colsum_bf16: bad shape"); return OASES_EINVAL; }
   const int groups = col_groups(rows);
-  hipLaunchKernelGGL(colsum_bf16_kernel, dim3(groups, (cols / 8 + NT - 1) / NT), dim3(NT), 0, s, (const uint16_t*)a, ld, rows,
+  hipLaunchKernelGGL(colsum_bf16_kernel, dim3(groups, (cols / 8 + 63) / 64), dim3(NT), 0, s, (const uint16_t*)a, ld, rows,
                      cols, scratch);
   OASES_LAUNCH_CHECK("colsum_bf16_kernel");
   return finish_colsums(sink, scratch, 0, out, nullptr, nullptr, groups, cols, s);

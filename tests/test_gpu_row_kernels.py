@@ -1,0 +1,102 @@
+"""Row kernels at the widths where their split changes: a wave per row up to 1024 columns, 256 threads below 4096, 1024 threads
+beyond (LayerNorm forward: 256 up to 4096), with whole and ragged chunks, and at few and odd numbers of rows."""
+import pytest
+import torch
+
+from tests.util import rel_err
+
+pytestmark = pytest.mark.gpu
+
+WIDTHS = [8, 248, 256, 264, 520, 776, 1016, 1024, 1032, 2048, 2056, 3080, 4088, 4096, 4104, 8192, 8200, 12288, 16384]
+
+
+def _rounds_to_bf16(got, ref):
+    """Every element within half a unit of the last of bf16's eight bits (2^-8 of its value at most), plus the fp32 error."""
+    rms = float(ref.pow(2).mean().sqrt())
+    return bool(((got.double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 4e-5 * rms).all())
+
+
+def _ptr(t):
+    return t.data_ptr() if t is not None else None
+
+
+@pytest.mark.parametrize("h", WIDTHS)
+@pytest.mark.parametrize("rows", [1, 7, 259, 1300])
+def test_backward_row_kernels_against_fp64(h, rows):
+    from paper_2305_16121_amd import binding as B
+    if rows * h > 6_000_000:
+        rows = 300
+    gen = torch.Generator(device="cuda").manual_seed(h * 7 + rows)
+    n = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    part, peer, dres, x = n(rows, h), n(rows, h), n(rows, h), n(rows, h) * 2 + 0.5
+    gamma = n(h) * 0.1 + 1
+    mu, rstd = x.mean(1), 1.0 / torch.sqrt(x.var(1, unbiased=False) + 1e-5)
+    dxo = torch.full_like(x, float("nan"))
+    dz = torch.full((rows, h), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sums = torch.ones(3, h, device="cuda")                    # accumulated into
+    scratch = torch.full((3 * 1024 * h,), float("nan"), device="cuda")
+    mask = torch.empty(rows, h, dtype=torch.uint8, device="cuda")
+    seed, layer, site, row0, p = 5, 3, 1, 40, 0.25
+    B.check(B.lib.oases_op_dropout_mask(_ptr(mask), seed, layer, site, row0, rows, h, p, None))
+    B.check(B.lib.oases_op_layernorm_bwd(_ptr(part), _ptr(peer), _ptr(dres), _ptr(x), _ptr(mu), _ptr(rstd), _ptr(gamma), _ptr(dxo),
+                                         _ptr(sums[0]), _ptr(sums[1]), _ptr(dz), _ptr(sums[2]), rows, h, seed, layer, site, row0, p,
+                                         _ptr(scratch), None))
+    torch.cuda.synchronize()
+    d = torch.float64
+    g, xh = part.to(d) + peer.to(d), (x.to(d) - mu.to(d)[:, None]) * rstd.to(d)[:, None]
+    gg = g * gamma.to(d)
+    ref = dres.to(d) + rstd.to(d)[:, None] * (gg - gg.mean(1, keepdim=True) - xh * (gg * xh).mean(1, keepdim=True))
+    refz = torch.where(mask.bool(), ref / (1 - p), torch.zeros_like(ref))
+    # fp32 arithmetic of sums of at most 16384 (row) and 1300 (column) terms: below 2e-5 of the root mean square per element
+    assert rel_err(dxo, ref) < 2e-5
+    assert _rounds_to_bf16(dz, refz)
+    for got, want in ((sums[0], (g * xh).sum(0)), (sums[1], g.sum(0)), (sums[2], refz.sum(0))):
+        assert rel_err(got, want + 1) < 2e-5
+    # dropout backward of the same rows
+    dz2 = torch.full_like(dz, float("nan"))
+    db = torch.ones(h, device="cuda")
+    B.check(B.lib.oases_op_dropout_bwd(_ptr(part), _ptr(dz2), _ptr(db), rows, h, seed, layer, site, row0, p, _ptr(scratch), None))
+    torch.cuda.synchronize()
+    refz = torch.where(mask.bool(), part.to(d) / (1 - p), torch.zeros_like(ref))
+    assert _rounds_to_bf16(dz2, refz) and rel_err(db, refz.sum(0) + 1) < 2e-5
+
+
+@pytest.mark.parametrize("h", WIDTHS)
+@pytest.mark.parametrize("rows", [1, 37])
+def test_forward_row_kernels_against_fp64(h, rows):
+    from paper_2305_16121_amd import binding as B
+    gen = torch.Generator(device="cuda").manual_seed(h * 3 + rows)
+    n = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    part, peer, xin, bias, gamma, beta = n(rows, h), n(rows, h), n(rows, h) * 2 + 3, n(h), n(h), n(h)
+    xo, ln = torch.full_like(xin, float("nan")), torch.full((rows, h), float("nan"), dtype=torch.bfloat16, device="cuda")
+    mu, rstd = torch.empty(rows, device="cuda"), torch.empty(rows, device="cuda")
+    mask = torch.empty(rows, h, dtype=torch.uint8, device="cuda")
+    B.check(B.lib.oases_op_dropout_mask(_ptr(mask), 9, 1, 0, 8, rows, h, 0.25, None))
+    B.check(B.lib.oases_op_bias_dropout_residual_ln(_ptr(part), _ptr(peer), _ptr(bias), _ptr(xin), _ptr(xo), _ptr(gamma), _ptr(beta),
+                                                    _ptr(ln), _ptr(mu), _ptr(rstd), rows, h, 1e-5, 9, 1, 0, 8, 0.25, None))
+    torch.cuda.synchronize()
+    d = torch.float64
+    z = part.to(d) + peer.to(d) + bias.to(d)
+    ref = xin.to(d) + torch.where(mask.bool(), z / 0.75, torch.zeros_like(z))
+    mean, var = ref.mean(1, keepdim=True), ref.var(1, unbiased=False, keepdim=True)
+    want = (ref - mean) / torch.sqrt(var + 1e-5) * gamma.to(d) + beta.to(d)
+    assert rel_err(xo, ref) < 2e-5 and rel_err(mu, mean[:, 0]) < 2e-5 and rel_err(rstd, 1 / torch.sqrt(var[:, 0] + 1e-5)) < 2e-5
+    assert _rounds_to_bf16(ln, want)
+    # the same row read back gives the same statistics and the same output, bit for bit
+    ln2, mu2, rstd2 = torch.empty_like(ln), torch.empty_like(mu), torch.empty_like(rstd)
+    B.check(B.lib.oases_op_layernorm_fwd(_ptr(xo), _ptr(gamma), _ptr(beta), _ptr(ln2), _ptr(mu2), _ptr(rstd2), rows, h, 1e-5, None))
+    torch.cuda.synchronize()
+    assert torch.equal(ln, ln2) and torch.equal(mu, mu2) and torch.equal(rstd, rstd2)
+
+
+@pytest.mark.parametrize("cols", [8, 504, 512, 520, 1024, 1376])
+@pytest.mark.parametrize("rows", [1, 5, 1021, 8200])
+def test_column_sums_against_fp64(rows, cols):
+    from paper_2305_16121_amd import binding as B
+    gen = torch.Generator(device="cuda").manual_seed(rows + cols)
+    a = torch.randn(rows, cols + 16, generator=gen, device="cuda").to(torch.bfloat16)
+    out = torch.ones(cols, device="cuda")
+    scratch = torch.full((1024 * cols,), float("nan"), device="cuda")
+    B.check(B.lib.oases_op_colsum_bf16(_ptr(a), cols + 16, rows, cols, _ptr(out), _ptr(scratch), None))
+    torch.cuda.synchronize()
+    assert rel_err(out, a[:, :cols].double().sum(0) + 1) < 2e-5
