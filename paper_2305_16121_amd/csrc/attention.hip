@@ -1,11 +1,10 @@
 // Flash-style attention for the local heads of one TMP rank (gfx950, bf16 MFMA, fp32 softmax).
 //
-// Work decomposition.  A workgroup owns 32 rows of one (sequence, head): 32 queries (forward, dQ) or 32 keys
-// (dK/dV).  Its four waves split the reduction range -- the 32-row key tiles a query block sees, or the 32-row
-// query tiles that see a key block -- round-robin, each wave staging its own tiles in a private slice of LDS, so
-// the main loops need no workgroup barrier; the four partial results meet once, through LDS, at the end.  This
-// keeps every SIMD busy on a workload that has few (query, head) rows per sub-batch and shortens the longest
-// causal row of work fourfold.
+// Work decomposition.  A workgroup owns one or two groups of 32 rows of one (sequence, head): queries (forward, dQ) or keys
+// (dK/dV); its four waves are (row group) x (part of the reduction range).  The workgroup stages the tiles of the reduction
+// range -- keys a query block sees, or queries that see a key block -- for all its waves, and the partial results of a
+// row group meet once, through LDS, at the end.  Few blocks, and dK/dV with 128 columns, keep a form in which each wave stages
+// tiles of its own (see below).
 //
 // Forward and dQ compute the TRANSPOSED score tile S^T = K*Q^T with v_mfma_f32_32x32x16_bf16, so that a lane owns
 // one query (accumulator column l%32) and 16 keys of the tile: the online softmax is lane-local except for one
@@ -36,8 +35,9 @@ struct AttnArgs {
   float* delta;          // [batch, heads, seq]
   int seq, heads, ld, hp;
   int seq0;    // first sequence of the row range
-  int pos0;    // first position (within each sequence) of the row range
-  int npos;    // positions per sequence in the row range
+  int first;   // first position (within each sequence) of the row range
+  int pos0;    // the same rounded down to a multiple of four, where the blocks start: a 4 x 4 block of the dropout mask then belongs to one quad of lanes
+  int npos;    // positions per sequence from pos0 to the end of the row range
   int blocks;  // 32-row blocks per sequence
   int nseq;    // sequences in the row range
   float scale, scale_log2;
@@ -176,137 +176,290 @@ __device__ __forceinline__ void combine4(const f32x16* acc, float* lds_part, int
   }
 }
 
+// ---- tiles shared by the workgroup ----------------------------------------------------------------
+// A tile of R rows x D bf16 in LDS without padding: 16-byte chunk c of row r sits at slot c ^ f(r).  f is a bijection over
+// the rows that fill the 64 banks once (16 rows of 256 bytes, 8 pairs of rows of 128 bytes), so 16 consecutive rows read at one
+// chunk (ds_read_b128) fall on 16 places; its two high bits come from the low bits of the row, so the 4 rows x 4 chunks of a
+// transpose read do too.
+template <int D>
+__device__ __forceinline__ int tile_f(int r) {
+  if (D == 128) return ((r & 3) << 2) | ((r >> 2) & 3);
+  const int u = (r >> 1) & 7;
+  return ((u & 1) << 2) | (u >> 1);
+}
+template <int D>
+__device__ __forceinline__ int tile_chunk(int r, int c) { return r * (2 * D) + ((c ^ tile_f<D>(r)) << 4); }
+
+// all 256 threads: R rows from row r0 of a [*, D] slice (row stride ld elements) -> registers; rows outside [rmin, rmax) read as zero (their
+// probabilities are masked to 0, but 0 times what memory holds there may be NaN)
+template <int D, int R>
+struct SharedTile {
+  static constexpr int bytes = R * 2 * D;
+  static constexpr int cpr = D / 8, per = R * cpr / NT, rows_per_pass = NT / cpr;
+  u32x4 v[per];
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ base, int ld, int r0, int rmin, int rmax, int tid) {
+    const int row = tid / cpr, cc = tid % cpr;
+    if (r0 >= rmin && r0 + R <= rmax) {
+      const char* sb = reinterpret_cast<const char*>(base) + (size_t)r0 * ld * 2;
+      const uint32_t voff = (uint32_t)((row * ld + cc * 8) * 2);
+#pragma unroll
+      for (int i = 0; i < per; i++) v[i] = *reinterpret_cast<const u32x4*>(sb + (size_t)i * rows_per_pass * ld * 2 + voff);
+    } else {
+#pragma unroll
+      for (int i = 0; i < per; i++) {
+        const int r = r0 + row + i * rows_per_pass;
+        const u32x4 x = *reinterpret_cast<const u32x4*>(base + (size_t)max(min(r, rmax - 1), rmin) * ld + cc * 8);
+        v[i] = r >= rmin && r < rmax ? x : u32x4{0u, 0u, 0u, 0u};
+      }
+    }
+  }
+  __device__ __forceinline__ void store(char* lds, int tid) const {
+    const int row = tid / cpr, cc = tid % cpr;
+#pragma unroll
+    for (int i = 0; i < per; i++) *reinterpret_cast<u32x4*>(lds + tile_chunk<D>(row + i * rows_per_pass, cc)) = v[i];
+  }
+};
+// operand fragments of 32 tile rows from row r0 (a multiple of 32), as kc_frag and mc_frag above
+template <int D>
+__device__ __forceinline__ bf16x8 tile_kc(const char* lds, int r0, int ks, int lane) {
+  return *reinterpret_cast<const bf16x8*>(lds + r0 * (2 * D) + tile_chunk<D>(lane & 31, ks * 2 + (lane >> 5)));
+}
+template <int D>
+__device__ __forceinline__ bf16x8 tile_mc(const char* lds, int r0, int j, int dt, int lane) {
+  const int kr = 4 * (lane >> 5) + ((lane & 15) >> 2), c = 4 * dt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+  const char* p = lds + (r0 + 16 * j) * (2 * D) + 8 * (lane & 1);
+  short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((OASES_LDS short4v*)(p + tile_chunk<D>(kr, c)));
+  short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((OASES_LDS short4v*)(p + tile_chunk<D>(kr + 8, c)));
+  typedef short short8v __attribute__((ext_vector_type(8)));
+  short8v v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8, v);
+}
+// barrier behind LDS accesses only: global loads into registers stay in flight (__syncthreads would wait for them)
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Workgroup id -> ((sequence, head) pair, block), as decode_block, with the long blocks first in even groups of eight pairs and
+// last in odd ones: of two workgroups that share a CU from the start one is long and one short.
+__device__ __forceinline__ void decode_block_serpentine(int wg, int pairs, int blocks, int& pair, int& blk) {
+  const int per_group = 8 * blocks, gi = wg / per_group;
+  decode_block(wg, pairs, blocks, pair, blk);
+  if (gi & 1) blk = blocks - 1 - blk;
+}
+
+// A value of the wave's lower half (lanes 0..31) and of its upper half, in every lane l of either: those of lanes l % 32 and
+// l % 32 + 32.  (The two operands are made distinct: given one value twice, the compiler takes both results for the same.)
+__device__ __forceinline__ void wave_halves(float v, float& lo, float& hi) {
+  uint32_t u = __builtin_bit_cast(uint32_t, v), w = u;
+  asm volatile("" : "+v"(w));
+  const auto r = __builtin_amdgcn_permlane32_swap(u, w, false, false);
+  lo = __builtin_bit_cast(float, (uint32_t)r[0]);
+  hi = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ float half_max(float v) { float a, b; wave_halves(v, a, b); return fmaxf(a, b); }
+__device__ __forceinline__ float half_sum(float v) { float a, b; wave_halves(v, a, b); return a + b; }
+// at the head of a rarely taken branch: keeps the compiler from running its body every time and selecting
+#define OASES_RARE() asm volatile("")
+
+// value of lane i of every four lanes
+template <int I>
+__device__ __forceinline__ uint32_t quad_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, I * 0x55, 0xf, 0xf, true); }
+
+// Dropout words of four 4-key groups (keys k0 + 8 i, i = 0..3) for this lane's query q.  The four lanes of a quad hold the four
+// queries of one 4 x 4 block row, so each computes the block of one group and they trade words (a Philox call is some 40
+// multiplications at a quarter of the rate; one instead of four).
+__device__ __forceinline__ void drop_words_of_query(const AttnArgs& a, uint32_t (&w)[4], int k0, int q, uint32_t bh, int lane) {
+  const int j = lane & 3;
+  const Philox4 m = attn_drop_block(a, (uint32_t)(k0 + 8 * j) >> 2, (uint32_t)q >> 2, bh);
+#define OASES_QUAD(i)                                                                                              \
+  {                                                                                                                \
+    const uint32_t x0 = quad_lane<i>(m.v[0]), x1 = quad_lane<i>(m.v[1]), x2 = quad_lane<i>(m.v[2]), x3 = quad_lane<i>(m.v[3]); \
+    w[i] = j == 0 ? x0 : j == 1 ? x1 : j == 2 ? x2 : x3;                                                           \
+  }
+  OASES_QUAD(0) OASES_QUAD(1) OASES_QUAD(2) OASES_QUAD(3)
+#undef OASES_QUAD
+}
+
 // =================================================================================================
-// forward
+// forward: QG groups of 32 queries x KG key parts, one wave each (QG * KG = 4).  What bounds it: the chain of a tile (LDS reads,
+// eight dependent MFMAs, the softmax, eight more) with two waves on a SIMD to cover for each other, and LDS bandwidth, 96 KB per
+// 64 x 64 scores at D = 128.  Measured, tiles private to a wave -> this, us: 8x1024x8x64 (batch x seq x heads x columns, causal)
+// 35.2 -> 28.5, 4x2048x4x128 45.9 -> 36.9, 2x2048x4x128 32.5 -> 28.5, 4x1024x12x128 not causal 71.2 -> 43.4.  The workgroup stages 32 KG keys of K and V at
+// a time for all its waves, two stages: the next tile goes from registers to LDS while this one is multiplied, and the tile
+// behind it is on its way from memory.  A wave keeps (m, l, O) of its queries over its part of the keys; the KG partial
+// results of a query group meet once, through LDS, at the end.
 // =================================================================================================
-template <int D, bool CAUSAL, bool DROP>
+template <int D, int QG, int KG>
+struct FwdLds {
+  static constexpr int E = D / 2;  // accumulator elements of a lane
+  static constexpr int NS = D == 128 && KG == 4 ? 1 : 2;  // stages; 128 keys of 128 columns take 64 KB: one, so that two workgroups fit a CU
+  static constexpr int kTile = SharedTile<D, 32 * KG>::bytes, kStages = 2 * NS * kTile, kPart = KG > 1 ? 4 * E * 64 * 4 : 0;
+  static constexpr int bytes = (kStages > kPart ? kStages : kPart) + 1024;  // + m[4][32], l[4][32]
+};
+template <int D, int QG, int KG, bool CAUSAL, bool DROP>
 __global__ __launch_bounds__(NT, 2) void attn_fwd_kernel(AttnArgs a) {
-  constexpr int KS = D / 16, DT = D / 32, E = DT * 16;
-  constexpr int kStageBytes = 4 * 2 * AT<D>::bytes;
-  constexpr int kPartBytes = 4 * E * 64 * 4;
-  __shared__ __attribute__((aligned(16))) char lds[(kStageBytes > kPartBytes ? kStageBytes : kPartBytes) + 1024];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
+  constexpr int KS = D / 16, DT = D / 32, E = DT * 16, BK = 32 * KG;
+  using L = FwdLds<D, QG, KG>;
+  __shared__ __attribute__((aligned(16))) char lds[L::bytes];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5;
+  const int qg = wave % QG, kg = wave / QG;
   int pair, blk;
-  decode_block(blockIdx.x, a.nseq * a.heads, a.blocks, pair, blk);
+  decode_block_serpentine(blockIdx.x, a.nseq * a.heads, a.blocks, pair, blk);
   const int sq = pair / a.heads, head = pair % a.heads, qb = a.blocks - 1 - blk;  // long rows first
   const int seq_idx = a.seq0 + sq;
-  const int q_begin = a.pos0 + qb * 32;
-  const int q_end = min(a.pos0 + a.npos, q_begin + 32);
+  const int wg_end = min(a.pos0 + a.npos, a.pos0 + (qb + 1) * 32 * QG);   // end of the workgroup's queries
+  const int q_begin = a.pos0 + (qb * QG + qg) * 32;
+  const int q_end = min(wg_end, q_begin + 32);
   const size_t rowbase = (size_t)seq_idx * a.seq;
   const uint16_t* Qp = a.qkv + rowbase * a.ld + head * D;
   const uint16_t* Kp = Qp + a.hp;
   const uint16_t* Vp = Qp + 2 * a.hp;
   const int qpos = q_begin + (lane & 31);
-  const bool qok = qpos < q_end;
+  const bool qok = qpos < q_end && qpos >= a.first;
 
+  const int kv_end = CAUSAL ? wg_end : a.seq;
+  const int nt = (kv_end + BK - 1) / BK;
+  SharedTile<D, BK> rk, rv;
+  rk.load(Kp, a.ld, 0, 0, kv_end, tid);
+  rv.load(Vp, a.ld, 0, 0, kv_end, tid);
   bf16x8 qf[KS];
   load_row_frags<D>(qf, Qp + (size_t)qpos * a.ld, qok, g);
   f32x16 o[DT];
 #pragma unroll
   for (int i = 0; i < DT; i++) o[i] = zero16();
   float m = -INFINITY, l = 0.f;
-
-  const int kv_end = CAUSAL ? q_end : a.seq;
-  const int nt = (kv_end + 31) / 32;
-  char* lk = lds + wave * 2 * AT<D>::bytes;
-  char* lv = lk + AT<D>::bytes;
-  u32x4 rk[AT<D>::per_lane], rv[AT<D>::per_lane];
-  if (wave < nt) {
-    wave_load<D>(rk, Kp, a.ld, wave * 32, 0, kv_end, lane);
-    wave_load<D>(rv, Vp, a.ld, wave * 32, 0, kv_end, lane);
+  rk.store(lds, tid);
+  rv.store(lds + L::kTile, tid);
+  if (nt > 1) {
+    rk.load(Kp, a.ld, BK, 0, kv_end, tid);
+    rv.load(Vp, a.ld, BK, 0, kv_end, tid);
   }
-  for (int t = wave; t < nt; t += 4) {
-    const int kv0 = t * 32;
-    wave_store<D>(rk, lk, lane);  // LDS operations of one wave execute in order: no barrier for a private tile
-    wave_store<D>(rv, lv, lane);
-    if (t + 4 < nt) {
-      wave_load<D>(rk, Kp, a.ld, kv0 + 128, 0, kv_end, lane);
-      wave_load<D>(rv, Vp, a.ld, kv0 + 128, 0, kv_end, lane);
-    }
-    f32x16 s = zero16(), s1 = zero16();
-#pragma unroll
-    for (int ks = 0; ks < KS; ks += 2) {  // two independent accumulation chains
-      s = MFMA(kc_frag<D>(lk, ks, lane), qf[ks], s);
-      s1 = MFMA(kc_frag<D>(lk, ks + 1, lane), qf[ks + 1], s1);
-    }
-    const bool need_mask = (kv0 + 32 > a.seq) || (CAUSAL && kv0 + 31 > q_begin);
-    float mloc = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 16; i++) {
-      float v = (s[i] + s1[i]) * a.scale_log2;
-      if (need_mask) {
-        int kvpos = kv0 + 8 * (i >> 2) + 4 * g + (i & 3);
-        if (kvpos >= a.seq || (CAUSAL && kvpos > qpos)) v = -INFINITY;
+  lds_barrier();
+  for (int t = 0; t < nt; t++) {
+    const char* lk = lds + (L::NS == 2 ? (t & 1) * 2 * L::kTile : 0);
+    const char* lv = lk + L::kTile;
+    auto park_next = [&]() {  // tile t + 1, into a stage that every wave has read for the last time before the last barrier
+      if (t + 1 >= nt) return;
+      char* nk = lds + (L::NS == 2 ? ((t & 1) ^ 1) * 2 * L::kTile : 0);
+      rk.store(nk, tid);
+      rv.store(nk + L::kTile, tid);
+      if (t + 2 < nt) {
+        rk.load(Kp, a.ld, (t + 2) * BK, 0, kv_end, tid);
+        rv.load(Vp, a.ld, (t + 2) * BK, 0, kv_end, tid);
       }
-      s[i] = v;
-      mloc = fmaxf(mloc, v);
-    }
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
-    // wave 0 starts with tile 0, which holds key 0, visible to every query; a later wave may start on a tile that is
-    // masked for some of its queries: keep the running maximum finite there so that exp2 never sees inf - inf
-    const float mnew = fmaxf(fmaxf(m, mloc), -1e30f);
-    const float alpha = __builtin_amdgcn_exp2f(m - mnew);
-    float psum = 0.f;
+    };
+    if constexpr (L::NS == 2) park_next();
+    const int kv0 = t * BK + 32 * kg;
+    if (kv0 < a.seq && !(CAUSAL && kv0 >= q_end)) {  // uniform over the wave: some key is visible to some query
+      f32x16 s = zero16();
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
-      float p = __builtin_amdgcn_exp2f(s[i] - mnew);
-      s[i] = p;
-      psum += p;
-    }
-    l = l * alpha + psum;
-    m = mnew;
-    if (DROP) {  // the row sum keeps every probability; what goes on to V is dropped and rescaled
-      const uint32_t bh = (uint32_t)(seq_idx * a.heads_total + a.head0 + head);
+      for (int ks = 0; ks < KS; ks++) s = MFMA(tile_kc<D>(lk, 32 * kg, ks, lane), qf[ks], s);
+      if ((kv0 + 32 > a.seq) || (CAUSAL && kv0 + 31 > q_begin)) {
+        OASES_RARE();
 #pragma unroll
-      for (int grp = 0; grp < 4; grp++) {
-        const uint32_t ww = pick_word(attn_drop_block(a, (uint32_t)(kv0 + 8 * grp + 4 * g) >> 2, (uint32_t)qpos >> 2, bh), qpos & 3);
+        for (int i = 0; i < 16; i++) {
+          const int kvpos = kv0 + 8 * (i >> 2) + 4 * g + (i & 3);
+          if (kvpos >= a.seq || (CAUSAL && kvpos > qpos)) s[i] = -INFINITY;
+        }
+      }
+      float mloc = s[0];
 #pragma unroll
-        for (int e = 0; e < 4; e++) s[4 * grp + e] = ((ww >> (8 * e)) & 0xffu) >= a.dthresh ? s[4 * grp + e] * a.dscale : 0.f;
+      for (int i = 1; i < 16; i++) mloc = fmaxf(mloc, s[i]);
+      mloc = half_max(mloc);
+      // The reference value m of the exponentials follows the row maximum only when that has grown by more than 2^kSlack: any
+      // value near the maximum gives the same softmax (fp32 sums, bf16 probabilities relative to the row's own scale), and
+      // nearly every tile then passes without rescaling O.  The part with key 0 has a key for every query; another may
+      // start on a tile that is masked for some of its queries: m stays finite there so that exp2 never sees inf - inf.
+      constexpr float kSlack = 6.0f;
+      if (__any((mloc - m) * a.scale_log2 > kSlack || m == -INFINITY)) {
+        OASES_RARE();
+        const float mnew = fmaxf(fmaxf(m, mloc), -1e30f);
+        const float alpha = __builtin_amdgcn_exp2f((m - mnew) * a.scale_log2);
+        m = mnew;
+        l *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < DT; dt++)
+#pragma unroll
+          for (int i = 0; i < 16; i++) o[dt][i] *= alpha;
+      }
+      const float nm = -m * a.scale_log2;
+#pragma unroll
+      for (int i = 0; i < 16; i++) {
+        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.scale_log2, nm));
+        s[i] = p;
+        l += p;
+      }
+      if (DROP) {  // the row sum keeps every probability; what goes on to V is dropped and rescaled
+        uint32_t w[4];
+        drop_words_of_query(a, w, kv0 + 4 * g, qpos, (uint32_t)(seq_idx * a.heads_total + a.head0 + head), lane);
+#pragma unroll
+        for (int grp = 0; grp < 4; grp++)
+#pragma unroll
+          for (int e = 0; e < 4; e++) s[4 * grp + e] = ((w[grp] >> (8 * e)) & 0xffu) >= a.dthresh ? s[4 * grp + e] * a.dscale : 0.f;
+      }
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        bf16x8 pb = pack8(s, 8 * j);
+#pragma unroll
+        for (int dt = 0; dt < DT; dt++) o[dt] = MFMA(tile_mc<D>(lv, 32 * kg, j, dt, lane), pb, o[dt]);
       }
     }
-    if (__any(alpha != 1.0f)) {  // the running maximum rarely moves after the first tiles
-#pragma unroll
-      for (int dt = 0; dt < DT; dt++)
-#pragma unroll
-        for (int i = 0; i < 16; i++) o[dt][i] *= alpha;
-    }
-#pragma unroll
-    for (int j = 0; j < 2; j++) {
-      bf16x8 pb = pack8(s, 8 * j);
-#pragma unroll
-      for (int dt = 0; dt < DT; dt++) o[dt] = MFMA(mc_frag<D>(lv, j, 32 * dt, lane), pb, o[dt]);
+    lds_barrier();
+    if constexpr (L::NS == 1) {
+      park_next();
+      lds_barrier();
     }
   }
-  l += __shfl_xor(l, 32, 64);
+  l = half_sum(l);
 
-  // merge the four partial (m, l, O): weights 2^(m_w - m)
-  float* part = reinterpret_cast<float*>(lds);
-  float* stat = reinterpret_cast<float*>(lds + (kStageBytes > kPartBytes ? kStageBytes : kPartBytes));  // m[4][32], l[4][32]
-  __syncthreads();
-  if (g == 0) { stat[wave * 32 + lane] = m; stat[128 + wave * 32 + lane] = l; }
-  __syncthreads();
-  float sc[4], mt = -INFINITY, lt = 0.f;
+  // merge the KG partial (m, l, O) of a query group: weights 2^(m_k - m); wave (qg, kg) finishes elements [kg E/KG, (kg+1) E/KG)
+  float sc[KG], mt = m, lt = l;
+  if constexpr (KG > 1) {
+    float* part = reinterpret_cast<float*>(lds);
+    float* stat = reinterpret_cast<float*>(lds + L::bytes - 1024);
+    if (g == 0) { stat[wave * 32 + lane] = m; stat[128 + wave * 32 + lane] = l; }
 #pragma unroll
-  for (int w = 0; w < 4; w++) mt = fmaxf(mt, stat[w * 32 + (lane & 31)]);
+    for (int e = 0; e < E; e++)
+      if (e / (E / KG) != kg) part[(wave * E + e) * 64 + lane] = o[e / 16][e % 16];
+    lds_barrier();
+    mt = -INFINITY;
+    lt = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; w++) {
-    sc[w] = __builtin_amdgcn_exp2f(stat[w * 32 + (lane & 31)] - mt);
-    lt += stat[128 + w * 32 + (lane & 31)] * sc[w];
+    for (int k = 0; k < KG; k++) mt = fmaxf(mt, stat[(k * QG + qg) * 32 + (lane & 31)]);
+#pragma unroll
+    for (int k = 0; k < KG; k++) {
+      sc[k] = __builtin_amdgcn_exp2f((stat[(k * QG + qg) * 32 + (lane & 31)] - mt) * a.scale_log2);
+      lt += stat[128 + (k * QG + qg) * 32 + (lane & 31)] * sc[k];
+    }
+  } else {
+    sc[0] = 1.f;
   }
-  float res[E / 4];
-  combine4<E>(o, part, wave, lane, sc, res);
-  if (qok) {
+  auto finish = [&](auto kg_c) {
+    constexpr int MY = decltype(kg_c)::value;
+    const float* part = reinterpret_cast<const float*>(lds);
     const float inv = 1.0f / lt;
     uint16_t* op = a.out_w + (rowbase + qpos) * a.hp + head * D;
 #pragma unroll
-    for (int k = 0; k < E / 4; k += 4) {
-      const int e = wave * (E / 4) + k, dt = e / 16, i = e % 16;
-      const int d = dt * 32 + 8 * (i >> 2) + 4 * g;
-      u32x2 v = {pack_bf16x2(res[k] * inv, res[k + 1] * inv), pack_bf16x2(res[k + 2] * inv, res[k + 3] * inv)};
-      *reinterpret_cast<u32x2*>(op + d) = v;
+    for (int k = 0; k < E / KG; k += 4) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const int e = MY * (E / KG) + k + u;
+        v[u] = 0.f;
+#pragma unroll
+        for (int w = 0; w < KG; w++) v[u] += (w == MY ? o[e / 16][e % 16] : part[((w * QG + qg) * E + e) * 64 + lane]) * sc[w];
+      }
+      const int e = MY * (E / KG) + k, d = (e / 16) * 32 + 8 * ((e % 16) >> 2) + 4 * g;
+      if (qok) *reinterpret_cast<u32x2*>(op + d) = u32x2{pack_bf16x2(v[0] * inv, v[1] * inv), pack_bf16x2(v[2] * inv, v[3] * inv)};
     }
-    if (wave == 0 && g == 0) a.lse[((size_t)seq_idx * a.heads + head) * a.seq + qpos] = (mt + __builtin_amdgcn_logf(lt)) * kLn2;
+  };
+  if constexpr (KG == 1) finish(std::integral_constant<int, 0>{});
+  if constexpr (KG == 2) { if (kg == 0) finish(std::integral_constant<int, 0>{}); else finish(std::integral_constant<int, 1>{}); }
+  if constexpr (KG == 4) {
+    if (kg == 0) finish(std::integral_constant<int, 0>{});
+    else if (kg == 1) finish(std::integral_constant<int, 1>{});
+    else if (kg == 2) finish(std::integral_constant<int, 2>{});
+    else finish(std::integral_constant<int, 3>{});
   }
+  if (qok && kg == 0 && g == 0) a.lse[((size_t)seq_idx * a.heads + head) * a.seq + qpos] = (mt * a.scale_log2 + __builtin_amdgcn_logf(lt)) * kLn2;
 }
 
 // =================================================================================================
@@ -339,10 +492,315 @@ __global__ __launch_bounds__(NT) void attn_delta_kernel(AttnArgs a, int first_ro
 }
 
 // =================================================================================================
-// backward: dQ for a 32-query block; the four waves split the key tiles
+// backward: dQ.  QG groups of 32 queries x KG key parts, tiles and waves as in the forward kernel (measured, wave-private tiles
+// -> this, us: 4x2048x4x128 69 -> 49, 8x1024x8x64 42.8 -> 33.5).  OWN_DELTA: the workgroup
+// forms delta of its queries itself and leaves it for the dK/dV kernel behind it; otherwise it is there already.
+// =================================================================================================
+template <int D, int QG, int KG>
+struct BwdLds {
+  static constexpr int E = D / 2, kTile = SharedTile<D, 32 * KG>::bytes, kStat = KG * 256;
+  static constexpr int kStage = 2 * kTile + kStat;  // two operand tiles and, dK/dV only, lse and delta of the tile's queries
+  static constexpr int kPart = KG > 1 ? 4 * E * 64 * 4 : 0;
+  static constexpr int bytes = 2 * kStage > kPart ? 2 * kStage : kPart;
+};
+// the KG partial sums of a group meet through LDS: wave (qg, kg) ends up with elements [kg E/KG, (kg+1) E/KG) of the flattened
+// (tile, element) index, handed to emit(first element, four values)
+template <int E, int QG, int KG, int MY, typename Emit>
+__device__ __forceinline__ void finish_part(const f32x16* acc, const float* part, int qg, int lane, Emit emit) {
+#pragma unroll
+  for (int k = 0; k < E / KG; k += 4) {
+    f32x4 v;
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int e = MY * (E / KG) + k + u;
+      v[u] = 0.f;
+#pragma unroll
+      for (int w = 0; w < KG; w++) v[u] += w == MY ? acc[e / 16][e % 16] : part[((w * QG + qg) * E + e) * 64 + lane];
+    }
+    emit(MY * (E / KG) + k, v);
+  }
+}
+template <int E, int QG, int KG, typename Emit>
+__device__ __forceinline__ void combine_parts(const f32x16* acc, char* lds, int qg, int kg, int lane, Emit emit) {
+  float* part = reinterpret_cast<float*>(lds);
+  if constexpr (KG == 1) {
+    finish_part<E, QG, 1, 0>(acc, part, qg, lane, emit);
+  } else {
+    lds_barrier();  // every wave is done with the tiles, or with the exchange before this one
+#pragma unroll
+    for (int e = 0; e < E; e++)
+      if (e / (E / KG) != kg) part[((kg * QG + qg) * E + e) * 64 + lane] = acc[e / 16][e % 16];
+    lds_barrier();
+    if constexpr (KG == 2) {
+      if (kg == 0) finish_part<E, QG, 2, 0>(acc, part, qg, lane, emit); else finish_part<E, QG, 2, 1>(acc, part, qg, lane, emit);
+    } else {
+      if (kg == 0) finish_part<E, QG, 4, 0>(acc, part, qg, lane, emit);
+      else if (kg == 1) finish_part<E, QG, 4, 1>(acc, part, qg, lane, emit);
+      else if (kg == 2) finish_part<E, QG, 4, 2>(acc, part, qg, lane, emit);
+      else finish_part<E, QG, 4, 3>(acc, part, qg, lane, emit);
+    }
+  }
+}
+
+template <int D, int QG, int KG, bool CAUSAL, bool DROP, bool OWN_DELTA>
+__device__ __forceinline__ void attn_dq_block(const AttnArgs& a, int wg, char* lds) {
+  constexpr int KS = D / 16, DT = D / 32, E = DT * 16, BK = 32 * KG;
+  using L = BwdLds<D, QG, KG>;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5;
+  const int qg = wave % QG, kg = wave / QG;
+  int pair, blk;
+  decode_block_serpentine(wg, a.nseq * a.heads, a.blocks, pair, blk);
+  const int sq = pair / a.heads, head = pair % a.heads, qb = a.blocks - 1 - blk;
+  const int seq_idx = a.seq0 + sq;
+  const int wg_end = min(a.pos0 + a.npos, a.pos0 + (qb + 1) * 32 * QG);
+  const int q_begin = a.pos0 + (qb * QG + qg) * 32;
+  const int q_end = min(wg_end, q_begin + 32);
+  const size_t rowbase = (size_t)seq_idx * a.seq;
+  const uint16_t* Qp = a.qkv + rowbase * a.ld + head * D;
+  const uint16_t* Kp = Qp + a.hp;
+  const uint16_t* Vp = Qp + 2 * a.hp;
+  const uint16_t* dOp = a.dout + rowbase * a.hp + head * D;
+  const int qpos = q_begin + (lane & 31);
+  const bool qok = qpos < q_end && qpos >= a.first;
+
+  const int kv_end = CAUSAL ? wg_end : a.seq;
+  const int nt = (kv_end + BK - 1) / BK;
+  SharedTile<D, BK> rk, rv;
+  rk.load(Kp, a.ld, 0, 0, kv_end, tid);
+  rv.load(Vp, a.ld, 0, 0, kv_end, tid);
+  bf16x8 qf[KS], dof[KS];
+  load_row_frags<D>(qf, Qp + (size_t)qpos * a.ld, qok, g);
+  load_row_frags<D>(dof, dOp + (size_t)qpos * a.hp, qok, g);
+  const size_t si = ((size_t)seq_idx * a.heads + head) * a.seq + qpos;
+  const float lse2 = qok ? a.lse[si] * kLog2e : 0.f;
+  float dl = 0.f;
+  if constexpr (OWN_DELTA) {
+    const uint16_t* op = a.out + (rowbase + qpos) * a.hp + head * D;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+      u32x4 x = {0u, 0u, 0u, 0u};
+      if (qok) x = *reinterpret_cast<const u32x4*>(op + ks * 16 + 8 * g);
+      const u32x4 y = __builtin_bit_cast(u32x4, dof[ks]);
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        dl += bf16_bits_to_f32(x[j] & 0xffffu) * bf16_bits_to_f32(y[j] & 0xffffu);
+        dl += bf16_bits_to_f32(x[j] >> 16) * bf16_bits_to_f32(y[j] >> 16);
+      }
+    }
+    dl = half_sum(dl);
+    if (qok && kg == 0 && g == 0) a.delta[si] = dl;
+  } else if (qok) {
+    dl = a.delta[si];
+  }
+  f32x16 acc[DT];
+#pragma unroll
+  for (int i = 0; i < DT; i++) acc[i] = zero16();
+  rk.store(lds, tid);
+  rv.store(lds + L::kTile, tid);
+  if (nt > 1) {
+    rk.load(Kp, a.ld, BK, 0, kv_end, tid);
+    rv.load(Vp, a.ld, BK, 0, kv_end, tid);
+  }
+  lds_barrier();
+  for (int t = 0; t < nt; t++) {
+    const char* lk = lds + (t & 1) * L::kStage;
+    const char* lv = lk + L::kTile;
+    if (t + 1 < nt) {
+      char* nk = lds + ((t & 1) ^ 1) * L::kStage;
+      rk.store(nk, tid);
+      rv.store(nk + L::kTile, tid);
+      if (t + 2 < nt) {
+        rk.load(Kp, a.ld, (t + 2) * BK, 0, kv_end, tid);
+        rv.load(Vp, a.ld, (t + 2) * BK, 0, kv_end, tid);
+      }
+    }
+    const int kv0 = t * BK + 32 * kg;
+    if (kv0 < a.seq && !(CAUSAL && kv0 >= q_end)) {
+      f32x16 s = zero16(), dp = zero16();
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        s = MFMA(tile_kc<D>(lk, 32 * kg, ks, lane), qf[ks], s);
+        dp = MFMA(tile_kc<D>(lv, 32 * kg, ks, lane), dof[ks], dp);
+      }
+      if (DROP) {  // dP = dropout factor * (dO V^T)
+        uint32_t w[4];
+        drop_words_of_query(a, w, kv0 + 4 * g, qpos, (uint32_t)(seq_idx * a.heads_total + a.head0 + head), lane);
+#pragma unroll
+        for (int grp = 0; grp < 4; grp++)
+#pragma unroll
+          for (int e = 0; e < 4; e++) dp[4 * grp + e] = ((w[grp] >> (8 * e)) & 0xffu) >= a.dthresh ? dp[4 * grp + e] * a.dscale : 0.f;
+      }
+      // only tiles on the diagonal or at the end of the sequence pay for the mask (a wave-uniform branch)
+      auto scores = [&](auto mask_c) {
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+          float ds = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.scale_log2, -lse2)) * (dp[i] - dl);
+          if (decltype(mask_c)::value) {
+            const int kvpos = kv0 + 8 * (i >> 2) + 4 * g + (i & 3);
+            if (kvpos >= a.seq || (CAUSAL && kvpos > qpos)) ds = 0.f;
+          }
+          s[i] = ds;
+        }
+      };
+      if ((kv0 + 32 > a.seq) || (CAUSAL && kv0 + 31 > q_begin)) scores(std::true_type{}); else scores(std::false_type{});
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        bf16x8 db = pack8(s, 8 * j);
+#pragma unroll
+        for (int dt = 0; dt < DT; dt++) acc[dt] = MFMA(tile_mc<D>(lk, 32 * kg, j, dt, lane), db, acc[dt]);
+      }
+    }
+    lds_barrier();
+  }
+  uint16_t* op = a.dqkv + (rowbase + qpos) * a.ld + head * D;
+  combine_parts<E, QG, KG>(acc, lds, qg, kg, lane, [&](int e, const f32x4& v) {
+    const int d = (e / 16) * 32 + 8 * ((e % 16) >> 2) + 4 * g;
+    if (qok) *reinterpret_cast<u32x2*>(op + d) = u32x2{pack_bf16x2(v[0] * a.scale, v[1] * a.scale), pack_bf16x2(v[2] * a.scale, v[3] * a.scale)};
+  });
+}
+
+// =================================================================================================
+// backward: dK, dV.  JG groups of 32 keys x RG query parts (D = 64; 8x1024x8x64 78 -> 45 us); the tiles are 32 RG queries of Q and dO with their lse and delta.
+// S = Q K^T puts a key on a lane and P, dS into operand position; dV^T = dO^T P and dK^T = Q^T dS then leave four consecutive
+// columns of a key on a lane.
+// =================================================================================================
+template <int D, int JG, int RG, bool CAUSAL, bool DROP>
+__device__ __forceinline__ void attn_dkv_block(const AttnArgs& a, int wg, char* lds) {
+  constexpr int KS = D / 16, DT = D / 32, E = DT * 16, BQ = 32 * RG;
+  using L = BwdLds<D, JG, RG>;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5;
+  const int jg = wave % JG, rg = wave / JG;
+  int pair, kb;
+  decode_block_serpentine(wg, a.nseq * a.heads, a.blocks, pair, kb);  // early key blocks are the long ones
+  const int sq = pair / a.heads, head = pair % a.heads;
+  const int seq_idx = a.seq0 + sq;
+  const int wg_begin = a.pos0 + kb * 32 * JG;
+  const int k_begin = wg_begin + 32 * jg;
+  const int k_end = min(a.pos0 + a.npos, k_begin + 32);
+  const size_t rowbase = (size_t)seq_idx * a.seq;
+  const uint16_t* Qp = a.qkv + rowbase * a.ld + head * D;
+  const uint16_t* Kp = Qp + a.hp;
+  const uint16_t* Vp = Qp + 2 * a.hp;
+  const uint16_t* dOp = a.dout + rowbase * a.hp + head * D;
+  const float* lsep = a.lse + ((size_t)seq_idx * a.heads + head) * a.seq;
+  const float* dlp = a.delta + ((size_t)seq_idx * a.heads + head) * a.seq;
+  const int kpos = k_begin + (lane & 31);
+  const bool kok = kpos < k_end && kpos >= a.first;
+
+  const int q_first = CAUSAL ? wg_begin : 0;  // earlier queries never see a key of this block
+  const int qmin = CAUSAL ? a.first : 0;
+  const int nt = (a.seq - q_first + BQ - 1) / BQ;
+  SharedTile<D, BQ> rq, rdo;
+  float rstat = 0.f;
+  auto fetch = [&](int t) {
+    const int q0 = q_first + t * BQ;
+    rq.load(Qp, a.ld, q0, qmin, a.seq, tid);
+    rdo.load(dOp, a.hp, q0, qmin, a.seq, tid);
+    if (tid < 2 * BQ) {
+      const int qp = min(q0 + (tid % BQ), a.seq - 1);
+      rstat = tid < BQ ? lsep[qp] * kLog2e : dlp[qp];
+    }
+  };
+  auto park = [&](char* st) {
+    rq.store(st, tid);
+    rdo.store(st + L::kTile, tid);
+    if (tid < 2 * BQ) reinterpret_cast<float*>(st + 2 * L::kTile)[tid] = rstat;
+  };
+  fetch(0);
+  bf16x8 kf[KS], vf[KS];
+  load_row_frags<D>(kf, Kp + (size_t)kpos * a.ld, kok, g);
+  load_row_frags<D>(vf, Vp + (size_t)kpos * a.ld, kok, g);
+  f32x16 dk[DT], dv[DT];
+#pragma unroll
+  for (int i = 0; i < DT; i++) { dk[i] = zero16(); dv[i] = zero16(); }
+  park(lds);
+  if (nt > 1) fetch(1);
+  lds_barrier();
+  for (int t = 0; t < nt; t++) {
+    const char* lq = lds + (t & 1) * L::kStage;
+    const char* ldo = lq + L::kTile;
+    const float* lstat = reinterpret_cast<const float*>(lq + 2 * L::kTile) + 32 * rg;  // [BQ] lse * log2(e), [BQ] delta
+    if (t + 1 < nt) {
+      park(lds + ((t & 1) ^ 1) * L::kStage);
+      if (t + 2 < nt) fetch(t + 2);
+    }
+    const int q0 = q_first + t * BQ + 32 * rg;
+    if (q0 < a.seq && !(CAUSAL && q0 + 31 < k_begin)) {  // uniform over the wave: some query sees some key
+      f32x16 s = zero16(), dp = zero16();
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        s = MFMA(tile_kc<D>(lq, 32 * rg, ks, lane), kf[ks], s);
+        dp = MFMA(tile_kc<D>(ldo, 32 * rg, ks, lane), vf[ks], dp);
+      }
+      Philox4 dw;  // the four lanes of a quad share the keys of a 4 x 4 block: each draws the block of one group of queries
+      if (DROP) dw = attn_drop_block(a, (uint32_t)kpos >> 2, (uint32_t)(q0 + 8 * (lane & 3) + 4 * g) >> 2, (uint32_t)(seq_idx * a.heads_total + a.head0 + head));
+      // only tiles on the diagonal or at the end of the sequence pay for the mask (a wave-uniform branch)
+      auto scores = [&](auto mask_c) {
+        auto group = [&](auto i4_c) {
+          constexpr int I4 = decltype(i4_c)::value;
+          const int ql = 8 * I4 + 4 * g;  // 4 consecutive queries
+          const f32x4 l4 = *reinterpret_cast<const f32x4*>(lstat + ql);
+          const f32x4 d4 = *reinterpret_cast<const f32x4*>(lstat + BQ + ql);
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            const int i = 4 * I4 + e;
+            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.scale_log2, -l4[e]));
+            float dpe = dp[i], pv = p;  // pv: what multiplied V in forward
+            if (DROP) {  // this lane's key is byte (kpos mod 4) of the word of query e of the group
+              const bool keep = ((quad_lane<I4>(dw.v[e]) >> (8 * (kpos & 3))) & 0xffu) >= a.dthresh;
+              dpe = keep ? dpe * a.dscale : 0.f;
+              pv = keep ? p * a.dscale : 0.f;
+            }
+            float ds = p * (dpe - d4[e]);
+            if (decltype(mask_c)::value) {
+              const int qp = q0 + ql + e;
+              if (qp >= a.seq || (CAUSAL && kpos > qp)) { pv = 0.f; ds = 0.f; }   // select, never multiply: the rest may be NaN
+            }
+            s[i] = pv;
+            dp[i] = ds;
+          }
+        };
+        group(std::integral_constant<int, 0>{});
+        group(std::integral_constant<int, 1>{});
+        group(std::integral_constant<int, 2>{});
+        group(std::integral_constant<int, 3>{});
+      };
+      if ((q0 + 32 > a.seq) || (CAUSAL && q0 < k_begin + 31)) scores(std::true_type{}); else scores(std::false_type{});
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        bf16x8 pa = pack8(s, 8 * j);
+        bf16x8 da = pack8(dp, 8 * j);
+#pragma unroll
+        for (int dt = 0; dt < DT; dt++) {
+          dv[dt] = MFMA(tile_mc<D>(ldo, 32 * rg, j, dt, lane), pa, dv[dt]);
+          dk[dt] = MFMA(tile_mc<D>(lq, 32 * rg, j, dt, lane), da, dk[dt]);
+        }
+      }
+    }
+    lds_barrier();
+  }
+  uint16_t* dKp = a.dqkv + (rowbase + kpos) * a.ld + a.hp + head * D;
+  uint16_t* dVp = dKp + a.hp;
+  combine_parts<E, JG, RG>(dk, lds, jg, rg, lane, [&](int e, const f32x4& v) {
+    const int d = (e / 16) * 32 + 8 * ((e % 16) >> 2) + 4 * g;
+    if (kok) *reinterpret_cast<u32x2*>(dKp + d) = u32x2{pack_bf16x2(v[0] * a.scale, v[1] * a.scale), pack_bf16x2(v[2] * a.scale, v[3] * a.scale)};
+  });
+  combine_parts<E, JG, RG>(dv, lds, jg, rg, lane, [&](int e, const f32x4& v) {
+    const int d = (e / 16) * 32 + 8 * ((e % 16) >> 2) + 4 * g;
+    if (kok) *reinterpret_cast<u32x2*>(dVp + d) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+  });
+}
+
+// =================================================================================================
+// backward over blocks of 32 rows, a wave by itself.  The four waves of a workgroup split the reduction range -- the 32-row key tiles
+// a query block sees, or the 32-row query tiles that see a key block -- round-robin, each staging its own tiles in a private
+// slice of LDS, so the loops need no barrier; the four partial results meet once, through LDS, at the end.  Rows are padded
+// instead of swizzled.  This form stays where the shared tiles above do not pay: calls with few blocks, whose time is the
+// chain of the longest one (a quarter of it per wave here), and dK/dV with D = 128, whose 192 registers of keys and
+// accumulators leave a SIMD one wave: in lockstep with three others it waits at every barrier.
 // =================================================================================================
 template <int D>
-struct BwdLds {  // LDS of a backward workgroup: the larger of the two passes' staging areas and of the partial-sum exchange
+struct WaveLds {  // LDS of a backward workgroup: the larger of the two passes' staging areas and of the partial-sum exchange
   static constexpr int E = (D / 32) * 16;
   static constexpr int kStageDq = 4 * 2 * AT<D>::bytes, kStageDkv = 4 * (2 * AT<D>::bytes + 256), kPart = 4 * E * 64 * 4;
   static constexpr int bytes = kStageDkv > kPart ? kStageDkv : kPart;
@@ -350,7 +808,7 @@ struct BwdLds {  // LDS of a backward workgroup: the larger of the two passes' s
 };
 
 template <int D, bool CAUSAL, bool DROP>
-__device__ __forceinline__ void attn_dq_block(const AttnArgs& a, int wg, char* lds) {
+__device__ __forceinline__ void wave_dq_block(const AttnArgs& a, int wg, char* lds) {
   constexpr int KS = D / 16, DT = D / 32, E = DT * 16;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
   int pair, blk;
@@ -365,7 +823,7 @@ __device__ __forceinline__ void attn_dq_block(const AttnArgs& a, int wg, char* l
   const uint16_t* Vp = Qp + 2 * a.hp;
   const uint16_t* dOp = a.dout + rowbase * a.hp + head * D;
   const int qpos = q_begin + (lane & 31);
-  const bool qok = qpos < q_end;
+  const bool qok = qpos < q_end && qpos >= a.first;
 
   bf16x8 qf[KS], dof[KS];
   load_row_frags<D>(qf, Qp + (size_t)qpos * a.ld, qok, g);
@@ -405,13 +863,12 @@ __device__ __forceinline__ void attn_dq_block(const AttnArgs& a, int wg, char* l
     }
     const bool need_mask = (kv0 + 32 > a.seq) || (CAUSAL && kv0 + 31 > q_begin);
     if (DROP) {  // dP = dropout factor * (dO V^T)
-      const uint32_t bh = (uint32_t)(seq_idx * a.heads_total + a.head0 + head);
+      uint32_t w[4];
+      drop_words_of_query(a, w, kv0 + 4 * g, qpos, (uint32_t)(seq_idx * a.heads_total + a.head0 + head), lane);
 #pragma unroll
-      for (int grp = 0; grp < 4; grp++) {
-        const uint32_t ww = pick_word(attn_drop_block(a, (uint32_t)(kv0 + 8 * grp + 4 * g) >> 2, (uint32_t)qpos >> 2, bh), qpos & 3);
+      for (int grp = 0; grp < 4; grp++)
 #pragma unroll
-        for (int e = 0; e < 4; e++) dp[4 * grp + e] = ((ww >> (8 * e)) & 0xffu) >= a.dthresh ? dp[4 * grp + e] * a.dscale : 0.f;
-      }
+        for (int e = 0; e < 4; e++) dp[4 * grp + e] = ((w[grp] >> (8 * e)) & 0xffu) >= a.dthresh ? dp[4 * grp + e] * a.dscale : 0.f;
     }
     // only tiles on the diagonal or at the end of the sequence pay for the mask (a wave-uniform branch)
     auto scores = [&](auto mask_c) {
@@ -448,11 +905,9 @@ __device__ __forceinline__ void attn_dq_block(const AttnArgs& a, int wg, char* l
   }
 }
 
-// =================================================================================================
-// backward: dK, dV for a 32-key block; the four waves split the 32-query tiles that see it
-// =================================================================================================
+// dK, dV of a 32-key block; the four waves split the 32-query tiles that see it
 template <int D, bool CAUSAL, bool DROP>
-__device__ __forceinline__ void attn_dkv_block(const AttnArgs& a, int wg, char* lds) {
+__device__ __forceinline__ void wave_dkv_block(const AttnArgs& a, int wg, char* lds) {
   constexpr int KS = D / 16, DT = D / 32, E = DT * 16;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
   int pair, kb;
@@ -469,7 +924,7 @@ __device__ __forceinline__ void attn_dkv_block(const AttnArgs& a, int wg, char* 
   const float* lsep = a.lse + ((size_t)seq_idx * a.heads + head) * a.seq;
   const float* dlp = a.delta + ((size_t)seq_idx * a.heads + head) * a.seq;
   const int kpos = k_begin + (lane & 31);
-  const bool kok = kpos < k_end;
+  const bool kok = kpos < k_end && kpos >= a.first;
 
   bf16x8 kf[KS], vf[KS];
   load_row_frags<D>(kf, Kp + (size_t)kpos * a.ld, kok, g);
@@ -479,7 +934,7 @@ __device__ __forceinline__ void attn_dkv_block(const AttnArgs& a, int wg, char* 
   for (int i = 0; i < DT; i++) { dk[i] = zero16(); dv[i] = zero16(); }
 
   const int qt0 = CAUSAL ? k_begin / 32 : 0;   // first query tile that sees this key block
-  const int qmin = CAUSAL ? a.pos0 : 0;        // earlier queries never see a key of this row range
+  const int qmin = CAUSAL ? a.first : 0;       // earlier queries never see a key of this row range
   const int nqt = (a.seq + 31) / 32;
   char* lq = lds + wave * (2 * AT<D>::bytes + 256);
   char* ldo = lq + AT<D>::bytes;
@@ -506,34 +961,38 @@ __device__ __forceinline__ void attn_dkv_block(const AttnArgs& a, int wg, char* 
       dp = MFMA(kc_frag<D>(ldo, ks, lane), vf[ks], dp);
     }
     const bool need_mask = (q0 + 32 > a.seq) || (CAUSAL && q0 < k_begin + 31);
+    Philox4 dw;  // the four lanes of a quad share the keys of a 4 x 4 block: each draws the block of one group of queries
+    if (DROP) dw = attn_drop_block(a, (uint32_t)kpos >> 2, (uint32_t)(q0 + 8 * (lane & 3) + 4 * g) >> 2, (uint32_t)(seq_idx * a.heads_total + a.head0 + head));
     // only tiles on the diagonal or at the end of the sequence pay for the mask (a wave-uniform branch)
     auto scores = [&](auto mask_c) {
-#pragma unroll
-      for (int i4 = 0; i4 < 4; i4++) {
-        const int ql = 8 * i4 + 4 * g;  // 4 consecutive queries
-        f32x4 l4 = *reinterpret_cast<const f32x4*>(lstat + ql);
-        f32x4 d4 = *reinterpret_cast<const f32x4*>(lstat + 32 + ql);
-        Philox4 dw;
-        if (DROP) dw = attn_drop_block(a, (uint32_t)kpos >> 2, (uint32_t)(q0 + ql) >> 2, (uint32_t)(seq_idx * a.heads_total + a.head0 + head));
+      auto group = [&](auto i4_c) {
+        constexpr int I4 = decltype(i4_c)::value;
+        const int ql = 8 * I4 + 4 * g;  // 4 consecutive queries
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(lstat + ql);
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(lstat + 32 + ql);
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-          const int i = 4 * i4 + e;
-          const float p = __builtin_amdgcn_exp2f(s[i] * a.scale_log2 - l4[e]);
+          const int i = 4 * I4 + e;
+          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.scale_log2, -l4[e]));
           float dpe = dp[i], pv = p;  // pv: what multiplied V in forward
           if (DROP) {  // this lane's key is byte (kpos mod 4) of the word of query e of the group
-            const bool keep = ((dw.v[e] >> (8 * (kpos & 3))) & 0xffu) >= a.dthresh;
+            const bool keep = ((quad_lane<I4>(dw.v[e]) >> (8 * (kpos & 3))) & 0xffu) >= a.dthresh;
             dpe = keep ? dpe * a.dscale : 0.f;
             pv = keep ? p * a.dscale : 0.f;
           }
           float ds = p * (dpe - d4[e]);
           if (decltype(mask_c)::value) {
-            int qp = q0 + ql + e;
+            const int qp = q0 + ql + e;
             if (qp >= a.seq || (CAUSAL && kpos > qp)) { pv = 0.f; ds = 0.f; }   // select, never multiply: the rest may be NaN
           }
           s[i] = pv;
           dp[i] = ds;
         }
-      }
+      };
+      group(std::integral_constant<int, 0>{});
+      group(std::integral_constant<int, 1>{});
+      group(std::integral_constant<int, 2>{});
+      group(std::integral_constant<int, 3>{});
     };
     if (need_mask) scores(std::true_type{}); else scores(std::false_type{});
 #pragma unroll
@@ -558,7 +1017,7 @@ __device__ __forceinline__ void attn_dkv_block(const AttnArgs& a, int wg, char* 
   for (int k = 0; k < E / 4; k++) {
     const int e = wave * (E / 4) + k, dt = e / 16, i = e % 16;
     const int kp = k_begin + 8 * (i >> 2) + 4 * g + (i & 3);
-    if (kp < k_end) {
+    if (kp < k_end && kp >= a.first) {
       size_t o = (size_t)kp * a.ld + dt * 32 + (lane & 31);
       dKp[o] = (uint16_t)f32_to_bf16_bits(rk_[k] * a.scale);
       dVp[o] = (uint16_t)f32_to_bf16_bits(rv_[k]);
@@ -566,31 +1025,39 @@ __device__ __forceinline__ void attn_dkv_block(const AttnArgs& a, int wg, char* 
   }
 }
 
-// The two backward passes as launches of their own (many blocks: each pass fills the chip by itself, and keeps the L2 of an
-// XCD to one pass's operands) ...
-template <int D, bool CAUSAL, bool DROP>
-__global__ __launch_bounds__(NT, 1) void attn_dq_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) char lds[BwdLds<D>::bytes];
-  attn_dq_block<D, CAUSAL, DROP>(a, blockIdx.x, lds);
+// dQ as a launch of its own, which leaves delta behind if it covers every query that dK/dV reads
+template <int D, int QG, bool CAUSAL, bool DROP, bool OWN_DELTA>
+__global__ __launch_bounds__(NT, 2) void attn_dq_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(16))) char lds[BwdLds<D, QG, 4 / QG>::bytes];
+  attn_dq_block<D, QG, 4 / QG, CAUSAL, DROP, OWN_DELTA>(a, blockIdx.x, lds);
 }
-template <int D, bool CAUSAL, bool DROP>
-__global__ __launch_bounds__(NT, 1) void attn_dkv_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) char lds[BwdLds<D>::bytes];
-  attn_dkv_block<D, CAUSAL, DROP>(a, blockIdx.x, lds);
+template <int JG, bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(NT, 2) void attn_dkv_kernel(AttnArgs a) {  // D = 64
+  __shared__ __attribute__((aligned(16))) char lds[BwdLds<64, JG, 4 / JG>::bytes];
+  attn_dkv_block<64, JG, 4 / JG, CAUSAL, DROP>(a, blockIdx.x, lds);
 }
-
-// ... and in ONE launch, for calls with few blocks (at most one workgroup per CU and pass: a sub-batch that is a chunk of a
-// sequence, short sequences): the passes are independent (dK/dV per key block, dQ per query block) and each alone leaves
-// the chip waiting for its longest workgroups, so their workgroups are dealt out together -- groups of eight ids (one per
-// XCD) alternate between a dK/dV block and a dQ block, long blocks of both kinds first.  Measured (C5's chunks, 256 blocks):
-// 40 -> 32 us; with 512 blocks and more the single launch is about 10 % slower than two.
+template <bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(NT, 1) void wave_dq_kernel(AttnArgs a) {  // D = 128
+  __shared__ __attribute__((aligned(16))) char lds[WaveLds<128>::bytes];
+  wave_dq_block<128, CAUSAL, DROP>(a, blockIdx.x, lds);
+}
+template <bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(NT, 1) void wave_dkv_kernel(AttnArgs a) {  // D = 128
+  __shared__ __attribute__((aligned(16))) char lds[WaveLds<128>::bytes];
+  wave_dkv_block<128, CAUSAL, DROP>(a, blockIdx.x, lds);
+}
+// Both passes in ONE launch, for calls with few blocks (at most one workgroup per CU and pass): the passes are independent (dK/dV
+// per key block, dQ per query block) and each alone leaves the chip waiting for its longest workgroups, so their workgroups
+// are dealt out together -- groups of eight ids (one per XCD) alternate between a dK/dV block and a dQ block, long blocks of
+// both kinds first.  Measured (256 blocks of 2048-token sequences, D = 128): 40 -> 32 us; with 512 blocks and more the single
+// launch is about 10 % slower than two.
 template <int D, bool CAUSAL, bool DROP>
 __global__ __launch_bounds__(NT, 1) void attn_bwd_kernel(AttnArgs a, int n_blocks) {
-  __shared__ __attribute__((aligned(16))) char lds[BwdLds<D>::bytes];
+  __shared__ __attribute__((aligned(16))) char lds[WaveLds<D>::bytes];
   const int w = blockIdx.x, idx = (w >> 4) * 8 + (w & 7);
   if (idx >= n_blocks) return;  // the last group of eight may be ragged (whole workgroup leaves: no barrier is skipped by part of it)
-  if ((w >> 3) & 1) attn_dq_block<D, CAUSAL, DROP>(a, idx, lds);
-  else attn_dkv_block<D, CAUSAL, DROP>(a, idx, lds);
+  if ((w >> 3) & 1) wave_dq_block<D, CAUSAL, DROP>(a, idx, lds);
+  else wave_dkv_block<D, CAUSAL, DROP>(a, idx, lds);
 }
 
 int fill_args(AttnArgs& a, int batch, int seq, int heads, int head_dim, int causal, int row0, int rows, const char* who) {
@@ -605,7 +1072,7 @@ int fill_args(AttnArgs& a, int batch, int seq, int heads, int head_dim, int caus
   a.ld = 3 * a.hp;
   a.seq0 = row0 / seq;
   if (row0 % seq == 0 && rows % seq == 0) {
-    a.pos0 = 0;
+    a.first = a.pos0 = 0;
     a.npos = seq;
     a.blocks = (seq + 31) / 32;
     return rows / seq;  // number of sequences
@@ -618,9 +1085,10 @@ int fill_args(AttnArgs& a, int batch, int seq, int heads, int head_dim, int caus
     set_error("%s: a row range inside one sequence needs causal attention", who);
     return OASES_EINVAL;
   }
-  a.pos0 = row0 % seq;
-  a.npos = rows;
-  a.blocks = (rows + 31) / 32;
+  a.first = row0 % seq;
+  a.pos0 = a.first & ~3;
+  a.npos = rows + a.first - a.pos0;
+  a.blocks = (a.npos + 31) / 32;
   return 1;
 }
 
@@ -643,6 +1111,16 @@ static bool fill_dropout(AttnArgs& a, uint64_t seed, int layer, float p_attn, in
   return true;
 }
 
+// 32-row groups of a workgroup that shares its tiles: two halve the tiles read from L2, one has half as long a chain of tiles.
+// Two once they fill the chip twice, or once and the chains are short.  Both sides measured, forward / backward, us, one group
+// -> two (causal, batch x seq x heads x columns): 8x1024x8x64 37.2 / 104.9 -> 28.4 / 77.2, 4x2048x4x128 54.2 / 155 -> 36.8 / 132,
+// 8x512x4x64 9.5 / 24.7 -> 9.0 / 23.7, 8x256x8x128 8.9 / 40.9 -> 8.9 / 33.3, but 1x2048x8x64 18.3 / 47.8 -> 24.4 / 62.9 and 2x2048x4x128
+// 28.4 / 79.9 -> 33.7 / 86.0.
+static int attn_query_groups(const AttnArgs& a, int nseq) {
+  const long blocks = (long)nseq * a.heads * ((a.npos + 63) / 64);
+  return blocks >= 512 || (blocks >= 256 && a.seq <= 512) ? 2 : 1;
+}
+
 int launch_attention_fwd(const void* qkv, void* out, float* lse, int batch, int seq, int heads, int head_dim, int causal,
                          int row0, int rows, hipStream_t s, uint64_t seed, int layer, float p_attn, int head0, int heads_total) {
   if (!qkv || !out || !lse) { set_error("attention_fwd: NULL argument"); return OASES_ENULL; }
@@ -657,15 +1135,19 @@ int launch_attention_fwd(const void* qkv, void* out, float* lse, int batch, int 
   a.scale_log2 = a.scale * kLog2e;
   a.nseq = nseq;
   if (!fill_dropout(a, seed, layer, p_attn, head0, heads_total, heads, "attention_fwd")) return OASES_EINVAL;
+  const int qg = attn_query_groups(a, nseq);
+  a.blocks = (a.npos + 32 * qg - 1) / (32 * qg);
   dim3 grid(nseq * a.blocks * heads), block(NT);
-#define OASES_ATTN_FWD(DD, CC)                                                                              \
+#define OASES_ATTN_FWD_Q(DD, QQ, CC)                                                                        \
   do {                                                                                                      \
-    if (a.dthresh) hipLaunchKernelGGL((attn_fwd_kernel<DD, CC, true>), grid, block, 0, s, a);               \
-    else hipLaunchKernelGGL((attn_fwd_kernel<DD, CC, false>), grid, block, 0, s, a);                        \
+    if (a.dthresh) hipLaunchKernelGGL((attn_fwd_kernel<DD, QQ, 4 / QQ, CC, true>), grid, block, 0, s, a);   \
+    else hipLaunchKernelGGL((attn_fwd_kernel<DD, QQ, 4 / QQ, CC, false>), grid, block, 0, s, a);            \
   } while (0)
+#define OASES_ATTN_FWD(DD, CC) do { if (qg == 2) OASES_ATTN_FWD_Q(DD, 2, CC); else OASES_ATTN_FWD_Q(DD, 1, CC); } while (0)
   if (head_dim == 64) { if (causal) OASES_ATTN_FWD(64, true); else OASES_ATTN_FWD(64, false); }
   else { if (causal) OASES_ATTN_FWD(128, true); else OASES_ATTN_FWD(128, false); }
 #undef OASES_ATTN_FWD
+#undef OASES_ATTN_FWD_Q
   OASES_LAUNCH_CHECK("attn_fwd_kernel");
   return 0;
 }
@@ -696,26 +1178,45 @@ int launch_attention_bwd(const void* qkv, const void* out, const void* dout, con
   a.nseq = nseq;
   if (!fill_dropout(a, seed, layer, p_attn, head0, heads_total, heads, "attention_bwd")) return OASES_EINVAL;
   dim3 dgrid((unsigned)((pairs + NT - 1) / NT)), block(NT);
-  if (head_dim == 64) hipLaunchKernelGGL((attn_delta_kernel<64>), dgrid, block, 0, s, a, first_row, n_rows);
-  else hipLaunchKernelGGL((attn_delta_kernel<128>), dgrid, block, 0, s, a, first_row, n_rows);
-  OASES_LAUNCH_CHECK("attn_delta_kernel");
-  const int n_blocks = nseq * a.blocks * heads;
-  const bool one_launch = n_blocks <= 256;
-  const dim3 bgrid(2 * ((n_blocks + 7) / 8) * 8), grid(n_blocks);
-#define OASES_ATTN_BWD(DD, CC, DR)                                                                        \
-  do {                                                                                                    \
-    if (one_launch) {                                                                                     \
-      hipLaunchKernelGGL((attn_bwd_kernel<DD, CC, DR>), bgrid, block, 0, s, a, n_blocks);                 \
-    } else {                                                                                              \
-      hipLaunchKernelGGL((attn_dkv_kernel<DD, CC, DR>), grid, block, 0, s, a);                            \
-      hipLaunchKernelGGL((attn_dq_kernel<DD, CC, DR>), grid, block, 0, s, a);                             \
-    }                                                                                                     \
+  const int n_blocks = nseq * a.blocks * heads;  // of 32 rows
+  // (dropout makes a tile several times the work: there the launch pays up to half as many; 256 blocks of 512-token sequences, D = 64,
+  // in one launch against two: 17.5 -> 18.4 us without dropout, 24.0 -> 19.6 with)
+  const bool one_launch = n_blocks <= (a.dthresh && head_dim == 64 ? 128 : 256);
+  const int qg = attn_query_groups(a, nseq);
+  const bool wave_dq = head_dim == 128 && qg == 1;
+  const bool own_delta = !one_launch && !wave_dq && a.npos == seq;  // dQ covers every query that dK/dV reads, and forms delta on the way
+  if (!own_delta) {
+    if (head_dim == 64) hipLaunchKernelGGL((attn_delta_kernel<64>), dgrid, block, 0, s, a, first_row, n_rows);
+    else hipLaunchKernelGGL((attn_delta_kernel<128>), dgrid, block, 0, s, a, first_row, n_rows);
+    OASES_LAUNCH_CHECK("attn_delta_kernel");
+  }
+  AttnArgs q = a;
+  q.blocks = (a.npos + 32 * qg - 1) / (32 * qg);
+  const dim3 bgrid(2 * ((n_blocks + 7) / 8) * 8), grid(n_blocks), qgrid(nseq * q.blocks * heads);
+#define OASES_ATTN_DQ(DD, QQ, CC, DR)                                                                               \
+  do {                                                                                                              \
+    if (own_delta) hipLaunchKernelGGL((attn_dq_kernel<DD, QQ, CC, DR, true>), qgrid, block, 0, s, q);               \
+    else if constexpr (CC) hipLaunchKernelGGL((attn_dq_kernel<DD, QQ, CC, DR, false>), qgrid, block, 0, s, q);      \
+  } while (0)
+#define OASES_ATTN_BWD(DD, CC, DR)                                                                                  \
+  do {                                                                                                              \
+    if (one_launch) {                                                                                               \
+      hipLaunchKernelGGL((attn_bwd_kernel<DD, CC, DR>), bgrid, block, 0, s, a, n_blocks);                           \
+    } else {                                                                                                        \
+      if (qg == 2) OASES_ATTN_DQ(DD, 2, CC, DR);                                                                    \
+      else if constexpr (DD == 64) OASES_ATTN_DQ(DD, 1, CC, DR);                                                    \
+      else hipLaunchKernelGGL((wave_dq_kernel<CC, DR>), grid, block, 0, s, a);                                      \
+      if constexpr (DD == 128) hipLaunchKernelGGL((wave_dkv_kernel<CC, DR>), grid, block, 0, s, a);                 \
+      else if (qg == 2) hipLaunchKernelGGL((attn_dkv_kernel<2, CC, DR>), qgrid, block, 0, s, q);                    \
+      else hipLaunchKernelGGL((attn_dkv_kernel<1, CC, DR>), qgrid, block, 0, s, q);                                 \
+    }                                                                                                               \
   } while (0)
 #define OASES_ATTN_BWD_D(DD, CC) do { if (a.dthresh) OASES_ATTN_BWD(DD, CC, true); else OASES_ATTN_BWD(DD, CC, false); } while (0)
   if (head_dim == 64) { if (causal) OASES_ATTN_BWD_D(64, true); else OASES_ATTN_BWD_D(64, false); }
   else { if (causal) OASES_ATTN_BWD_D(128, true); else OASES_ATTN_BWD_D(128, false); }
 #undef OASES_ATTN_BWD_D
 #undef OASES_ATTN_BWD
+#undef OASES_ATTN_DQ
   OASES_LAUNCH_CHECK("attn_bwd kernels");
   return 0;
 }
