@@ -339,6 +339,15 @@ int oases_op_gemm_forced(int variant, int op, int epi, int M, int N, int K, cons
 int oases_op_gemm_tn_pair(int K, int M0, int N0, const void *A0, int lda0, const void *B0, int ldb0, void *C0,
                           int ldc0, int M1, int N1, const void *A1, int lda1, const void *B1, int ldb1, void *C1,
                           int ldc1, void *stream);
+/* The same for any two weight gradients over the same K rows, on the kernel that `variant` names (0: the library's choice): 30S128256 =
+ * eight-wave 128x256 tiles over S = 1, 2, 4 or 8 k slices (K % 64 == 0; any M, N the GEMM accepts), 401064064 and 401064128
+ * = small tiles (any K).  k slices are added up, in slice order, by the launch itself: workspace holds 4096 bytes of counters (set to
+ * zero by this call) and then the partial sums, slices x tiles x 128 KiB.  NULL: never split.  EINVAL, EALIGN, ENULL before
+ * the product is launched.  A whole pass issues the two weight gradients of a block this way where that is expected to take less time than
+ * two launches. */
+int oases_op_gemm_tn_group(int variant, int K, int M0, int N0, const void *A0, int lda0, const void *B0, int ldb0, void *C0,
+                           int ldc0, int M1, int N1, const void *A1, int lda1, const void *B1, int ldb1, void *C1,
+                           int ldc1, void *workspace, size_t workspace_bytes, void *stream);
 /* Host only: 1 if the library issues two such weight gradients as one launch (both fit whole 128x256 tiles, more than 128
  * tiles together, fewer rounds of 256 workgroups together than apart, and not so few rows K that the small-tile kernel is
  * chosen for both), else 0. */

@@ -44,13 +44,15 @@ enum OpKind {
   // PROJ.wgrad and QKV.wgrad as one launch, where the shapes make that the faster way
   B_PQ_WGRAD,
   // second stage of every column reduction of the backward pass (bias and LayerNorm-parameter gradients), one launch
-  B_COLSUMS
+  B_COLSUMS,
+  // the two weight gradients of a block as one launch, in what a pass executes (see group_weight_gradients)
+  B_FF_GROUP, B_PQ_GROUP
 };
 static const char* kOpName[] = {
     "LN1", "QKV", "ATTN", "PROJ", "R1+BDR1+LN2", "FC1+GELU", "FC2", "R2+BDR2",
     "BDR2.b", "FC2.dgrad+dGELU", "FC1.dgrad", "R3+LN2.b+BDR1.b", "FC2.wgrad", "FC1.wgrad", "b1.sum", "PROJ.dgrad",
     "PROJ.wgrad", "ATTN.b", "QKV.dgrad", "R4+LN1.b", "QKV.wgrad", "bqkv.sum",
-    "LN2.r", "FC1+GELU.r", "LN1.r", "QKV.r", "ATTN.r", "join", "ROPE.table", "ROPE", "ROPE.r", "ROPE.b", "PROJ+QKV.wgrad", "colsums"};
+    "LN2.r", "FC1+GELU.r", "LN1.r", "QKV.r", "ATTN.r", "join", "ROPE.table", "ROPE", "ROPE.r", "ROPE.b", "PROJ+QKV.wgrad", "colsums", "FC2+FC1.wgrad", "PROJ+QKV.wgrad"};
 // names of the same operator slots in the LLaMA-style layer (RMSNorm, SwiGLU)
 static const char* op_name(int kind, bool llama, bool bert) {
   if (bert) {  // post-LN: the normalisation sits behind the residual sum, the layer input enters the GEMM as it is
@@ -122,7 +124,7 @@ struct oases_handle {
   std::vector<hipEvent_t> prof[2];  // OASES_FLAG_PROFILE: start/stop event per operator of each pass
   bool prof_ran[2] = {false, false};
   std::vector<Tensor> tensors;     // per-layer tensors, offsets relative to the layer base
-  size_t layer_bytes, shared_off, scratch_comm_off, scratch_compute_off, gemm_ws_off, gemm_ws_bytes, total_bytes;
+  size_t layer_bytes, shared_off, scratch_comm_off, scratch_compute_off, gemm_ws_off, gemm_ws_bytes, slice_counters_off, total_bytes;
   // arena of partial rows of the backward pass's column reductions, per layer: five slots (see ColsumSlot)
   size_t colsum_off, colsum_layer_bytes, colsum_slot_off[5];
   int colsum_groups_sub, colsum_groups_all;  // row groups of a reduction over xMs rows / over all M rows
@@ -197,6 +199,8 @@ static bool plan_workspace(oases_handle* H) {
   H->gemm_ws_off = tot;
   H->gemm_ws_bytes = 8 * mn * 4 < kSplitKWorkspaceBytes ? 8 * mn * 4 : kSplitKWorkspaceBytes;
   tot += align_up(H->gemm_ws_bytes);
+  H->slice_counters_off = tot;  // of k slices that a launch adds up by itself: set to zero where a forward pass begins, left at zero by every launch
+  tot += align_up(kSliceCounters * 4);
   H->total_bytes = tot;
   return true;
 }
@@ -320,6 +324,24 @@ static int pass_sub_batches(const oases_handle* H) {
   return H->n;
 }
 
+// What a pass executes of the schedule's weight gradients: the two of a block share a launch where that is expected to take less
+// time.  Under OASES_FLAG_PIN_GEMM a pass launches what the schedule of a profiling handle launches, so that both give the same bits.
+static void group_weight_gradients(const oases_handle* H, std::vector<Op>& ops) {
+  if (H->cfg.flags & (OASES_FLAG_PIN_GEMM | OASES_FLAG_PROFILE)) return;
+  bool ff = false, pq = false;
+  gemm_tn_group_variant(H->M, H->fp, H->h, H->h, H->fw, H->gemm_ws_bytes, &ff);
+  gemm_tn_group_variant(H->M, H->hp, H->h, H->h, 3 * H->hp, H->gemm_ws_bytes, &pq);
+  std::vector<Op> out;
+  for (Op op : ops) {
+    if (ff && op.kind == B_FC1_WGRAD) continue;
+    if (ff && op.kind == B_FC2_WGRAD) op.kind = B_FF_GROUP;
+    if (pq && op.kind == B_QKV_WGRAD) continue;
+    if (pq && op.kind == B_PROJ_WGRAD) op.kind = B_PQ_GROUP;
+    out.push_back(op);
+  }
+  ops.swap(out);
+}
+
 static int check_ptrs(const void* const* p, int n, const char* who) {
   for (int i = 0; i < n; i++) {
     if (!p[i]) { set_error("%s: NULL device pointer (argument %d)", who, i); return OASES_ENULL; }
@@ -427,6 +449,7 @@ static int run_op(const Run& R, const Op& op) {
     return rc;
   };
   void* gws = R.ws + H->gemm_ws_off;  // split-K partial planes (compute stream only)
+  uint32_t* counters = reinterpret_cast<uint32_t*>(R.ws + H->slice_counters_off);
   const int pin = (H->cfg.flags & OASES_FLAG_PIN_GEMM) ? H->M : 0;  // kernels chosen as for all M rows, whatever the sub-batch
   uint16_t* u = wsp<uint16_t>(R, T_u, l);
   uint16_t* qkv = wsp<uint16_t>(R, T_qkv, l);
@@ -444,7 +467,7 @@ static int run_op(const Run& R, const Op& op) {
     switch (op.kind) {
       case F_LN1:
       case R_LN1:
-        return launch_cast_bf16(xin + r0 * h, u + r0 * h, (int64_t)Ms * h, s);
+        return launch_cast_bf16(xin + r0 * h, u + r0 * h, (int64_t)Ms * h, s, op.kind == F_LN1 ? counters : nullptr);
       case R_LN2:
         return launch_cast_bf16(wsp<float>(R, T_x1, l) + r0 * h, v2 + r0 * h, (int64_t)Ms * h, s);
       case F_R1:
@@ -489,7 +512,7 @@ static int run_op(const Run& R, const Op& op) {
   switch (op.kind) {
     case F_LN1:
       return launch_layernorm_fwd(xin + r0 * h, (const float*)W.ln1_g, (const float*)W.ln1_b, u + r0 * h,
-                                  wsp<float>(R, T_mu1, l) + r0, wsp<float>(R, T_rstd1, l) + r0, Ms, h, H->eps, s, rms);
+                                  wsp<float>(R, T_mu1, l) + r0, wsp<float>(R, T_rstd1, l) + r0, Ms, h, H->eps, s, rms, counters);
     case F_QKV:
       return launch_gemm(OASES_GEMM_NN, rms ? OASES_EPI_BF16 : OASES_EPI_BIAS_BF16, Ms, 3 * hp, h, u + r0 * h, h, W.wqkv, 3 * hp,
                          qkv + r0 * 3 * hp, 3 * hp, (const float*)W.bqkv, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin);
@@ -584,6 +607,12 @@ static int run_op(const Run& R, const Op& op) {
     case B_PQ_WGRAD:
       return launch_gemm_tn_pair(Ms, hp, h, attn + r0 * hp, hp, wsp<uint16_t>(R, T_dz1, l) + r0 * h, h, R.g[l].wo, h, h, 3 * hp, u + r0 * h, h,
                                  wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp, R.g[l].wqkv, 3 * hp, s);
+    case B_FF_GROUP:
+      return launch_gemm_tn_group(0, Ms, TnProblem{fp, h, f, fp, wsp<uint16_t>(R, T_dz2, l), h, R.g[l].w2, h},
+                                  TnProblem{h, fw, v2, h, wsp<uint16_t>(R, T_dg, l), fw, R.g[l].w1, fw}, (float*)gws, H->gemm_ws_bytes, counters, s);
+    case B_PQ_GROUP:
+      return launch_gemm_tn_group(0, Ms, TnProblem{hp, h, attn, hp, wsp<uint16_t>(R, T_dz1, l), h, R.g[l].wo, h},
+                                  TnProblem{h, 3 * hp, u, h, wsp<uint16_t>(R, T_dqkv, l), 3 * hp, R.g[l].wqkv, 3 * hp}, (float*)gws, H->gemm_ws_bytes, counters, s);
     case B_BQKV_SUM:
       { ColsumSink* cs = colsum(4); return colsum_done(launch_colsum_bf16(wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp, Ms, 3 * hp, (float*)R.g[l].bqkv, cs_scratch, s, cs)); }
     // ---------------------------------------------------------------- recompute: the forward kernels again
@@ -779,6 +808,7 @@ int oases_create(const oases_layer_cfg* c, oases_handle** out) {
   build_backward(H, H->n, H->bwd);
   build_forward(H, H->xn, H->xfwd);
   build_backward(H, H->xn, H->xbwd);
+  group_weight_gradients(H, H->xbwd);
   for (auto* ops : {&H->xfwd, &H->xbwd})
     for (Op& op : *ops) op.wait = op.record = -1;
   *out = H;
@@ -912,9 +942,9 @@ static int segment_of(int kind, bool backward) {
   }
   switch (kind) {
     case B_BDR2: return 2;
-    case R_LN2: case R_FC1: case B_FC2_DGRAD: case B_FC1_DGRAD: case B_FC2_WGRAD: case B_FC1_WGRAD: case B_B1_SUM: return 1;
+    case R_LN2: case R_FC1: case B_FC2_DGRAD: case B_FC1_DGRAD: case B_FC2_WGRAD: case B_FC1_WGRAD: case B_FF_GROUP: case B_B1_SUM: return 1;
     case B_R3: case R_LN1: case R_QKV: case R_ROPE: case R_ATTN: case B_PROJ_DGRAD: case B_ATTN: case B_ROPE: case B_QKV_DGRAD:
-    case B_PROJ_WGRAD: case B_QKV_WGRAD: case B_PQ_WGRAD: case B_BQKV_SUM: return 0;
+    case B_PROJ_WGRAD: case B_QKV_WGRAD: case B_PQ_WGRAD: case B_PQ_GROUP: case B_BQKV_SUM: return 0;
     case B_R4: return 3;
     default: return -1;
   }
@@ -1058,6 +1088,21 @@ int oases_op_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace
 int oases_op_gemm_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0, void* C0, int ldc0, int M1, int N1,
                           const void* A1, int lda1, const void* B1, int ldb1, void* C1, int ldc1, void* stream) {
   return launch_gemm_tn_pair(K, M0, N0, A0, lda0, B0, ldb0, C0, ldc0, M1, N1, A1, lda1, B1, ldb1, C1, ldc1, (hipStream_t)stream);
+}
+int oases_op_gemm_tn_group(int variant, int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0, void* C0, int ldc0, int M1, int N1,
+                           const void* A1, int lda1, const void* B1, int ldb1, void* C1, int ldc1, void* workspace, size_t workspace_bytes,
+                           void* stream) {
+  if (workspace && !aligned16(workspace)) { set_error("gemm_tn_group: workspace not 16-byte aligned"); return OASES_EALIGN; }
+  const size_t head = kSliceCounters * 4;
+  const bool room = workspace && workspace_bytes > head;
+  uint32_t* counters = room ? (uint32_t*)workspace : nullptr;
+  if (variant < 0) { set_error("gemm_tn_group: negative variant"); return OASES_EINVAL; }
+  if (room) {
+    int rc = launch_zero_counters(counters, (hipStream_t)stream);
+    if (rc) return rc;
+  }
+  return launch_gemm_tn_group(variant, K, TnProblem{M0, N0, A0, lda0, B0, ldb0, C0, ldc0}, TnProblem{M1, N1, A1, lda1, B1, ldb1, C1, ldc1},
+                              room ? (float*)((char*)workspace + head) : nullptr, room ? workspace_bytes - head : 0, counters, (hipStream_t)stream);
 }
 int oases_op_gemm_tn_pair_wins(int K, int M0, int N0, int M1, int N1) { return gemm_tn_pair_wins(K, M0, N0, M1, N1) ? 1 : 0; }
 size_t oases_gemm_workspace_bytes(const oases_handle* H) { return H ? H->gemm_ws_bytes : 0; }

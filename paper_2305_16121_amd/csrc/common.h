@@ -129,14 +129,16 @@ int launch_colsum_finalize(const ColsumJob* jobs, int n, hipStream_t s);
 
 // ---- kernel launchers (one per .hip file), all enqueue-only, return 0 or OASES_E* ---------------
 int launch_dropout_mask(uint8_t* mask, const DropCfg& d, int64_t row0, int rows, int h, hipStream_t s);
+// counters (layernorm_fwd, cast_bf16): kSliceCounters words that the launch sets to zero on the way
 // rms = true: RMSNorm (no mean, no beta; mu / beta unused and may be NULL); bias may be NULL with rms
 int launch_layernorm_fwd(const float* x, const float* gamma, const float* beta, void* out, float* mu,
-                         float* rstd, int rows, int h, float eps, hipStream_t s, bool rms = false);
+                         float* rstd, int rows, int h, float eps, hipStream_t s, bool rms = false, uint32_t* counters = nullptr);
 int launch_bdr_ln(const float* part, const float* peer, const float* bias, const float* xin, float* xo,
                   const float* gamma, const float* beta, void* ln_out, float* mu, float* rstd, int rows,
-                  int h, float eps, const DropCfg& d, int64_t row0, hipStream_t s, bool rms = false, float* ln_f32 = nullptr);
+                  int h, float eps, const DropCfg& d, int64_t row0, hipStream_t s, bool rms = false, float* ln_f32 = nullptr, uint32_t* counters = nullptr);
 // post-LN layers: out (bf16) = x (fp32), n elements; out = a + b (+ c) fp32
-int launch_cast_bf16(const float* x, void* out, int64_t n, hipStream_t s);
+int launch_cast_bf16(const float* x, void* out, int64_t n, hipStream_t s, uint32_t* counters = nullptr);
+int launch_zero_counters(uint32_t* counters, hipStream_t s);
 int launch_add3(const float* a, const float* b, const float* c, float* out, int64_t n, hipStream_t s);
 // rotary embedding: table [seq][head_dim/2] of (cos, sin) fp32; rotation in place on the Q and K parts of qkv
 int launch_rope_table(float* tab, int seq, int head_dim, float theta, hipStream_t s);
@@ -166,6 +168,22 @@ int gemm_variant(int op, int epi, int M, int N, int K, size_t ws_bytes);  // 1e8
 int launch_gemm_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0, void* C0, int ldc0, int M1, int N1,
                         const void* A1, int lda1, const void* B1, int ldb1, void* C1, int ldc1, hipStream_t s);
 bool gemm_tn_pair_wins(int K, int M0, int N0, int M1, int N1);
+// Two weight gradients C_i[M_i,N_i] += A_i[K,M_i]^T B_i[K,N_i] over the same K rows in one launch, on the kernel and with the k slices that `variant`
+// names (0: the library's choice).  k slices are added up by the launch itself, which takes partial sums in ws and one counter
+// per tile: kSliceCounters of them, zero before the launch and zero again behind it.
+struct TnProblem {
+  int M, N;
+  const void* A;
+  int lda;
+  const void* B;
+  int ldb;
+  void* C;
+  int ldc;
+};
+constexpr int kSliceCounters = 1024;
+int launch_gemm_tn_group(int variant, int K, const TnProblem& a, const TnProblem& b, float* ws, size_t ws_bytes, uint32_t* counters, hipStream_t s);
+// the library's choice; wins: whether one launch is expected to take less time than two
+int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes, bool* wins = nullptr);
 constexpr size_t kSplitKWorkspaceBytes = 256u << 20;
 // p_attn > 0: dropout on the probabilities (mask keyed by seed, layer, sequence, global head = head0 + local head, q, k)
 // pin: block shapes chosen as for all batch * seq rows, so that calls over parts of those rows add in one order whatever the part

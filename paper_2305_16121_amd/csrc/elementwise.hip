@@ -81,9 +81,12 @@ __global__ __launch_bounds__(T) void bdr_ln_kernel(const float* __restrict__ par
                                                     float* __restrict__ xo, const float* __restrict__ gamma,
                                                     const float* __restrict__ beta, uint16_t* __restrict__ ln_out,
                                                     float* __restrict__ mu_out, float* __restrict__ rstd_out, int h,
-                                                    float eps, DropCfg d, int64_t row0, float* __restrict__ ln_f32) {
+                                                    float eps, DropCfg d, int64_t row0, float* __restrict__ ln_f32,
+                                                    uint32_t* __restrict__ counters) {
   __shared__ float red[2 * (T / 64)];
   const int row = blockIdx.x, tid = threadIdx.x;
+  if (counters && row == 0)
+    for (int i = tid; i < kSliceCounters; i += T) counters[i] = 0;
   const int nc = h >> 2;
   const size_t base = (size_t)row * h;
   f32x4 v[NC], z[NC];
@@ -420,11 +423,17 @@ __global__ __launch_bounds__(NT) void rope_kernel(uint16_t* __restrict__ qkv, in
 
 // ------------------------------------------------------------------------------------------------
 // out (bf16) = x (fp32); n4 groups of 4 elements
-__global__ __launch_bounds__(NT) void cast_bf16_kernel(const float* __restrict__ x, uint16_t* __restrict__ out, int64_t n4) {
+__global__ __launch_bounds__(NT) void cast_bf16_kernel(const float* __restrict__ x, uint16_t* __restrict__ out, int64_t n4,
+                                                       uint32_t* __restrict__ counters) {
+  if (counters && blockIdx.x == 0)
+    for (int c = threadIdx.x; c < kSliceCounters; c += NT) counters[c] = 0;
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
   if (i >= n4) return;
   const f32x4 v = *reinterpret_cast<const f32x4*>(x + 4 * i);
   store_bf16x4(out + 4 * i, v[0], v[1], v[2], v[3]);
+}
+__global__ __launch_bounds__(NT) void zero_counters_kernel(uint32_t* __restrict__ counters) {
+  for (int c = threadIdx.x; c < kSliceCounters; c += NT) counters[c] = 0;
 }
 // out = a + b (+ c), fp32
 __global__ __launch_bounds__(NT) void add3_kernel(const float* __restrict__ a, const float* __restrict__ b, const float* __restrict__ c,
@@ -516,7 +525,7 @@ int launch_dropout_mask(uint8_t* mask, const DropCfg& d, int64_t row0, int rows,
 
 int launch_bdr_ln(const float* part, const float* peer, const float* bias, const float* xin, float* xo,
                   const float* gamma, const float* beta, void* ln_out, float* mu, float* rstd, int rows, int h,
-                  float eps, const DropCfg& d, int64_t row0, hipStream_t s, bool rms, float* ln_f32) {
+                  float eps, const DropCfg& d, int64_t row0, hipStream_t s, bool rms, float* ln_f32, uint32_t* counters) {
   if (!check_h(rows, h, "bias_dropout_residual_ln")) return OASES_EINVAL;
   if (!xin || (part && !xo) || (part && !rms && !bias) || ((ln_out || ln_f32) && (!gamma || !rstd || (!rms && (!beta || !mu))))) {
     set_error("bias_dropout_residual_ln: NULL argument");
@@ -524,7 +533,7 @@ int launch_bdr_ln(const float* part, const float* peer, const float* bias, const
   }
 #define OASES_BDR_LN(RMS)                                                                                                       \
   OASES_ROW_DISPATCH(h, hipLaunchKernelGGL((bdr_ln_kernel<NC, T, RMS>), dim3(rows), dim3(T), 0, s, part, peer, bias, xin, xo, gamma, \
-                                           beta, (uint16_t*)ln_out, mu, rstd, h, eps, d, row0, ln_f32))
+                                           beta, (uint16_t*)ln_out, mu, rstd, h, eps, d, row0, ln_f32, counters))
   if (rms) { OASES_BDR_LN(true); } else { OASES_BDR_LN(false); }
 #undef OASES_BDR_LN
   OASES_LAUNCH_CHECK("bdr_ln_kernel");
@@ -532,10 +541,10 @@ int launch_bdr_ln(const float* part, const float* peer, const float* bias, const
 }
 
 int launch_layernorm_fwd(const float* x, const float* gamma, const float* beta, void* out, float* mu, float* rstd,
-                         int rows, int h, float eps, hipStream_t s, bool rms) {
+                         int rows, int h, float eps, hipStream_t s, bool rms, uint32_t* counters) {
   DropCfg d = make_drop_cfg(0, 0, 0, 0.f);
   if (!out) { set_error("layernorm_fwd: NULL output"); return OASES_ENULL; }
-  return launch_bdr_ln(nullptr, nullptr, nullptr, x, nullptr, gamma, beta, out, mu, rstd, rows, h, eps, d, 0, s, rms, nullptr);
+  return launch_bdr_ln(nullptr, nullptr, nullptr, x, nullptr, gamma, beta, out, mu, rstd, rows, h, eps, d, 0, s, rms, nullptr, counters);
 }
 
 int colsum_groups(int rows) { return col_groups(rows); }
@@ -601,11 +610,17 @@ int launch_layernorm_bwd(const float* part, const float* peer, const float* dres
   return finish_colsums(sink, scratch, kstride, dgamma, rms ? nullptr : dbeta, want_dbias ? dbias : nullptr, groups, h, s);
 }
 
-int launch_cast_bf16(const float* x, void* out, int64_t n, hipStream_t s) {
+int launch_cast_bf16(const float* x, void* out, int64_t n, hipStream_t s, uint32_t* counters) {
   if (!x || !out) { set_error("cast_bf16: NULL argument"); return OASES_ENULL; }
   if (n <= 0 || n % 4 || !aligned16(x) || (reinterpret_cast<uintptr_t>(out) & 7u)) { set_error("cast_bf16: n must be a positive multiple of 4, pointers aligned"); return OASES_EINVAL; }
-  hipLaunchKernelGGL(cast_bf16_kernel, dim3((unsigned)((n / 4 + NT - 1) / NT)), dim3(NT), 0, s, x, (uint16_t*)out, n / 4);
+  hipLaunchKernelGGL(cast_bf16_kernel, dim3((unsigned)((n / 4 + NT - 1) / NT)), dim3(NT), 0, s, x, (uint16_t*)out, n / 4, counters);
   OASES_LAUNCH_CHECK("cast_bf16_kernel");
+  return 0;
+}
+
+int launch_zero_counters(uint32_t* counters, hipStream_t s) {
+  hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(NT), 0, s, counters);
+  OASES_LAUNCH_CHECK("zero_counters_kernel");
   return 0;
 }
 

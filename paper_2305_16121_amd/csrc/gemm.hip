@@ -9,6 +9,7 @@
 // with the LDS transpose read ds_read_b64_tr_b16, which hands each lane 4 consecutive k of one row.
 // v_mfma_f32_32x32x16_bf16: A lane l holds row l%32, k = 8*(l/32)..+7; B the same with columns;
 // accumulator element i of lane l is C[8*(i/4) + 4*(l/32) + i%4][l%32].
+#include <algorithm>
 #include <type_traits>
 #ifdef OASES_GEMM_TUNE_HOOK
 #include <stdio.h>
@@ -1119,9 +1120,48 @@ constexpr int kPpLds256 = NSD * kDtlStage;                                  // 1
 constexpr int kPpExchange = 8 * 2 * 2 * 4 * 64 * 16;                        // 128 x 256 tiles: half of every wave's accumulator
 constexpr int kPpLds128 = NSR * kRectStage > kPpExchange ? NSR * kRectStage : kPpExchange;  // 144 KB
 
-template <int BM, bool A_KC, bool B_KC, int EPI, bool FULL>
-__device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds) {
+// k slices that are added up by the launch itself: every workgroup of a tile leaves its partial sums in `part`
+// ([tile][slice][wave][quarter][half][lane] x 2 floats, so that each access of a wave is whole lines) and counts itself in; whoever counts last
+// has all of them, adds them in slice order (its own from registers, at its place) and runs the epilogue.  Nobody waits for
+// anybody, so it does not matter how many workgroups are resident.  The counter is 0 before the launch and again behind it.
+// Partial sums and counters cross XCDs, whose L2s do not see each other's lines: they are stored and loaded as relaxed atomics of
+// agent scope, i.e. past the L2, and a wave has waited for its stores when its workgroup counts itself in.  (Plain stores between
+// release and acquire fences, which write back and drop whole L2s, took 15 us and more per launch.)
+struct SliceSum {
+  float* part;
+  uint32_t* counter;
+  int slice, slices;
+};
+constexpr int kSlicePartFloats = 128 * 256;  // partial sums of one workgroup
+// true in every thread of the workgroup that came last.  lds: four bytes that no wave uses any more
+__device__ __forceinline__ bool last_slice(const SliceSum& ss, char* lds) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();  // the whole workgroup's partial sums are written
+  uint32_t* flag = reinterpret_cast<uint32_t*>(lds);
+  if (threadIdx.x == 0) {
+    const uint32_t before = __hip_atomic_fetch_add(ss.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = before == (uint32_t)ss.slices - 1;
+    if (last) __hip_atomic_store(ss.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *flag = last;
+  }
+  __syncthreads();
+  return *flag != 0;
+}
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void slice_store(uint64_t* p, const f32x4& v) {
+  const u64x2 w = __builtin_bit_cast(u64x2, v);
+  __hip_atomic_store(p, w[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(p + 64, w[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ f32x4 slice_load(uint64_t* p) {
+  const u64x2 w = {__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), __hip_atomic_load(p + 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
+  return __builtin_bit_cast(f32x4, w);
+}
+
+template <int BM, bool A_KC, bool B_KC, int EPI, bool FULL, bool SLICED = false>
+__device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, const SliceSum& ss = SliceSum{}) {
   static_assert(BM == 256 || BM == 128, "block tiles 256 x 256 and 128 x 256");
+  static_assert(!SLICED || (BM == 128 && EPI != EPI_F32 && EPI != EPI_SWIGLU), "slices: transposed accumulators of 128 x 256 tiles");
   constexpr bool SQ = BM == 256;
   constexpr int NS = SQ ? NSD : NSR;                 // LDS stages
   constexpr int KT = SQ ? BKD : BKR;                 // k extent of a stage
@@ -1314,6 +1354,50 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds) {
       }
     };
     if (grp == 0) hand_over(std::integral_constant<int, 1>{}); else hand_over(std::integral_constant<int, 0>{});
+    if constexpr (SLICED) {
+      __syncthreads();
+      // this wave's 64 x 64 part of the tile, both k halves
+      f32x4 v[16];
+      auto gather = [&](auto half_c) {
+        constexpr int H = decltype(half_c)::value;
+#pragma unroll
+        for (int q = 0; q < 16; q++) {
+          const f32x16& a = acc[H * 2 + (q >> 3)][(q >> 2) & 1];
+          v[q] = f32x4{a[4 * (q & 3)], a[4 * (q & 3) + 1], a[4 * (q & 3) + 2], a[4 * (q & 3) + 3]} + xch[(theirs + q) * 64 + lane];
+        }
+      };
+      if (grp == 0) gather(std::integral_constant<int, 0>{}); else gather(std::integral_constant<int, 1>{});
+      uint64_t* tile_part = reinterpret_cast<uint64_t*>(ss.part) + (size_t)wave * 16 * 128 + lane;
+      constexpr int kPlane = kSlicePartFloats / 2;
+#pragma unroll
+      for (int q = 0; q < 16; q++) slice_store(tile_part + (size_t)ss.slice * kPlane + q * 128, v[q]);
+      if (!last_slice(ss, lds + kPpLds128 - 16)) return;
+      if constexpr (READS) {
+        request(eo[0], m0 + grp * 64);
+        if (!BIAS) request(eo[1], m0 + grp * 64 + 32);
+      }
+      f32x4 sum[16];
+#pragma unroll
+      for (int q = 0; q < 16; q++) sum[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int sl = 0; sl < ss.slices; sl++) {
+        const bool own = sl == ss.slice;
+        f32x4 p[16];
+#pragma unroll
+        for (int q = 0; q < 16; q++) p[q] = own ? v[q] : slice_load(tile_part + (size_t)sl * kPlane + q * 128);
+#pragma unroll
+        for (int q = 0; q < 16; q++) sum[q] = sl == 0 ? p[q] : sum[q] + p[q];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+          f32x16 a;
+#pragma unroll
+          for (int e = 0; e < 16; e++) a[e] = sum[(i * 2 + j) * 4 + (e >> 2)][e & 3];
+          epi_finish<EPI, FULL>(g, m0 + (grp * 2 + i) * 32, n0 + wn * 64 + 32 * j, lane, a, eo[BIAS ? 0 : i][j]);
+        }
+      return;
+    }
     if constexpr (READS) {
       request(eo[0], m0 + grp * 64);
       if (!BIAS) request(eo[1], m0 + grp * 64 + 32);
@@ -1339,12 +1423,28 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs g) {  // g: by va
 }
 
 // Two weight-gradient contractions over the same K rows in one launch: the tiles of the second problem follow those of
-// the first, so that two launches that would each leave CUs idle (or need k slices to fill them) share one round.
-__global__ __launch_bounds__(512) void gemm_pp_pair_kernel(GemmArgs g0, GemmArgs g1) {
+// the first, so that two launches that would each leave CUs idle (or need k slices to fill them) share one round.  SLICED: slice
+// after slice of all tiles, added up as above.
+template <bool FULL, bool SLICED>
+__global__ __launch_bounds__(512) void gemm_pp_group_kernel(GemmArgs g0, GemmArgs g1, float* part, uint32_t* counters) {
   __shared__ __attribute__((aligned(1024))) char lds[kPpLds128];
-  const int first = g0.tiles_m * g0.tiles_n;
-  if ((int)blockIdx.x < first) pp_tile<128, false, false, EPI_ACC_F32, true>(g0, blockIdx.x, lds);
-  else pp_tile<128, false, false, EPI_ACC_F32, true>(g1, blockIdx.x - first, lds);
+  const int first = g0.tiles_m * g0.tiles_n, T = first + g1.tiles_m * g1.tiles_n;
+  int pid = blockIdx.x;
+  SliceSum ss{};
+  if constexpr (SLICED) {
+    const int slice = pid / T;
+    pid -= slice * T;
+    ss = SliceSum{part + (size_t)pid * g0.ksplit * kSlicePartFloats, counters + pid, slice, g0.ksplit};
+  }
+  const bool second = pid >= first;
+  GemmArgs g = second ? g1 : g0;
+  if constexpr (SLICED) {
+    const int k0 = ss.slice * g.k_per;
+    g.A += (size_t)k0 * g.lda;
+    g.B += (size_t)k0 * g.ldb;
+    g.K = min(g.K - k0, g.k_per);
+  }
+  pp_tile<128, false, false, EPI_ACC_F32, FULL, SLICED>(g, second ? pid - first : pid, lds, ss);
 }
 
 // =================================================================================================
@@ -1430,23 +1530,17 @@ __device__ __forceinline__ void st_wait_frags(u32x4 (&a)[2][1], u32x4 (&b)[2][2]
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0][0]), "+v"(a[1][0]), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
 }
 
+template <int TN, int NS>
+struct StLds {
+  static constexpr int kStage = (64 + 64 * TN) * BKS * 2, kExchange = 8 * TN * 2 * 64 * 16;  // exchange: half of every wave's accumulator
+  static constexpr int bytes = NS * kStage > kExchange ? NS * kStage : kExchange;
+};
 template <int TN, int NS, bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(512) void gemm_st_kernel(GemmArgs g) {  // g: by value, adjusted per k slice
+__device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds) {
   constexpr int BM = 64, BN = 64 * TN;
-  constexpr int kOpA = BM * BKS * 2, kStage = (BM + BN) * BKS * 2;
+  constexpr int kOpA = BM * BKS * 2, kStage = StLds<TN, NS>::kStage;
   constexpr int PER_A = 1, PER_B = TN, PER = PER_A + PER_B;  // direct-to-LDS instructions of a wave per stage
-  constexpr int kExchange = 8 * TN * 2 * 64 * 16;                       // half of every wave's accumulator
   static_assert(EPI != EPI_SWIGLU || TN == 2, "gate and up columns of a block must belong to one wave");
-  __shared__ __attribute__((aligned(1024))) char lds[NS * kStage > kExchange ? NS * kStage : kExchange];
-  int pid = blockIdx.x;
-  if (g.ksplit > 1) {  // this workgroup's k range (k_per: a whole number of stages) and fp32 partial-result plane
-    const int T = g.tiles_m * g.tiles_n, slice = pid / T, k0 = slice * g.k_per;
-    pid -= slice * T;
-    g.A += A_KC ? (size_t)k0 : (size_t)k0 * g.lda;
-    g.B += B_KC ? (size_t)k0 : (size_t)k0 * g.ldb;
-    g.K = min(g.K - k0, g.k_per);
-    g.C = reinterpret_cast<float*>(g.C) + (size_t)slice * g.M * g.ldc;
-  }
   int tile_m, tile_n;
   tile_of_workgroup(pid, g.tiles_m, g.tiles_n, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
@@ -1607,6 +1701,31 @@ __global__ __launch_bounds__(512) void gemm_st_kernel(GemmArgs g) {  // g: by va
   else { if (wk == 0) finish(H0{}, std::false_type{}); else finish(H1{}, std::false_type{}); }
 }
 
+template <int TN, int NS, bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(512) void gemm_st_kernel(GemmArgs g) {  // g: by value, adjusted per k slice
+  __shared__ __attribute__((aligned(1024))) char lds[StLds<TN, NS>::bytes];
+  int pid = blockIdx.x;
+  if (g.ksplit > 1) {  // this workgroup's k range (k_per: a whole number of stages) and fp32 partial-result plane
+    const int T = g.tiles_m * g.tiles_n, slice = pid / T, k0 = slice * g.k_per;
+    pid -= slice * T;
+    g.A += A_KC ? (size_t)k0 : (size_t)k0 * g.lda;
+    g.B += B_KC ? (size_t)k0 : (size_t)k0 * g.ldb;
+    g.K = min(g.K - k0, g.k_per);
+    g.C = reinterpret_cast<float*>(g.C) + (size_t)slice * g.M * g.ldc;
+  }
+  st_tile<TN, NS, A_KC, B_KC, EPI>(g, pid, lds);
+}
+
+// two weight gradients over the same K rows, tiles of the second behind those of the first
+template <int TN, int NS>
+__global__ __launch_bounds__(512) void gemm_st_group_kernel(GemmArgs g0, GemmArgs g1) {
+  __shared__ __attribute__((aligned(1024))) char lds[StLds<TN, NS>::bytes];
+  const int first = g0.tiles_m * g0.tiles_n;
+  const bool second = (int)blockIdx.x >= first;
+  const GemmArgs g = second ? g1 : g0;
+  st_tile<TN, NS, false, false, EPI_ACC_F32>(g, second ? blockIdx.x - first : blockIdx.x, lds);
+}
+
 // split-K second pass: C = epilogue(sum over slices of the fp32 partial planes), slices added in index order
 template <int EPI>
 __global__ __launch_bounds__(256) void splitk_fixup_kernel(const float* __restrict__ part, int S, GemmArgs g) {
@@ -1744,7 +1863,7 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
 // us, large tile -> small: 4096 x 1536 x 2048 NN bias 31.6 -> 34.8 (stays large), 1024 x 3072 x 8192 56.2 -> 71.6 (stays
 // large), 4096 x 512 x 4096 NT 29.8 -> 22.9, 1024 x 1024 x 4096 TN 21.4 -> 16.9, 64 x 4608 x 12288 NN 53.5 -> 34.8,
 // 6144 x 12288 x 128 TN 195 -> 152.  Slices of 8192 k and more stay with the large tiles.
-TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes) {
+TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, double* seconds = nullptr) {
   const TileChoice large = pick_large_tile(kind, epi, M, N, K, ws_bytes);
   const KindTable& kt = g_kinds[kind];
   const double out = (double)M * N * (epi == EPI_F32 ? 4.0 : kind == 2 ? 8.0 : epi == EPI_SWIGLU ? 3.0 : epi == EPI_DSWIGLU ? 8.0 : epi == EPI_BIAS_GELU || epi == EPI_DGELU ? 4.0 : 2.0);
@@ -1768,6 +1887,7 @@ TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes) {
         best.st = true;
       }
     }
+  if (seconds) *seconds = best_t;
   return best;
 }
 
@@ -2012,8 +2132,101 @@ int launch_gemm_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const v
   }
   GemmArgs g0{(const uint16_t*)A0, (const uint16_t*)B0, C0, nullptr, nullptr, M0, N0, K, lda0, ldb0, ldc0, 0, M0 / 128, N0 / 256, 1, K};
   GemmArgs g1{(const uint16_t*)A1, (const uint16_t*)B1, C1, nullptr, nullptr, M1, N1, K, lda1, ldb1, ldc1, 0, M1 / 128, N1 / 256, 1, K};
-  hipLaunchKernelGGL(gemm_pp_pair_kernel, dim3(g0.tiles_m * g0.tiles_n + g1.tiles_m * g1.tiles_n), dim3(512), 0, s, g0, g1);
-  OASES_LAUNCH_CHECK("gemm_pp_pair_kernel");
+  hipLaunchKernelGGL((gemm_pp_group_kernel<true, false>), dim3(g0.tiles_m * g0.tiles_n + g1.tiles_m * g1.tiles_n), dim3(512), 0, s, g0, g1, nullptr, nullptr);
+  OASES_LAUNCH_CHECK("gemm_pp_group_kernel");
+  return 0;
+}
+
+// Two weight gradients of a block in one launch.  Variants as those of a single GEMM: 30S128256 (here S = 1, 2, 4 or 8 slices, summed by the launch
+// itself), 401064064, 401064128.
+static bool tn_group_fits(int variant, int K, int M0, int N0, int M1, int N1, size_t ws_bytes) {
+  if (variant == 401064064 || variant == 401064128) return true;
+  const int S = variant / 1000000 % 100;
+  if (variant != 300128256 + S * 1000000 || (S != 1 && S != 2 && S != 4 && S != 8) || K % BKR) return false;
+  const long T = (long)((M0 + 127) / 128) * ((N0 + 255) / 256) + (long)((M1 + 127) / 128) * ((N1 + 255) / 256);
+  // every slice has stages of its own
+  const int k_per = (K / BKR + S - 1) / S * BKR;
+  return S == 1 || (T <= kSliceCounters && (long)(S - 1) * k_per < K && (size_t)T * S * kSlicePartFloats * 4 <= ws_bytes);
+}
+// Time of an eight-wave launch over wgs workgroups, seconds.  What the MFMA loops are bound by is the power they draw together, so a
+// round that leaves CUs idle runs its stages faster, down to three quarters of the time of a full one (128x256 tiles, a 64-wide
+// stage: 256 workgroups 0.9 us, 144 or fewer 0.68); the output, read and written, moves at 4.5 TB/s.
+static double pp_seconds(int bm, long wgs, int k_per, double out_bytes) {
+  double t = out_bytes / 4.5e12;
+  for (; wgs > 0; wgs -= 256)
+    t += 4.0e-6 + k_per / 64 * (bm == 256 ? 1.75e-6 : 0.9e-6) * std::max(0.75, (double)std::min(wgs, 256L) / 256.0);
+  return t;
+}
+static double tn_single_seconds(int M, int N, int K, size_t ws_bytes) {
+  double t;
+  const TileChoice c = pick_tile(2, EPI_ACC_F32, M, N, K, ws_bytes, &t);
+  if (c.st || c.bn != 256) return t;
+  t = pp_seconds(c.bm, (long)((M + c.bm - 1) / c.bm) * ((N + 255) / 256) * c.ksplit, K / c.ksplit, 8.0 * M * N);
+  return c.ksplit > 1 ? t + 3.2e-6 + 8.0 * c.ksplit * M * N / 6.0e12 : t;
+}
+// Which kernel, how many slices, and whether one launch takes less time than two.  k slices cost 2 us and 2.7 us each: the last
+// workgroup of a tile reads the others' sums one after the other.  Both sides measured, us, two launches -> one: 8192 rows,
+// 2048x2048 twice 141 -> 116 (one round instead of two with slices), 512x2048 and 2048x1536 84 -> 68 (two slices; one 83, four 81), 1376x4096 and
+// 4096x2752 268 -> 290 (stays two launches: 176 tiles of 256x256 each fill one round); 4096 rows, 1024x1024 twice 35 -> 26; 2048
+// rows, 256x1024 and 1024x768 18 -> 12; 512 rows, 1024x512 twice 9.7 -> 7.
+int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes, bool* wins) {
+  const double out = ((double)M0 * N0 + (double)M1 * N1) * 8.0;
+  double best_t = 1e30;
+  int best = 0;
+  const long T = (long)((M0 + 127) / 128) * ((N0 + 255) / 256) + (long)((M1 + 127) / 128) * ((N1 + 255) / 256);
+  for (int S = 1; S <= 8; S *= 2) {
+    const int v = 300128256 + S * 1000000;
+    if (!tn_group_fits(v, K, M0, N0, M1, N1, ws_bytes)) continue;
+    const double t = pp_seconds(128, T * S, (K / BKR + S - 1) / S * BKR, out) + (S > 1 ? 2.0e-6 + 2.7e-6 * S : 0.0);
+    if (t < best_t) { best_t = t; best = v; }
+  }
+  for (int bn = 64; bn <= 128; bn += 64) {
+    const long per_cu = ((long)((M0 + 63) / 64) * ((N0 + bn - 1) / bn) + (long)((M1 + 63) / 64) * ((N1 + bn - 1) / bn) + 255) / 256;
+    const double t = 2.9e-6 + (double)per_cu * ((K + BKS - 1) / BKS) * (bn == 64 ? 0.225e-6 : 0.335e-6) + out / 4.0e12;
+    if (t < best_t) { best_t = t; best = 401064000 + bn; }
+  }
+  if (wins) *wins = gemm_span_fits(K, std::max({M0, N0, M1, N1})) && best_t < tn_single_seconds(M0, N0, K, ws_bytes) + tn_single_seconds(M1, N1, K, ws_bytes);
+  return best;
+}
+
+int launch_gemm_tn_group(int variant, int K, const TnProblem& a, const TnProblem& b, float* ws, size_t ws_bytes, uint32_t* counters, hipStream_t s) {
+  for (const TnProblem* p : {&a, &b}) {
+    if (K <= 0 || p->M <= 0 || p->N <= 0 || K % 8 || p->M % 8 || p->N % 8 || p->lda % 8 || p->ldb % 8 || p->ldc % 4 || p->lda < p->M || p->ldb < p->N ||
+        p->ldc < p->N) {
+      set_error("gemm_tn_group: K, M, N, lda, ldb must be positive multiples of 8, ldc of 4, no leading dimension below its width (K=%d M=%d N=%d)", K, p->M, p->N);
+      return OASES_EINVAL;
+    }
+    if (!gemm_span_fits(K, p->lda) || !gemm_span_fits(K, p->ldb)) { set_error("gemm_tn_group: an operand spans 2 GiB or more (K=%d rows)", K); return OASES_EINVAL; }
+    if (!p->A || !p->B || !p->C) { set_error("gemm_tn_group: NULL operand"); return OASES_ENULL; }
+    if (!aligned16(p->A) || !aligned16(p->B) || !aligned16(p->C)) { set_error("gemm_tn_group: operand not 16-byte aligned"); return OASES_EALIGN; }
+  }
+  if (!variant) variant = gemm_tn_group_variant(K, a.M, a.N, b.M, b.N, ws && counters ? ws_bytes : 0);
+  if (!tn_group_fits(variant, K, a.M, a.N, b.M, b.N, ws && counters ? ws_bytes : 0)) {
+    set_error("gemm_tn_group: variant %d does not exist or does not fit K=%d, %dx%d and %dx%d with %zu workspace bytes", variant, K, a.M, a.N, b.M, b.N, ws_bytes);
+    return OASES_EINVAL;
+  }
+  const int bm = variant / 1000 % 1000, bn = variant % 1000, S = variant / 1000000 % 100;
+  auto args = [&](const TnProblem& p) {
+    return GemmArgs{(const uint16_t*)p.A, (const uint16_t*)p.B, p.C, nullptr, nullptr, p.M, p.N, K, p.lda, p.ldb, p.ldc, 0,
+                    (p.M + bm - 1) / bm, (p.N + bn - 1) / bn, S, (K / BKR + S - 1) / S * BKR};
+  };
+  const GemmArgs g0 = args(a), g1 = args(b);
+  const dim3 grid((unsigned)((g0.tiles_m * g0.tiles_n + g1.tiles_m * g1.tiles_n) * S));
+  if (bm == 64) {
+    if (bn == 64) hipLaunchKernelGGL((gemm_st_group_kernel<1, 5>), grid, dim3(512), 0, s, g0, g1);
+    else hipLaunchKernelGGL((gemm_st_group_kernel<2, 3>), grid, dim3(512), 0, s, g0, g1);
+    OASES_LAUNCH_CHECK("gemm_st_group_kernel");
+    return 0;
+  }
+  const bool whole = a.M % 128 == 0 && a.N % 256 == 0 && b.M % 128 == 0 && b.N % 256 == 0;
+  if (S > 1) {
+    if (whole) hipLaunchKernelGGL((gemm_pp_group_kernel<true, true>), grid, dim3(512), 0, s, g0, g1, ws, counters);
+    else hipLaunchKernelGGL((gemm_pp_group_kernel<false, true>), grid, dim3(512), 0, s, g0, g1, ws, counters);
+  } else {
+    if (whole) hipLaunchKernelGGL((gemm_pp_group_kernel<true, false>), grid, dim3(512), 0, s, g0, g1, nullptr, nullptr);
+    else hipLaunchKernelGGL((gemm_pp_group_kernel<false, false>), grid, dim3(512), 0, s, g0, g1, nullptr, nullptr);
+  }
+  OASES_LAUNCH_CHECK("gemm_pp_group_kernel");
   return 0;
 }
 
