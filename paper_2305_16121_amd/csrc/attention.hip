@@ -142,6 +142,8 @@ __device__ __forceinline__ f32x16 zero16() {
   for (int i = 0; i < 16; i++) z[i] = 0.f;
   return z;
 }
+// What stands before it is issued before what stands behind it.
+#define OASES_ISSUED() __builtin_amdgcn_sched_barrier(0)
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
 
 // 32 x D bf16 rows of one operand straight from global memory into B/A-operand registers: lane l holds row l%32,
@@ -347,9 +349,21 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_kernel(AttnArgs a) {
     if constexpr (L::NS == 2) park_next();
     const int kv0 = t * BK + 32 * kg;
     if (kv0 < a.seq && !(CAUSAL && kv0 >= q_end)) {  // uniform over the wave: some key is visible to some query
+      // The fragments of K are requested together, and those of V ahead of the softmax that covers their latency; left to itself the compiler
+      // requests one or two at a time and every product waits for one.  us: 8x1024x8x64 30 -> 26, 4x2048x4x128 43.4 -> 42.2, not causal 58 -> 54.
       f32x16 s = zero16();
+      bf16x8 kf[KS], vf[2][DT];
 #pragma unroll
-      for (int ks = 0; ks < KS; ks++) s = MFMA(tile_kc<D>(lk, 32 * kg, ks, lane), qf[ks], s);
+      for (int ks = 0; ks < KS; ks++) kf[ks] = tile_kc<D>(lk, 32 * kg, ks, lane);
+      OASES_ISSUED();
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) s = MFMA(kf[ks], qf[ks], s);
+      OASES_ISSUED();
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int dt = 0; dt < DT; dt++) vf[j][dt] = tile_mc<D>(lv, 32 * kg, j, dt, lane);
+      OASES_ISSUED();
       if ((kv0 + 32 > a.seq) || (CAUSAL && kv0 + 31 > q_begin)) {
         OASES_RARE();
 #pragma unroll
@@ -398,7 +412,7 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_kernel(AttnArgs a) {
       for (int j = 0; j < 2; j++) {
         bf16x8 pb = pack8(s, 8 * j);
 #pragma unroll
-        for (int dt = 0; dt < DT; dt++) o[dt] = MFMA(tile_mc<D>(lv, 32 * kg, j, dt, lane), pb, o[dt]);
+        for (int dt = 0; dt < DT; dt++) o[dt] = MFMA(vf[j][dt], pb, o[dt]);
       }
     }
     lds_barrier();
