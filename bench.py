@@ -90,10 +90,10 @@ def gemm_kernel_label(line, cfg, B, ws_bytes):
         return None
     form, epi, m, n, k = shapes[op]
     epi_id = {"f32": 0, "bf16": 1, "bias_bf16": 2, "bias_gelu": 3, "dgelu": 4, "acc_f32": 0, "swiglu": 6, "dswiglu": 7}[epi]
-    tile = B.lib.oases_op_gemm_variant({"NN": 0, "NT": 1, "TN": 2}[form], epi_id, m, n, k, ws_bytes)
+    tile = B.lib.oases_pass_gemm_variant({"NN": 0, "NT": 1, "TN": 2}[form], epi_id, m, n, k, ws_bytes)
     slices = tile // 1000000 % 100
     split = f"_splitk{slices}" if slices >= 2 else ""
-    wk = {0: "", 1: "_wavek2", 2: "_dtl", 3: "_pp", 4: "_st"}[tile // 100000000]
+    wk = {0: "", 1: "_wavek2", 2: "_dtl", 3: "_pp", 4: "_st", 5: "_st"}[tile // 100000000]
     return f"gemm_{form}_{epi}_{tile // 1000 % 1000}x{tile % 1000}{wk}{split}"
 
 

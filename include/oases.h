@@ -313,16 +313,20 @@ int oases_op_gemm(int op, int epi, int M, int N, int K, const void *A, int lda, 
  * the same tiles (two waves per SIMD that alternate between loading and multiplying): 301256256, 301128256, 302128256,
  * 304128256, on the shapes of their W = 2 counterparts; 301128256 gives bit for bit what 201128256 gives.  W = 4 names the
  * small-tile kernels 64x64 and 64x128 (401064064, 401064128; direct-to-LDS loads, waves split k, any shape the GEMM
- * accepts, up to 16 slices of whole 64-wide stages; the forward SwiGLU epilogue on 64x128 only).  The W >= 2
+ * accepts, up to 16 slices of whole 64-wide stages; the forward SwiGLU epilogue on 64x128 only), W = 5 the same with 128x128 tiles
+ * (501128128; chosen in passes only, see below).  The W >= 2
  * kernels address an operand with 32-bit byte offsets: oases_op_gemm launches them only if rows x leading
  * dimension x 2 bytes of A and of B stay under 2 GiB (the staged kernel of the same tile otherwise), and
  * oases_op_gemm_forced returns EINVAL for them on larger operands.
  * Host only; used to group per-operator timings by kernel. */
 int oases_op_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace_bytes);
+/* The same for a GEMM of a pass.  There the launches of the W = 3, 4 and 5 kernels add up their k slices themselves, in slice order (the same
+ * result bit for bit), with counters that the pass keeps at zero in its workspace, so slices cost less and more shapes take them. */
+int oases_pass_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace_bytes);
 /* oases_op_gemm on the instantiation `variant` names (encoding above) instead of the one the library would choose:
  * for tests and tuning sweeps.  EINVAL if no such instantiation exists (block tiles 256x256, 128x256, 256x128,
- * 128x128; W = 1 only with the rectangular ones; W = 2, 3 only as x01256256, x01128256, x02128256 or x04128256 on shapes they fit, W = 4 as 4SS064064 or 4SS064128; 1..8
- * slices, W = 4: 1..16), if the slices do not fit K (every slice needs at least
+ * 128x128; W = 1 only with the rectangular ones; W = 2, 3 only as x01256256, x01128256, x02128256 or x04128256 on shapes they fit, W = 4 as 4SS064064 or 4SS064128, W = 5 as 5SS128128; 1..8
+ * slices, W = 4, 5: 1..16), if the slices do not fit K (every slice needs at least
  * one k column) or if the workspace is smaller than slices*M*N*4 bytes.  Results of different variants differ only
  * by the fp32 summation order. */
 int oases_op_gemm_forced(int variant, int op, int epi, int M, int N, int K, const void *A, int lda,

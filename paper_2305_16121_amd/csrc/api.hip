@@ -515,7 +515,7 @@ static int run_op(const Run& R, const Op& op) {
                                   wsp<float>(R, T_mu1, l) + r0, wsp<float>(R, T_rstd1, l) + r0, Ms, h, H->eps, s, rms, counters);
     case F_QKV:
       return launch_gemm(OASES_GEMM_NN, rms ? OASES_EPI_BF16 : OASES_EPI_BIAS_BF16, Ms, 3 * hp, h, u + r0 * h, h, W.wqkv, 3 * hp,
-                         qkv + r0 * 3 * hp, 3 * hp, (const float*)W.bqkv, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin);
+                         qkv + r0 * 3 * hp, 3 * hp, (const float*)W.bqkv, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
     case F_ROPE_TABLE:
       return launch_rope_table(wsp<float>(R, T_rope, 0), H->s, H->d, H->theta, s);
     case F_ROPE:
@@ -529,7 +529,7 @@ static int run_op(const Run& R, const Op& op) {
                                   seed, l, H->cfg.attn_dropout_p, H->r * H->heads_l, H->nh, pin > 0);
     case F_PROJ:
       return launch_gemm(OASES_GEMM_NN, OASES_EPI_F32, Ms, h, hp, attn + r0 * hp, hp, W.wo, h, part_w(0), h,
-                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin);
+                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
     case F_R1:
       return launch_bdr_ln(part_r(0), peer_k(0), (const float*)W.bo, xin + r0 * h,
                            wsp<float>(R, T_x1, l) + r0 * h, (const float*)W.ln2_g, (const float*)W.ln2_b, v2 + r0 * h,
@@ -538,12 +538,12 @@ static int run_op(const Run& R, const Op& op) {
     case F_FC1:
       if (H->llama)  // w1 = [gate | up] columns interleaved in blocks of 32; pre = both pre-activations, f = silu(gate)*up
         return launch_gemm(OASES_GEMM_NN, OASES_EPI_SWIGLU, Ms, fw, h, v2 + r0 * h, h, W.w1, fw, f + r0 * fp, fp, nullptr,
-                           pre + r0 * fw, fw, gws, H->gemm_ws_bytes, 0, s, pin);
+                           pre + r0 * fw, fw, gws, H->gemm_ws_bytes, 0, s, pin, counters);
       return launch_gemm(OASES_GEMM_NN, OASES_EPI_BIAS_GELU, Ms, fp, h, v2 + r0 * h, h, W.w1, fp, f + r0 * fp, fp,
-                         (const float*)W.b1, pre + r0 * fp, fp, gws, H->gemm_ws_bytes, 0, s, pin);
+                         (const float*)W.b1, pre + r0 * fp, fp, gws, H->gemm_ws_bytes, 0, s, pin, counters);
     case F_FC2:
       return launch_gemm(OASES_GEMM_NN, OASES_EPI_F32, Ms, h, fp, f + r0 * fp, fp, W.w2, h, part_w(1), h,
-                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin);
+                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
     case F_R2: {
       const bool more = l + 1 < L;  // fuse the next layer's LN1 behind this layer's output
       return launch_bdr_ln(part_r(1), peer_k(1), (const float*)W.b2,
@@ -559,12 +559,12 @@ static int run_op(const Run& R, const Op& op) {
     case B_FC2_DGRAD:
       if (H->llama)
         return launch_gemm(OASES_GEMM_NT, OASES_EPI_DSWIGLU, Ms, fp, h, wsp<uint16_t>(R, T_dz2, l) + r0 * h, h, W.w2, h,
-                           wsp<uint16_t>(R, T_dg, l) + r0 * fw, fw, nullptr, pre + r0 * fw, fw, gws, H->gemm_ws_bytes, 0, s, pin);
+                           wsp<uint16_t>(R, T_dg, l) + r0 * fw, fw, nullptr, pre + r0 * fw, fw, gws, H->gemm_ws_bytes, 0, s, pin, counters);
       return launch_gemm(OASES_GEMM_NT, OASES_EPI_DGELU, Ms, fp, h, wsp<uint16_t>(R, T_dz2, l) + r0 * h, h, W.w2, h,
-                         wsp<uint16_t>(R, T_dg, l) + r0 * fp, fp, nullptr, pre + r0 * fp, fp, gws, H->gemm_ws_bytes, 0, s, pin);
+                         wsp<uint16_t>(R, T_dg, l) + r0 * fp, fp, nullptr, pre + r0 * fp, fp, gws, H->gemm_ws_bytes, 0, s, pin, counters);
     case B_FC1_DGRAD:
       return launch_gemm(OASES_GEMM_NT, OASES_EPI_F32, Ms, h, fw, wsp<uint16_t>(R, T_dg, l) + r0 * fw, fw, W.w1, fw,
-                         part_w(2), h, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin);
+                         part_w(2), h, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
     case B_R3:
       { ColsumSink* cs = colsum(1); return colsum_done(launch_layernorm_bwd(part_r(2), peer_k(2), dyin + r0 * h,
                                   wsp<float>(R, T_x1, l) + r0 * h, wsp<float>(R, T_mu2, l) + r0, wsp<float>(R, T_rstd2, l) + r0,
@@ -573,25 +573,25 @@ static int run_op(const Run& R, const Op& op) {
                                   make_drop_cfg(seed, l, 0, p), (int64_t)r0, cs_scratch, s, rms, false, cs)); }
     case B_FC2_WGRAD:
       return launch_gemm(OASES_GEMM_TN, 0, fp, h, Ms, f + r0 * fp, fp, wsp<uint16_t>(R, T_dz2, l) + r0 * h, h, R.g[l].w2, h,
-                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s);
+                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, 0, counters);
     case B_FC1_WGRAD:
       return launch_gemm(OASES_GEMM_TN, 0, h, fw, Ms, v2 + r0 * h, h, wsp<uint16_t>(R, T_dg, l) + r0 * fw, fw, R.g[l].w1, fw,
-                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s);
+                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, 0, counters);
     case B_B1_SUM:
       { ColsumSink* cs = colsum(3); return colsum_done(launch_colsum_bf16(wsp<uint16_t>(R, T_dg, l) + r0 * fp, fp, Ms, fp, (float*)R.g[l].b1, cs_scratch, s, cs)); }
     case B_PROJ_DGRAD:
       return launch_gemm(OASES_GEMM_NT, OASES_EPI_BF16, Ms, hp, h, wsp<uint16_t>(R, T_dz1, l) + r0 * h, h, W.wo, h,
-                         wsp<uint16_t>(R, T_da, l) + r0 * hp, hp, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin);
+                         wsp<uint16_t>(R, T_da, l) + r0 * hp, hp, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
     case B_PROJ_WGRAD:
       return launch_gemm(OASES_GEMM_TN, 0, hp, h, Ms, attn + r0 * hp, hp, wsp<uint16_t>(R, T_dz1, l) + r0 * h, h, R.g[l].wo, h,
-                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s);
+                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, 0, counters);
     case B_ATTN:
       return launch_attention_bwd(qkv, attn, wsp<uint16_t>(R, T_da, l), wsp<float>(R, T_lse, l), wsp<float>(R, T_delta, l),
                                   wsp<uint16_t>(R, T_dqkv, l), H->b, H->s, H->heads_l, H->d, H->cfg.causal, (int)r0, Ms, s, seed, l,
                                   H->cfg.attn_dropout_p, H->r * H->heads_l, H->nh, pin > 0);
     case B_QKV_DGRAD:
       return launch_gemm(OASES_GEMM_NT, OASES_EPI_F32, Ms, h, 3 * hp, wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp, W.wqkv,
-                         3 * hp, part_w(3), h, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin);
+                         3 * hp, part_w(3), h, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
     case B_R4: {
       const bool more = l > 0;  // fuse the dropout backward of the layer below (its BDR2) behind dx
       { ColsumSink* cs = colsum(2); return colsum_done(launch_layernorm_bwd(part_r(3), peer_k(3),
@@ -603,7 +603,7 @@ static int run_op(const Run& R, const Op& op) {
     }
     case B_QKV_WGRAD:
       return launch_gemm(OASES_GEMM_TN, 0, h, 3 * hp, Ms, u + r0 * h, h, wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp,
-                         R.g[l].wqkv, 3 * hp, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s);
+                         R.g[l].wqkv, 3 * hp, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, 0, counters);
     case B_PQ_WGRAD:
       return launch_gemm_tn_pair(Ms, hp, h, attn + r0 * hp, hp, wsp<uint16_t>(R, T_dz1, l) + r0 * h, h, R.g[l].wo, h, h, 3 * hp, u + r0 * h, h,
                                  wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp, R.g[l].wqkv, 3 * hp, s);
@@ -1084,6 +1084,10 @@ int oases_op_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace
   (void)epi;
   if (op < 0 || op > 2 || M <= 0 || N <= 0 || K <= 0) { set_error("oases_op_gemm_variant: bad argument"); return OASES_EINVAL; }
   return gemm_variant(op, epi, M, N, K, workspace_bytes);
+}
+int oases_pass_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace_bytes) {
+  if (op < 0 || op > 2 || M <= 0 || N <= 0 || K <= 0) { set_error("oases_pass_gemm_variant: bad argument"); return OASES_EINVAL; }
+  return gemm_variant(op, epi, M, N, K, workspace_bytes, true);
 }
 int oases_op_gemm_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0, void* C0, int ldc0, int M1, int N1,
                           const void* A1, int lda1, const void* B1, int ldb1, void* C1, int ldc1, void* stream) {

@@ -38,6 +38,8 @@ struct GemmArgs {
   int lda, ldb, ldc, ldaux;
   int tiles_m, tiles_n;
   int ksplit, k_per;  // split-K: slice s covers k in [s*k_per, min(K, (s+1)*k_per)) and writes partial s
+  float* part;         // slices that the launch adds up itself (SliceSum): partial sums, and a counter per tile
+  uint32_t* counters;  // nullptr: slices write planes that a second launch adds up
 };
 
 // one launcher per contraction form, each defined in its own part
@@ -1121,7 +1123,7 @@ constexpr int kPpExchange = 8 * 2 * 2 * 4 * 64 * 16;                        // 1
 constexpr int kPpLds128 = NSR * kRectStage > kPpExchange ? NSR * kRectStage : kPpExchange;  // 144 KB
 
 // k slices that are added up by the launch itself: every workgroup of a tile leaves its partial sums in `part`
-// ([tile][slice][wave][quarter][half][lane] x 2 floats, so that each access of a wave is whole lines) and counts itself in; whoever counts last
+// ([tile][slice][wave][group of four][half][lane] x 2 floats, so that each access of a wave is whole lines) and counts itself in; whoever counts last
 // has all of them, adds them in slice order (its own from registers, at its place) and runs the epilogue.  Nobody waits for
 // anybody, so it does not matter how many workgroups are resident.  The counter is 0 before the launch and again behind it.
 // Partial sums and counters cross XCDs, whose L2s do not see each other's lines: they are stored and loaded as relaxed atomics of
@@ -1132,7 +1134,6 @@ struct SliceSum {
   uint32_t* counter;
   int slice, slices;
 };
-constexpr int kSlicePartFloats = 128 * 256;  // partial sums of one workgroup
 // true in every thread of the workgroup that came last.  lds: four bytes that no wave uses any more
 __device__ __forceinline__ bool last_slice(const SliceSum& ss, char* lds) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1158,10 +1159,34 @@ __device__ __forceinline__ f32x4 slice_load(uint64_t* p) {
   return __builtin_bit_cast(f32x4, w);
 }
 
+// v: this lane's N groups of four partial sums, replaced by the sums over the slices where the function returns true (the workgroup that came last)
+template <int N>
+__device__ __forceinline__ bool sum_slices(const SliceSum& ss, f32x4 (&v)[N], char* flag) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const size_t plane = (size_t)(blockDim.x >> 6) * N * 128;  // in pairs of floats
+  uint64_t* p = reinterpret_cast<uint64_t*>(ss.part) + (size_t)wave * N * 128 + lane;
+#pragma unroll
+  for (int q = 0; q < N; q++) slice_store(p + ss.slice * plane + q * 128, v[q]);
+  if (!last_slice(ss, flag)) return false;
+  f32x4 sum[N];
+#pragma unroll
+  for (int q = 0; q < N; q++) sum[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int sl = 0; sl < ss.slices; sl++) {
+    f32x4 x[N];
+#pragma unroll
+    for (int q = 0; q < N; q++) x[q] = sl == ss.slice ? v[q] : slice_load(p + sl * plane + q * 128);
+#pragma unroll
+    for (int q = 0; q < N; q++) sum[q] = sl == 0 ? x[q] : sum[q] + x[q];
+  }
+#pragma unroll
+  for (int q = 0; q < N; q++) v[q] = sum[q];
+  return true;
+}
+
 template <int BM, bool A_KC, bool B_KC, int EPI, bool FULL, bool SLICED = false>
 __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, const SliceSum& ss = SliceSum{}) {
   static_assert(BM == 256 || BM == 128, "block tiles 256 x 256 and 128 x 256");
-  static_assert(!SLICED || (BM == 128 && EPI != EPI_F32 && EPI != EPI_SWIGLU), "slices: transposed accumulators of 128 x 256 tiles");
+  static_assert(!SLICED || BM == 128, "slices: 128 x 256 tiles");
   constexpr bool SQ = BM == 256;
   constexpr int NS = SQ ? NSD : NSR;                 // LDS stages
   constexpr int KT = SQ ? BKD : BKR;                 // k extent of a stage
@@ -1367,25 +1392,10 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
         }
       };
       if (grp == 0) gather(std::integral_constant<int, 0>{}); else gather(std::integral_constant<int, 1>{});
-      uint64_t* tile_part = reinterpret_cast<uint64_t*>(ss.part) + (size_t)wave * 16 * 128 + lane;
-      constexpr int kPlane = kSlicePartFloats / 2;
-#pragma unroll
-      for (int q = 0; q < 16; q++) slice_store(tile_part + (size_t)ss.slice * kPlane + q * 128, v[q]);
-      if (!last_slice(ss, lds + kPpLds128 - 16)) return;
+      if (!sum_slices<16>(ss, v, lds + kPpLds128 - 16)) return;
       if constexpr (READS) {
         request(eo[0], m0 + grp * 64);
         if (!BIAS) request(eo[1], m0 + grp * 64 + 32);
-      }
-      f32x4 sum[16];
-#pragma unroll
-      for (int q = 0; q < 16; q++) sum[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int sl = 0; sl < ss.slices; sl++) {
-        const bool own = sl == ss.slice;
-        f32x4 p[16];
-#pragma unroll
-        for (int q = 0; q < 16; q++) p[q] = own ? v[q] : slice_load(tile_part + (size_t)sl * kPlane + q * 128);
-#pragma unroll
-        for (int q = 0; q < 16; q++) sum[q] = sl == 0 ? p[q] : sum[q] + p[q];
       }
 #pragma unroll
       for (int i = 0; i < 2; i++)
@@ -1393,8 +1403,10 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
         for (int j = 0; j < 2; j++) {
           f32x16 a;
 #pragma unroll
-          for (int e = 0; e < 16; e++) a[e] = sum[(i * 2 + j) * 4 + (e >> 2)][e & 3];
-          epi_finish<EPI, FULL>(g, m0 + (grp * 2 + i) * 32, n0 + wn * 64 + 32 * j, lane, a, eo[BIAS ? 0 : i][j]);
+          for (int e = 0; e < 16; e++) a[e] = v[(i * 2 + j) * 4 + (e >> 2)][e & 3];
+          const int row = m0 + (grp * 2 + i) * 32, col = n0 + wn * 64 + 32 * j;
+          if constexpr (EPI == EPI_F32) epilogue_tile<EPI, FULL>(g, row, col, lane, a);
+          else epi_finish<EPI, FULL>(g, row, col, lane, a, eo[BIAS ? 0 : i][j]);
         }
       return;
     }
@@ -1407,19 +1419,26 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
   }
 }
 
-template <int BM, bool A_KC, bool B_KC, int EPI, bool FULL>
+// this workgroup's k range (k_per: a whole number of stages) and, where a second launch adds the slices up, its fp32 plane; floats: partial sums of a workgroup
+template <bool A_KC, bool B_KC>
+__device__ __forceinline__ SliceSum take_slice(GemmArgs& g, int& pid, int floats) {
+  const int T = g.tiles_m * g.tiles_n, slice = pid / T, k0 = slice * g.k_per;
+  pid -= slice * T;
+  g.A += A_KC ? (size_t)k0 : (size_t)k0 * g.lda;
+  g.B += B_KC ? (size_t)k0 : (size_t)k0 * g.ldb;
+  g.K = min(g.K - k0, g.k_per);
+  if (!g.counters) g.C = reinterpret_cast<float*>(g.C) + (size_t)slice * g.M * g.ldc;
+  return SliceSum{g.part + (size_t)pid * g.ksplit * floats, g.counters + pid, slice, g.ksplit};
+}
+
+// SLICED: k slices that the launch adds up itself
+template <int BM, bool A_KC, bool B_KC, int EPI, bool FULL, bool SLICED = false>
 __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs g) {  // g: by value, adjusted per k slice
   __shared__ __attribute__((aligned(1024))) char lds[BM == 256 ? kPpLds256 : kPpLds128];
   int pid = blockIdx.x;
-  if (BM == 128 && g.ksplit > 1) {  // this workgroup's k range (k_per: a whole number of stages) and fp32 partial-result plane
-    const int T = g.tiles_m * g.tiles_n, slice = pid / T, k0 = slice * g.k_per;
-    pid -= slice * T;
-    g.A += A_KC ? (size_t)k0 : (size_t)k0 * g.lda;
-    g.B += B_KC ? (size_t)k0 : (size_t)k0 * g.ldb;
-    g.K = g.k_per;
-    g.C = reinterpret_cast<float*>(g.C) + (size_t)slice * g.M * g.ldc;
-  }
-  pp_tile<BM, A_KC, B_KC, EPI, FULL>(g, pid, lds);
+  SliceSum ss{};
+  if (BM == 128 && g.ksplit > 1) ss = take_slice<A_KC, B_KC>(g, pid, 128 * 256);
+  pp_tile<BM, A_KC, B_KC, EPI, FULL, SLICED>(g, pid, lds, ss);
 }
 
 // Two weight-gradient contractions over the same K rows in one launch: the tiles of the second problem follow those of
@@ -1434,7 +1453,7 @@ __global__ __launch_bounds__(512) void gemm_pp_group_kernel(GemmArgs g0, GemmArg
   if constexpr (SLICED) {
     const int slice = pid / T;
     pid -= slice * T;
-    ss = SliceSum{part + (size_t)pid * g0.ksplit * kSlicePartFloats, counters + pid, slice, g0.ksplit};
+    ss = SliceSum{part + (size_t)pid * g0.ksplit * 128 * 256, counters + pid, slice, g0.ksplit};
   }
   const bool second = pid >= first;
   GemmArgs g = second ? g1 : g0;
@@ -1526,44 +1545,51 @@ __device__ __forceinline__ void st_frag_offsets(uint32_t (&off)[2], int R0, int 
 __device__ __forceinline__ void st_wait_frags(u32x4 (&a)[2][1], u32x4 (&b)[2][1]) {
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0][0]), "+v"(a[1][0]), "+v"(b[0][0]), "+v"(b[1][0]));
 }
+__device__ __forceinline__ void st_wait_frags(u32x4 (&a)[2][2], u32x4 (&b)[2][2]) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(a[0][0]), "+v"(a[0][1]), "+v"(a[1][0]), "+v"(a[1][1]), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
+}
 __device__ __forceinline__ void st_wait_frags(u32x4 (&a)[2][1], u32x4 (&b)[2][2]) {
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0][0]), "+v"(a[1][0]), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
 }
 
-template <int TN, int NS>
+template <int TM, int TN, int NS>
 struct StLds {
-  static constexpr int kStage = (64 + 64 * TN) * BKS * 2, kExchange = 8 * TN * 2 * 64 * 16;  // exchange: half of every wave's accumulator
+  static constexpr int kStage = 64 * (TM + TN) * BKS * 2, kExchange = 8 * TM * TN * 2 * 64 * 16;  // exchange: half of every wave's accumulator
   static constexpr int bytes = NS * kStage > kExchange ? NS * kStage : kExchange;
 };
-template <int TN, int NS, bool A_KC, bool B_KC, int EPI>
-__device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds) {
-  constexpr int BM = 64, BN = 64 * TN;
-  constexpr int kOpA = BM * BKS * 2, kStage = StLds<TN, NS>::kStage;
-  constexpr int PER_A = 1, PER_B = TN, PER = PER_A + PER_B;  // direct-to-LDS instructions of a wave per stage
+template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI>
+__device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, const SliceSum& ss = SliceSum{}) {
+  constexpr int BM = 64 * TM, BN = 64 * TN;
+  constexpr int kOpA = BM * BKS * 2, kStage = StLds<TM, TN, NS>::kStage;
+  constexpr int PER_A = TM, PER_B = TN, PER = PER_A + PER_B;  // direct-to-LDS instructions of a wave per stage
   static_assert(EPI != EPI_SWIGLU || TN == 2, "gate and up columns of a block must belong to one wave");
   int tile_m, tile_n;
   tile_of_workgroup(pid, g.tiles_m, g.tiles_n, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wk = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
-  const int row0 = m0 + wm * 32, col0 = n0 + wn * 32 * TN;
+  const int row0 = m0 + wm * 32 * TM, col0 = n0 + wn * 32 * TN;
   const int nk = (g.K + BKS - 1) / BKS, ktail = g.K % BKS;
 
   // operands of the epilogue.  A wave finishes quarters 2 wk and 2 wk + 1 of its accumulator tiles (quarter q of a
   // transposed accumulator: columns 8 q + 4 (lane/32) ..+3 of row lane%32)
-  EpiOperands pre[TN][2];
+  EpiOperands pre[TM][TN][2];
   if constexpr (EPI != EPI_F32 && EPI != EPI_SWIGLU) {
 #pragma unroll
-    for (int j = 0; j < TN; j++)
+    for (int i = 0; i < TM; i++)
 #pragma unroll
-      for (int q = 0; q < 2; q++)
-        pre[j][q] = epi_load<EPI>(g, min(row0 + (lane & 31), g.M - 1), min(col0 + 32 * j + 8 * (2 * wk + q) + 4 * (lane >> 5), g.N - 4));
+      for (int j = 0; j < TN; j++)
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+          pre[i][j][q] = epi_load<EPI>(g, min(row0 + 32 * i + (lane & 31), g.M - 1), min(col0 + 32 * j + 8 * (2 * wk + q) + 4 * (lane >> 5), g.N - 4));
   }
 
   const __amdgpu_buffer_rsrc_t rsA = operand_rsrc(g.A), rsB = operand_rsrc(g.B);
-  uint32_t srcB[PER_B];
-  int kA, kB[PER_B];
-  const uint32_t srcA = st_src<A_KC, BM>(g.lda, m0, wave, lane, g.M, &kA);
+  uint32_t srcA[PER_A], srcB[PER_B];
+  int kA[PER_A], kB[PER_B];
+#pragma unroll
+  for (int j = 0; j < PER_A; j++) srcA[j] = st_src<A_KC, BM>(g.lda, m0, PER_A * wave + j, lane, g.M, &kA[j]);
 #pragma unroll
   for (int j = 0; j < PER_B; j++) srcB[j] = st_src<B_KC, BN>(g.ldb, n0, PER_B * wave + j, lane, g.N, &kB[j]);
   const uint32_t unitA = A_KC ? 2u : 2u * g.lda, unitB = B_KC ? 2u : 2u * g.ldb;  // one k further
@@ -1571,31 +1597,35 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds) {
     char* st = lds + stage * kStage;
     const uint32_t tA = (uint32_t)t * BKS * unitA, tB = (uint32_t)t * BKS * unitB;
     if (ktail && t == nk - 1) {  // k >= K: fetched from k = 0 of the same row / column (valid memory, zeroed later)
-      dma16(rsA, kA < ktail ? srcA + tA : srcA - kA * unitA, 0, st + wave * 1024);
+#pragma unroll
+      for (int j = 0; j < PER_A; j++) dma16(rsA, kA[j] < ktail ? srcA[j] + tA : srcA[j] - kA[j] * unitA, 0, st + (PER_A * wave + j) * 1024);
 #pragma unroll
       for (int j = 0; j < PER_B; j++) dma16(rsB, kB[j] < ktail ? srcB[j] + tB : srcB[j] - kB[j] * unitB, 0, st + kOpA + (PER_B * wave + j) * 1024);
     } else {
-      dma16(rsA, srcA, tA, st + wave * 1024);
+#pragma unroll
+      for (int j = 0; j < PER_A; j++) dma16(rsA, srcA[j], tA, st + (PER_A * wave + j) * 1024);
 #pragma unroll
       for (int j = 0; j < PER_B; j++) dma16(rsB, srcB[j], tB, st + kOpA + (PER_B * wave + j) * 1024);
     }
   };
   uint32_t offA[2], offB[2];
-  st_frag_offsets<A_KC, BM, 1>(offA, wm * 32, wk, lane);
+  st_frag_offsets<A_KC, BM, TM>(offA, wm * 32 * TM, wk, lane);
   st_frag_offsets<B_KC, BN, TN>(offB, wn * 32 * TN, wk, lane);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(OASES_LDS char*)lds;
 
-  f32x16 acc[TN];
+  f32x16 acc[TM][TN];
 #pragma unroll
-  for (int j = 0; j < TN; j++)
+  for (int i = 0; i < TM; i++)
 #pragma unroll
-    for (int e = 0; e < 16; e++) acc[j][e] = 0.f;
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
 
 #pragma unroll
   for (int t = 0; t < NS - 1; t++)
     if (t < nk) issue(t, t);
 
-  u32x4 fa[2][1], fb[2][TN];
+  u32x4 fa[2][TM], fb[2][TN];
   int stage = 0;
   // one tile; YOUNG: tiles behind it that may still be in flight (compile-time, for the wait); steady: tile kt+NS-1 exists
   auto iteration = [&](auto young_c, auto steady_c, int kt) {
@@ -1607,9 +1637,9 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds) {
     __builtin_amdgcn_sched_barrier(0);
     if (STEADY) issue(kt + NS - 1, stage == 0 ? NS - 1 : stage - 1);
     const uint32_t st = lds0 + (uint32_t)stage * kStage;
-    st_read_frags<A_KC, BM, 1, 0>(fa[0], st, offA);
+    st_read_frags<A_KC, BM, TM, 0>(fa[0], st, offA);
     st_read_frags<B_KC, BN, TN, 0>(fb[0], st + kOpA, offB);
-    st_read_frags<A_KC, BM, 1, 1>(fa[1], st, offA);
+    st_read_frags<A_KC, BM, TM, 1>(fa[1], st, offA);
     st_read_frags<B_KC, BN, TN, 1>(fb[1], st + kOpA, offB);
     st_wait_frags(fa, fb);
     __builtin_amdgcn_sched_barrier(0);
@@ -1617,7 +1647,8 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds) {
 #pragma unroll
       for (int kk = 0; kk < 2; kk++)
         if (32 * wk + 16 * kk + 8 * (lane >> 5) >= ktail) {
-          fa[kk][0] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+          for (int i = 0; i < TM; i++) fa[kk][i] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
           for (int j = 0; j < TN; j++) fb[kk][j] = u32x4{0u, 0u, 0u, 0u};
         }
@@ -1625,11 +1656,13 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds) {
 #pragma unroll
     for (int kk = 0; kk < 2; kk++)
 #pragma unroll
-      for (int j = 0; j < TN; j++) {
-        const bf16x8 a = __builtin_bit_cast(bf16x8, fa[kk][0]), b = __builtin_bit_cast(bf16x8, fb[kk][j]);
-        if constexpr (EPI == EPI_F32) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[j], 0, 0, 0);
-        else acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[j], 0, 0, 0);
-      }
+      for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int j = 0; j < TN; j++) {
+          const bf16x8 a = __builtin_bit_cast(bf16x8, fa[kk][i]), b = __builtin_bit_cast(bf16x8, fb[kk][j]);
+          if constexpr (EPI == EPI_F32) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[i][j], 0, 0, 0);
+          else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[i][j], 0, 0, 0);
+        }
     stage = stage == NS - 1 ? 0 : stage + 1;
   };
   int kt = 0;
@@ -1649,81 +1682,87 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds) {
   auto hand_over = [&](auto half_c) {
     constexpr int E = 8 * decltype(half_c)::value;
 #pragma unroll
-    for (int j = 0; j < TN; j++)
+    for (int t = 0; t < TM * TN; t++)
 #pragma unroll
-      for (int q = 0; q < 2; q++)
-        xch[((wave * TN + j) * 2 + q) * 64 + lane] = f32x4{acc[j][E + 4 * q], acc[j][E + 4 * q + 1], acc[j][E + 4 * q + 2], acc[j][E + 4 * q + 3]};
+      for (int q = 0; q < 2; q++) {
+        const f32x16& a = acc[t / TN][t % TN];
+        xch[((wave * TM * TN + t) * 2 + q) * 64 + lane] = f32x4{a[E + 4 * q], a[E + 4 * q + 1], a[E + 4 * q + 2], a[E + 4 * q + 3]};
+      }
   };
   if (wk == 0) hand_over(std::integral_constant<int, 1>{}); else hand_over(std::integral_constant<int, 0>{});
   __syncthreads();
-  auto finish = [&](auto half_c, auto full_c) {
-    constexpr int H = decltype(half_c)::value;
-    constexpr bool FULL = decltype(full_c)::value;
-    f32x4 v[TN][2];
+  f32x4 v[TM * TN * 2];  // [row part][column part][quarter]
+  auto gather = [&](auto half_c) {
+    constexpr int E = 8 * decltype(half_c)::value;
 #pragma unroll
-    for (int j = 0; j < TN; j++)
+    for (int t = 0; t < TM * TN; t++)
 #pragma unroll
       for (int q = 0; q < 2; q++) {
-        v[j][q] = xch[(((wave ^ 4) * TN + j) * 2 + q) * 64 + lane];
+        const f32x16& a = acc[t / TN][t % TN];
+        v[2 * t + q] = xch[(((wave ^ 4) * TM * TN + t) * 2 + q) * 64 + lane];
 #pragma unroll
-        for (int e = 0; e < 4; e++) v[j][q][e] += acc[j][8 * H + 4 * q + e];
+        for (int e = 0; e < 4; e++) v[2 * t + q][e] += a[E + 4 * q + e];
       }
+  };
+  if (wk == 0) gather(std::integral_constant<int, 0>{}); else gather(std::integral_constant<int, 1>{});
+  if (ss.counter) {  // k slices that the launch adds up itself
+    static_assert(StLds<TM, TN, NS>::kExchange < StLds<TM, TN, NS>::bytes, "four bytes behind the exchange");
+    if (!sum_slices<TM * TN * 2>(ss, v, lds + StLds<TM, TN, NS>::kExchange)) return;
+  }
+  auto finish = [&](auto full_c) {
+    constexpr bool FULL = decltype(full_c)::value;
 #pragma unroll
-    for (int q = 0; q < 2; q++) {
-      const int c = 8 * (2 * H + q) + 4 * (lane >> 5);
-      if constexpr (EPI == EPI_F32) {  // plain accumulator: element e of the quarter is C[row0 + c + e][column lane%32 of the tile]
+    for (int i = 0; i < TM; i++)
 #pragma unroll
-        for (int j = 0; j < TN; j++) {
-          const int col = col0 + 32 * j + (lane & 31), row = row0 + c;
-          if (!FULL && col >= g.N) continue;
-          float* p = reinterpret_cast<float*>(g.C) + (size_t)row * g.ldc + col;
+      for (int q = 0; q < 2; q++) {
+        const int c = 8 * (2 * wk + q) + 4 * (lane >> 5);
+        if constexpr (EPI == EPI_F32) {  // plain accumulator: element e of the quarter is C[row0 + 32 i + c + e][column lane%32 of the tile]
 #pragma unroll
-          for (int e = 0; e < 4; e++)
-            if (FULL || row + e < g.M) p[(size_t)e * g.ldc] = v[j][q][e];
-        }
-      } else {
-        const int row = row0 + (lane & 31);
-        if (!FULL && row >= g.M) continue;
-        if constexpr (EPI == EPI_SWIGLU) {
-          if (FULL || col0 + c < g.N) epi_swiglu(g, row, col0 + c, col0 / 2 + c, v[0][q], v[1][q]);
+          for (int j = 0; j < TN; j++) {
+            const int col = col0 + 32 * j + (lane & 31), row = row0 + 32 * i + c;
+            if (!FULL && col >= g.N) continue;
+            float* p = reinterpret_cast<float*>(g.C) + (size_t)row * g.ldc + col;
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+              if (FULL || row + e < g.M) p[(size_t)e * g.ldc] = v[(i * TN + j) * 2 + q][e];
+          }
         } else {
+          const int row = row0 + 32 * i + (lane & 31);
+          if (!FULL && row >= g.M) continue;
+          if constexpr (EPI == EPI_SWIGLU) {
+            if (FULL || col0 + c < g.N) epi_swiglu(g, row, col0 + c, col0 / 2 + c, v[i * TN * 2 + q], v[(i * TN + 1) * 2 + q]);
+          } else {
 #pragma unroll
-          for (int j = 0; j < TN; j++)
-            if (FULL || col0 + 32 * j + c < g.N) epi_apply<EPI>(g, row, col0 + 32 * j + c, v[j][q], pre[j][q]);
+            for (int j = 0; j < TN; j++)
+              if (FULL || col0 + 32 * j + c < g.N) epi_apply<EPI>(g, row, col0 + 32 * j + c, v[(i * TN + j) * 2 + q], pre[i][j][q]);
+          }
         }
       }
-    }
   };
   const bool full = m0 + BM <= g.M && n0 + BN <= g.N;
-  using H0 = std::integral_constant<int, 0>;
-  using H1 = std::integral_constant<int, 1>;
-  if (full) { if (wk == 0) finish(H0{}, std::true_type{}); else finish(H1{}, std::true_type{}); }
-  else { if (wk == 0) finish(H0{}, std::false_type{}); else finish(H1{}, std::false_type{}); }
+  if (full) finish(std::true_type{}); else finish(std::false_type{});
 }
 
-template <int TN, int NS, bool A_KC, bool B_KC, int EPI>
+template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__(512) void gemm_st_kernel(GemmArgs g) {  // g: by value, adjusted per k slice
-  __shared__ __attribute__((aligned(1024))) char lds[StLds<TN, NS>::bytes];
+  __shared__ __attribute__((aligned(1024))) char lds[StLds<TM, TN, NS>::bytes];
   int pid = blockIdx.x;
-  if (g.ksplit > 1) {  // this workgroup's k range (k_per: a whole number of stages) and fp32 partial-result plane
-    const int T = g.tiles_m * g.tiles_n, slice = pid / T, k0 = slice * g.k_per;
-    pid -= slice * T;
-    g.A += A_KC ? (size_t)k0 : (size_t)k0 * g.lda;
-    g.B += B_KC ? (size_t)k0 : (size_t)k0 * g.ldb;
-    g.K = min(g.K - k0, g.k_per);
-    g.C = reinterpret_cast<float*>(g.C) + (size_t)slice * g.M * g.ldc;
+  SliceSum ss{};
+  if (g.ksplit > 1) {
+    ss = take_slice<A_KC, B_KC>(g, pid, 64 * TM * 64 * TN);
+    if (!g.counters) ss.counter = nullptr;
   }
-  st_tile<TN, NS, A_KC, B_KC, EPI>(g, pid, lds);
+  st_tile<TM, TN, NS, A_KC, B_KC, EPI>(g, pid, lds, ss);
 }
 
 // two weight gradients over the same K rows, tiles of the second behind those of the first
 template <int TN, int NS>
 __global__ __launch_bounds__(512) void gemm_st_group_kernel(GemmArgs g0, GemmArgs g1) {
-  __shared__ __attribute__((aligned(1024))) char lds[StLds<TN, NS>::bytes];
+  __shared__ __attribute__((aligned(1024))) char lds[StLds<1, TN, NS>::bytes];
   const int first = g0.tiles_m * g0.tiles_n;
   const bool second = (int)blockIdx.x >= first;
   const GemmArgs g = second ? g1 : g0;
-  st_tile<TN, NS, false, false, EPI_ACC_F32>(g, second ? blockIdx.x - first : blockIdx.x, lds);
+  st_tile<1, TN, NS, false, false, EPI_ACC_F32>(g, second ? blockIdx.x - first : blockIdx.x, lds);
 }
 
 // split-K second pass: C = epilogue(sum over slices of the fp32 partial planes), slices added in index order
@@ -1770,13 +1809,18 @@ int launch_one(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
 
 inline int st_k_per(int K, int slices) { return ((K + slices - 1) / slices + BKS - 1) / BKS * BKS; }  // k of one slice
 
-template <int TN, int NS, bool A_KC, bool B_KC, int EPI>
+template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI>
 int launch_small(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
   GemmArgs g = g0;
-  g.tiles_m = (g.M + 63) / 64;
+  g.tiles_m = (g.M + 64 * TM - 1) / (64 * TM);
   g.tiles_n = (g.N + 64 * TN - 1) / (64 * TN);
-  if (ksplit <= 1) {
-    hipLaunchKernelGGL((gemm_st_kernel<TN, NS, A_KC, B_KC, EPI>), dim3(g.tiles_m * g.tiles_n), dim3(512), 0, s, g);
+  if (ksplit <= 1 || g.counters) {
+    if (ksplit > 1) {
+      g.ksplit = ksplit;
+      g.k_per = st_k_per(g.K, ksplit);
+      g.part = ws;
+    }
+    hipLaunchKernelGGL((gemm_st_kernel<TM, TN, NS, A_KC, B_KC, EPI>), dim3(g.tiles_m * g.tiles_n * (ksplit > 1 ? ksplit : 1)), dim3(512), 0, s, g);
     OASES_LAUNCH_CHECK("gemm_st_kernel");
     return 0;
   }
@@ -1790,7 +1834,7 @@ int launch_small(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
     p.k_per = st_k_per(g.K, ksplit);
     p.C = ws;
     p.ldc = g.N;
-    hipLaunchKernelGGL((gemm_st_kernel<TN, NS, A_KC, B_KC, EPI_F32>), dim3(g.tiles_m * g.tiles_n * ksplit), dim3(512), 0, s, p);
+    hipLaunchKernelGGL((gemm_st_kernel<TM, TN, NS, A_KC, B_KC, EPI_F32>), dim3(g.tiles_m * g.tiles_n * ksplit), dim3(512), 0, s, p);
     OASES_LAUNCH_CHECK("gemm_st_kernel (split-K)");
     const long n4 = (long)g.M * (g.N / 4);
     hipLaunchKernelGGL((splitk_fixup_kernel<EPI>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, ws, ksplit, g);
@@ -1829,8 +1873,11 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
     for (int S = 1; S <= 8; S *= 2) {
       if (S > 1 && ((size_t)S * M * N * 4 > ws_bytes || K / S < 512)) break;
       const long wgs = tm * tn * S, rounds = (wgs + 255) / 256;
+      // 256x256 tiles that the direct-to-LDS kernels do not cover run on the register-staged kernel (NT dSwiGLU 8192 x 1376 x 4096: 153 us
+      // against 130 on 128x256 tiles, which may be ragged)
+      const double tflops = c.bm == 256 && c.bn == 256 && S == 1 && !dtl_fits(kind, M, N, K) ? 900.f : c.tflops;
       // time of one workgroup's tile slice at the tile's rate (one workgroup per CU), times the number of rounds
-      double t = (double)rounds * (2.0 * c.bm * c.bn * ((double)K / S) + 3.0e6) / (c.tflops * 1e12 / 256.0);
+      double t = (double)rounds * (2.0 * c.bm * c.bn * ((double)K / S) + 3.0e6) / (tflops * 1e12 / 256.0);
       if (S > 1) t += ((double)(2 * S + 1) * M * N * 4.0) / 3.0e12 + 4e-6;
       if (t < best_t) { best_t = t; best = TileChoice{c.bm, c.bn, S, kt.wave_ksplit}; }
     }
@@ -1854,6 +1901,16 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
   return best;
 }
 
+// Time of an eight-wave launch over wgs workgroups, seconds.  What the MFMA loops are bound by is the power they draw together, so a
+// round that leaves CUs idle runs its stages faster, down to three quarters of the time of a full one (128x256 tiles, a 64-wide
+// stage: 256 workgroups 0.9 us, 144 or fewer 0.68); the output, read and written, moves at 4 TB/s.
+double pp_seconds(int bm, long wgs, int k_per, double out_bytes) {
+  double t = out_bytes / 4.0e12;
+  for (; wgs > 0; wgs -= 256)
+    t += 4.0e-6 + k_per / 64 * (bm == 256 ? 1.75e-6 : 0.9e-6) * std::max(0.75, (double)std::min(wgs, 256L) / 256.0);
+  return t;
+}
+
 // Small tiles against the choice above, by the same kind of model (measured on this part): a launch costs 2.9 us, a
 // workgroup 0.225 us (64 x 64) or 0.335 us (64 x 128) per 64-wide stage of its slice, two workgroups on a CU take turns at the
 // LDS, so the busiest CU's workgroups add up; the output moves at 4 TB/s (3.1 TB/s with the large tiles, one workgroup per
@@ -1863,27 +1920,54 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
 // us, large tile -> small: 4096 x 1536 x 2048 NN bias 31.6 -> 34.8 (stays large), 1024 x 3072 x 8192 56.2 -> 71.6 (stays
 // large), 4096 x 512 x 4096 NT 29.8 -> 22.9, 1024 x 1024 x 4096 TN 21.4 -> 16.9, 64 x 4608 x 12288 NN 53.5 -> 34.8,
 // 6144 x 12288 x 128 TN 195 -> 152.  Slices of 8192 k and more stay with the large tiles.
-TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, double* seconds = nullptr) {
+// own_sum: the launch adds its slices up by itself (SliceSum): a call of a pass.  The last workgroup of a tile then reads the other slices'
+// sums, one after the other at some 47 GB/s, instead of a second launch; 128x128 tiles on the same scheme are candidates, with any
+// number of slices (0.6 us a stage).  Measured, us, the choice without -> with: inside a step 128 x 4608 x 12288 NN 52 -> 48
+// (register-staged kernel over eight slices -> 128x128 over six), NT 128 x 6144 x 12288 78 -> 75; 512 x 8192 x 3072 NT 47 -> 36, 8192 x 512 x
+// 2048 NT 31 -> 26, 200 x 3072 x 8192 36 -> 27; 1488 x 3072 x 3072 NN stays on 144 tiles of 128x256 (40; 64x128 over two slices 72).
+TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, double* seconds = nullptr, bool own_sum = false) {
   const TileChoice large = pick_large_tile(kind, epi, M, N, K, ws_bytes);
   const KindTable& kt = g_kinds[kind];
   const double out = (double)M * N * (epi == EPI_F32 ? 4.0 : kind == 2 ? 8.0 : epi == EPI_SWIGLU ? 3.0 : epi == EPI_DSWIGLU ? 8.0 : epi == EPI_BIAS_GELU || epi == EPI_DGELU ? 4.0 : 2.0);
-  auto slices = [&](int S) { return S > 1 ? 3.2e-6 + 2.0 * S * M * N * 4.0 / 6.0e12 : 0.0; };
+  auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  auto slices = [&](int S, int bm, int bn, bool own) {
+    return S <= 1 ? 0.0 : 2.0 * S * M * N * 4.0 / 6.0e12 + (own ? 2.0e-6 + (S - 1) * bm * bn * 4.0 / 47.0e9 : 3.2e-6);
+  };
+  auto room = [&](int S, int bm, int bn) {  // partial sums and counters of slices that the launch adds up
+    return S <= 1 || (tiles(bm, bn) <= kSliceCounters && (size_t)tiles(bm, bn) * S * bm * bn * 4 <= ws_bytes);
+  };
   const double rate = large.bm == 256 && large.bn == 256 ? kt.r256x256 : large.bm == 256 ? kt.r256x128 : large.bn == 256 ? kt.r128x256 : kt.r128x128;
   const long wgs = (long)((M + large.bm - 1) / large.bm) * ((N + large.bn - 1) / large.bn) * large.ksplit;
-  double best_t = (double)((wgs + 255) / 256) * (2.0 * large.bm * large.bn * ((double)K / large.ksplit) + 3.0e6) / (rate * 1e12 / 256.0) + out / 3.1e12 +
-                  slices(large.ksplit);
+  double best_t = (double)((wgs + 255) / 256) * (2.0 * large.bm * large.bn * ((double)K / large.ksplit) + 3.0e6) / (rate * 1e12 / 256.0) +
+                  out / 3.1e12 + slices(large.ksplit, 128, 256, false);
   if (large.pp) best_t *= 0.9; else best_t += 2.0e-6;
+  if (own_sum && large.pp) best_t = pp_seconds(large.bm, wgs, K / large.ksplit, out) + slices(large.ksplit, 128, 256, true);
   TileChoice best = large;
+  // weights that no cache keeps are read once per row of tiles: not on 64-row tiles when there are more rows (128 x 6144 x 12288 NN over
+  // eight slices 59, NT 80, against 52 and 75 on 128 rows; a plain reduction over the 151 MB takes 47)
+  const bool streams = own_sum && kind != 2 && M > 64 && 2.0 * N * K > 64.0e6;
   for (int bn = epi == EPI_SWIGLU ? 128 : 64; bn <= 128; bn += 64)
     for (int S = 1; S <= 16; S *= 2) {
       const int k_per = st_k_per(K, S);
       if (S > 1 && ((size_t)S * M * N * 4 > ws_bytes || k_per < 2 * BKS || (long)(S - 1) * k_per >= K)) break;
-      if (k_per >= 8192) continue;
-      const long per_cu = ((long)((M + 63) / 64) * ((N + bn - 1) / bn) * S + 255) / 256;
-      const double t = 2.9e-6 + (double)per_cu * ((k_per + BKS - 1) / BKS) * (bn == 64 ? 0.225e-6 : 0.335e-6) + out / 4.0e12 + slices(S);
+      if (k_per >= 8192 || streams || (own_sum && !room(S, 64, bn))) continue;
+      const long wgs = tiles(64, bn) * S, per_cu = (wgs + 255) / 256;
+      const double t = 2.9e-6 + (double)per_cu * ((k_per + BKS - 1) / BKS) * (bn == 64 ? 0.225e-6 : 0.335e-6) + out / 4.0e12 + slices(S, 64, bn, own_sum);
       if (t < best_t) {
         best_t = t;
         best = TileChoice{64, bn, S, true};
+        best.st = true;
+      }
+    }
+  if (own_sum)
+    for (int S = 1; S <= 16; S++) {
+      const int k_per = st_k_per(K, S);
+      if (S > 1 && (!room(S, 128, 128) || k_per < 2 * BKS || (long)(S - 1) * k_per >= K)) break;
+      const long wgs = tiles(128, 128) * S;
+      const double t = 4.0e-6 + (double)((wgs + 255) / 256) * ((k_per + BKS - 1) / BKS) * 0.6e-6 * (wgs < 218 ? 0.85 : 1.0) + out / 4.0e12 + slices(S, 128, 128, true);
+      if (t < best_t) {
+        best_t = t;
+        best = TileChoice{128, 128, S, true};
         best.st = true;
       }
     }
@@ -1893,7 +1977,7 @@ TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, do
 
 int encode_variant(const TileChoice& t) {
   const bool rect = t.bm != t.bn;
-  return (t.st ? 400000000 : t.dtl ? (t.pp ? 300000000 : 200000000) : rect && t.wave_ksplit ? 100000000 : 0) + t.ksplit * 1000000 + t.bm * 1000 + t.bn;
+  return (t.st ? (t.bm == 128 ? 500000000 : 400000000) : t.dtl ? (t.pp ? 300000000 : 200000000) : rect && t.wave_ksplit ? 100000000 : 0) + t.ksplit * 1000000 + t.bm * 1000 + t.bn;
 }
 // variant -> TileChoice; false if no such instantiation exists or the k slices do not fit the problem / workspace
 bool decode_variant(int variant, int kind, int M, int N, int K, size_t ws_bytes, TileChoice* t) {
@@ -1911,8 +1995,8 @@ bool decode_variant(int variant, int kind, int M, int N, int K, size_t ws_bytes,
     return true;
   }
   if (wk >= 4) {  // small tiles; k slices of whole stages that all start inside K
-    const bool tile = bm == 64 && (bn == 64 || bn == 128);
-    if (wk > 4 || !tile || S < 1 || S > 16) return false;
+    const bool tile = (wk == 4 && bm == 64 && (bn == 64 || bn == 128)) || (wk == 5 && bm == 128 && bn == 128);
+    if (!tile || S < 1 || S > 16) return false;
     if (S > 1 && ((size_t)S * M * N * 4 > ws_bytes || (long)(S - 1) * st_k_per(K, S) >= K)) return false;
     *t = TileChoice{bm, bn, S, true};
     t->st = true;
@@ -1938,7 +2022,7 @@ int launch_shape(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_varia
     // those rows adds in the same order.  The 256 x 256 direct-to-LDS kernels need whole row tiles; a part that has none
     // runs the staged kernel of the same tile, which adds in the same order.
     const bool pinned = kind != 2 && choice_rows > g.M;
-    t = pick_tile(kind, EPI, pinned ? choice_rows : g.M, g.N, g.K, ws ? ws_bytes : 0);
+    t = pick_tile(kind, EPI, pinned ? choice_rows : g.M, g.N, g.K, ws ? ws_bytes : 0, nullptr, g.counters != nullptr);
     if (pinned && t.dtl && t.bm == 256 && !dtl_fits(kind, g.M, g.N, g.K)) t.dtl = t.pp = false;
     const int rows = pinned ? choice_rows : g.M;
     if ((t.dtl || t.st) && !(gemm_span_fits(A_KC ? rows : g.K, g.lda) && gemm_span_fits(B_KC ? g.N : g.K, g.ldb))) {
@@ -1965,8 +2049,9 @@ int launch_shape(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_varia
     return OASES_EINVAL;
   }
   if (t.st) {
-    if (t.bn == 128) return launch_small<2, 3, A_KC, B_KC, EPI>(g, t.ksplit, ws, s);
-    if constexpr (EPI != EPI_SWIGLU) return launch_small<1, 5, A_KC, B_KC, EPI>(g, t.ksplit, ws, s);
+    if (t.bm == 128) return launch_small<2, 2, 4, A_KC, B_KC, EPI>(g, t.ksplit, ws, s);
+    if (t.bn == 128) return launch_small<1, 2, 3, A_KC, B_KC, EPI>(g, t.ksplit, ws, s);
+    if constexpr (EPI != EPI_SWIGLU) return launch_small<1, 1, 5, A_KC, B_KC, EPI>(g, t.ksplit, ws, s);
     set_error("gemm: the 64x64 kernel has no SwiGLU epilogue");
     return OASES_EINVAL;
   }
@@ -1987,9 +2072,17 @@ int launch_shape(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_varia
         GemmArgs p = d;
         p.ksplit = t.ksplit;
         p.k_per = g.K / t.ksplit;
+        const dim3 sgrid(d.tiles_m * d.tiles_n * t.ksplit);
+        if (g.counters && d.tiles_m * d.tiles_n <= kSliceCounters && (size_t)d.tiles_m * d.tiles_n * t.ksplit * 128 * 256 * 4 <= ws_bytes) {
+          p.part = ws;
+          if (whole) hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, true, true>), sgrid, dim3(512), 0, s, p);
+          else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, false, true>), sgrid, dim3(512), 0, s, p);
+          OASES_LAUNCH_CHECK("gemm_pp_kernel (slices)");
+          return 0;
+        }
+        p.counters = nullptr;
         p.C = ws;
         p.ldc = g.N;
-        const dim3 sgrid(d.tiles_m * d.tiles_n * t.ksplit);
         if (whole) hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI_F32, true>), sgrid, dim3(512), 0, s, p);
         else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI_F32, false>), sgrid, dim3(512), 0, s, p);
         OASES_LAUNCH_CHECK("gemm_pp_kernel (split-K)");
@@ -2144,25 +2237,14 @@ static bool tn_group_fits(int variant, int K, int M0, int N0, int M1, int N1, si
   const int S = variant / 1000000 % 100;
   if (variant != 300128256 + S * 1000000 || (S != 1 && S != 2 && S != 4 && S != 8) || K % BKR) return false;
   const long T = (long)((M0 + 127) / 128) * ((N0 + 255) / 256) + (long)((M1 + 127) / 128) * ((N1 + 255) / 256);
-  // every slice has stages of its own
-  const int k_per = (K / BKR + S - 1) / S * BKR;
-  return S == 1 || (T <= kSliceCounters && (long)(S - 1) * k_per < K && (size_t)T * S * kSlicePartFloats * 4 <= ws_bytes);
-}
-// Time of an eight-wave launch over wgs workgroups, seconds.  What the MFMA loops are bound by is the power they draw together, so a
-// round that leaves CUs idle runs its stages faster, down to three quarters of the time of a full one (128x256 tiles, a 64-wide
-// stage: 256 workgroups 0.9 us, 144 or fewer 0.68); the output, read and written, moves at 4.5 TB/s.
-static double pp_seconds(int bm, long wgs, int k_per, double out_bytes) {
-  double t = out_bytes / 4.5e12;
-  for (; wgs > 0; wgs -= 256)
-    t += 4.0e-6 + k_per / 64 * (bm == 256 ? 1.75e-6 : 0.9e-6) * std::max(0.75, (double)std::min(wgs, 256L) / 256.0);
-  return t;
+  return S == 1 || (T <= kSliceCounters && (long)(S - 1) * st_k_per(K, S) < K && (size_t)T * S * 128 * 256 * 4 <= ws_bytes);  // every slice has stages of its own
 }
 static double tn_single_seconds(int M, int N, int K, size_t ws_bytes) {
   double t;
-  const TileChoice c = pick_tile(2, EPI_ACC_F32, M, N, K, ws_bytes, &t);
-  if (c.st || c.bn != 256) return t;
+  const TileChoice c = pick_tile(2, EPI_ACC_F32, M, N, K, ws_bytes, &t, true);
+  if (c.st || !c.pp) return t;
   t = pp_seconds(c.bm, (long)((M + c.bm - 1) / c.bm) * ((N + 255) / 256) * c.ksplit, K / c.ksplit, 8.0 * M * N);
-  return c.ksplit > 1 ? t + 3.2e-6 + 8.0 * c.ksplit * M * N / 6.0e12 : t;
+  return c.ksplit > 1 ? t + 2.0e-6 + 2.7e-6 * (c.ksplit - 1) : t;
 }
 // Which kernel, how many slices, and whether one launch takes less time than two.  k slices cost 2 us and 2.7 us each: the last
 // workgroup of a tile reads the others' sums one after the other.  Both sides measured, us, two launches -> one: 8192 rows,
@@ -2208,7 +2290,7 @@ int launch_gemm_tn_group(int variant, int K, const TnProblem& a, const TnProblem
   const int bm = variant / 1000 % 1000, bn = variant % 1000, S = variant / 1000000 % 100;
   auto args = [&](const TnProblem& p) {
     return GemmArgs{(const uint16_t*)p.A, (const uint16_t*)p.B, p.C, nullptr, nullptr, p.M, p.N, K, p.lda, p.ldb, p.ldc, 0,
-                    (p.M + bm - 1) / bm, (p.N + bn - 1) / bn, S, (K / BKR + S - 1) / S * BKR};
+                    (p.M + bm - 1) / bm, (p.N + bn - 1) / bn, S, st_k_per(K, S), ws, counters};
   };
   const GemmArgs g0 = args(a), g1 = args(b);
   const dim3 grid((unsigned)((g0.tiles_m * g0.tiles_n + g1.tiles_m * g1.tiles_n) * S));
@@ -2232,15 +2314,15 @@ int launch_gemm_tn_group(int variant, int K, const TnProblem& a, const TnProblem
 
 #endif  // TN part
 #if OASES_GEMM_HAS(0)
-int gemm_variant(int op, int epi, int M, int N, int K, size_t ws_bytes) {
+int gemm_variant(int op, int epi, int M, int N, int K, size_t ws_bytes, bool pass) {
   const int kind = op == OASES_GEMM_TN ? 2 : op == OASES_GEMM_NT ? 1 : (epi == EPI_BIAS_GELU || epi == EPI_SWIGLU) ? 3 : 0;
   if (epi == EPI_SWIGLU || epi == EPI_DSWIGLU) ws_bytes = 0;
-  return encode_variant(pick_tile(kind, op == OASES_GEMM_TN ? EPI_ACC_F32 : epi, M, N, K, ws_bytes));
+  return encode_variant(pick_tile(kind, op == OASES_GEMM_TN ? EPI_ACC_F32 : epi, M, N, K, ws_bytes, nullptr, pass));
 }
 
 int launch_gemm(int op, int epi, int M, int N, int K, const void* A, int lda, const void* B, int ldb, void* C,
                 int ldc, const float* bias, void* aux, int ldaux, void* splitk_ws, size_t splitk_ws_bytes, int forced_variant,
-                hipStream_t s, int choice_rows) {
+                hipStream_t s, int choice_rows, uint32_t* counters) {
   float* ws = reinterpret_cast<float*>(splitk_ws);
   const size_t wsb = splitk_ws_bytes;
   if (M <= 0 || N <= 0 || K <= 0 || (M % 8) || (N % 8) || (K % 8) || (lda % 8) || (ldb % 8) || (ldc % 4) || (aux && ldaux % 4)) {
@@ -2250,6 +2332,7 @@ int launch_gemm(int op, int epi, int M, int N, int K, const void* A, int lda, co
   if (!A || !B || !C) { set_error("gemm: NULL operand"); return OASES_ENULL; }
   if (!aligned16(A) || !aligned16(B) || !aligned16(C) || !aligned16(bias) || !aligned16(aux)) { set_error("gemm: operand not 16-byte aligned"); return OASES_EALIGN; }
   GemmArgs g{(const uint16_t*)A, (const uint16_t*)B, C, bias, (uint16_t*)aux, M, N, K, lda, ldb, ldc, ldaux, 0, 0, 1, K};
+  g.counters = ws ? counters : nullptr;
   if (op == OASES_GEMM_TN) {
     if (lda < M || ldb < N || ldc < N) { set_error("gemm TN: leading dimension too small"); return OASES_EINVAL; }
     return launch_gemm_tn(g, ws, wsb, forced_variant, s);

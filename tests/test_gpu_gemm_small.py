@@ -1,4 +1,4 @@
-"""The small-tile GEMM kernels (variants 4SS064064 and 4SS064128) at the sizes where they can go wrong: fewer k tiles than LDS
+"""The small-tile GEMM kernels (variants 4SS064064, 4SS064128 and 5SS128128) at the sizes where they can go wrong: fewer k tiles than LDS
 stages, as many, more; k tails; operands that end inside the only or the last tile; k slices, the last one shorter."""
 import pytest
 import torch
@@ -21,7 +21,7 @@ def operands(B, op, M, N, K, g):
     return a @ b, ad, bd, opc, (K if op != "TN" else M), (N if op != "NT" else K)
 
 
-@pytest.mark.parametrize("variant", [401064064, 401064128, 402064064, 403064128])
+@pytest.mark.parametrize("variant", [401064064, 401064128, 402064064, 403064128, 501128128, 503128128])
 @pytest.mark.parametrize("op", ["NN", "NT", "TN"])
 def test_small_tiles(B, lo, op, variant):
     """fp32 output (accumulated into for TN) inside a larger buffer that must stay as it was, then the fused epilogues.
