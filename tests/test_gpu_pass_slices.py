@@ -1,0 +1,53 @@
+"""Products of a pass whose k slices the launch adds up itself: what a pass leaves in its workspace against the product of the operands
+it leaves there, in 64 bits, twice in a workspace that starts as NaN with counters that are not zero."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# hidden, tp, tokens -> kernels with slices among the products of the pass (128x256 eight-wave tiles, small tiles, 128x128 tiles)
+CASES = {(4096, 1, 136): {302128256}, (3072, 1, 264): {503128128, 402064128}, (2048, 1, 128): {404064064}, (4096, 1, 264): {304128256},
+         (4096, 2, 400): {502128128}}
+
+
+@pytest.mark.parametrize("h,tp,M", list(CASES))
+def test_products_with_slices(h, tp, M):
+    from paper_2305_16121_amd import binding as B
+    cfg = dict(hidden=h, n_heads=h // 64, seq=M // 2, batch=2, tp=tp, n_sub=1, n_layers=1, causal=1, dropout_p=0.0)
+    H = B.Handle(B.make_cfg(cfg, seed=1))
+    hp, fp = h // tp, 4 * h // tp
+    g = torch.Generator(device="cuda").manual_seed(h + M)
+    n = lambda *s: torch.randn(s, generator=g, device="cuda")
+    W = dict(wqkv=n(h, 3 * hp) / h ** 0.5, wo=n(hp, h) / h ** 0.5, w1=n(h, fp) / h ** 0.5, w2=n(fp, h) / h ** 0.5)
+    W = {k: v.bfloat16() for k, v in W.items()}
+    W.update(bqkv=n(3 * hp), bo=n(h), b1=n(fp), b2=n(h), ln1_g=n(h), ln1_b=n(h), ln2_g=n(h), ln2_b=n(h))
+    G = {k: torch.zeros(v.shape, device="cuda") for k, v in W.items()}
+    x, dy, y, dx = n(M, h), n(M, h), torch.empty(M, h, device="cuda"), torch.empty(M, h, device="cuda")
+    ws = torch.full((H.workspace_bytes,), 0xFF, dtype=torch.uint8, device="cuda")
+
+    def tensor(name, cols, dtype):
+        off, nb = H.tensor_span(name, 0)
+        return ws[off:off + nb].view(dtype).view(M, cols)
+    bf, f32 = torch.bfloat16, torch.float32
+    # product, its operand and its weights; +bias where the epilogue has one
+    products = [("NN", 2, tensor("qkv", 3 * hp, bf), tensor("u", h, bf), W["wqkv"], W["bqkv"]), ("NN", 0, tensor("z1", h, f32), tensor("attn", hp, bf), W["wo"], None),
+                ("NN", 3, tensor("pre", fp, bf), tensor("v2", h, bf), W["w1"], W["b1"]), ("NN", 0, tensor("z2", h, f32), tensor("f", fp, bf), W["w2"], None),
+                ("NT", 0, tensor("dv2", h, f32), tensor("dg", fp, bf), W["w1"], None), ("NT", 1, tensor("da", hp, bf), tensor("dz1", h, bf), W["wo"], None),
+                ("NT", 0, tensor("du", h, f32), tensor("dqkv", 3 * hp, bf), W["wqkv"], None)]
+    seen = {B.lib.oases_pass_gemm_variant({"NN": 0, "NT": 1}[op], epi, M, c.shape[1], a.shape[1], H.gemm_workspace_bytes) for op, epi, c, a, _, _ in products}
+    assert CASES[(h, tp, M)] <= seen
+    for _ in range(2):
+        H.forward([W], x, y, ws)
+        H.backward([W], x, dy, dx, [G], ws)
+        torch.cuda.synchronize()
+        for op, epi, c, a, w, bias in products:
+            ref = a.double() @ (w.double() if op == "NN" else w.double().t().contiguous())
+            if bias is not None:
+                ref += bias.double()
+            err = (c.double() - ref).abs()
+            # fp32 sums of K products (K roundings at most of partial sums below the sum of their magnitudes), and half a bf16 ulp
+            bound = a.shape[1] * 2.0 ** -24 * (a.double().abs() @ (w.double() if op == "NN" else w.double().t().contiguous()).abs())
+            if c.dtype == bf:
+                bound = bound + ref.abs() * 2.0 ** -8
+            assert bool((err <= bound + 1e-30).all()), (op, epi, tuple(c.shape), float((err / (bound + 1e-30)).max()))
+    H.close()
