@@ -802,12 +802,184 @@ __device__ __forceinline__ void attn_dkv_block(const AttnArgs& a, int wg, char* 
 }
 
 // =================================================================================================
+// backward: dK, dV with 128 columns.  64 keys x 64 queries at a time: two groups of 32 keys x two halves of a query tile, one wave each,
+// which is alone on its SIMD (keys, values and accumulators take 192 registers).  What bounded the wave-private form below on
+// large calls is the path from L2 to the registers: 16 KB of Q and dO for 32 x 32 scores, some 1850 of the 4600 cycles of a
+// tile just to issue; here the four waves share them (half the bytes a score), and a wave's chain is covered by its own
+// next tile: the products S and dP of tile t+1 stand between the exponentials of tile t.  Three stages: tile t+1 is read for these
+// products, tile t for dV and dK, and tile t+2 written over tile t-1, whose last reads lie before the barrier that ended
+// iteration t-1.  Measured (both backward
+// passes, us): 4x2048x4x128 causal 148 -> 122, not causal 222 -> 173, 8x1024x8x128 174 -> 152, 8x512x4x128 42 -> 35.
+// =================================================================================================
+struct Dkv128Lds {
+  static constexpr int kTile = SharedTile<128, 64>::bytes, kStage = 2 * kTile + 512;  // Q, dO, lse * log2(e) [64], delta [64]
+  static constexpr int kStages = 3 * kStage, kPart = 4 * 64 * 64 * 4;
+  static constexpr int bytes = kStages > kPart ? kStages : kPart;
+};
+template <bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(NT, 1) void attn_dkv128_kernel(AttnArgs a) {
+  constexpr int D = 128, KS = D / 16, DT = D / 32, E = DT * 16;
+  using L = Dkv128Lds;
+  __shared__ __attribute__((aligned(16))) char lds[L::bytes];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5;
+  const int jg = wave & 1, rg = wave >> 1;
+  int pair, kb;
+  decode_block(blockIdx.x, a.nseq * a.heads, a.blocks, pair, kb);  // early key blocks are the long ones
+  const int sq = pair / a.heads, head = pair % a.heads;
+  const int seq_idx = a.seq0 + sq;
+  const int wg_begin = a.pos0 + kb * 64;
+  const int k_begin = wg_begin + 32 * jg;
+  const int k_end = min(a.pos0 + a.npos, k_begin + 32);
+  const size_t rowbase = (size_t)seq_idx * a.seq;
+  const uint16_t* Qp = a.qkv + rowbase * a.ld + head * D;
+  const uint16_t* Kp = Qp + a.hp;
+  const uint16_t* Vp = Qp + 2 * a.hp;
+  const uint16_t* dOp = a.dout + rowbase * a.hp + head * D;
+  const float* lsep = a.lse + ((size_t)seq_idx * a.heads + head) * a.seq;
+  const float* dlp = a.delta + ((size_t)seq_idx * a.heads + head) * a.seq;
+  const int kpos = k_begin + (lane & 31);
+  const bool kok = kpos < k_end && kpos >= a.first;
+
+  const int q_first = CAUSAL ? wg_begin : 0;  // earlier queries never see a key of this block
+  const int qmin = CAUSAL ? a.first : 0;
+  const int nt = (a.seq - q_first + 63) / 64;
+  SharedTile<D, 64> rq, rdo;
+  float rstat = 0.f;
+  auto fetch = [&](int t) {
+    const int q0 = q_first + t * 64;
+    rq.load(Qp, a.ld, q0, qmin, a.seq, tid);
+    rdo.load(dOp, a.hp, q0, qmin, a.seq, tid);
+    if (tid < 128) {
+      const int qp = min(q0 + (tid & 63), a.seq - 1);
+      rstat = (tid < 64 ? lsep : dlp)[qp];
+    }
+  };
+  auto park = [&](int t) {
+    char* st = lds + (t % 3) * L::kStage;
+    rq.store(st, tid);
+    rdo.store(st + L::kTile, tid);
+    if (tid < 128) reinterpret_cast<float*>(st + 2 * L::kTile)[tid] = tid < 64 ? rstat * kLog2e : rstat;
+  };
+  bf16x8 kf[KS], vf[KS];
+  {
+    SharedTile<D, 64> rk, rv;
+    rk.load(Kp, a.ld, wg_begin, a.first, a.pos0 + a.npos, tid);
+    rv.load(Vp, a.ld, wg_begin, a.first, a.pos0 + a.npos, tid);
+    fetch(0);
+    char* st = lds + 2 * L::kStage;
+    rk.store(st, tid);
+    rv.store(st + L::kTile, tid);
+    park(0);
+    if (nt > 1) fetch(1);
+    lds_barrier();
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+      kf[ks] = tile_kc<D>(st, 32 * jg, ks, lane);
+      vf[ks] = tile_kc<D>(st + L::kTile, 32 * jg, ks, lane);
+    }
+  }
+  f32x16 dk[DT], dv[DT];
+#pragma unroll
+  for (int i = 0; i < DT; i++) { dk[i] = zero16(); dv[i] = zero16(); }
+  f32x16 s, dp;
+  auto products = [&](const char* st, f32x16& s1, f32x16& dp1) {  // S and dP of this wave's half of the tile in st
+    s1 = zero16();
+    dp1 = zero16();
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+      s1 = MFMA(tile_kc<D>(st, 32 * rg, ks, lane), kf[ks], s1);
+      dp1 = MFMA(tile_kc<D>(st + L::kTile, 32 * rg, ks, lane), vf[ks], dp1);
+    }
+  };
+  products(lds, s, dp);
+  if (nt > 1) park(1);
+  if (nt > 2) fetch(2);
+  lds_barrier();  // also: every wave has its keys, so stage 2 may take tile 2
+  auto tile = [&](auto mask_c, auto next_c, int t) {
+    constexpr bool MASK = decltype(mask_c)::value, NEXT = decltype(next_c)::value;
+    const char* cur = lds + (t % 3) * L::kStage;
+    const float* lstat = reinterpret_cast<const float*>(cur + 2 * L::kTile) + 32 * rg;  // [64] lse * log2(e), [64] delta
+    const int q0 = q_first + t * 64 + 32 * rg;
+    if (NEXT && t + 2 < nt) {
+      park(t + 2);
+      if (t + 3 < nt) fetch(t + 3);
+    }
+    Philox4 dw;  // the four lanes of a quad share the keys of a 4 x 4 block: each draws the block of one group of queries
+    if (DROP) dw = attn_drop_block(a, (uint32_t)kpos >> 2, (uint32_t)(q0 + 8 * (lane & 3) + 4 * g) >> 2, (uint32_t)(seq_idx * a.heads_total + a.head0 + head));
+    f32x16 sn, dpn;
+    if constexpr (NEXT) products(lds + ((t + 1) % 3) * L::kStage, sn, dpn);
+    auto group = [&](auto i4_c) {
+      constexpr int I4 = decltype(i4_c)::value;
+      const int ql = 8 * I4 + 4 * g;  // 4 consecutive queries
+      const f32x4 l4 = *reinterpret_cast<const f32x4*>(lstat + ql);
+      const f32x4 d4 = *reinterpret_cast<const f32x4*>(lstat + 64 + ql);
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const int i = 4 * I4 + e;
+        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], a.scale_log2, -l4[e]));
+        float dpe = dp[i], pv = p;  // pv: what multiplied V in forward
+        if (DROP) {  // this lane's key is byte (kpos mod 4) of the word of query e of the group
+          const bool keep = ((quad_lane<I4>(dw.v[e]) >> (8 * (kpos & 3))) & 0xffu) >= a.dthresh;
+          dpe = keep ? dpe * a.dscale : 0.f;
+          pv = keep ? p * a.dscale : 0.f;
+        }
+        float ds = p * (dpe - d4[e]);
+        if (MASK) {
+          const int qp = q0 + ql + e;
+          if (qp >= a.seq || (CAUSAL && kpos > qp)) { pv = 0.f; ds = 0.f; }   // select, never multiply: the rest may be NaN
+        }
+        s[i] = pv;
+        dp[i] = ds;
+      }
+    };
+    group(std::integral_constant<int, 0>{});
+    group(std::integral_constant<int, 1>{});
+    group(std::integral_constant<int, 2>{});
+    group(std::integral_constant<int, 3>{});
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      bf16x8 pa = pack8(s, 8 * j);
+      bf16x8 da = pack8(dp, 8 * j);
+#pragma unroll
+      for (int dt = 0; dt < DT; dt++) {
+        dv[dt] = MFMA(tile_mc<D>(cur + L::kTile, 32 * rg, j, dt, lane), pa, dv[dt]);
+        dk[dt] = MFMA(tile_mc<D>(cur, 32 * rg, j, dt, lane), da, dk[dt]);
+      }
+    }
+    if constexpr (NEXT) {
+      s = sn;
+      dp = dpn;
+      lds_barrier();
+    }
+  };
+  // The mask matters to the first tile (diagonal) and to the last (end of the sequence); in between there is one form of a tile, so that the
+  // accumulators stay where they are.
+  using T_ = std::true_type;
+  using F_ = std::false_type;
+  int t = 0;
+  if (nt > 1) {
+    tile(T_{}, T_{}, 0);
+    for (t = 1; t + 1 < nt; t++) tile(F_{}, T_{}, t);
+  }
+  tile(T_{}, F_{}, t);
+  uint16_t* dKp = a.dqkv + (rowbase + kpos) * a.ld + a.hp + head * D;
+  uint16_t* dVp = dKp + a.hp;
+  combine_parts<E, 2, 2>(dk, lds, jg, rg, lane, [&](int e, const f32x4& v) {
+    const int d = (e / 16) * 32 + 8 * ((e % 16) >> 2) + 4 * g;
+    if (kok) *reinterpret_cast<u32x2*>(dKp + d) = u32x2{pack_bf16x2(v[0] * a.scale, v[1] * a.scale), pack_bf16x2(v[2] * a.scale, v[3] * a.scale)};
+  });
+  combine_parts<E, 2, 2>(dv, lds, jg, rg, lane, [&](int e, const f32x4& v) {
+    const int d = (e / 16) * 32 + 8 * ((e % 16) >> 2) + 4 * g;
+    if (kok) *reinterpret_cast<u32x2*>(dVp + d) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+  });
+}
+
+// =================================================================================================
 // backward over blocks of 32 rows, a wave by itself.  The four waves of a workgroup split the reduction range -- the 32-row key tiles
 // a query block sees, or the 32-row query tiles that see a key block -- round-robin, each staging its own tiles in a private
 // slice of LDS, so the loops need no barrier; the four partial results meet once, through LDS, at the end.  Rows are padded
 // instead of swizzled.  This form stays where the shared tiles above do not pay: calls with few blocks, whose time is the
-// chain of the longest one (a quarter of it per wave here), and dK/dV with D = 128, whose 192 registers of keys and
-// accumulators leave a SIMD one wave: in lockstep with three others it waits at every barrier.
+// chain of the longest one (a quarter of it per wave here).
 // =================================================================================================
 template <int D>
 struct WaveLds {  // LDS of a backward workgroup: the larger of the two passes' staging areas and of the partial-sum exchange
@@ -1227,7 +1399,8 @@ int launch_attention_bwd(const void* qkv, const void* out, const void* dout, con
       if (qg == 2) OASES_ATTN_DQ(DD, 2, CC, DR);                                                                    \
       else if constexpr (DD == 64) OASES_ATTN_DQ(DD, 1, CC, DR);                                                    \
       else hipLaunchKernelGGL((wave_dq_kernel<CC, DR>), grid, block, 0, s, a);                                      \
-      if constexpr (DD == 128) hipLaunchKernelGGL((wave_dkv_kernel<CC, DR>), grid, block, 0, s, a);                 \
+      if (DD == 128 && qg == 2) hipLaunchKernelGGL((attn_dkv128_kernel<CC, DR>), qgrid, block, 0, s, q);               \
+      else if constexpr (DD == 128) hipLaunchKernelGGL((wave_dkv_kernel<CC, DR>), grid, block, 0, s, a);                 \
       else if (qg == 2) hipLaunchKernelGGL((attn_dkv_kernel<2, CC, DR>), qgrid, block, 0, s, q);                    \
       else hipLaunchKernelGGL((attn_dkv_kernel<1, CC, DR>), qgrid, block, 0, s, q);                                 \
     }                                                                                                               \
