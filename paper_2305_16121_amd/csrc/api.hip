@@ -127,6 +127,7 @@ struct oases_handle {
   size_t layer_bytes, shared_off, scratch_comm_off, scratch_compute_off, gemm_ws_off, gemm_ws_bytes, slice_counters_off, total_bytes;
   // arena of partial rows of the backward pass's column reductions, per layer: five slots (see ColsumSlot)
   size_t colsum_off, colsum_layer_bytes, colsum_slot_off[5];
+  int ff_group = 0, pq_group = 0;  // kernel of a block's two weight gradients in one launch (gemm_tn_group_variant), 0: two launches
   int colsum_groups_sub, colsum_groups_all;  // row groups of a reduction over xMs rows / over all M rows
 };
 
@@ -326,17 +327,24 @@ static int pass_sub_batches(const oases_handle* H) {
 
 // What a pass executes of the schedule's weight gradients: the two of a block share a launch where that is expected to take less
 // time.  Under OASES_FLAG_PIN_GEMM a pass launches what the schedule of a profiling handle launches, so that both give the same bits.
-static void group_weight_gradients(const oases_handle* H, std::vector<Op>& ops) {
+// The small-tile kernel brings the bias gradient with it, a column sum of the same operand.
+static bool group_sums_bias(const oases_handle* H, int variant) { return !H->llama && variant / 100000000 == 4; }
+static void group_weight_gradients(oases_handle* H, std::vector<Op>& ops) {
   if (H->cfg.flags & (OASES_FLAG_PIN_GEMM | OASES_FLAG_PROFILE)) return;
-  bool ff = false, pq = false;
-  gemm_tn_group_variant(H->M, H->fp, H->h, H->h, H->fw, H->gemm_ws_bytes, &ff);
-  gemm_tn_group_variant(H->M, H->hp, H->h, H->h, 3 * H->hp, H->gemm_ws_bytes, &pq);
+  bool wins;
+  int v = gemm_tn_group_variant(H->M, H->fp, H->h, H->h, H->fw, H->gemm_ws_bytes, &wins);
+  if (wins) H->ff_group = v;
+  v = gemm_tn_group_variant(H->M, H->hp, H->h, H->h, 3 * H->hp, H->gemm_ws_bytes, &wins);
+  for (const Op& op : ops) wins = wins && op.kind != B_PQ_WGRAD;
+  if (wins) H->pq_group = v;
   std::vector<Op> out;
   for (Op op : ops) {
-    if (ff && op.kind == B_FC1_WGRAD) continue;
-    if (ff && op.kind == B_FC2_WGRAD) op.kind = B_FF_GROUP;
-    if (pq && op.kind == B_QKV_WGRAD) continue;
-    if (pq && op.kind == B_PROJ_WGRAD) op.kind = B_PQ_GROUP;
+    if (H->ff_group && op.kind == B_FC1_WGRAD) continue;
+    if (H->ff_group && op.kind == B_FC2_WGRAD) op.kind = B_FF_GROUP;
+    if (H->pq_group && op.kind == B_QKV_WGRAD) continue;
+    if (H->pq_group && op.kind == B_PROJ_WGRAD) op.kind = B_PQ_GROUP;
+    if (op.kind == B_B1_SUM && group_sums_bias(H, H->ff_group)) continue;
+    if (op.kind == B_BQKV_SUM && group_sums_bias(H, H->pq_group)) continue;
     out.push_back(op);
   }
   ops.swap(out);
@@ -608,11 +616,11 @@ static int run_op(const Run& R, const Op& op) {
       return launch_gemm_tn_pair(Ms, hp, h, attn + r0 * hp, hp, wsp<uint16_t>(R, T_dz1, l) + r0 * h, h, R.g[l].wo, h, h, 3 * hp, u + r0 * h, h,
                                  wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp, R.g[l].wqkv, 3 * hp, s);
     case B_FF_GROUP:
-      return launch_gemm_tn_group(0, Ms, TnProblem{fp, h, f, fp, wsp<uint16_t>(R, T_dz2, l), h, R.g[l].w2, h},
-                                  TnProblem{h, fw, v2, h, wsp<uint16_t>(R, T_dg, l), fw, R.g[l].w1, fw}, (float*)gws, H->gemm_ws_bytes, counters, s);
+      return launch_gemm_tn_group(H->ff_group, Ms, TnProblem{fp, h, f, fp, wsp<uint16_t>(R, T_dz2, l), h, R.g[l].w2, h},
+                                  TnProblem{h, fw, v2, h, wsp<uint16_t>(R, T_dg, l), fw, R.g[l].w1, fw, group_sums_bias(H, H->ff_group) ? (float*)R.g[l].b1 : nullptr}, (float*)gws, H->gemm_ws_bytes, counters, s);
     case B_PQ_GROUP:
-      return launch_gemm_tn_group(0, Ms, TnProblem{hp, h, attn, hp, wsp<uint16_t>(R, T_dz1, l), h, R.g[l].wo, h},
-                                  TnProblem{h, 3 * hp, u, h, wsp<uint16_t>(R, T_dqkv, l), 3 * hp, R.g[l].wqkv, 3 * hp}, (float*)gws, H->gemm_ws_bytes, counters, s);
+      return launch_gemm_tn_group(H->pq_group, Ms, TnProblem{hp, h, attn, hp, wsp<uint16_t>(R, T_dz1, l), h, R.g[l].wo, h},
+                                  TnProblem{h, 3 * hp, u, h, wsp<uint16_t>(R, T_dqkv, l), 3 * hp, R.g[l].wqkv, 3 * hp, group_sums_bias(H, H->pq_group) ? (float*)R.g[l].bqkv : nullptr}, (float*)gws, H->gemm_ws_bytes, counters, s);
     case B_BQKV_SUM:
       { ColsumSink* cs = colsum(4); return colsum_done(launch_colsum_bf16(wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp, Ms, 3 * hp, (float*)R.g[l].bqkv, cs_scratch, s, cs)); }
     // ---------------------------------------------------------------- recompute: the forward kernels again

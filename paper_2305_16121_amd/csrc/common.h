@@ -180,6 +180,7 @@ struct TnProblem {
   int ldb;
   void* C;
   int ldc;
+  float* colsum = nullptr;  // [N], += column sums of B; small tiles (variants 4...) only
 };
 constexpr int kSliceCounters = 1024;
 int launch_gemm_tn_group(int variant, int K, const TnProblem& a, const TnProblem& b, float* ws, size_t ws_bytes, uint32_t* counters, hipStream_t s);

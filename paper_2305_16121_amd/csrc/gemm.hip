@@ -40,6 +40,7 @@ struct GemmArgs {
   int ksplit, k_per;  // split-K: slice s covers k in [s*k_per, min(K, (s+1)*k_per)) and writes partial s
   float* part;         // slices that the launch adds up itself (SliceSum): partial sums, and a counter per tile
   uint32_t* counters;  // nullptr: slices write planes that a second launch adds up
+  float* colsum;       // weight gradients of a group: [N], += the column sums of B (a bias gradient); or nullptr
 };
 
 // one launcher per contraction form, each defined in its own part
@@ -1558,7 +1559,17 @@ struct StLds {
   static constexpr int kStage = 64 * (TM + TN) * BKS * 2, kExchange = 8 * TM * TN * 2 * 64 * 16;  // exchange: half of every wave's accumulator
   static constexpr int bytes = NS * kStage > kExchange ? NS * kStage : kExchange;
 };
-template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI>
+// sum of the eight bf16 values of a fragment, in fp32
+__device__ __forceinline__ float frag_sum(const u32x4& f) {
+  const bf16x2_ one = {(__bf16)1.0f, (__bf16)1.0f};
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; i++) s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_, (uint32_t)f[i]), one, s, false);
+  return s;
+}
+// COLSUM (weight gradients): the waves of the first row of tiles that hold the first 32 rows also add up B's columns, whose fragments they
+// have in registers (eight k of a column to a lane): the vector ALU has time, LDS is what the kernel waits for.  Eight tiles to a partial sum.
+template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI, bool COLSUM = false>
 __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, const SliceSum& ss = SliceSum{}) {
   constexpr int BM = 64 * TM, BN = 64 * TN;
   constexpr int kOpA = BM * BKS * 2, kStage = StLds<TM, TN, NS>::kStage;
@@ -1627,6 +1638,10 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, c
 
   u32x4 fa[2][TM], fb[2][TN];
   int stage = 0;
+  const bool sums = COLSUM && g.colsum && tile_m == 0 && wm == 0;
+  float csum[TN], part[TN];
+#pragma unroll
+  for (int j = 0; j < TN; j++) csum[j] = part[j] = 0.f;
   // one tile; YOUNG: tiles behind it that may still be in flight (compile-time, for the wait); steady: tile kt+NS-1 exists
   auto iteration = [&](auto young_c, auto steady_c, int kt) {
     constexpr int Y = PER * decltype(young_c)::value;
@@ -1652,6 +1667,16 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, c
 #pragma unroll
           for (int j = 0; j < TN; j++) fb[kk][j] = u32x4{0u, 0u, 0u, 0u};
         }
+    }
+    if (COLSUM && sums) {
+#pragma unroll
+      for (int j = 0; j < TN; j++) {
+        part[j] += frag_sum(fb[0][j]) + frag_sum(fb[1][j]);
+        if ((kt & 7) == 7) {
+          csum[j] += part[j];
+          part[j] = 0.f;
+        }
+      }
     }
 #pragma unroll
     for (int kk = 0; kk < 2; kk++)
@@ -1690,7 +1715,25 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, c
       }
   };
   if (wk == 0) hand_over(std::integral_constant<int, 1>{}); else hand_over(std::integral_constant<int, 0>{});
+  float* xsum = reinterpret_cast<float*>(lds + StLds<TM, TN, NS>::kExchange) + 64 * TN * wn;
+  if (COLSUM && sums) {
+#pragma unroll
+    for (int j = 0; j < TN; j++) {
+      csum[j] += part[j];
+      if (wk == 1) xsum[64 * j + lane] = csum[j];
+    }
+  }
   __syncthreads();
+  if (COLSUM && sums && wk == 0) {
+    static_assert(StLds<TM, TN, NS>::kExchange + 512 * TN <= StLds<TM, TN, NS>::bytes, "column sums behind the exchange");
+#pragma unroll
+    for (int j = 0; j < TN; j++) {
+      float t = csum[j] + xsum[64 * j + lane];
+      t += __shfl_xor(t, 32, 64);  // the other eight k of a step
+      const int col = col0 + 32 * j + (lane & 31);
+      if (lane < 32 && col < g.N) g.colsum[col] += t;
+    }
+  }
   f32x4 v[TM * TN * 2];  // [row part][column part][quarter]
   auto gather = [&](auto half_c) {
     constexpr int E = 8 * decltype(half_c)::value;
@@ -1762,7 +1805,7 @@ __global__ __launch_bounds__(512) void gemm_st_group_kernel(GemmArgs g0, GemmArg
   const int first = g0.tiles_m * g0.tiles_n;
   const bool second = (int)blockIdx.x >= first;
   const GemmArgs g = second ? g1 : g0;
-  st_tile<1, TN, NS, false, false, EPI_ACC_F32>(g, second ? blockIdx.x - first : blockIdx.x, lds);
+  st_tile<1, TN, NS, false, false, EPI_ACC_F32, true>(g, second ? blockIdx.x - first : blockIdx.x, lds);
 }
 
 // split-K second pass: C = epilogue(sum over slices of the fp32 partial planes), slices added in index order
@@ -2288,9 +2331,10 @@ int launch_gemm_tn_group(int variant, int K, const TnProblem& a, const TnProblem
     return OASES_EINVAL;
   }
   const int bm = variant / 1000 % 1000, bn = variant % 1000, S = variant / 1000000 % 100;
+  if (bm != 64 && (a.colsum || b.colsum)) { set_error("gemm_tn_group: column sums come with the small tiles only"); return OASES_EINVAL; }
   auto args = [&](const TnProblem& p) {
     return GemmArgs{(const uint16_t*)p.A, (const uint16_t*)p.B, p.C, nullptr, nullptr, p.M, p.N, K, p.lda, p.ldb, p.ldc, 0,
-                    (p.M + bm - 1) / bm, (p.N + bn - 1) / bn, S, st_k_per(K, S), ws, counters};
+                    (p.M + bm - 1) / bm, (p.N + bn - 1) / bn, S, st_k_per(K, S), ws, counters, p.colsum};
   };
   const GemmArgs g0 = args(a), g1 = args(b);
   const dim3 grid((unsigned)((g0.tiles_m * g0.tiles_n + g1.tiles_m * g1.tiles_n) * S));

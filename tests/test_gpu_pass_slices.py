@@ -51,3 +51,30 @@ def test_products_with_slices(h, tp, M):
                 bound = bound + ref.abs() * 2.0 ** -8
             assert bool((err <= bound + 1e-30).all()), (op, epi, tuple(c.shape), float((err / (bound + 1e-30)).max()))
     H.close()
+
+
+@pytest.mark.parametrize("M,h", [(200, 512), (72, 1024), (1032, 512), (2056, 256)])
+def test_bias_gradients_that_come_with_the_weight_gradients(M, h):
+    """Small-tile weight gradients add up the columns of their second operand on the way: the bias gradients of a pass against the column sums of
+    the operands it leaves in its workspace, in 64 bits, accumulated into what was there; tokens that end inside a 64-wide tile of k."""
+    from paper_2305_16121_amd import binding as B
+    H = B.Handle(B.make_cfg(dict(hidden=h, n_heads=h // 64, seq=M // 8, batch=8, tp=1, n_sub=1, n_layers=1, causal=1, dropout_p=0.0), seed=1))
+    g = torch.Generator(device="cuda").manual_seed(M)
+    n = lambda *s: torch.randn(s, generator=g, device="cuda")
+    W = {k: (n(*s) / h ** 0.5).bfloat16() for k, s in dict(wqkv=(h, 3 * h), wo=(h, h), w1=(h, 4 * h), w2=(4 * h, h)).items()}
+    W.update(bqkv=n(3 * h), bo=n(h), b1=n(4 * h), b2=n(h), ln1_g=n(h), ln1_b=n(h), ln2_g=n(h), ln2_b=n(h))
+    G = {k: n(*v.shape) for k, v in W.items()}
+    old = {k: G[k].clone() for k in ("b1", "bqkv")}
+    x, y, dx = n(M, h), torch.empty(M, h, device="cuda"), torch.empty(M, h, device="cuda")
+    ws = torch.full((H.workspace_bytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    H.forward([W], x, y, ws)
+    H.backward([W], x, n(M, h), dx, [G], ws)
+    torch.cuda.synchronize()
+    for name, k, w in (("dg", "b1", 4 * h), ("dqkv", "bqkv", 3 * h)):
+        off, nb = H.tensor_span(name, 0)
+        t = ws[off:off + nb].view(torch.bfloat16).view(M, w).double()
+        err = (G[k].double() - old[k].double() - t.sum(dim=0)).abs()
+        # at most M / 16 + 64 roundings of partial sums below the sum of the magnitudes, and those of the old value and the result
+        bound = (M / 16 + 64) * 2.0 ** -24 * t.abs().sum(dim=0) + 2.0 ** -23 * (old[k].abs() + G[k].abs()).double()
+        assert bool((err <= bound).all()), (k, float((err / bound).max()))
+    H.close()
