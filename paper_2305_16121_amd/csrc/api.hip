@@ -127,6 +127,7 @@ struct oases_handle {
   size_t layer_bytes, shared_off, scratch_comm_off, scratch_compute_off, gemm_ws_off, gemm_ws_bytes, slice_counters_off, total_bytes;
   // arena of partial rows of the backward pass's column reductions, per layer: five slots (see ColsumSlot)
   size_t colsum_off, colsum_layer_bytes, colsum_slot_off[5];
+  int variant[B_PQ_GROUP + 1] = {};  // by operator: the kernel of its GEMM as gemm_variant encodes it, chosen once (see choose_gemms); 0: chosen by the launch
   int ff_group = 0, pq_group = 0;  // kernel of a block's two weight gradients in one launch (gemm_tn_group_variant), 0: two launches
   int colsum_groups_sub, colsum_groups_all;  // row groups of a reduction over xMs rows / over all M rows
 };
@@ -350,6 +351,24 @@ static void group_weight_gradients(oases_handle* H, std::vector<Op>& ops) {
   ops.swap(out);
 }
 
+// The kernel of every GEMM of a pass, chosen once for the rows that its launches have: a launch that runs the time model takes half a
+// microsecond to a microsecond more on the host, and issuing bounds a pass of the smallest layers (host time of a training step, us, model
+// run per launch -> per handle: h 512 155 -> 143 of 149 in all, three layers of h 1024 with 200 rows 326 -> 284).  The choice is the one that
+// launch_gemm makes.  Under OASES_FLAG_PIN_GEMM and for operands that may span 2 GiB the launch goes on choosing, part by part.
+static void choose_gemms(oases_handle* H) {
+  if (H->cfg.flags & OASES_FLAG_PIN_GEMM) return;
+  const int Ms = H->xMs, M = H->M, h = H->h, hp = H->hp, fp = H->fp, fw = H->fw;
+  if (!gemm_span_fits(M, std::max({h, 3 * hp, fw})) || !gemm_span_fits(h, std::max(3 * hp, fw)) || !gemm_span_fits(std::max(hp, fp), h)) return;
+  const struct { int kind, op, epi, M, N, K; } list[] = {
+      {F_QKV, OASES_GEMM_NN, H->llama ? OASES_EPI_BF16 : OASES_EPI_BIAS_BF16, Ms, 3 * hp, h}, {F_PROJ, OASES_GEMM_NN, OASES_EPI_F32, Ms, h, hp},
+      {F_FC1, OASES_GEMM_NN, H->llama ? OASES_EPI_SWIGLU : OASES_EPI_BIAS_GELU, Ms, fw, h}, {F_FC2, OASES_GEMM_NN, OASES_EPI_F32, Ms, h, fp},
+      {B_FC2_DGRAD, OASES_GEMM_NT, H->llama ? OASES_EPI_DSWIGLU : OASES_EPI_DGELU, Ms, fp, h}, {B_FC1_DGRAD, OASES_GEMM_NT, OASES_EPI_F32, Ms, h, fw},
+      {B_PROJ_DGRAD, OASES_GEMM_NT, OASES_EPI_BF16, Ms, hp, h}, {B_QKV_DGRAD, OASES_GEMM_NT, OASES_EPI_F32, Ms, h, 3 * hp},
+      {B_FC2_WGRAD, OASES_GEMM_TN, 0, fp, h, M}, {B_FC1_WGRAD, OASES_GEMM_TN, 0, h, fw, M}, {B_PROJ_WGRAD, OASES_GEMM_TN, 0, hp, h, M},
+      {B_QKV_WGRAD, OASES_GEMM_TN, 0, h, 3 * hp, M}};
+  for (const auto& e : list) H->variant[e.kind] = gemm_variant(e.op, e.epi, e.M, e.N, e.K, H->gemm_ws_bytes, true);
+}
+
 static int check_ptrs(const void* const* p, int n, const char* who) {
   for (int i = 0; i < n; i++) {
     if (!p[i]) { set_error("%s: NULL device pointer (argument %d)", who, i); return OASES_ENULL; }
@@ -523,7 +542,7 @@ static int run_op(const Run& R, const Op& op) {
                                   wsp<float>(R, T_mu1, l) + r0, wsp<float>(R, T_rstd1, l) + r0, Ms, h, H->eps, s, rms, counters);
     case F_QKV:
       return launch_gemm(OASES_GEMM_NN, rms ? OASES_EPI_BF16 : OASES_EPI_BIAS_BF16, Ms, 3 * hp, h, u + r0 * h, h, W.wqkv, 3 * hp,
-                         qkv + r0 * 3 * hp, 3 * hp, (const float*)W.bqkv, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
+                         qkv + r0 * 3 * hp, 3 * hp, (const float*)W.bqkv, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);
     case F_ROPE_TABLE:
       return launch_rope_table(wsp<float>(R, T_rope, 0), H->s, H->d, H->theta, s);
     case F_ROPE:
@@ -537,7 +556,7 @@ static int run_op(const Run& R, const Op& op) {
                                   seed, l, H->cfg.attn_dropout_p, H->r * H->heads_l, H->nh, pin > 0);
     case F_PROJ:
       return launch_gemm(OASES_GEMM_NN, OASES_EPI_F32, Ms, h, hp, attn + r0 * hp, hp, W.wo, h, part_w(0), h,
-                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
+                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);
     case F_R1:
       return launch_bdr_ln(part_r(0), peer_k(0), (const float*)W.bo, xin + r0 * h,
                            wsp<float>(R, T_x1, l) + r0 * h, (const float*)W.ln2_g, (const float*)W.ln2_b, v2 + r0 * h,
@@ -546,12 +565,12 @@ static int run_op(const Run& R, const Op& op) {
     case F_FC1:
       if (H->llama)  // w1 = [gate | up] columns interleaved in blocks of 32; pre = both pre-activations, f = silu(gate)*up
         return launch_gemm(OASES_GEMM_NN, OASES_EPI_SWIGLU, Ms, fw, h, v2 + r0 * h, h, W.w1, fw, f + r0 * fp, fp, nullptr,
-                           pre + r0 * fw, fw, gws, H->gemm_ws_bytes, 0, s, pin, counters);
+                           pre + r0 * fw, fw, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);
       return launch_gemm(OASES_GEMM_NN, OASES_EPI_BIAS_GELU, Ms, fp, h, v2 + r0 * h, h, W.w1, fp, f + r0 * fp, fp,
-                         (const float*)W.b1, pre + r0 * fp, fp, gws, H->gemm_ws_bytes, 0, s, pin, counters);
+                         (const float*)W.b1, pre + r0 * fp, fp, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);
     case F_FC2:
       return launch_gemm(OASES_GEMM_NN, OASES_EPI_F32, Ms, h, fp, f + r0 * fp, fp, W.w2, h, part_w(1), h,
-                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
+                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);
     case F_R2: {
       const bool more = l + 1 < L;  // fuse the next layer's LN1 behind this layer's output
       return launch_bdr_ln(part_r(1), peer_k(1), (const float*)W.b2,
@@ -567,12 +586,12 @@ static int run_op(const Run& R, const Op& op) {
     case B_FC2_DGRAD:
       if (H->llama)
         return launch_gemm(OASES_GEMM_NT, OASES_EPI_DSWIGLU, Ms, fp, h, wsp<uint16_t>(R, T_dz2, l) + r0 * h, h, W.w2, h,
-                           wsp<uint16_t>(R, T_dg, l) + r0 * fw, fw, nullptr, pre + r0 * fw, fw, gws, H->gemm_ws_bytes, 0, s, pin, counters);
+                           wsp<uint16_t>(R, T_dg, l) + r0 * fw, fw, nullptr, pre + r0 * fw, fw, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);
       return launch_gemm(OASES_GEMM_NT, OASES_EPI_DGELU, Ms, fp, h, wsp<uint16_t>(R, T_dz2, l) + r0 * h, h, W.w2, h,
-                         wsp<uint16_t>(R, T_dg, l) + r0 * fp, fp, nullptr, pre + r0 * fp, fp, gws, H->gemm_ws_bytes, 0, s, pin, counters);
+                         wsp<uint16_t>(R, T_dg, l) + r0 * fp, fp, nullptr, pre + r0 * fp, fp, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);
     case B_FC1_DGRAD:
       return launch_gemm(OASES_GEMM_NT, OASES_EPI_F32, Ms, h, fw, wsp<uint16_t>(R, T_dg, l) + r0 * fw, fw, W.w1, fw,
-                         part_w(2), h, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
+                         part_w(2), h, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);
     case B_R3:
       { ColsumSink* cs = colsum(1); return colsum_done(launch_layernorm_bwd(part_r(2), peer_k(2), dyin + r0 * h,
                                   wsp<float>(R, T_x1, l) + r0 * h, wsp<float>(R, T_mu2, l) + r0, wsp<float>(R, T_rstd2, l) + r0,
@@ -581,25 +600,25 @@ static int run_op(const Run& R, const Op& op) {
                                   make_drop_cfg(seed, l, 0, p), (int64_t)r0, cs_scratch, s, rms, false, cs)); }
     case B_FC2_WGRAD:
       return launch_gemm(OASES_GEMM_TN, 0, fp, h, Ms, f + r0 * fp, fp, wsp<uint16_t>(R, T_dz2, l) + r0 * h, h, R.g[l].w2, h,
-                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, 0, counters);
+                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, 0, counters);
     case B_FC1_WGRAD:
       return launch_gemm(OASES_GEMM_TN, 0, h, fw, Ms, v2 + r0 * h, h, wsp<uint16_t>(R, T_dg, l) + r0 * fw, fw, R.g[l].w1, fw,
-                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, 0, counters);
+                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, 0, counters);
     case B_B1_SUM:
       { ColsumSink* cs = colsum(3); return colsum_done(launch_colsum_bf16(wsp<uint16_t>(R, T_dg, l) + r0 * fp, fp, Ms, fp, (float*)R.g[l].b1, cs_scratch, s, cs)); }
     case B_PROJ_DGRAD:
       return launch_gemm(OASES_GEMM_NT, OASES_EPI_BF16, Ms, hp, h, wsp<uint16_t>(R, T_dz1, l) + r0 * h, h, W.wo, h,
-                         wsp<uint16_t>(R, T_da, l) + r0 * hp, hp, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
+                         wsp<uint16_t>(R, T_da, l) + r0 * hp, hp, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);
     case B_PROJ_WGRAD:
       return launch_gemm(OASES_GEMM_TN, 0, hp, h, Ms, attn + r0 * hp, hp, wsp<uint16_t>(R, T_dz1, l) + r0 * h, h, R.g[l].wo, h,
-                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, 0, counters);
+                         nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, 0, counters);
     case B_ATTN:
       return launch_attention_bwd(qkv, attn, wsp<uint16_t>(R, T_da, l), wsp<float>(R, T_lse, l), wsp<float>(R, T_delta, l),
                                   wsp<uint16_t>(R, T_dqkv, l), H->b, H->s, H->heads_l, H->d, H->cfg.causal, (int)r0, Ms, s, seed, l,
                                   H->cfg.attn_dropout_p, H->r * H->heads_l, H->nh, pin > 0);
     case B_QKV_DGRAD:
       return launch_gemm(OASES_GEMM_NT, OASES_EPI_F32, Ms, h, 3 * hp, wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp, W.wqkv,
-                         3 * hp, part_w(3), h, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, pin, counters);
+                         3 * hp, part_w(3), h, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);
     case B_R4: {
       const bool more = l > 0;  // fuse the dropout backward of the layer below (its BDR2) behind dx
       { ColsumSink* cs = colsum(2); return colsum_done(launch_layernorm_bwd(part_r(3), peer_k(3),
@@ -611,7 +630,7 @@ static int run_op(const Run& R, const Op& op) {
     }
     case B_QKV_WGRAD:
       return launch_gemm(OASES_GEMM_TN, 0, h, 3 * hp, Ms, u + r0 * h, h, wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp,
-                         R.g[l].wqkv, 3 * hp, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, 0, s, 0, counters);
+                         R.g[l].wqkv, 3 * hp, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, 0, counters);
     case B_PQ_WGRAD:
       return launch_gemm_tn_pair(Ms, hp, h, attn + r0 * hp, hp, wsp<uint16_t>(R, T_dz1, l) + r0 * h, h, R.g[l].wo, h, h, 3 * hp, u + r0 * h, h,
                                  wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp, R.g[l].wqkv, 3 * hp, s);
@@ -817,6 +836,7 @@ int oases_create(const oases_layer_cfg* c, oases_handle** out) {
   build_forward(H, H->xn, H->xfwd);
   build_backward(H, H->xn, H->xbwd);
   group_weight_gradients(H, H->xbwd);
+  choose_gemms(H);
   for (auto* ops : {&H->xfwd, &H->xbwd})
     for (Op& op : *ops) op.wait = op.record = -1;
   *out = H;
