@@ -128,6 +128,7 @@ struct oases_handle {
   // arena of partial rows of the backward pass's column reductions, per layer: five slots (see ColsumSlot)
   size_t colsum_off, colsum_layer_bytes, colsum_slot_off[5];
   int variant[B_PQ_GROUP + 1] = {};  // by operator: the kernel of its GEMM as gemm_variant encodes it, chosen once (see choose_gemms); 0: chosen by the launch
+  int proj_delta = 0;  // kernel of PROJ_DGRAD that leaves the attention backward's delta behind (gemm_delta_variant), 0: it does not
   int ff_group = 0, pq_group = 0;  // kernel of a block's two weight gradients in one launch (gemm_tn_group_variant), 0: two launches
   int colsum_groups_sub, colsum_groups_all;  // row groups of a reduction over xMs rows / over all M rows
 };
@@ -367,6 +368,10 @@ static void choose_gemms(oases_handle* H) {
       {B_FC2_WGRAD, OASES_GEMM_TN, 0, fp, h, M}, {B_FC1_WGRAD, OASES_GEMM_TN, 0, h, fw, M}, {B_PROJ_WGRAD, OASES_GEMM_TN, 0, hp, h, M},
       {B_QKV_WGRAD, OASES_GEMM_TN, 0, h, 3 * hp, M}};
   for (const auto& e : list) H->variant[e.kind] = gemm_variant(e.op, e.epi, e.M, e.N, e.K, H->gemm_ws_bytes, true);
+  // delta comes with the product that makes dO where the attention backward would have a launch of its own for it
+  if (!(H->cfg.flags & OASES_FLAG_PROFILE) && H->xn == 1 &&
+      !attention_bwd_forms_delta(H->b, H->s, H->heads_l, H->d, H->cfg.causal, H->cfg.attn_dropout_p))
+    H->proj_delta = gemm_delta_variant(M, hp, h, H->d, H->gemm_ws_bytes);
 }
 
 static int check_ptrs(const void* const* p, int n, const char* who) {
@@ -607,6 +612,9 @@ static int run_op(const Run& R, const Op& op) {
     case B_B1_SUM:
       { ColsumSink* cs = colsum(3); return colsum_done(launch_colsum_bf16(wsp<uint16_t>(R, T_dg, l) + r0 * fp, fp, Ms, fp, (float*)R.g[l].b1, cs_scratch, s, cs)); }
     case B_PROJ_DGRAD:
+      if (H->proj_delta)
+        return launch_gemm_delta(H->proj_delta, Ms, hp, h, wsp<uint16_t>(R, T_dz1, l) + r0 * h, W.wo, wsp<uint16_t>(R, T_da, l) + r0 * hp,
+                                 attn + r0 * hp, wsp<float>(R, T_delta, l), H->s, H->d, (float*)gws, H->gemm_ws_bytes, counters, s);
       return launch_gemm(OASES_GEMM_NT, OASES_EPI_BF16, Ms, hp, h, wsp<uint16_t>(R, T_dz1, l) + r0 * h, h, W.wo, h,
                          wsp<uint16_t>(R, T_da, l) + r0 * hp, hp, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);
     case B_PROJ_WGRAD:
@@ -615,7 +623,7 @@ static int run_op(const Run& R, const Op& op) {
     case B_ATTN:
       return launch_attention_bwd(qkv, attn, wsp<uint16_t>(R, T_da, l), wsp<float>(R, T_lse, l), wsp<float>(R, T_delta, l),
                                   wsp<uint16_t>(R, T_dqkv, l), H->b, H->s, H->heads_l, H->d, H->cfg.causal, (int)r0, Ms, s, seed, l,
-                                  H->cfg.attn_dropout_p, H->r * H->heads_l, H->nh, pin > 0);
+                                  H->cfg.attn_dropout_p, H->r * H->heads_l, H->nh, pin > 0, H->proj_delta != 0);
     case B_QKV_DGRAD:
       return launch_gemm(OASES_GEMM_NT, OASES_EPI_F32, Ms, h, 3 * hp, wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp, W.wqkv,
                          3 * hp, part_w(3), h, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);

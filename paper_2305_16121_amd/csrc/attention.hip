@@ -1344,9 +1344,32 @@ int launch_attention_fwd(const void* qkv, void* out, float* lse, int batch, int 
   return 0;
 }
 
+// How the backward of a call is launched.
+struct BwdPlan {
+  bool one_launch;  // both passes together
+  int qg;           // 32-row groups of a workgroup that shares its tiles
+  bool own_delta;   // dQ covers every query that dK/dV reads, and forms delta on the way
+};
+static BwdPlan bwd_plan(const AttnArgs& a, int nseq, int batch, int head_dim, bool pin) {
+  BwdPlan p;
+  const int choice_blocks = (pin ? batch * ((a.seq + 31) / 32) : nseq * a.blocks) * a.heads;
+  // (dropout makes a tile several times the work: there the launch pays up to half as many; 256 blocks of 512-token sequences, D = 64,
+  // in one launch against two: 17.5 -> 18.4 us without dropout, 24.0 -> 19.6 with)
+  p.one_launch = choice_blocks <= (a.dthresh && head_dim == 64 ? 128 : 256);
+  p.qg = attn_query_groups(a, pin ? batch : nseq, pin ? a.seq : a.npos);
+  const bool wave_dq = head_dim == 128 && p.qg == 1;
+  p.own_delta = !p.one_launch && !wave_dq && a.npos == a.seq;
+  return p;
+}
+bool attention_bwd_forms_delta(int batch, int seq, int heads, int head_dim, int causal, float p_attn) {
+  AttnArgs a{};
+  const int nseq = fill_args(a, batch, seq, heads, head_dim, causal, 0, batch * seq, "attention_bwd");
+  return nseq > 0 && fill_dropout(a, 0, 0, p_attn, 0, heads, heads, "attention_bwd") && bwd_plan(a, nseq, batch, head_dim, false).own_delta;
+}
+
 int launch_attention_bwd(const void* qkv, const void* out, const void* dout, const float* lse, float* delta, void* dqkv,
                          int batch, int seq, int heads, int head_dim, int causal, int row0, int rows, hipStream_t s, uint64_t seed,
-                         int layer, float p_attn, int head0, int heads_total, bool pin) {
+                         int layer, float p_attn, int head0, int heads_total, bool pin, bool delta_ready) {
   if (!qkv || !out || !dout || !lse || !delta || !dqkv) { set_error("attention_bwd: NULL argument"); return OASES_ENULL; }
   if (!aligned16(qkv) || !aligned16(out) || !aligned16(dout) || !aligned16(dqkv)) {
     set_error("attention_bwd: pointer not 16-byte aligned");
@@ -1371,14 +1394,10 @@ int launch_attention_bwd(const void* qkv, const void* out, const void* dout, con
   if (!fill_dropout(a, seed, layer, p_attn, head0, heads_total, heads, "attention_bwd")) return OASES_EINVAL;
   dim3 dgrid((unsigned)((pairs + NT - 1) / NT)), block(NT);
   const int n_blocks = nseq * a.blocks * heads;  // of 32 rows
-  // (dropout makes a tile several times the work: there the launch pays up to half as many; 256 blocks of 512-token sequences, D = 64,
-  // in one launch against two: 17.5 -> 18.4 us without dropout, 24.0 -> 19.6 with)
-  const int choice_blocks = pin ? batch * ((seq + 31) / 32) * heads : n_blocks;
-  const bool one_launch = choice_blocks <= (a.dthresh && head_dim == 64 ? 128 : 256);
-  const int qg = attn_query_groups(a, pin ? batch : nseq, pin ? seq : a.npos);
-  const bool wave_dq = head_dim == 128 && qg == 1;
-  const bool own_delta = !one_launch && !wave_dq && a.npos == seq;  // dQ covers every query that dK/dV reads, and forms delta on the way
-  if (!own_delta) {
+  const BwdPlan plan = bwd_plan(a, nseq, batch, head_dim, pin);
+  const bool one_launch = plan.one_launch, own_delta = plan.own_delta;
+  const int qg = plan.qg;
+  if (!own_delta && !delta_ready) {
     if (head_dim == 64) hipLaunchKernelGGL((attn_delta_kernel<64>), dgrid, block, 0, s, a, first_row, n_rows);
     else hipLaunchKernelGGL((attn_delta_kernel<128>), dgrid, block, 0, s, a, first_row, n_rows);
     OASES_LAUNCH_CHECK("attn_delta_kernel");

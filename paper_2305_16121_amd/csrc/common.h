@@ -192,10 +192,17 @@ constexpr size_t kSplitKWorkspaceBytes = 256u << 20;
 int launch_attention_fwd(const void* qkv, void* out, float* lse, int batch, int seq, int heads, int head_dim,
                          int causal, int row0, int rows, hipStream_t s, uint64_t seed = 0, int layer = 0, float p_attn = 0.f,
                          int head0 = 0, int heads_total = 0, bool pin = false);
+// C (bf16) = A[M,K] B[N,K]^T as launch_gemm makes it with that variant, and with it the delta of the attention backward, the row sums of C * out per
+// head ([M / seq, N / head_dim, seq]), in which a launch and a pass over both arrays are saved.  All arrays are dense.
+int gemm_delta_variant(int M, int N, int K, int head_dim, size_t ws_bytes);
+int launch_gemm_delta(int variant, int M, int N, int K, const void* A, const void* B, void* C, const void* out, float* delta, int seq, int head_dim,
+                      float* ws, size_t ws_bytes, uint32_t* counters, hipStream_t s);
+// whether the attention backward over whole sequences forms delta by itself (no need of delta_ready)
+bool attention_bwd_forms_delta(int batch, int seq, int heads, int head_dim, int causal, float p_attn);
 int launch_attention_bwd(const void* qkv, const void* out, const void* dout, const float* lse, float* delta,
                          void* dqkv, int batch, int seq, int heads, int head_dim, int causal, int row0,
                          int rows, hipStream_t s, uint64_t seed = 0, int layer = 0, float p_attn = 0.f, int head0 = 0,
-                         int heads_total = 0, bool pin = false);
+                         int heads_total = 0, bool pin = false, bool delta_ready = false);
 
 constexpr int kColPartials = 1024;  // row-groups of the two-stage column reductions
 

@@ -41,6 +41,8 @@ struct GemmArgs {
   float* part;         // slices that the launch adds up itself (SliceSum): partial sums, and a counter per tile
   uint32_t* counters;  // nullptr: slices write planes that a second launch adds up
   float* colsum;       // weight gradients of a group: [N], += the column sums of B (a bias gradient); or nullptr
+  float* delta;        // EPI_BF16_DELTA: [M / seq, heads, seq], the row sums of C * aux over the head_dim columns of a head
+  int seq, heads, head_dim;
 };
 
 // one launcher per contraction form, each defined in its own part
@@ -129,7 +131,8 @@ __device__ __forceinline__ bf16x8 read_frag(const char* lds, int r0, int kk, int
   }
 }
 
-enum { EPI_F32 = 0, EPI_BF16 = 1, EPI_BIAS_BF16 = 2, EPI_BIAS_GELU = 3, EPI_DGELU = 4, EPI_ACC_F32 = 5, EPI_SWIGLU = 6, EPI_DSWIGLU = 7 };
+enum { EPI_F32 = 0, EPI_BF16 = 1, EPI_BIAS_BF16 = 2, EPI_BIAS_GELU = 3, EPI_DGELU = 4, EPI_ACC_F32 = 5, EPI_SWIGLU = 6, EPI_DSWIGLU = 7,
+       EPI_BF16_DELTA = 8 };  // EPI_BF16, and delta (small-tile kernels of the NT form: launch_gemm_delta)
 
 // silu(z) = z * sigmoid(z) and its derivative, on the fast exp2 / rcp units
 __device__ __forceinline__ float fast_sigmoid(float z) { return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z)); }
@@ -150,7 +153,7 @@ __device__ __forceinline__ EpiOperands epi_load(const GemmArgs& g, int row, int 
   EpiOperands o;
   if constexpr (EPI == EPI_BIAS_BF16 || EPI == EPI_BIAS_GELU) o.f = *reinterpret_cast<const f32x4*>(g.bias + col);
   if constexpr (EPI == EPI_ACC_F32) o.f = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.C) + (size_t)row * g.ldc + col);
-  if constexpr (EPI == EPI_DGELU) o.a = *reinterpret_cast<const u32x2*>(g.aux + (size_t)row * g.ldaux + col);
+  if constexpr (EPI == EPI_DGELU || EPI == EPI_BF16_DELTA) o.a = *reinterpret_cast<const u32x2*>(g.aux + (size_t)row * g.ldaux + col);
   if constexpr (EPI == EPI_DSWIGLU) {
     // gate and up pre-activations of 32 columns sit in blocks side by side in aux ([gate 32 | up 32] per block)
     const uint16_t* p = g.aux + (size_t)row * g.ldaux + (size_t)col + (col & ~31);
@@ -1567,6 +1570,9 @@ __device__ __forceinline__ float frag_sum(const u32x4& f) {
   for (int i = 0; i < 4; i++) s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_, (uint32_t)f[i]), one, s, false);
   return s;
 }
+// EPI_BF16_DELTA (dO = dZ1 Wo^T): the tile holds whole heads of dO, so the row sums of dO * O come from the registers that store it, for one
+// more operand of the epilogue; the launch that read both arrays again is saved (a step of two recomputed layers, h 1024, 512 tokens:
+// 544.7 -> 538.2 us; three layers of h 1024, 600 tokens, 128 columns a head: 534.9 -> 533.0, on 64x128 instead of 64x64 tiles).
 // COLSUM (weight gradients): the waves of the first row of tiles that hold the first 32 rows also add up B's columns, whose fragments they
 // have in registers (eight k of a column to a lane): the vector ALU has time, LDS is what the kernel waits for.  Eight tiles to a partial sum.
 template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI, bool COLSUM = false>
@@ -1752,6 +1758,9 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, c
     static_assert(StLds<TM, TN, NS>::kExchange < StLds<TM, TN, NS>::bytes, "four bytes behind the exchange");
     if (!sum_slices<TM * TN * 2>(ss, v, lds + StLds<TM, TN, NS>::kExchange)) return;
   }
+  float dsum[TM];  // EPI_BF16_DELTA: this lane's part of a row's sum over the wave's columns, which belong to one head
+#pragma unroll
+  for (int i = 0; i < TM; i++) dsum[i] = 0.f;
   auto finish = [&](auto full_c) {
     constexpr bool FULL = decltype(full_c)::value;
 #pragma unroll
@@ -1774,6 +1783,19 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, c
           if (!FULL && row >= g.M) continue;
           if constexpr (EPI == EPI_SWIGLU) {
             if (FULL || col0 + c < g.N) epi_swiglu(g, row, col0 + c, col0 / 2 + c, v[i * TN * 2 + q], v[(i * TN + 1) * 2 + q]);
+          } else if constexpr (EPI == EPI_BF16_DELTA) {
+#pragma unroll
+            for (int j = 0; j < TN; j++) {
+              if (!FULL && col0 + 32 * j + c >= g.N) continue;
+              const f32x4& x = v[(i * TN + j) * 2 + q];
+              const u32x2 o = pre[i][j][q].a, r = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])};
+              *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + (size_t)row * g.ldc + col0 + 32 * j + c) = r;
+#pragma unroll
+              for (int k = 0; k < 2; k++) {
+                dsum[i] += bf16_bits_to_f32(r[k] & 0xffffu) * bf16_bits_to_f32(o[k] & 0xffffu);
+                dsum[i] += bf16_bits_to_f32(r[k] >> 16) * bf16_bits_to_f32(o[k] >> 16);
+              }
+            }
           } else {
 #pragma unroll
             for (int j = 0; j < TN; j++)
@@ -1784,6 +1806,24 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, c
   };
   const bool full = m0 + BM <= g.M && n0 + BN <= g.N;
   if (full) finish(std::true_type{}); else finish(std::false_type{});
+  if constexpr (EPI == EPI_BF16_DELTA) {  // the four waves of a row (two k halves, two column parts) put their sums together in LDS
+    constexpr int at = StLds<TM, TN, NS>::kExchange + 1024;
+    static_assert(at + BM * 16 <= StLds<TM, TN, NS>::bytes, "row sums behind the exchange");
+    float* red = reinterpret_cast<float*>(lds + at);
+#pragma unroll
+    for (int i = 0; i < TM; i++) {
+      dsum[i] += __shfl_xor(dsum[i], 32, 64);
+      if (lane < 32) red[4 * (wm * 32 * TM + 32 * i + lane) + 2 * wn + wk] = dsum[i];
+    }
+    __syncthreads();
+    const int r = tid % BM, part = tid / BM;  // a head is 64 columns (one column part of a 128-wide tile) or all columns of the tile
+    const bool one = g.head_dim == BN;
+    const int row = m0 + r, head = n0 / g.head_dim + part;
+    if (part < (one ? 1 : 2) && row < g.M && head < g.heads) {
+      const float* p = red + 4 * r + 2 * part;
+      g.delta[((size_t)(row / g.seq) * g.heads + head) * g.seq + row % g.seq] = one ? (p[0] + p[1]) + (p[2] + p[3]) : p[0] + p[1];
+    }
+  }
 }
 
 template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI>
@@ -1867,8 +1907,8 @@ int launch_small(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
     OASES_LAUNCH_CHECK("gemm_st_kernel");
     return 0;
   }
-  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_DSWIGLU) {
-    set_error("gemm: the SwiGLU epilogues do not run over k slices");
+  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_DSWIGLU || EPI == EPI_BF16_DELTA) {
+    set_error("gemm: an epilogue that pairs columns does not run over k slices of two launches");
     return OASES_EINVAL;
   } else {
     if (!ws) { set_error("gemm: split-K chosen without a workspace"); return OASES_ENULL; }
@@ -1968,7 +2008,7 @@ double pp_seconds(int bm, long wgs, int k_per, double out_bytes) {
 // number of slices (0.6 us a stage).  Measured, us, the choice without -> with: inside a step 128 x 4608 x 12288 NN 52 -> 48
 // (register-staged kernel over eight slices -> 128x128 over six), NT 128 x 6144 x 12288 78 -> 75; 512 x 8192 x 3072 NT 47 -> 36, 8192 x 512 x
 // 2048 NT 31 -> 26, 200 x 3072 x 8192 36 -> 27; 1488 x 3072 x 3072 NN stays on 144 tiles of 128x256 (40; 64x128 over two slices 72).
-TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, double* seconds = nullptr, bool own_sum = false) {
+TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, double* seconds = nullptr, bool own_sum = false, int bn_min = 0) {
   const TileChoice large = pick_large_tile(kind, epi, M, N, K, ws_bytes);
   const KindTable& kt = g_kinds[kind];
   const double out = (double)M * N * (epi == EPI_F32 ? 4.0 : kind == 2 ? 8.0 : epi == EPI_SWIGLU ? 3.0 : epi == EPI_DSWIGLU ? 8.0 : epi == EPI_BIAS_GELU || epi == EPI_DGELU ? 4.0 : 2.0);
@@ -1985,11 +2025,12 @@ TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, do
                   out / 3.1e12 + slices(large.ksplit, 128, 256, false);
   if (large.pp) best_t *= 0.9; else best_t += 2.0e-6;
   if (own_sum && large.pp) best_t = pp_seconds(large.bm, wgs, K / large.ksplit, out) + slices(large.ksplit, 128, 256, true);
+  if (bn_min) best_t = 1e30;  // the small-tile kernels alone
   TileChoice best = large;
   // weights that no cache keeps are read once per row of tiles: not on 64-row tiles when there are more rows (128 x 6144 x 12288 NN over
   // eight slices 59, NT 80, against 52 and 75 on 128 rows; a plain reduction over the 151 MB takes 47)
   const bool streams = own_sum && kind != 2 && M > 64 && 2.0 * N * K > 64.0e6;
-  for (int bn = epi == EPI_SWIGLU ? 128 : 64; bn <= 128; bn += 64)
+  for (int bn = epi == EPI_SWIGLU || bn_min == 128 ? 128 : 64; bn <= 128; bn += 64)
     for (int S = 1; S <= 16; S *= 2) {
       const int k_per = st_k_per(K, S);
       if (S > 1 && ((size_t)S * M * N * 4 > ws_bytes || k_per < 2 * BKS || (long)(S - 1) * k_per >= K)) break;
@@ -2232,6 +2273,35 @@ int launch_gemm_nt(const GemmArgs& g, int epi, float* ws, size_t ws_bytes, int f
   }
 }
 #endif
+#if OASES_GEMM_HAS(1)
+// The small-tile kernel for launch_gemm_delta, whose tiles hold whole heads, or 0 where it is expected to take more than 3 us longer than the
+// kernel that the product alone would get: attn_delta_kernel, which is saved, takes 3.5 us and the launch gap ahead of it 1 to 2.
+int gemm_delta_variant(int M, int N, int K, int head_dim, size_t ws_bytes) {
+  double alone, t;
+  pick_tile(1, EPI_BF16, M, N, K, ws_bytes, &alone, true);
+  const TileChoice c = pick_tile(1, EPI_BF16, M, N, K, ws_bytes, &t, true, head_dim);
+  return c.st && t < alone + 3.0e-6 ? encode_variant(c) : 0;
+}
+int launch_gemm_delta(int variant, int M, int N, int K, const void* A, const void* B, void* C, const void* out, float* delta, int seq, int head_dim,
+                      float* ws, size_t ws_bytes, uint32_t* counters, hipStream_t s) {
+  TileChoice t;
+  if (!A || !B || !C || !out || !delta || !ws || !counters) { set_error("gemm_delta: NULL argument"); return OASES_ENULL; }
+  if (head_dim <= 0 || seq <= 0 || M % 8 || K % 8 || N % head_dim || M % seq || variant < 400000000 ||
+      (variant % 1000 != head_dim && variant % 1000 != 2 * head_dim) || !decode_variant(variant, 1, M, N, K, ws_bytes, &t) || !gemm_span_fits(M, K) || !gemm_span_fits(N, K)) {
+    set_error("gemm_delta: variant %d does not fit M=%d N=%d K=%d seq=%d head_dim=%d", variant, M, N, K, seq, head_dim);
+    return OASES_EINVAL;
+  }
+  GemmArgs g{(const uint16_t*)A, (const uint16_t*)B, C, nullptr, (uint16_t*)const_cast<void*>(out), M, N, K, K, K, N, N, 0, 0, 1, K};
+  g.counters = counters;
+  g.delta = delta;
+  g.seq = seq;
+  g.heads = N / head_dim;
+  g.head_dim = head_dim;
+  if (t.bm == 128) return launch_small<2, 2, 4, true, true, EPI_BF16_DELTA>(g, t.ksplit, ws, s);
+  if (t.bn == 128) return launch_small<1, 2, 3, true, true, EPI_BF16_DELTA>(g, t.ksplit, ws, s);
+  return launch_small<1, 1, 5, true, true, EPI_BF16_DELTA>(g, t.ksplit, ws, s);
+}
+#endif  // NT part
 #if OASES_GEMM_HAS(2)
 int launch_gemm_tn(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_variant, hipStream_t s) {
   return launch_shape<false, false, EPI_ACC_F32>(g, ws, ws_bytes, forced_variant, 0, s);
