@@ -129,6 +129,7 @@ struct oases_handle {
   size_t colsum_off, colsum_layer_bytes, colsum_slot_off[5];
   int variant[B_PQ_GROUP + 1] = {};  // by operator: the kernel of its GEMM as gemm_variant encodes it, chosen once (see choose_gemms); 0: chosen by the launch
   int proj_delta = 0;  // kernel of PROJ_DGRAD that leaves the attention backward's delta behind (gemm_delta_variant), 0: it does not
+  bool attn_rope = false;  // the attention backward turns dQ and dK back itself
   int ff_group = 0, pq_group = 0;  // kernel of a block's two weight gradients in one launch (gemm_tn_group_variant), 0: two launches
   int colsum_groups_sub, colsum_groups_all;  // row groups of a reduction over xMs rows / over all M rows
 };
@@ -372,6 +373,10 @@ static void choose_gemms(oases_handle* H) {
   if (!(H->cfg.flags & OASES_FLAG_PROFILE) && H->xn == 1 &&
       !attention_bwd_forms_delta(H->b, H->s, H->heads_l, H->d, H->cfg.causal, H->cfg.attn_dropout_p))
     H->proj_delta = gemm_delta_variant(M, hp, h, H->d, H->gemm_ws_bytes);
+  H->attn_rope = H->llama && !(H->cfg.flags & OASES_FLAG_PROFILE) && H->xn == 1 &&
+                 attention_bwd_turns_back(H->b, H->s, H->heads_l, H->d, H->cfg.causal, H->cfg.attn_dropout_p);
+  if (H->attn_rope)
+    H->xbwd.erase(std::remove_if(H->xbwd.begin(), H->xbwd.end(), [](const Op& op) { return op.kind == B_ROPE; }), H->xbwd.end());
 }
 
 static int check_ptrs(const void* const* p, int n, const char* who) {
@@ -623,7 +628,8 @@ static int run_op(const Run& R, const Op& op) {
     case B_ATTN:
       return launch_attention_bwd(qkv, attn, wsp<uint16_t>(R, T_da, l), wsp<float>(R, T_lse, l), wsp<float>(R, T_delta, l),
                                   wsp<uint16_t>(R, T_dqkv, l), H->b, H->s, H->heads_l, H->d, H->cfg.causal, (int)r0, Ms, s, seed, l,
-                                  H->cfg.attn_dropout_p, H->r * H->heads_l, H->nh, pin > 0, H->proj_delta != 0);
+                                  H->cfg.attn_dropout_p, H->r * H->heads_l, H->nh, pin > 0, H->proj_delta != 0,
+                                  H->attn_rope ? wsp<float>(R, T_rope, 0) : nullptr);
     case B_QKV_DGRAD:
       return launch_gemm(OASES_GEMM_NT, OASES_EPI_F32, Ms, h, 3 * hp, wsp<uint16_t>(R, T_dqkv, l) + r0 * 3 * hp, 3 * hp, W.wqkv,
                          3 * hp, part_w(3), h, nullptr, nullptr, 0, gws, H->gemm_ws_bytes, H->variant[op.kind], s, pin, counters);

@@ -3,8 +3,8 @@
 // Work decomposition.  A workgroup owns one or two groups of 32 rows of one (sequence, head): queries (forward, dQ) or keys
 // (dK/dV); its four waves are (row group) x (part of the reduction range).  The workgroup stages the tiles of the reduction
 // range -- keys a query block sees, or queries that see a key block -- for all its waves, and the partial results of a
-// row group meet once, through LDS, at the end.  Few blocks, and dK/dV with 128 columns, keep a form in which each wave stages
-// tiles of its own (see below).
+// row group meet once, through LDS, at the end.  Calls with few blocks keep a form in which each wave
+// stages tiles of its own (see below).
 //
 // Forward and dQ compute the TRANSPOSED score tile S^T = K*Q^T with v_mfma_f32_32x32x16_bf16, so that a lane owns
 // one query (accumulator column l%32) and 16 keys of the tile: the online softmax is lane-local except for one
@@ -47,6 +47,7 @@ struct AttnArgs {
   uint32_t dk0, dk1, dc3, dthresh;
   float dscale;
   int head0, heads_total;
+  const float2* rope;  // backward over blocks of 32 rows: (cos, sin) [seq, D / 2], dQ and dK are stored turned back by them; or nullptr
 };
 
 // Dropout mask of the probabilities: the 4 x 4 block (q div 4, k div 4) of (sequence b, global head) draws one
@@ -158,8 +159,17 @@ __device__ __forceinline__ void load_row_frags(bf16x8* f, const uint16_t* __rest
   }
 }
 
-// sum of the four waves' partial accumulators through LDS: wave w ends up with elements [w*E/4, (w+1)*E/4) of the
-// flattened (tile, element) index, summed over the four partials with the weights sc[0..3]
+// the inverse rotation of columns d and d + D/2
+__device__ __forceinline__ void turn_back(float& x1, float& x2, const float2& t) {
+  const float cs = t.x, sn = -t.y, a = x1, b = x2;
+  x1 = a * cs - b * sn;
+  x2 = b * cs + a * sn;
+}
+
+// sum of the four waves' partial accumulators through LDS: wave w ends up with elements [w*E/8, (w+1)*E/8) of each half of the flattened
+// (tile, element) index -- columns d and d + D/2, which a rotation takes together -- summed over the four partials with the weights sc[0..3]
+template <int E>
+__device__ __forceinline__ int part_element(int wave, int k) { return wave * (E / 8) + k % (E / 8) + (k >= E / 8 ? E / 2 : 0); }
 template <int E>
 __device__ __forceinline__ void combine4(const f32x16* acc, float* lds_part, int wave, int lane, const float* sc, float* out) {
   __syncthreads();  // every wave is done with its tiles: the staging area is free
@@ -168,7 +178,7 @@ __device__ __forceinline__ void combine4(const f32x16* acc, float* lds_part, int
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < E / 4; k++) {
-    const int e = wave * (E / 4) + k;
+    const int e = part_element<E>(wave, k);
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; w++) v += lds_part[(w * E + e) * 64 + lane] * sc[w];
@@ -979,7 +989,9 @@ __global__ __launch_bounds__(NT, 1) void attn_dkv128_kernel(AttnArgs a) {
 // a query block sees, or the 32-row query tiles that see a key block -- round-robin, each staging its own tiles in a private
 // slice of LDS, so the loops need no barrier; the four partial results meet once, through LDS, at the end.  Rows are padded
 // instead of swizzled.  This form stays where the shared tiles above do not pay: calls with few blocks, whose time is the
-// chain of the longest one (a quarter of it per wave here).
+// chain of the longest one (a quarter of it per wave here).  With rotary embeddings dQ and dK can leave it as gradients of what was
+// rotated -- the values that a launch over dqkv would read, rounded like them -- which saves that launch and its gap: two
+// recomputed layers of h 1024, 512 tokens, 538 -> 534 us a step.
 // =================================================================================================
 template <int D>
 struct WaveLds {  // LDS of a backward workgroup: the larger of the two passes' staging areas and of the partial-sum exchange
@@ -1078,11 +1090,25 @@ __device__ __forceinline__ void wave_dq_block(const AttnArgs& a, int wg, char* l
   if (qok) {
     uint16_t* op = a.dqkv + (rowbase + qpos) * a.ld + head * D;
 #pragma unroll
-    for (int k = 0; k < E / 4; k += 4) {
-      const int e = wave * (E / 4) + k, dt = e / 16, i = e % 16;
+    for (int k = 0; k < E / 8; k += 4) {
+      const int e = part_element<E>(wave, k), dt = e / 16, i = e % 16;
       const int d = dt * 32 + 8 * (i >> 2) + 4 * g;
+      const float* hi = res + E / 8 + k;
       u32x2 v = {pack_bf16x2(res[k] * a.scale, res[k + 1] * a.scale), pack_bf16x2(res[k + 2] * a.scale, res[k + 3] * a.scale)};
+      u32x2 w = {pack_bf16x2(hi[0] * a.scale, hi[1] * a.scale), pack_bf16x2(hi[2] * a.scale, hi[3] * a.scale)};
+      if (a.rope) {
+        float lo_[4], hi_[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+          lo_[j] = bf16_bits_to_f32((j & 1) ? v[j >> 1] >> 16 : v[j >> 1] & 0xffffu);
+          hi_[j] = bf16_bits_to_f32((j & 1) ? w[j >> 1] >> 16 : w[j >> 1] & 0xffffu);
+          turn_back(lo_[j], hi_[j], a.rope[(size_t)qpos * (D / 2) + d + j]);
+        }
+        v = u32x2{pack_bf16x2(lo_[0], lo_[1]), pack_bf16x2(lo_[2], lo_[3])};
+        w = u32x2{pack_bf16x2(hi_[0], hi_[1]), pack_bf16x2(hi_[2], hi_[3])};
+      }
       *reinterpret_cast<u32x2*>(op + d) = v;
+      *reinterpret_cast<u32x2*>(op + d + D / 2) = w;
     }
   }
 }
@@ -1196,13 +1222,22 @@ __device__ __forceinline__ void wave_dkv_block(const AttnArgs& a, int wg, char* 
   uint16_t* dKp = a.dqkv + rowbase * a.ld + a.hp + head * D;
   uint16_t* dVp = dKp + a.hp;
 #pragma unroll
-  for (int k = 0; k < E / 4; k++) {
-    const int e = wave * (E / 4) + k, dt = e / 16, i = e % 16;
-    const int kp = k_begin + 8 * (i >> 2) + 4 * g + (i & 3);
+  for (int k = 0; k < E / 8; k++) {
+    const int e = part_element<E>(wave, k), dt = e / 16, i = e % 16, k2 = E / 8 + k;
+    const int kp = k_begin + 8 * (i >> 2) + 4 * g + (i & 3), d = dt * 32 + (lane & 31);
     if (kp < k_end && kp >= a.first) {
-      size_t o = (size_t)kp * a.ld + dt * 32 + (lane & 31);
-      dKp[o] = (uint16_t)f32_to_bf16_bits(rk_[k] * a.scale);
+      const size_t o = (size_t)kp * a.ld + d;
+      uint16_t lo = (uint16_t)f32_to_bf16_bits(rk_[k] * a.scale), hi = (uint16_t)f32_to_bf16_bits(rk_[k2] * a.scale);
+      if (a.rope) {
+        float x1 = bf16_bits_to_f32(lo), x2 = bf16_bits_to_f32(hi);
+        turn_back(x1, x2, a.rope[(size_t)kp * (D / 2) + d]);
+        lo = (uint16_t)f32_to_bf16_bits(x1);
+        hi = (uint16_t)f32_to_bf16_bits(x2);
+      }
+      dKp[o] = lo;
+      dKp[o + D / 2] = hi;
       dVp[o] = (uint16_t)f32_to_bf16_bits(rv_[k]);
+      dVp[o + D / 2] = (uint16_t)f32_to_bf16_bits(rv_[k2]);
     }
   }
 }
@@ -1361,6 +1396,11 @@ static BwdPlan bwd_plan(const AttnArgs& a, int nseq, int batch, int head_dim, bo
   p.own_delta = !p.one_launch && !wave_dq && a.npos == a.seq;
   return p;
 }
+bool attention_bwd_turns_back(int batch, int seq, int heads, int head_dim, int causal, float p_attn) {
+  AttnArgs a{};
+  const int nseq = fill_args(a, batch, seq, heads, head_dim, causal, 0, batch * seq, "attention_bwd");
+  return nseq > 0 && fill_dropout(a, 0, 0, p_attn, 0, heads, heads, "attention_bwd") && bwd_plan(a, nseq, batch, head_dim, false).one_launch;
+}
 bool attention_bwd_forms_delta(int batch, int seq, int heads, int head_dim, int causal, float p_attn) {
   AttnArgs a{};
   const int nseq = fill_args(a, batch, seq, heads, head_dim, causal, 0, batch * seq, "attention_bwd");
@@ -1369,7 +1409,8 @@ bool attention_bwd_forms_delta(int batch, int seq, int heads, int head_dim, int 
 
 int launch_attention_bwd(const void* qkv, const void* out, const void* dout, const float* lse, float* delta, void* dqkv,
                          int batch, int seq, int heads, int head_dim, int causal, int row0, int rows, hipStream_t s, uint64_t seed,
-                         int layer, float p_attn, int head0, int heads_total, bool pin, bool delta_ready) {
+                         int layer, float p_attn, int head0, int heads_total, bool pin, bool delta_ready,
+                         const float* rope) {
   if (!qkv || !out || !dout || !lse || !delta || !dqkv) { set_error("attention_bwd: NULL argument"); return OASES_ENULL; }
   if (!aligned16(qkv) || !aligned16(out) || !aligned16(dout) || !aligned16(dqkv)) {
     set_error("attention_bwd: pointer not 16-byte aligned");
@@ -1395,6 +1436,8 @@ int launch_attention_bwd(const void* qkv, const void* out, const void* dout, con
   dim3 dgrid((unsigned)((pairs + NT - 1) / NT)), block(NT);
   const int n_blocks = nseq * a.blocks * heads;  // of 32 rows
   const BwdPlan plan = bwd_plan(a, nseq, batch, head_dim, pin);
+  if (rope && !plan.one_launch) { set_error("attention_bwd: dQ and dK are turned back by the kernel of both passes only"); return OASES_EINVAL; }
+  a.rope = reinterpret_cast<const float2*>(rope);
   const bool one_launch = plan.one_launch, own_delta = plan.own_delta;
   const int qg = plan.qg;
   if (!own_delta && !delta_ready) {

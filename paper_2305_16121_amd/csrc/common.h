@@ -199,10 +199,12 @@ int launch_gemm_delta(int variant, int M, int N, int K, const void* A, const voi
                       float* ws, size_t ws_bytes, uint32_t* counters, hipStream_t s);
 // whether the attention backward over whole sequences forms delta by itself (no need of delta_ready)
 bool attention_bwd_forms_delta(int batch, int seq, int heads, int head_dim, int causal, float p_attn);
+// whether it can store dQ and dK turned back by the rotary embedding (rope: the table of launch_rope_table): calls of one launch
+bool attention_bwd_turns_back(int batch, int seq, int heads, int head_dim, int causal, float p_attn);
 int launch_attention_bwd(const void* qkv, const void* out, const void* dout, const float* lse, float* delta,
                          void* dqkv, int batch, int seq, int heads, int head_dim, int causal, int row0,
                          int rows, hipStream_t s, uint64_t seed = 0, int layer = 0, float p_attn = 0.f, int head0 = 0,
-                         int heads_total = 0, bool pin = false, bool delta_ready = false);
+                         int heads_total = 0, bool pin = false, bool delta_ready = false, const float* rope = nullptr);
 
 constexpr int kColPartials = 1024;  // row-groups of the two-stage column reductions
 

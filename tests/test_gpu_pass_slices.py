@@ -108,3 +108,41 @@ def test_delta_that_comes_with_the_gradient_of_the_attention_output(h, d, seq, b
     bound = d * 2.0 ** -24 * products.abs().sum(dim=3).transpose(1, 2)  # d roundings at most of partial sums below the sum of the magnitudes
     assert bool((err <= bound + 1e-30).all()), float((err / (bound + 1e-30)).max())
     H.close()
+
+
+@pytest.mark.parametrize("d,seq,batch,p", [(64, 8, 1, 0.0), (64, 200, 2, 0.0), (64, 136, 1, 0.25), (128, 72, 3, 0.0), (128, 264, 1, 0.25)])
+def test_gradients_turned_back_by_the_attention_backward(d, seq, batch, p):
+    """A pass of few attention blocks stores dQ and dK turned back by the rotary embedding, with delta from the product that makes dO: against the
+    attention backward and the inverse rotation as operators on the arrays that the pass leaves."""
+    from paper_2305_16121_amd import binding as B
+    h, heads, M = 8 * d, 8, seq * batch
+    H = B.Handle(B.make_cfg(dict(arch="llama", hidden=h, n_heads=heads, ffn_hidden=2 * h, seq=seq, batch=batch, tp=1, n_sub=1, n_layers=1, causal=1,
+                                 dropout_p=0.0, attn_dropout_p=p, rope_theta=10000.0), seed=7))
+    g = torch.Generator(device="cuda").manual_seed(M + d)
+    n = lambda *s: torch.randn(s, generator=g, device="cuda")
+    W = {k: (n(*s) / h ** 0.5).bfloat16() for k, s in dict(wqkv=(h, 3 * h), wo=(h, h), w1=(h, 4 * h), w2=(2 * h, h)).items()}
+    W.update(ln1_g=n(h), ln2_g=n(h))
+    G = {k: torch.zeros(v.shape, device="cuda") for k, v in W.items()}
+    x, y, dx = n(M, h), torch.empty(M, h, device="cuda"), torch.empty(M, h, device="cuda")
+    ws = torch.full((H.workspace_bytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    H.forward([W], x, y, ws)
+    H.backward([W], x, n(M, h), dx, [G], ws)
+    torch.cuda.synchronize()
+
+    def at(name):
+        off, nb = H.tensor_span(name, 0)
+        return ws[off:off + nb]
+    tab, delta = torch.empty(seq, d, device="cuda"), torch.empty(M * heads, device="cuda")
+    ref = torch.empty(M, 3 * h, dtype=torch.bfloat16, device="cuda")
+    B.check(B.lib.oases_op_rope_table(tab.data_ptr(), seq, d, 10000.0, None))
+    B.check(B.lib.oases_op_attention_dropout_bwd(at("qkv").data_ptr(), at("attn").data_ptr(), at("da").data_ptr(), at("lse").data_ptr(), delta.data_ptr(),
+                                                 ref.data_ptr(), batch, seq, heads, d, 1, 0, M, 7, 0, p, 0, heads, None))
+    B.check(B.lib.oases_op_rope(ref.data_ptr(), 3 * h, M, 0, seq, heads, d, tab.data_ptr(), 1, None))
+    torch.cuda.synchronize()
+    got, ref = (t.view(torch.bfloat16).view(M, 3, heads, 2, d // 2).double() for t in (at("dqkv"), ref))
+    # delta's sums run in another order: a value to be rotated may round to the neighbouring bf16, 2^-7 of it at most, which the rotation mixes into
+    # both of a pair (at most sqrt 2 of the pair's length), and the result too; near zero, d + seq roundings of fp32 sums
+    pair = (ref ** 2).sum(dim=3, keepdim=True).sqrt()
+    bound = 2.0 ** -7 * (1.5 * pair + ref.abs()) + (d + seq) * 2.0 ** -24 * ref.abs().max() * 8
+    assert bool(((got - ref).abs() <= bound).all()), float(((got - ref).abs() / bound).max())
+    H.close()
