@@ -85,8 +85,8 @@ __global__ __launch_bounds__(T) void bdr_ln_kernel(const float* __restrict__ par
                                                     uint32_t* __restrict__ counters) {
   __shared__ float red[2 * (T / 64)];
   const int row = blockIdx.x, tid = threadIdx.x;
-  if (counters)
-    for (int i = row * T + tid; i < kSliceCounters; i += gridDim.x * T) counters[i] = 0;
+  if (counters && row == 0)  // (without gridDim: a kernel that reads launch dimensions gets another 256 bytes of arguments at every launch)
+    for (int i = tid; i < kSliceCounters; i += T) counters[i] = 0;
   const int nc = h >> 2;
   const size_t base = (size_t)row * h;
   f32x4 v[NC], z[NC];
@@ -425,8 +425,8 @@ __global__ __launch_bounds__(NT) void rope_kernel(uint16_t* __restrict__ qkv, in
 // out (bf16) = x (fp32); n4 groups of 4 elements
 __global__ __launch_bounds__(NT) void cast_bf16_kernel(const float* __restrict__ x, uint16_t* __restrict__ out, int64_t n4,
                                                        uint32_t* __restrict__ counters) {
-  if (counters)
-    for (int c = blockIdx.x * NT + threadIdx.x; c < kSliceCounters; c += gridDim.x * NT) counters[c] = 0;
+  if (counters && blockIdx.x == 0)
+    for (int c = threadIdx.x; c < kSliceCounters; c += NT) counters[c] = 0;
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
   if (i >= n4) return;
   const f32x4 v = *reinterpret_cast<const f32x4*>(x + 4 * i);

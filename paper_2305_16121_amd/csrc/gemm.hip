@@ -1167,7 +1167,7 @@ __device__ __forceinline__ f32x4 slice_load(uint64_t* p) {
 template <int N>
 __device__ __forceinline__ bool sum_slices(const SliceSum& ss, f32x4 (&v)[N], char* flag) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const size_t plane = (size_t)(blockDim.x >> 6) * N * 128;  // in pairs of floats
+  constexpr size_t plane = 8 * N * 128;  // in pairs of floats; eight waves
   uint64_t* p = reinterpret_cast<uint64_t*>(ss.part) + (size_t)wave * N * 128 + lane;
 #pragma unroll
   for (int q = 0; q < N; q++) slice_store(p + ss.slice * plane + q * 128, v[q]);

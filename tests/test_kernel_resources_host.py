@@ -1,0 +1,57 @@
+"""What the kernels of the built library ask of a launch (their metadata in the code objects): arguments, registers, scratch memory."""
+import re
+import struct
+import subprocess
+
+import pytest
+
+msgpack = pytest.importorskip("msgpack")
+
+
+def metadata(path):
+    """{demangled kernel name: its metadata map} of every gfx950 code object in the library."""
+    blob, kernels, at = open(path, "rb").read(), {}, 0
+    while (at := blob.find(b"__CLANG_OFFLOAD_BUNDLE__", at)) >= 0:
+        entry = at + 32
+        for _ in range(struct.unpack_from("<Q", blob, at + 24)[0]):
+            offset, size, length = struct.unpack_from("<QQQ", blob, entry)
+            triple = blob[entry + 24:entry + 24 + length]
+            entry += 24 + length
+            if b"gfx950" in triple and size:
+                for k in notes(blob[at + offset:at + offset + size]):
+                    kernels[k[".name"]] = k
+        at += 24
+    names = subprocess.run(["c++filt"], input="\n".join(kernels), capture_output=True, text=True, check=True).stdout.split("\n")
+    short = lambda n: re.sub(r"\(anonymous namespace\)::|oases::|^void ", "", n).split("(")[0]
+    return {short(re.sub(r"oases::\(anonymous namespace\)::", "", n)): k for n, k in zip(names, kernels.values())}
+
+
+def notes(elf):
+    start, entry, count = struct.unpack_from("<Q", elf, 40)[0], *struct.unpack_from("<HH", elf, 58)
+    for i in range(count):
+        kind, = struct.unpack_from("<I", elf, start + i * entry + 4)
+        offset, size = struct.unpack_from("<QQ", elf, start + i * entry + 24)
+        at = offset
+        while kind == 7 and at < offset + size:   # SHT_NOTE
+            n, d, t = struct.unpack_from("<III", elf, at)
+            at += 12 + (n + 3) // 4 * 4
+            if t == 32:                           # NT_AMDGPU_METADATA
+                yield from msgpack.unpackb(elf[at:at + d])["amdhsa.kernels"]
+            at += (d + 3) // 4 * 4
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    from paper_2305_16121_amd import binding
+    found = metadata(binding.LIB_PATH)
+    assert len(found) > 100
+    return found
+
+
+def test_no_launch_dimensions_among_the_arguments(kernels):
+    """A kernel that reads gridDim or blockDim gets 256 more bytes of arguments, which the host fills in at every launch: not the kernels of which a
+    pass launches several a layer."""
+    some = [n for n in kernels if n.startswith(("gemm_", "bdr_ln_kernel", "cast_bf16_kernel", "attn_", "wave_d", "rope_kernel"))]
+    assert len(some) > 80
+    for n in some:
+        assert not any(a[".value_kind"].startswith("hidden_") for a in kernels[n][".args"]), n
