@@ -244,6 +244,20 @@ __device__ __forceinline__ bf16x8 tile_mc(const char* lds, int r0, int j, int dt
   short8v v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   return __builtin_bit_cast(bf16x8, v);
 }
+// the same from one address for all fragments of a tile.  off: tile_mc_offset of the lane plus the tile's offset in lds, a multiple of its row (2 D
+// bytes): the columns of a fragment (bits 6, 7) and the swizzle eight rows on (bit 5) are bits of it
+template <int D>
+__device__ __forceinline__ int tile_mc_offset(int lane) {
+  return tile_chunk<D>(4 * (lane >> 5) + ((lane & 15) >> 2), 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) + 8 * (lane & 1);
+}
+template <int D>
+__device__ __forceinline__ bf16x8 tile_mc_at(const char* lds, uint32_t off, int j, int dt) {
+  const uint32_t o = off ^ (dt << 6);
+  short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((OASES_LDS short4v*)(lds + o + 16 * j * 2 * D));
+  short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((OASES_LDS short4v*)(lds + (o ^ 32) + (16 * j + 8) * 2 * D));
+  typedef short short8v __attribute__((ext_vector_type(8)));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
 // barrier behind LDS accesses only: global loads into registers stay in flight (__syncthreads would wait for them)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -253,6 +267,13 @@ __device__ __forceinline__ void decode_block_serpentine(int wg, int pairs, int b
   const int per_group = 8 * blocks, gi = wg / per_group;
   decode_block(wg, pairs, blocks, pair, blk);
   if (gi & 1) blk = blocks - 1 - blk;
+}
+// The same where a CU holds four workgroups.  An XCD deals its workgroups to 32 CUs layer by layer; with 16, 8, 4.. blocks an even number of
+// groups fills a layer, so every layer would be dealt alike and a CU would get four long workgroups: odd layers are turned round.  us, causal,
+// turned or not (D = 64): 8x1024x8 28.2 -> 21.3, 8x512x16 17.7 -> 14.2, 16x512x16 27.3 -> 27.6, 8x960x8 (15 blocks: not turned) 23.7.
+__device__ __forceinline__ void decode_block_layers(int wg, int pairs, int blocks, int& pair, int& blk) {
+  decode_block_serpentine(wg, pairs, blocks, pair, blk);
+  if (16 % blocks == 0 && ((wg >> 8) & 1)) blk = blocks - 1 - blk;
 }
 
 // A value of the wave's lower half (lanes 0..31) and of its upper half, in every lane l of either: those of lanes l % 32 and
@@ -304,15 +325,20 @@ struct FwdLds {
   static constexpr int kTile = SharedTile<D, 32 * KG>::bytes, kStages = 2 * NS * kTile, kPart = 4 * E * 64 * 4;
   static constexpr int bytes = (kStages > kPart ? kStages : kPart) + 1024;  // + m[4][32], l[4][32]
 };
+// FOUR: 64 columns, two query groups and no dropout fit four workgroups on a CU (33 KB of LDS each) as long as a wave has 128 registers.
+template <int D, int QG, bool DROP>
+constexpr bool kFwdFour = D == 64 && QG == 2 && !DROP;
 template <int D, int QG, int KG, bool CAUSAL, bool DROP>
-__global__ __launch_bounds__(NT, 2) void attn_fwd_kernel(AttnArgs a) {
+__global__ __launch_bounds__(NT, (kFwdFour<D, QG, DROP> ? 4 : 2)) void attn_fwd_kernel(AttnArgs a) {
   constexpr int KS = D / 16, DT = D / 32, E = DT * 16, BK = 32 * KG;
+  constexpr bool FOUR = kFwdFour<D, QG, DROP>;
   using L = FwdLds<D, QG, KG>;
   __shared__ __attribute__((aligned(16))) char lds[L::bytes];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5;
   const int qg = wave % QG, kg = wave / QG;
   int pair, blk;
-  decode_block_serpentine(blockIdx.x, a.nseq * a.heads, a.blocks, pair, blk);
+  if constexpr (FOUR && CAUSAL) decode_block_layers(blockIdx.x, a.nseq * a.heads, a.blocks, pair, blk);
+  else decode_block_serpentine(blockIdx.x, a.nseq * a.heads, a.blocks, pair, blk);
   const int sq = pair / a.heads, head = pair % a.heads, qb = a.blocks - 1 - blk;  // long rows first
   const int seq_idx = a.seq0 + sq;
   const int wg_end = min(a.pos0 + a.npos, a.pos0 + (qb + 1) * 32 * QG);   // end of the workgroup's queries
@@ -360,20 +386,35 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_kernel(AttnArgs a) {
     const int kv0 = t * BK + 32 * kg;
     if (kv0 < a.seq && !(CAUSAL && kv0 >= q_end)) {  // uniform over the wave: some key is visible to some query
       // The fragments of K are requested together, and those of V ahead of the softmax that covers their latency; left to itself the compiler
-      // requests one or two at a time and every product waits for one.  us: 8x1024x8x64 30 -> 26, 4x2048x4x128 43.4 -> 42.2, not causal 58 -> 54.
+      // requests one or two at a time and every product waits for one.  us: 4x2048x4x128 43.4 -> 42.2, not causal 58 -> 54.  FOUR: eight addresses
+      // would take the registers past 128, and with them the fourth workgroup of a CU (8x1896x4x64 36.4 -> 42.2 us); the fragments of an operand
+      // lie where two or three bits of one offset differ, which is formed here and again for every tile: 34.1 us.
+      // Not V ahead with dropout, 128 columns and one query group, where the registers spill (4x1032x3 24.2 -> 25.5 us).
+      constexpr bool V_AHEAD = !(D == 128 && QG == 1 && DROP);
       f32x16 s = zero16();
       bf16x8 kf[KS], vf[2][DT];
+      uint32_t ko = (uint32_t)(lk - lds) + 32 * kg * 2 * D + tile_chunk<D>(lane & 31, g);
+      uint32_t vo = (uint32_t)(lv - lds) + 32 * kg * 2 * D + tile_mc_offset<D>(lane);
+      if constexpr (FOUR) asm volatile("" : "+v"(ko), "+v"(vo));
 #pragma unroll
-      for (int ks = 0; ks < KS; ks++) kf[ks] = tile_kc<D>(lk, 32 * kg, ks, lane);
+      for (int ks = 0; ks < KS; ks++) {
+        if constexpr (FOUR) kf[ks] = *reinterpret_cast<const bf16x8*>(lds + (ko ^ (ks << 5)));
+        else kf[ks] = tile_kc<D>(lk, 32 * kg, ks, lane);
+      }
       OASES_ISSUED();
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) s = MFMA(kf[ks], qf[ks], s);
-      OASES_ISSUED();
+      if constexpr (V_AHEAD) {
+        OASES_ISSUED();
 #pragma unroll
-      for (int j = 0; j < 2; j++)
+        for (int j = 0; j < 2; j++)
 #pragma unroll
-        for (int dt = 0; dt < DT; dt++) vf[j][dt] = tile_mc<D>(lv, 32 * kg, j, dt, lane);
-      OASES_ISSUED();
+          for (int dt = 0; dt < DT; dt++) {
+            if constexpr (FOUR) vf[j][dt] = tile_mc_at<D>(lds, vo, j, dt);
+            else vf[j][dt] = tile_mc<D>(lv, 32 * kg, j, dt, lane);
+          }
+        OASES_ISSUED();
+      }
       if ((kv0 + 32 > a.seq) || (CAUSAL && kv0 + 31 > q_begin)) {
         OASES_RARE();
 #pragma unroll
@@ -422,7 +463,7 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_kernel(AttnArgs a) {
       for (int j = 0; j < 2; j++) {
         bf16x8 pb = pack8(s, 8 * j);
 #pragma unroll
-        for (int dt = 0; dt < DT; dt++) o[dt] = MFMA(vf[j][dt], pb, o[dt]);
+        for (int dt = 0; dt < DT; dt++) o[dt] = MFMA(V_AHEAD ? vf[j][dt] : tile_mc<D>(lv, 32 * kg, j, dt, lane), pb, o[dt]);
       }
     }
     lds_barrier();

@@ -21,7 +21,10 @@ CASES = [(32, 72, 8, 64, 1, 0.0),                   # 512 / 768: two groups, the
          (2, 520, 8, 128, 1, 0.0),                  # wave-private dQ and dK/dV
          (2, 520, 8, 128, 0, 0.25),
          (2, 264, 10, 64, 1, 0.1),                  # 100 / 180: dropout, two launches
-         (2, 264, 6, 64, 1, 0.1)]                   # 60 / 108: dropout, one launch
+         (2, 264, 6, 64, 1, 0.1),                   # 60 / 108: dropout, one launch
+         (2, 264, 6, 128, 1, 0.1),                  # forward: one group, dropout
+         (16, 72, 10, 64, 1, 0.0),                  # 320 of two blocks a sequence: forward workgroups from 256 on take theirs in the other order
+         (4, 512, 10, 64, 1, 0.0)]                  # 320 of eight
 
 
 @pytest.mark.parametrize("batch,seq,heads,d,causal,p", CASES)

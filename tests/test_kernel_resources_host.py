@@ -55,3 +55,14 @@ def test_no_launch_dimensions_among_the_arguments(kernels):
     assert len(some) > 80
     for n in some:
         assert not any(a[".value_kind"].startswith("hidden_") for a in kernels[n][".args"]), n
+
+
+def test_attention_forward_registers(kernels):
+    """No scratch memory; and with 64 columns, two query groups and no dropout four workgroups of four waves on a CU: 128 registers of the 512 of a SIMD
+    lane, a quarter of the 160 KiB of LDS."""
+    forward = {n: k for n, k in kernels.items() if n.startswith("attn_fwd_kernel")}
+    assert len(forward) == 16
+    for n, k in forward.items():
+        assert k[".private_segment_fixed_size"] == 0, n
+        if n.startswith("attn_fwd_kernel<64, 2,") and n.endswith("false>"):
+            assert k[".vgpr_count"] + k[".agpr_count"] <= 128 and k[".group_segment_fixed_size"] <= 40960, (n, k[".vgpr_count"])
