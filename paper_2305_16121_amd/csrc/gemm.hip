@@ -38,18 +38,23 @@ struct GemmArgs {
   int lda, ldb, ldc, ldaux;
   int tiles_m, tiles_n;
   int ksplit, k_per;  // split-K: slice s covers k in [s*k_per, min(K, (s+1)*k_per)) and writes partial s
-  float* part;         // slices that the launch adds up itself (SliceSum): partial sums, and a counter per tile
-  uint32_t* counters;  // nullptr: slices write planes that a second launch adds up
-  float* colsum;       // weight gradients of a group: [N], += the column sums of B (a bias gradient); or nullptr
-  float* delta;        // EPI_BF16_DELTA: [M / seq, heads, seq], the row sums of C * aux over the head_dim columns of a head
-  int seq, heads, head_dim;
+};
+// What only some kernels read, apart so that the others are not given it (copying a kernel's arguments is a part of the host time of a launch:
+// 88 -> 136 bytes 0.1 us)
+struct GemmCall : GemmArgs {
+  float* part = nullptr;         // slices that the launch adds up itself (SliceSum): partial sums, and a counter per tile
+  uint32_t* counters = nullptr;  // nullptr: slices write planes that a second launch adds up
+  // weight gradients of a group: [N], += the column sums of B (a bias gradient), or nullptr; EPI_BF16_DELTA: [M / seq, N / head_dim, seq], the row
+  // sums of C * aux over the head_dim columns of a head
+  float* sums = nullptr;
+  int seq = 0, head_dim = 0;
 };
 
 // one launcher per contraction form, each defined in its own part
 // choice_rows > 0: the kernel is chosen as if the launch had that many rows (see launch_gemm)
-int launch_gemm_nn(const GemmArgs& g, int epi, float* ws, size_t ws_bytes, int forced_variant, int choice_rows, hipStream_t s);
-int launch_gemm_nt(const GemmArgs& g, int epi, float* ws, size_t ws_bytes, int forced_variant, int choice_rows, hipStream_t s);
-int launch_gemm_tn(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_variant, hipStream_t s);
+int launch_gemm_nn(const GemmCall& g, int epi, float* ws, size_t ws_bytes, int forced_variant, int choice_rows, hipStream_t s);
+int launch_gemm_nt(const GemmCall& g, int epi, float* ws, size_t ws_bytes, int forced_variant, int choice_rows, hipStream_t s);
+int launch_gemm_tn(const GemmCall& g, float* ws, size_t ws_bytes, int forced_variant, hipStream_t s);
 
 namespace {
 
@@ -1423,25 +1428,30 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
   }
 }
 
-// this workgroup's k range (k_per: a whole number of stages) and, where a second launch adds the slices up, its fp32 plane; floats: partial sums of a workgroup
-template <bool A_KC, bool B_KC>
-__device__ __forceinline__ SliceSum take_slice(GemmArgs& g, int& pid, int floats) {
+// this workgroup's k range (k_per: a whole number of stages) and, unless the launch adds its slices up itself (OWN), its fp32 plane; floats: partial
+// sums of a workgroup
+template <bool A_KC, bool B_KC, bool OWN, class G>
+__device__ __forceinline__ SliceSum take_slice(G& g, int& pid, int floats) {
   const int T = g.tiles_m * g.tiles_n, slice = pid / T, k0 = slice * g.k_per;
   pid -= slice * T;
   g.A += A_KC ? (size_t)k0 : (size_t)k0 * g.lda;
   g.B += B_KC ? (size_t)k0 : (size_t)k0 * g.ldb;
   g.K = min(g.K - k0, g.k_per);
-  if (!g.counters) g.C = reinterpret_cast<float*>(g.C) + (size_t)slice * g.M * g.ldc;
-  return SliceSum{g.part + (size_t)pid * g.ksplit * floats, g.counters + pid, slice, g.ksplit};
+  if constexpr (OWN) {
+    return SliceSum{g.part + (size_t)pid * g.ksplit * floats, g.counters + pid, slice, g.ksplit};
+  } else {
+    g.C = reinterpret_cast<float*>(g.C) + (size_t)slice * g.M * g.ldc;
+    return SliceSum{};
+  }
 }
 
 // SLICED: k slices that the launch adds up itself
-template <int BM, bool A_KC, bool B_KC, int EPI, bool FULL, bool SLICED = false>
-__global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs g) {  // g: by value, adjusted per k slice
+template <int BM, bool A_KC, bool B_KC, int EPI, bool FULL, bool SLICED = false, class G = std::conditional_t<SLICED, GemmCall, GemmArgs>>
+__global__ __launch_bounds__(512) void gemm_pp_kernel(G g) {  // by value, adjusted per k slice
   __shared__ __attribute__((aligned(1024))) char lds[BM == 256 ? kPpLds256 : kPpLds128];
   int pid = blockIdx.x;
   SliceSum ss{};
-  if (BM == 128 && g.ksplit > 1) ss = take_slice<A_KC, B_KC>(g, pid, 128 * 256);
+  if (BM == 128 && g.ksplit > 1) ss = take_slice<A_KC, B_KC, SLICED>(g, pid, 128 * 256);
   pp_tile<BM, A_KC, B_KC, EPI, FULL, SLICED>(g, pid, lds, ss);
 }
 
@@ -1575,8 +1585,10 @@ __device__ __forceinline__ float frag_sum(const u32x4& f) {
 // 544.7 -> 538.2 us; three layers of h 1024, 600 tokens, 128 columns a head: 534.9 -> 533.0, on 64x128 instead of 64x64 tiles).
 // COLSUM (weight gradients): the waves of the first row of tiles that hold the first 32 rows also add up B's columns, whose fragments they
 // have in registers (eight k of a column to a lane): the vector ALU has time, LDS is what the kernel waits for.  Eight tiles to a partial sum.
-template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI, bool COLSUM = false>
-__device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, const SliceSum& ss = SliceSum{}) {
+// SLICED: k slices that the launch adds up itself; in a kernel of its own, since the code of the sum, even where it is passed over, costs
+// every launch 0.1 us (216x1024x256 NN 3.31 -> 3.40, 64x64x64 2.50 -> 2.60).
+template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI, bool COLSUM = false, bool SLICED = false, class G>
+__device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const SliceSum& ss = SliceSum{}) {
   constexpr int BM = 64 * TM, BN = 64 * TN;
   constexpr int kOpA = BM * BKS * 2, kStage = StLds<TM, TN, NS>::kStage;
   constexpr int PER_A = TM, PER_B = TN, PER = PER_A + PER_B;  // direct-to-LDS instructions of a wave per stage
@@ -1644,7 +1656,8 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, c
 
   u32x4 fa[2][TM], fb[2][TN];
   int stage = 0;
-  const bool sums = COLSUM && g.colsum && tile_m == 0 && wm == 0;
+  bool sums = false;
+  if constexpr (COLSUM) sums = g.sums && tile_m == 0 && wm == 0;
   float csum[TN], part[TN];
 #pragma unroll
   for (int j = 0; j < TN; j++) csum[j] = part[j] = 0.f;
@@ -1730,14 +1743,14 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, c
     }
   }
   __syncthreads();
-  if (COLSUM && sums && wk == 0) {
+  if constexpr (COLSUM) if (sums && wk == 0) {
     static_assert(StLds<TM, TN, NS>::kExchange + 512 * TN <= StLds<TM, TN, NS>::bytes, "column sums behind the exchange");
 #pragma unroll
     for (int j = 0; j < TN; j++) {
       float t = csum[j] + xsum[64 * j + lane];
       t += __shfl_xor(t, 32, 64);  // the other eight k of a step
       const int col = col0 + 32 * j + (lane & 31);
-      if (lane < 32 && col < g.N) g.colsum[col] += t;
+      if (lane < 32 && col < g.N) g.sums[col] += t;
     }
   }
   f32x4 v[TM * TN * 2];  // [row part][column part][quarter]
@@ -1753,21 +1766,17 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, c
         for (int e = 0; e < 4; e++) v[2 * t + q][e] += a[E + 4 * q + e];
       }
   };
-  if (wk == 0) gather(std::integral_constant<int, 0>{}); else gather(std::integral_constant<int, 1>{});
-  if (ss.counter) {  // k slices that the launch adds up itself
-    static_assert(StLds<TM, TN, NS>::kExchange < StLds<TM, TN, NS>::bytes, "four bytes behind the exchange");
-    if (!sum_slices<TM * TN * 2>(ss, v, lds + StLds<TM, TN, NS>::kExchange)) return;
-  }
   float dsum[TM];  // EPI_BF16_DELTA: this lane's part of a row's sum over the wave's columns, which belong to one head
 #pragma unroll
   for (int i = 0; i < TM; i++) dsum[i] = 0.f;
-  auto finish = [&](auto full_c) {
+  auto finish = [&](auto half_c, auto full_c) {
+    constexpr int H = decltype(half_c)::value;
     constexpr bool FULL = decltype(full_c)::value;
 #pragma unroll
     for (int i = 0; i < TM; i++)
 #pragma unroll
       for (int q = 0; q < 2; q++) {
-        const int c = 8 * (2 * wk + q) + 4 * (lane >> 5);
+        const int c = 8 * (2 * H + q) + 4 * (lane >> 5);
         if constexpr (EPI == EPI_F32) {  // plain accumulator: element e of the quarter is C[row0 + 32 i + c + e][column lane%32 of the tile]
 #pragma unroll
           for (int j = 0; j < TN; j++) {
@@ -1804,8 +1813,19 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, c
         }
       }
   };
+  using H0 = std::integral_constant<int, 0>;
+  using H1 = std::integral_constant<int, 1>;
+  if constexpr (SLICED) {
+    static_assert(StLds<TM, TN, NS>::kExchange < StLds<TM, TN, NS>::bytes, "four bytes behind the exchange");
+    if (wk == 0) gather(H0{}); else gather(H1{});
+    if (!sum_slices<TM * TN * 2>(ss, v, lds + StLds<TM, TN, NS>::kExchange)) return;
+  }
   const bool full = m0 + BM <= g.M && n0 + BN <= g.N;
-  if (full) finish(std::true_type{}); else finish(std::false_type{});
+  auto tail = [&](auto half_c) {
+    if constexpr (!SLICED) gather(half_c);
+    if (full) finish(half_c, std::true_type{}); else finish(half_c, std::false_type{});
+  };
+  if (wk == 0) tail(H0{}); else tail(H1{});
   if constexpr (EPI == EPI_BF16_DELTA) {  // the four waves of a row (two k halves, two column parts) put their sums together in LDS
     constexpr int at = StLds<TM, TN, NS>::kExchange + 1024;
     static_assert(at + BM * 16 <= StLds<TM, TN, NS>::bytes, "row sums behind the exchange");
@@ -1818,33 +1838,31 @@ __device__ __forceinline__ void st_tile(const GemmArgs& g, int pid, char* lds, c
     __syncthreads();
     const int r = tid % BM, part = tid / BM;  // a head is 64 columns (one column part of a 128-wide tile) or all columns of the tile
     const bool one = g.head_dim == BN;
-    const int row = m0 + r, head = n0 / g.head_dim + part;
-    if (part < (one ? 1 : 2) && row < g.M && head < g.heads) {
+    const int row = m0 + r, head = n0 / g.head_dim + part, heads = g.N / g.head_dim;
+    if (part < (one ? 1 : 2) && row < g.M && head < heads) {
       const float* p = red + 4 * r + 2 * part;
-      g.delta[((size_t)(row / g.seq) * g.heads + head) * g.seq + row % g.seq] = one ? (p[0] + p[1]) + (p[2] + p[3]) : p[0] + p[1];
+      g.sums[((size_t)(row / g.seq) * heads + head) * g.seq + row % g.seq] = one ? (p[0] + p[1]) + (p[2] + p[3]) : p[0] + p[1];
     }
   }
 }
 
-template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(512) void gemm_st_kernel(GemmArgs g) {  // g: by value, adjusted per k slice
+// G: GemmArgs or GemmCall, written out where the kernel is launched (a type that is formed from an unnamed enumeration has another name for the host)
+template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI, bool SLICED, class G>
+__global__ __launch_bounds__(512) void gemm_st_kernel(G g) {  // by value, adjusted per k slice
   __shared__ __attribute__((aligned(1024))) char lds[StLds<TM, TN, NS>::bytes];
   int pid = blockIdx.x;
   SliceSum ss{};
-  if (g.ksplit > 1) {
-    ss = take_slice<A_KC, B_KC>(g, pid, 64 * TM * 64 * TN);
-    if (!g.counters) ss.counter = nullptr;
-  }
-  st_tile<TM, TN, NS, A_KC, B_KC, EPI>(g, pid, lds, ss);
+  if (SLICED || g.ksplit > 1) ss = take_slice<A_KC, B_KC, SLICED>(g, pid, 64 * TM * 64 * TN);
+  st_tile<TM, TN, NS, A_KC, B_KC, EPI, false, SLICED>(g, pid, lds, ss);
 }
 
 // two weight gradients over the same K rows, tiles of the second behind those of the first
 template <int TN, int NS>
-__global__ __launch_bounds__(512) void gemm_st_group_kernel(GemmArgs g0, GemmArgs g1) {
+__global__ __launch_bounds__(512) void gemm_st_group_kernel(GemmCall g0, GemmCall g1) {
   __shared__ __attribute__((aligned(1024))) char lds[StLds<1, TN, NS>::bytes];
   const int first = g0.tiles_m * g0.tiles_n;
   const bool second = (int)blockIdx.x >= first;
-  const GemmArgs g = second ? g1 : g0;
+  const GemmCall g = second ? g1 : g0;
   st_tile<1, TN, NS, false, false, EPI_ACC_F32, true>(g, second ? blockIdx.x - first : blockIdx.x, lds);
 }
 
@@ -1893,20 +1911,25 @@ int launch_one(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
 inline int st_k_per(int K, int slices) { return ((K + slices - 1) / slices + BKS - 1) / BKS * BKS; }  // k of one slice
 
 template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI>
-int launch_small(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
-  GemmArgs g = g0;
+int launch_small(const GemmCall& g0, int ksplit, float* ws, hipStream_t s) {
+  GemmCall g = g0;
   g.tiles_m = (g.M + 64 * TM - 1) / (64 * TM);
   g.tiles_n = (g.N + 64 * TN - 1) / (64 * TN);
-  if (ksplit <= 1 || g.counters) {
-    if (ksplit > 1) {
-      g.ksplit = ksplit;
-      g.k_per = st_k_per(g.K, ksplit);
-      g.part = ws;
-    }
-    hipLaunchKernelGGL((gemm_st_kernel<TM, TN, NS, A_KC, B_KC, EPI>), dim3(g.tiles_m * g.tiles_n * (ksplit > 1 ? ksplit : 1)), dim3(512), 0, s, g);
+  using G = std::conditional_t<EPI == EPI_BF16_DELTA, GemmCall, GemmArgs>;
+  if (ksplit <= 1) {
+    hipLaunchKernelGGL((gemm_st_kernel<TM, TN, NS, A_KC, B_KC, EPI, false, G>), dim3(g.tiles_m * g.tiles_n), dim3(512), 0, s, g);
     OASES_LAUNCH_CHECK("gemm_st_kernel");
     return 0;
   }
+  if constexpr (EPI != EPI_SWIGLU && EPI != EPI_DSWIGLU)
+    if (g.counters) {
+      g.ksplit = ksplit;
+      g.k_per = st_k_per(g.K, ksplit);
+      g.part = ws;
+      hipLaunchKernelGGL((gemm_st_kernel<TM, TN, NS, A_KC, B_KC, EPI, true, GemmCall>), dim3(g.tiles_m * g.tiles_n * ksplit), dim3(512), 0, s, g);
+      OASES_LAUNCH_CHECK("gemm_st_kernel (slices)");
+      return 0;
+    }
   if constexpr (EPI == EPI_SWIGLU || EPI == EPI_DSWIGLU || EPI == EPI_BF16_DELTA) {
     set_error("gemm: an epilogue that pairs columns does not run over k slices of two launches");
     return OASES_EINVAL;
@@ -1917,7 +1940,7 @@ int launch_small(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
     p.k_per = st_k_per(g.K, ksplit);
     p.C = ws;
     p.ldc = g.N;
-    hipLaunchKernelGGL((gemm_st_kernel<TM, TN, NS, A_KC, B_KC, EPI_F32>), dim3(g.tiles_m * g.tiles_n * ksplit), dim3(512), 0, s, p);
+    hipLaunchKernelGGL((gemm_st_kernel<TM, TN, NS, A_KC, B_KC, EPI_F32, false, GemmArgs>), dim3(g.tiles_m * g.tiles_n * ksplit), dim3(512), 0, s, p);
     OASES_LAUNCH_CHECK("gemm_st_kernel (split-K)");
     const long n4 = (long)g.M * (g.N / 4);
     hipLaunchKernelGGL((splitk_fixup_kernel<EPI>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, ws, ksplit, g);
@@ -2096,7 +2119,7 @@ bool decode_variant(int variant, int kind, int M, int N, int K, size_t ws_bytes,
 }
 
 template <bool A_KC, bool B_KC, int EPI>
-int launch_shape(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_variant, int choice_rows, hipStream_t s) {
+int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_variant, int choice_rows, hipStream_t s) {
   constexpr int kind = !A_KC ? 2 : B_KC ? 1 : (EPI == EPI_BIAS_GELU || EPI == EPI_SWIGLU) ? 3 : 0;
   if (EPI == EPI_SWIGLU || EPI == EPI_DSWIGLU) ws_bytes = 0;  // their epilogues pair columns: no second pass over partial planes
   TileChoice t;
@@ -2142,7 +2165,7 @@ int launch_shape(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_varia
   if (t.dtl && t.pp) {
     constexpr bool kCanBeRagged = !A_KC || !B_KC;
     const int bm = t.bm;
-    GemmArgs d = g;
+    GemmCall d = g;
     d.tiles_m = (g.M + bm - 1) / bm;
     d.tiles_n = (g.N + 255) / 256;
     const bool whole = g.M % bm == 0 && g.N % 256 == 0;
@@ -2153,7 +2176,7 @@ int launch_shape(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_varia
         return OASES_EINVAL;
       } else {
         if (!ws) { set_error("gemm: split-K chosen without a workspace"); return OASES_ENULL; }
-        GemmArgs p = d;
+        GemmCall p = d;
         p.ksplit = t.ksplit;
         p.k_per = g.K / t.ksplit;
         const dim3 sgrid(d.tiles_m * d.tiles_n * t.ksplit);
@@ -2248,7 +2271,7 @@ int launch_shape(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_varia
 }  // namespace
 
 #if OASES_GEMM_HAS(0)
-int launch_gemm_nn(const GemmArgs& g, int epi, float* ws, size_t ws_bytes, int forced_variant, int choice_rows, hipStream_t s) {
+int launch_gemm_nn(const GemmCall& g, int epi, float* ws, size_t ws_bytes, int forced_variant, int choice_rows, hipStream_t s) {
   switch (epi) {
     case EPI_F32: return launch_shape<true, false, EPI_F32>(g, ws, ws_bytes, forced_variant, choice_rows, s);
     case EPI_BF16: return launch_shape<true, false, EPI_BF16>(g, ws, ws_bytes, forced_variant, choice_rows, s);
@@ -2261,7 +2284,7 @@ int launch_gemm_nn(const GemmArgs& g, int epi, float* ws, size_t ws_bytes, int f
 }
 #endif
 #if OASES_GEMM_HAS(1)
-int launch_gemm_nt(const GemmArgs& g, int epi, float* ws, size_t ws_bytes, int forced_variant, int choice_rows, hipStream_t s) {
+int launch_gemm_nt(const GemmCall& g, int epi, float* ws, size_t ws_bytes, int forced_variant, int choice_rows, hipStream_t s) {
   switch (epi) {
     case EPI_F32: return launch_shape<true, true, EPI_F32>(g, ws, ws_bytes, forced_variant, choice_rows, s);
     case EPI_BF16: return launch_shape<true, true, EPI_BF16>(g, ws, ws_bytes, forced_variant, choice_rows, s);
@@ -2291,11 +2314,10 @@ int launch_gemm_delta(int variant, int M, int N, int K, const void* A, const voi
     set_error("gemm_delta: variant %d does not fit M=%d N=%d K=%d seq=%d head_dim=%d", variant, M, N, K, seq, head_dim);
     return OASES_EINVAL;
   }
-  GemmArgs g{(const uint16_t*)A, (const uint16_t*)B, C, nullptr, (uint16_t*)const_cast<void*>(out), M, N, K, K, K, N, N, 0, 0, 1, K};
+  GemmCall g{{(const uint16_t*)A, (const uint16_t*)B, C, nullptr, (uint16_t*)const_cast<void*>(out), M, N, K, K, K, N, N, 0, 0, 1, K}};
   g.counters = counters;
-  g.delta = delta;
+  g.sums = delta;
   g.seq = seq;
-  g.heads = N / head_dim;
   g.head_dim = head_dim;
   if (t.bm == 128) return launch_small<2, 2, 4, true, true, EPI_BF16_DELTA>(g, t.ksplit, ws, s);
   if (t.bn == 128) return launch_small<1, 2, 3, true, true, EPI_BF16_DELTA>(g, t.ksplit, ws, s);
@@ -2303,7 +2325,7 @@ int launch_gemm_delta(int variant, int M, int N, int K, const void* A, const voi
 }
 #endif  // NT part
 #if OASES_GEMM_HAS(2)
-int launch_gemm_tn(const GemmArgs& g, float* ws, size_t ws_bytes, int forced_variant, hipStream_t s) {
+int launch_gemm_tn(const GemmCall& g, float* ws, size_t ws_bytes, int forced_variant, hipStream_t s) {
   return launch_shape<false, false, EPI_ACC_F32>(g, ws, ws_bytes, forced_variant, 0, s);
 }
 
@@ -2403,10 +2425,10 @@ int launch_gemm_tn_group(int variant, int K, const TnProblem& a, const TnProblem
   const int bm = variant / 1000 % 1000, bn = variant % 1000, S = variant / 1000000 % 100;
   if (bm != 64 && (a.colsum || b.colsum)) { set_error("gemm_tn_group: column sums come with the small tiles only"); return OASES_EINVAL; }
   auto args = [&](const TnProblem& p) {
-    return GemmArgs{(const uint16_t*)p.A, (const uint16_t*)p.B, p.C, nullptr, nullptr, p.M, p.N, K, p.lda, p.ldb, p.ldc, 0,
-                    (p.M + bm - 1) / bm, (p.N + bn - 1) / bn, S, st_k_per(K, S), ws, counters, p.colsum};
+    return GemmCall{{(const uint16_t*)p.A, (const uint16_t*)p.B, p.C, nullptr, nullptr, p.M, p.N, K, p.lda, p.ldb, p.ldc, 0,
+                     (p.M + bm - 1) / bm, (p.N + bn - 1) / bn, S, st_k_per(K, S)}, ws, counters, p.colsum};
   };
-  const GemmArgs g0 = args(a), g1 = args(b);
+  const GemmCall g0 = args(a), g1 = args(b);
   const dim3 grid((unsigned)((g0.tiles_m * g0.tiles_n + g1.tiles_m * g1.tiles_n) * S));
   if (bm == 64) {
     if (bn == 64) hipLaunchKernelGGL((gemm_st_group_kernel<1, 5>), grid, dim3(512), 0, s, g0, g1);
@@ -2445,7 +2467,7 @@ int launch_gemm(int op, int epi, int M, int N, int K, const void* A, int lda, co
   }
   if (!A || !B || !C) { set_error("gemm: NULL operand"); return OASES_ENULL; }
   if (!aligned16(A) || !aligned16(B) || !aligned16(C) || !aligned16(bias) || !aligned16(aux)) { set_error("gemm: operand not 16-byte aligned"); return OASES_EALIGN; }
-  GemmArgs g{(const uint16_t*)A, (const uint16_t*)B, C, bias, (uint16_t*)aux, M, N, K, lda, ldb, ldc, ldaux, 0, 0, 1, K};
+  GemmCall g{{(const uint16_t*)A, (const uint16_t*)B, C, bias, (uint16_t*)aux, M, N, K, lda, ldb, ldc, ldaux, 0, 0, 1, K}};
   g.counters = ws ? counters : nullptr;
   if (op == OASES_GEMM_TN) {
     if (lda < M || ldb < N || ldc < N) { set_error("gemm TN: leading dimension too small"); return OASES_EINVAL; }

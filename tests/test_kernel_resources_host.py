@@ -66,3 +66,21 @@ def test_attention_forward_registers(kernels):
         assert k[".private_segment_fixed_size"] == 0, n
         if n.startswith("attn_fwd_kernel<64, 2,") and n.endswith("false>"):
             assert k[".vgpr_count"] + k[".agpr_count"] <= 128 and k[".group_segment_fixed_size"] <= 40960, (n, k[".vgpr_count"])
+
+
+def test_gemm_arguments(kernels):
+    """A GEMM kernel of one problem is given what it reads: 88 bytes, and 32 more where it adds up its own k slices or leaves row sums behind."""
+    some = [n for n in kernels if n.startswith("gemm_") and "group" not in n]
+    assert len(some) > 100
+    for n in some:
+        assert kernels[n][".kernarg_segment_size"] == (120 if "GemmCall" in n else 88), n
+    assert sum("GemmCall" in n for n in some) < len(some) // 2
+
+
+def test_every_kernel_of_the_host_is_in_a_code_object(kernels):
+    """The names under which the host asks for kernels are those that the device code has."""
+    from paper_2305_16121_amd import binding
+    blob = open(binding.LIB_PATH, "rb").read()
+    host = blob[:blob.index(b"__CLANG_OFFLOAD_BUNDLE__")]
+    asked = {m.decode() for m in re.findall(rb"\0(_ZN5oases12_GLOBAL__N_1\d+\w*_kernelI?[\w$]*)(?=\0)", host)}
+    assert len(asked) > 100 and asked <= {k[".name"] for k in kernels.values()}, sorted(asked - {k[".name"] for k in kernels.values()})[:3]
