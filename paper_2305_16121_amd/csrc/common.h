@@ -135,7 +135,7 @@ int launch_layernorm_fwd(const float* x, const float* gamma, const float* beta, 
                          float* rstd, int rows, int h, float eps, hipStream_t s, bool rms = false, uint32_t* counters = nullptr);
 int launch_bdr_ln(const float* part, const float* peer, const float* bias, const float* xin, float* xo,
                   const float* gamma, const float* beta, void* ln_out, float* mu, float* rstd, int rows,
-                  int h, float eps, const DropCfg& d, int64_t row0, hipStream_t s, bool rms = false, float* ln_f32 = nullptr, uint32_t* counters = nullptr);
+                  int h, float eps, const DropCfg& d, int64_t row0, hipStream_t s, bool rms = false, float* ln_f32 = nullptr);
 // post-LN layers: out (bf16) = x (fp32), n elements; out = a + b (+ c) fp32
 int launch_cast_bf16(const float* x, void* out, int64_t n, hipStream_t s, uint32_t* counters = nullptr);
 int launch_zero_counters(uint32_t* counters, hipStream_t s);
