@@ -1445,8 +1445,9 @@ __device__ __forceinline__ SliceSum take_slice(G& g, int& pid, int floats) {
   }
 }
 
-// SLICED: k slices that the launch adds up itself
-template <int BM, bool A_KC, bool B_KC, int EPI, bool FULL, bool SLICED = false, class G = std::conditional_t<SLICED, GemmCall, GemmArgs>>
+// SLICED: k slices that the launch adds up itself.  G: GemmArgs or GemmCall, written out where a kernel is launched (a type formed from an unnamed
+// enumeration would have another name on the host)
+template <int BM, bool A_KC, bool B_KC, int EPI, bool FULL, bool SLICED, class G>
 __global__ __launch_bounds__(512) void gemm_pp_kernel(G g) {  // by value, adjusted per k slice
   __shared__ __attribute__((aligned(1024))) char lds[BM == 256 ? kPpLds256 : kPpLds128];
   int pid = blockIdx.x;
@@ -1846,7 +1847,6 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
   }
 }
 
-// G: GemmArgs or GemmCall, written out where the kernel is launched (a type that is formed from an unnamed enumeration has another name for the host)
 template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI, bool SLICED, class G>
 __global__ __launch_bounds__(512) void gemm_st_kernel(G g) {  // by value, adjusted per k slice
   __shared__ __attribute__((aligned(1024))) char lds[StLds<TM, TN, NS>::bytes];
@@ -2182,16 +2182,16 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
         const dim3 sgrid(d.tiles_m * d.tiles_n * t.ksplit);
         if (g.counters && d.tiles_m * d.tiles_n <= kSliceCounters && (size_t)d.tiles_m * d.tiles_n * t.ksplit * 128 * 256 * 4 <= ws_bytes) {
           p.part = ws;
-          if (whole) hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, true, true>), sgrid, dim3(512), 0, s, p);
-          else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, false, true>), sgrid, dim3(512), 0, s, p);
+          if (whole) hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, true, true, GemmCall>), sgrid, dim3(512), 0, s, p);
+          else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, false, true, GemmCall>), sgrid, dim3(512), 0, s, p);
           OASES_LAUNCH_CHECK("gemm_pp_kernel (slices)");
           return 0;
         }
         p.counters = nullptr;
         p.C = ws;
         p.ldc = g.N;
-        if (whole) hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI_F32, true>), sgrid, dim3(512), 0, s, p);
-        else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI_F32, false>), sgrid, dim3(512), 0, s, p);
+        if (whole) hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI_F32, true, false, GemmArgs>), sgrid, dim3(512), 0, s, p);
+        else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI_F32, false, false, GemmArgs>), sgrid, dim3(512), 0, s, p);
         OASES_LAUNCH_CHECK("gemm_pp_kernel (split-K)");
         const long n4 = (long)g.M * (g.N / 4);
         hipLaunchKernelGGL((splitk_fixup_kernel<EPI>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, ws, t.ksplit, d);
@@ -2201,11 +2201,11 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
     }
     const dim3 grid(d.tiles_m * d.tiles_n);
     if (bm == 128) {
-      if (whole) hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, true>), grid, dim3(512), 0, s, d);
-      else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, false>), grid, dim3(512), 0, s, d);
+      if (whole) hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, true, false, GemmArgs>), grid, dim3(512), 0, s, d);
+      else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, false, false, GemmArgs>), grid, dim3(512), 0, s, d);
     } else {
-      if (whole) hipLaunchKernelGGL((gemm_pp_kernel<256, A_KC, B_KC, EPI, true>), grid, dim3(512), 0, s, d);
-      else if constexpr (kCanBeRagged) hipLaunchKernelGGL((gemm_pp_kernel<256, A_KC, B_KC, EPI, false>), grid, dim3(512), 0, s, d);
+      if (whole) hipLaunchKernelGGL((gemm_pp_kernel<256, A_KC, B_KC, EPI, true, false, GemmArgs>), grid, dim3(512), 0, s, d);
+      else if constexpr (kCanBeRagged) hipLaunchKernelGGL((gemm_pp_kernel<256, A_KC, B_KC, EPI, false, false, GemmArgs>), grid, dim3(512), 0, s, d);
     }
     OASES_LAUNCH_CHECK("gemm_pp_kernel");
     return 0;

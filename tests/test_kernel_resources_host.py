@@ -73,8 +73,11 @@ def test_gemm_arguments(kernels):
     some = [n for n in kernels if n.startswith("gemm_") and "group" not in n]
     assert len(some) > 100
     for n in some:
+        if n.startswith(("gemm_st", "gemm_pp")):   # <..., epilogue, whole tiles (pp), slices, type of the arguments>
+            flags = n[n.index("<") + 1:-1].split(", ")
+            more = flags[-2] == "true" or flags[-3] == "8"
+            assert flags[-1] == ("GemmCall" if more else "GemmArgs"), n
         assert kernels[n][".kernarg_segment_size"] == (120 if "GemmCall" in n else 88), n
-    assert sum("GemmCall" in n for n in some) < len(some) // 2
 
 
 def test_every_kernel_of_the_host_is_in_a_code_object(kernels):
