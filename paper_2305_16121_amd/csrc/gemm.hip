@@ -1911,7 +1911,7 @@ int launch_one(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
 inline int st_k_per(int K, int slices) { return ((K + slices - 1) / slices + BKS - 1) / BKS * BKS; }  // k of one slice
 
 template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI>
-int launch_small(const GemmCall& g0, int ksplit, float* ws, hipStream_t s) {
+int launch_small(const GemmCall& g0, int ksplit, float* ws, size_t ws_bytes, hipStream_t s) {
   GemmCall g = g0;
   g.tiles_m = (g.M + 64 * TM - 1) / (64 * TM);
   g.tiles_n = (g.N + 64 * TN - 1) / (64 * TN);
@@ -1921,8 +1921,9 @@ int launch_small(const GemmCall& g0, int ksplit, float* ws, hipStream_t s) {
     OASES_LAUNCH_CHECK("gemm_st_kernel");
     return 0;
   }
+  const size_t T = (size_t)g.tiles_m * g.tiles_n;
   if constexpr (EPI != EPI_SWIGLU && EPI != EPI_DSWIGLU)
-    if (g.counters) {
+    if (g.counters && ws && T <= kSliceCounters && T * ksplit * (64 * TM * 64 * TN * 4) <= ws_bytes) {
       g.ksplit = ksplit;
       g.k_per = st_k_per(g.K, ksplit);
       g.part = ws;
@@ -2156,9 +2157,9 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
     return OASES_EINVAL;
   }
   if (t.st) {
-    if (t.bm == 128) return launch_small<2, 2, 4, A_KC, B_KC, EPI>(g, t.ksplit, ws, s);
-    if (t.bn == 128) return launch_small<1, 2, 3, A_KC, B_KC, EPI>(g, t.ksplit, ws, s);
-    if constexpr (EPI != EPI_SWIGLU) return launch_small<1, 1, 5, A_KC, B_KC, EPI>(g, t.ksplit, ws, s);
+    if (t.bm == 128) return launch_small<2, 2, 4, A_KC, B_KC, EPI>(g, t.ksplit, ws, ws_bytes, s);
+    if (t.bn == 128) return launch_small<1, 2, 3, A_KC, B_KC, EPI>(g, t.ksplit, ws, ws_bytes, s);
+    if constexpr (EPI != EPI_SWIGLU) return launch_small<1, 1, 5, A_KC, B_KC, EPI>(g, t.ksplit, ws, ws_bytes, s);
     set_error("gemm: the 64x64 kernel has no SwiGLU epilogue");
     return OASES_EINVAL;
   }
@@ -2319,9 +2320,9 @@ int launch_gemm_delta(int variant, int M, int N, int K, const void* A, const voi
   g.sums = delta;
   g.seq = seq;
   g.head_dim = head_dim;
-  if (t.bm == 128) return launch_small<2, 2, 4, true, true, EPI_BF16_DELTA>(g, t.ksplit, ws, s);
-  if (t.bn == 128) return launch_small<1, 2, 3, true, true, EPI_BF16_DELTA>(g, t.ksplit, ws, s);
-  return launch_small<1, 1, 5, true, true, EPI_BF16_DELTA>(g, t.ksplit, ws, s);
+  if (t.bm == 128) return launch_small<2, 2, 4, true, true, EPI_BF16_DELTA>(g, t.ksplit, ws, ws_bytes, s);
+  if (t.bn == 128) return launch_small<1, 2, 3, true, true, EPI_BF16_DELTA>(g, t.ksplit, ws, ws_bytes, s);
+  return launch_small<1, 1, 5, true, true, EPI_BF16_DELTA>(g, t.ksplit, ws, ws_bytes, s);
 }
 #endif  // NT part
 #if OASES_GEMM_HAS(2)
