@@ -1908,6 +1908,12 @@ int launch_one(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
   return 0;
 }
 
+// Whether a launch of a pass adds up its own k slices, or a second launch does: the last workgroup of a tile reads the other slices' sums at some
+// 47 GB/s; a second launch costs 6 to 9 us inside a step.  us, own -> two launches: inside a step 400 x 2560 x 5120 over three of 128x128 25.3 -> 30,
+// 256 x 256 x 12600 TN over eight of 64x64 14 -> 17; over four of 128x256 two launches are the faster (forward pass of three layers with 400 x 4096 x
+// 8192 519 -> 508, of two with 304 x 3840 x 10240 and 304 x 5120 x 10240 468 -> 449, of one with 160 x 5632 x 11264 207 -> 198);
+// over two of 128x256 the two are within 1 % of a step (24 of them).
+inline bool own_slices(int slices, int bm, int bn) { return (slices - 1) * bm * bn * 4 <= 208 << 10; }
 inline int st_k_per(int K, int slices) { return ((K + slices - 1) / slices + BKS - 1) / BKS * BKS; }  // k of one slice
 
 template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI>
@@ -1923,7 +1929,7 @@ int launch_small(const GemmCall& g0, int ksplit, float* ws, size_t ws_bytes, hip
   }
   const size_t T = (size_t)g.tiles_m * g.tiles_n;
   if constexpr (EPI != EPI_SWIGLU && EPI != EPI_DSWIGLU)
-    if (g.counters && ws && T <= kSliceCounters && T * ksplit * (64 * TM * 64 * TN * 4) <= ws_bytes) {
+    if (g.counters && ws && (EPI == EPI_BF16_DELTA || own_slices(ksplit, 64 * TM, 64 * TN)) && T <= kSliceCounters && T * ksplit * (64 * TM * 64 * TN * 4) <= ws_bytes) {
       g.ksplit = ksplit;
       g.k_per = st_k_per(g.K, ksplit);
       g.part = ws;
@@ -1972,7 +1978,13 @@ const KindTable g_kinds[4] = {{true, 1200.f, 1080.f, 960.f, 740.f}, {true, 1200.
                         {true, 1200.f, 1080.f, 960.f, 740.f}, {false, 1200.f, 1080.f, 900.f, 740.f}};
 TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes) {
   const KindTable& kt = g_kinds[kind];
-  const struct { int bm, bn; float tflops; } cand[] = {{256, 256, kt.r256x256}, {128, 256, kt.r128x256}, {256, 128, kt.r256x128}, {128, 128, kt.r128x128}};
+  // Tiles that the direct-to-LDS kernels do not cover run on the register-staged kernels.  256x256: at three quarters of their rate (NT dSwiGLU 8192 x
+  // 1376 x 4096: 138 us against 133 on 128x256 tiles, which may be ragged, 9984 x 2624 x 1600 153 against 138, NT 8656 x 1984 x 1344 76 against 60).  128x256
+  // where k is no whole number of stages: at half (NN 9576 x 1536 x 1376: 81 us, 62 on 256x256); TN at 700 and 740 (2560 x 5120 x 808: 256x256 75 us,
+  // 128x256 75, 64x128 60).
+  const bool rect = dtl_rect_fits(kind, M, N, K);
+  const float r128 = rect ? kt.r128x256 : kind == 2 ? 740.f : 650.f, r256x128 = rect ? kt.r256x128 : kind == 2 ? 740.f : 600.f;
+  const struct { int bm, bn; float tflops; } cand[] = {{256, 256, kt.r256x256}, {128, 256, r128}, {256, 128, r256x128}, {128, 128, kt.r128x128}};
   TileChoice best{128, 128, 1, kt.wave_ksplit};
   double best_t = 1e30;
   for (auto& c : cand) {
@@ -1980,10 +1992,8 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
     for (int S = 1; S <= 8; S *= 2) {
       if (S > 1 && ((size_t)S * M * N * 4 > ws_bytes || K / S < 512)) break;
       const long wgs = tm * tn * S, rounds = (wgs + 255) / 256;
-      // 256x256 tiles that the direct-to-LDS kernels do not cover run on the register-staged kernel (NT dSwiGLU 8192 x 1376 x 4096: 153 us
-      // against 130 on 128x256 tiles, which may be ragged)
-      const double tflops = c.bm == 256 && c.bn == 256 && S == 1 && !dtl_fits(kind, M, N, K) ? 900.f : c.tflops;
       // time of one workgroup's tile slice at the tile's rate (one workgroup per CU), times the number of rounds
+      const double tflops = c.bm == 256 && c.bn == 256 && !(S == 1 && dtl_fits(kind, M, N, K)) ? (kind == 2 ? 700.f : 900.f) : c.tflops;
       double t = (double)rounds * (2.0 * c.bm * c.bn * ((double)K / S) + 3.0e6) / (tflops * 1e12 / 256.0);
       if (S > 1) t += ((double)(2 * S + 1) * M * N * 4.0) / 3.0e12 + 4e-6;
       if (t < best_t) { best_t = t; best = TileChoice{c.bm, c.bn, S, kt.wave_ksplit}; }
@@ -2028,8 +2038,9 @@ double pp_seconds(int bm, long wgs, int k_per, double out_bytes) {
 // large), 4096 x 512 x 4096 NT 29.8 -> 22.9, 1024 x 1024 x 4096 TN 21.4 -> 16.9, 64 x 4608 x 12288 NN 53.5 -> 34.8,
 // 6144 x 12288 x 128 TN 195 -> 152.  Slices of 8192 k and more stay with the large tiles.
 // own_sum: the launch adds its slices up by itself (SliceSum): a call of a pass.  The last workgroup of a tile then reads the other slices'
-// sums, one after the other at some 47 GB/s, instead of a second launch; 128x128 tiles on the same scheme are candidates, with any
-// number of slices (0.6 us a stage).  Measured, us, the choice without -> with: inside a step 128 x 4608 x 12288 NN 52 -> 48
+// sums, one after the other at some 47 GB/s, instead of a second launch (own_slices); 128x128 tiles on the same scheme are candidates, with any
+// number of slices (0.6 us a stage, 0.85 of that where 218 and fewer workgroups leave CUs idle and the others more of the power; what TN reads and writes moves at
+// 3.4 TB/s from the second round on, since a CU holds one workgroup: 10240 x 3840 x 208 92 us on 64x128, 118 on 128x128).  Measured, us, the choice without -> with: inside a step 128 x 4608 x 12288 NN 52 -> 48
 // (register-staged kernel over eight slices -> 128x128 over six), NT 128 x 6144 x 12288 78 -> 75; 512 x 8192 x 3072 NT 47 -> 36, 8192 x 512 x
 // 2048 NT 31 -> 26, 200 x 3072 x 8192 36 -> 27; 1488 x 3072 x 3072 NN stays on 144 tiles of 128x256 (40; 64x128 over two slices 72).
 TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, double* seconds = nullptr, bool own_sum = false, int bn_min = 0) {
@@ -2037,30 +2048,36 @@ TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, do
   const KindTable& kt = g_kinds[kind];
   const double out = (double)M * N * (epi == EPI_F32 ? 4.0 : kind == 2 ? 8.0 : epi == EPI_SWIGLU ? 3.0 : epi == EPI_DSWIGLU ? 8.0 : epi == EPI_BIAS_GELU || epi == EPI_DGELU ? 4.0 : 2.0);
   auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  auto slices = [&](int S, int bm, int bn, bool own) {
-    return S <= 1 ? 0.0 : 2.0 * S * M * N * 4.0 / 6.0e12 + (own ? 2.0e-6 + (S - 1) * bm * bn * 4.0 / 47.0e9 : 3.2e-6);
+  // a second launch: 3.2 us by itself, up to 9 in a pass (see own_slices; at 6.5 400 x 4096 x 8192 goes to four slices of 128x256, 508 us for that
+  // pass, 490 on two of 128x128)
+  auto slices = [&](int S, int bm, int bn) {
+    const bool own = own_sum && (bn_min || own_slices(S, bm, bn));
+    return S <= 1 ? 0.0 : 2.0 * S * M * N * 4.0 / 6.0e12 + (own ? 2.0e-6 + (S - 1) * bm * bn * 4.0 / 47.0e9 : own_sum ? 9.0e-6 : 3.2e-6);
   };
   auto room = [&](int S, int bm, int bn) {  // partial sums and counters of slices that the launch adds up
     return S <= 1 || (tiles(bm, bn) <= kSliceCounters && (size_t)tiles(bm, bn) * S * bm * bn * 4 <= ws_bytes);
   };
-  const double rate = large.bm == 256 && large.bn == 256 ? kt.r256x256 : large.bm == 256 ? kt.r256x128 : large.bn == 256 ? kt.r128x256 : kt.r128x128;
+  // (in a pass the register-staged 128x256 kernel, over slices that are no whole stages, runs at its own rate: 208 x 7168 x 4800 over four 43 us, not 36)
+  const double rate = large.bm == 256 && large.bn == 256 ? kt.r256x256 : large.bm == 256 ? kt.r256x128 : large.bn == 256 ? (own_sum && !large.pp ? 650.f : kt.r128x256) : kt.r128x128;
   const long wgs = (long)((M + large.bm - 1) / large.bm) * ((N + large.bn - 1) / large.bn) * large.ksplit;
   double best_t = (double)((wgs + 255) / 256) * (2.0 * large.bm * large.bn * ((double)K / large.ksplit) + 3.0e6) / (rate * 1e12 / 256.0) +
-                  out / 3.1e12 + slices(large.ksplit, 128, 256, false);
+                  out / 3.1e12 + slices(large.ksplit, 128, 256);
   if (large.pp) best_t *= 0.9; else best_t += 2.0e-6;
-  if (own_sum && large.pp) best_t = pp_seconds(large.bm, wgs, K / large.ksplit, out) + slices(large.ksplit, 128, 256, true);
+  if (own_sum && large.pp) best_t = pp_seconds(large.bm, wgs, K / large.ksplit, out) + slices(large.ksplit, 128, 256);
   if (bn_min) best_t = 1e30;  // the small-tile kernels alone
   TileChoice best = large;
-  // weights that no cache keeps are read once per row of tiles: not on 64-row tiles when there are more rows (128 x 6144 x 12288 NN over
-  // eight slices 59, NT 80, against 52 and 75 on 128 rows; a plain reduction over the 151 MB takes 47)
-  const bool streams = own_sum && kind != 2 && M > 64 && 2.0 * N * K > 64.0e6;
+  // Weights that no cache keeps are read once per row of tiles: not on 64-row tiles when there are more rows and k can be sliced, which 128-row tiles
+  // need to fill the chip.  The model has no term for weight bytes.  us, 64 -> 128 rows: 128 x 4608 x 12288 (113 MB) NN 51 -> 39, NT 48 -> 42, 128 x 4800 x
+  // 7168 (69 MB) 32 -> 27, 208 x 7168 x 4800 38 -> 34; below, 128 x 3072 x 8192 (50 MB) 25 -> 27.  The SwiGLU epilogues, which take no slices: 128 x
+  // 4800 x 7168 53 -> 67, its gradient 38 -> 77.
+  const bool streams = own_sum && kind != 2 && M > 64 && 2.0 * N * K > 64.0e6 && epi != EPI_SWIGLU && epi != EPI_DSWIGLU;
   for (int bn = epi == EPI_SWIGLU || bn_min == 128 ? 128 : 64; bn <= 128; bn += 64)
     for (int S = 1; S <= 16; S *= 2) {
       const int k_per = st_k_per(K, S);
       if (S > 1 && ((size_t)S * M * N * 4 > ws_bytes || k_per < 2 * BKS || (long)(S - 1) * k_per >= K)) break;
       if (k_per >= 8192 || streams || (own_sum && !room(S, 64, bn))) continue;
       const long wgs = tiles(64, bn) * S, per_cu = (wgs + 255) / 256;
-      const double t = 2.9e-6 + (double)per_cu * ((k_per + BKS - 1) / BKS) * (bn == 64 ? 0.225e-6 : 0.335e-6) + out / 4.0e12 + slices(S, 64, bn, own_sum);
+      const double t = 2.9e-6 + (double)per_cu * ((k_per + BKS - 1) / BKS) * (bn == 64 ? 0.225e-6 : 0.335e-6) + out / 4.0e12 + slices(S, 64, bn);
       if (t < best_t) {
         best_t = t;
         best = TileChoice{64, bn, S, true};
@@ -2072,7 +2089,7 @@ TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, do
       const int k_per = st_k_per(K, S);
       if (S > 1 && (!room(S, 128, 128) || k_per < 2 * BKS || (long)(S - 1) * k_per >= K)) break;
       const long wgs = tiles(128, 128) * S;
-      const double t = 4.0e-6 + (double)((wgs + 255) / 256) * ((k_per + BKS - 1) / BKS) * 0.6e-6 * (wgs < 218 ? 0.85 : 1.0) + out / 4.0e12 + slices(S, 128, 128, true);
+      const double t = 4.0e-6 + (double)((wgs + 255) / 256) * ((k_per + BKS - 1) / BKS) * 0.6e-6 * (wgs < 218 ? 0.85 : 1.0) + out / (kind == 2 && wgs > 256 ? 3.4e12 : 4.0e12) + slices(S, 128, 128);
       if (t < best_t) {
         best_t = t;
         best = TileChoice{128, 128, S, true};
@@ -2181,7 +2198,7 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
         p.ksplit = t.ksplit;
         p.k_per = g.K / t.ksplit;
         const dim3 sgrid(d.tiles_m * d.tiles_n * t.ksplit);
-        if (g.counters && d.tiles_m * d.tiles_n <= kSliceCounters && (size_t)d.tiles_m * d.tiles_n * t.ksplit * 128 * 256 * 4 <= ws_bytes) {
+        if (g.counters && own_slices(t.ksplit, 128, 256) && d.tiles_m * d.tiles_n <= kSliceCounters && (size_t)d.tiles_m * d.tiles_n * t.ksplit * 128 * 256 * 4 <= ws_bytes) {
           p.part = ws;
           if (whole) hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, true, true, GemmCall>), sgrid, dim3(512), 0, s, p);
           else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, false, true, GemmCall>), sgrid, dim3(512), 0, s, p);

@@ -213,6 +213,20 @@ def test_gemm_choice_for_the_measured_workloads(B):
     assert v(B.GEMM_NT, B.EPI_DSWIGLU, 4096, 1376, 4096, ws) == 301128256      # L4: FC2 input gradient
 
 
+def test_gemm_choice_of_a_pass(B):
+    """Launches of a pass where a kernel that looks cheaper is the slower one (us beside them: chosen, not chosen)."""
+    v = B.lib.oases_pass_gemm_variant
+    ws = 256 << 20
+    assert v(B.GEMM_NT, B.EPI_DSWIGLU, 128, 4800, 7168, ws) == 401064064       # 38, 77 on 38 tiles of 128x128: this epilogue takes no slices
+    assert v(B.GEMM_NN, B.EPI_SWIGLU, 128, 4800, 7168, ws) == 401064128        # 53, 67
+    assert v(B.GEMM_NN, B.EPI_BIAS_GELU, 128, 4608, 12288, ws) // 1000000 > 501  # 39, 51 on 64 rows: weights of 113 MB read once
+    assert v(B.GEMM_TN, B.EPI_F32, 10240, 3840, 520, ws) == 401064128          # 120, 142 on 128x128: several rounds that read and write the output
+    assert v(B.GEMM_TN, B.EPI_F32, 2560, 5120, 808, ws) == 401064128           # 60, 75 on 256x256: k of no whole stages, the register-staged kernel
+    assert v(B.GEMM_NN, B.EPI_F32, 9576, 1536, 1376, ws) == 1256256            # 62, 81 on 128x256: no whole stages, the register-staged kernel
+    assert v(B.GEMM_NN, B.EPI_F32, 208, 7168, 4800, ws) == 502128128           # 34, 43 over four slices of 128x256, no whole stages
+    assert v(B.GEMM_NN, B.EPI_F32, 400, 4096, 8192, ws) == 502128128           # 4 us a layer less than four slices of 128x256 and a second launch
+
+
 # ------------------------------------------------------------------ LLaMA-style layer: schedule and configuration checks
 LLAMA_FWD_TRACE = """\
 compute ROPE.table sb*
