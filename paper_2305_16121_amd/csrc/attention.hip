@@ -47,7 +47,6 @@ struct AttnArgs {
   uint32_t dk0, dk1, dc3, dthresh;
   float dscale;
   int head0, heads_total;
-  const float2* rope;  // backward over blocks of 32 rows: (cos, sin) [seq, D / 2], dQ and dK are stored turned back by them; or nullptr
 };
 
 // Dropout mask of the probabilities: the 4 x 4 block (q div 4, k div 4) of (sequence b, global head) draws one
@@ -166,11 +165,14 @@ __device__ __forceinline__ void turn_back(float& x1, float& x2, const float2& t)
   x2 = b * cs + a * sn;
 }
 
-// sum of the four waves' partial accumulators through LDS: wave w ends up with elements [w*E/8, (w+1)*E/8) of each half of the flattened
-// (tile, element) index -- columns d and d + D/2, which a rotation takes together -- summed over the four partials with the weights sc[0..3]
-template <int E>
-__device__ __forceinline__ int part_element(int wave, int k) { return wave * (E / 8) + k % (E / 8) + (k >= E / 8 ? E / 2 : 0); }
-template <int E>
+// sum of the four waves' partial accumulators through LDS: wave w ends up with elements [w*E/4, (w+1)*E/4) of the flattened (tile, element)
+// index, or (HALVES) with [w*E/8, (w+1)*E/8) of each half of it -- columns d and d + D/2, which a rotation takes together -- summed over
+// the four partials with the weights sc[0..3]
+template <int E, bool HALVES>
+__device__ __forceinline__ int part_element(int wave, int k) {
+  return HALVES ? wave * (E / 8) + k % (E / 8) + (k >= E / 8 ? E / 2 : 0) : wave * (E / 4) + k;
+}
+template <int E, bool HALVES>
 __device__ __forceinline__ void combine4(const f32x16* acc, float* lds_part, int wave, int lane, const float* sc, float* out) {
   __syncthreads();  // every wave is done with its tiles: the staging area is free
 #pragma unroll
@@ -178,7 +180,7 @@ __device__ __forceinline__ void combine4(const f32x16* acc, float* lds_part, int
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < E / 4; k++) {
-    const int e = part_element<E>(wave, k);
+    const int e = part_element<E, HALVES>(wave, k);
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; w++) v += lds_part[(w * E + e) * 64 + lane] * sc[w];
@@ -1042,8 +1044,8 @@ struct WaveLds {  // LDS of a backward workgroup: the larger of the two passes' 
   static_assert(kStageDkv >= kStageDq, "the dK/dV staging area is the larger one");
 };
 
-template <int D, bool CAUSAL, bool DROP>
-__device__ __forceinline__ void wave_dq_block(const AttnArgs& a, int wg, char* lds) {
+template <int D, bool CAUSAL, bool DROP, bool ROPE = false>
+__device__ __forceinline__ void wave_dq_block(const AttnArgs& a, int wg, char* lds, const float2* rope = nullptr) {
   constexpr int KS = D / 16, DT = D / 32, E = DT * 16;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
   int pair, blk;
@@ -1127,36 +1129,35 @@ __device__ __forceinline__ void wave_dq_block(const AttnArgs& a, int wg, char* l
   }
   const float one[4] = {1.f, 1.f, 1.f, 1.f};
   float res[E / 4];
-  combine4<E>(acc, reinterpret_cast<float*>(lds), wave, lane, one, res);
+  combine4<E, ROPE>(acc, reinterpret_cast<float*>(lds), wave, lane, one, res);
   if (qok) {
     uint16_t* op = a.dqkv + (rowbase + qpos) * a.ld + head * D;
 #pragma unroll
-    for (int k = 0; k < E / 8; k += 4) {
-      const int e = part_element<E>(wave, k), dt = e / 16, i = e % 16;
+    for (int k = 0; k < (ROPE ? E / 8 : E / 4); k += 4) {
+      const int e = part_element<E, ROPE>(wave, k), dt = e / 16, i = e % 16;
       const int d = dt * 32 + 8 * (i >> 2) + 4 * g;
-      const float* hi = res + E / 8 + k;
       u32x2 v = {pack_bf16x2(res[k] * a.scale, res[k + 1] * a.scale), pack_bf16x2(res[k + 2] * a.scale, res[k + 3] * a.scale)};
-      u32x2 w = {pack_bf16x2(hi[0] * a.scale, hi[1] * a.scale), pack_bf16x2(hi[2] * a.scale, hi[3] * a.scale)};
-      if (a.rope) {
+      if constexpr (ROPE) {
+        const float* hi = res + E / 8 + k;
+        u32x2 w = {pack_bf16x2(hi[0] * a.scale, hi[1] * a.scale), pack_bf16x2(hi[2] * a.scale, hi[3] * a.scale)};
         float lo_[4], hi_[4];
 #pragma unroll
         for (int j = 0; j < 4; j++) {
           lo_[j] = bf16_bits_to_f32((j & 1) ? v[j >> 1] >> 16 : v[j >> 1] & 0xffffu);
           hi_[j] = bf16_bits_to_f32((j & 1) ? w[j >> 1] >> 16 : w[j >> 1] & 0xffffu);
-          turn_back(lo_[j], hi_[j], a.rope[(size_t)qpos * (D / 2) + d + j]);
+          turn_back(lo_[j], hi_[j], rope[(size_t)qpos * (D / 2) + d + j]);
         }
         v = u32x2{pack_bf16x2(lo_[0], lo_[1]), pack_bf16x2(lo_[2], lo_[3])};
-        w = u32x2{pack_bf16x2(hi_[0], hi_[1]), pack_bf16x2(hi_[2], hi_[3])};
+        *reinterpret_cast<u32x2*>(op + d + D / 2) = u32x2{pack_bf16x2(hi_[0], hi_[1]), pack_bf16x2(hi_[2], hi_[3])};
       }
       *reinterpret_cast<u32x2*>(op + d) = v;
-      *reinterpret_cast<u32x2*>(op + d + D / 2) = w;
     }
   }
 }
 
 // dK, dV of a 32-key block; the four waves split the 32-query tiles that see it
-template <int D, bool CAUSAL, bool DROP>
-__device__ __forceinline__ void wave_dkv_block(const AttnArgs& a, int wg, char* lds) {
+template <int D, bool CAUSAL, bool DROP, bool ROPE = false>
+__device__ __forceinline__ void wave_dkv_block(const AttnArgs& a, int wg, char* lds, const float2* rope = nullptr) {
   constexpr int KS = D / 16, DT = D / 32, E = DT * 16;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
   int pair, kb;
@@ -1258,27 +1259,28 @@ __device__ __forceinline__ void wave_dkv_block(const AttnArgs& a, int wg, char* 
   // accumulator row = key 8*(i/4) + 4g + i%4 of the block, column = d = 32*dt + l%32
   const float one[4] = {1.f, 1.f, 1.f, 1.f};
   float rk_[E / 4], rv_[E / 4];
-  combine4<E>(dk, reinterpret_cast<float*>(lds), wave, lane, one, rk_);
-  combine4<E>(dv, reinterpret_cast<float*>(lds), wave, lane, one, rv_);
+  combine4<E, ROPE>(dk, reinterpret_cast<float*>(lds), wave, lane, one, rk_);
+  combine4<E, ROPE>(dv, reinterpret_cast<float*>(lds), wave, lane, one, rv_);
   uint16_t* dKp = a.dqkv + rowbase * a.ld + a.hp + head * D;
   uint16_t* dVp = dKp + a.hp;
 #pragma unroll
-  for (int k = 0; k < E / 8; k++) {
-    const int e = part_element<E>(wave, k), dt = e / 16, i = e % 16, k2 = E / 8 + k;
+  for (int k = 0; k < (ROPE ? E / 8 : E / 4); k++) {
+    const int e = part_element<E, ROPE>(wave, k), dt = e / 16, i = e % 16;
     const int kp = k_begin + 8 * (i >> 2) + 4 * g + (i & 3), d = dt * 32 + (lane & 31);
     if (kp < k_end && kp >= a.first) {
       const size_t o = (size_t)kp * a.ld + d;
-      uint16_t lo = (uint16_t)f32_to_bf16_bits(rk_[k] * a.scale), hi = (uint16_t)f32_to_bf16_bits(rk_[k2] * a.scale);
-      if (a.rope) {
+      uint16_t lo = (uint16_t)f32_to_bf16_bits(rk_[k] * a.scale);
+      if constexpr (ROPE) {
+        constexpr int H = E / 8;
+        uint16_t hi = (uint16_t)f32_to_bf16_bits(rk_[H + k] * a.scale);
         float x1 = bf16_bits_to_f32(lo), x2 = bf16_bits_to_f32(hi);
-        turn_back(x1, x2, a.rope[(size_t)kp * (D / 2) + d]);
+        turn_back(x1, x2, rope[(size_t)kp * (D / 2) + d]);
         lo = (uint16_t)f32_to_bf16_bits(x1);
-        hi = (uint16_t)f32_to_bf16_bits(x2);
+        dKp[o + D / 2] = (uint16_t)f32_to_bf16_bits(x2);
+        dVp[o + D / 2] = (uint16_t)f32_to_bf16_bits(rv_[H + k]);
       }
       dKp[o] = lo;
-      dKp[o + D / 2] = hi;
       dVp[o] = (uint16_t)f32_to_bf16_bits(rv_[k]);
-      dVp[o + D / 2] = (uint16_t)f32_to_bf16_bits(rv_[k2]);
     }
   }
 }
@@ -1309,13 +1311,24 @@ __global__ __launch_bounds__(NT, 1) void wave_dkv_kernel(AttnArgs a) {  // D = 1
 // are dealt out together -- groups of eight ids (one per XCD) alternate between a dK/dV block and a dQ block, long blocks of
 // both kinds first.  Measured (256 blocks of 2048-token sequences, D = 128): 40 -> 32 us; with 512 blocks and more the single
 // launch is about 10 % slower than two.
+template <int D, bool CAUSAL, bool DROP, bool ROPE>
+__device__ __forceinline__ void both_passes_block(const AttnArgs& a, int n_blocks, const float2* rope, char* lds) {
+  const int w = blockIdx.x, idx = (w >> 4) * 8 + (w & 7);
+  if (idx >= n_blocks) return;  // the last group of eight may be ragged (whole workgroup leaves: no barrier is skipped by part of it)
+  if ((w >> 3) & 1) wave_dq_block<D, CAUSAL, DROP, ROPE>(a, idx, lds, rope);
+  else wave_dkv_block<D, CAUSAL, DROP, ROPE>(a, idx, lds, rope);
+}
 template <int D, bool CAUSAL, bool DROP>
 __global__ __launch_bounds__(NT, 1) void attn_bwd_kernel(AttnArgs a, int n_blocks) {
   __shared__ __attribute__((aligned(16))) char lds[WaveLds<D>::bytes];
-  const int w = blockIdx.x, idx = (w >> 4) * 8 + (w & 7);
-  if (idx >= n_blocks) return;  // the last group of eight may be ragged (whole workgroup leaves: no barrier is skipped by part of it)
-  if ((w >> 3) & 1) wave_dq_block<D, CAUSAL, DROP>(a, idx, lds);
-  else wave_dkv_block<D, CAUSAL, DROP>(a, idx, lds);
+  both_passes_block<D, CAUSAL, DROP, false>(a, n_blocks, nullptr, lds);
+}
+// the same for a pass with rotary embeddings: dQ and dK stored turned back by rope, (cos, sin) [seq, D / 2].  A kernel of its own: with the table
+// among its arguments and the other order of stores the one above took, D = 128, 10.0 -> 10.4 us for 4 x 16 x 8 and 17.6 -> 18.1 for 5 x 80 x 10.
+template <int D, bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(NT, 1) void attn_bwd_rope_kernel(AttnArgs a, int n_blocks, const float2* rope) {
+  __shared__ __attribute__((aligned(16))) char lds[WaveLds<D>::bytes];
+  both_passes_block<D, CAUSAL, DROP, true>(a, n_blocks, rope, lds);
 }
 
 // blocks of `groups` x 32 rows over the positions of the row range
@@ -1478,7 +1491,7 @@ int launch_attention_bwd(const void* qkv, const void* out, const void* dout, con
   const int n_blocks = nseq * a.blocks * heads;  // of 32 rows
   const BwdPlan plan = bwd_plan(a, nseq, batch, head_dim, pin);
   if (rope && !plan.one_launch) { set_error("attention_bwd: dQ and dK are turned back by the kernel of both passes only"); return OASES_EINVAL; }
-  a.rope = reinterpret_cast<const float2*>(rope);
+  const float2* const table = reinterpret_cast<const float2*>(rope);
   const bool one_launch = plan.one_launch, own_delta = plan.own_delta;
   const int qg = plan.qg;
   if (!own_delta && !delta_ready) {
@@ -1497,7 +1510,8 @@ int launch_attention_bwd(const void* qkv, const void* out, const void* dout, con
 #define OASES_ATTN_BWD(DD, CC, DR)                                                                                  \
   do {                                                                                                              \
     if (one_launch) {                                                                                               \
-      hipLaunchKernelGGL((attn_bwd_kernel<DD, CC, DR>), bgrid, block, 0, s, a, n_blocks);                           \
+      if (table) hipLaunchKernelGGL((attn_bwd_rope_kernel<DD, CC, DR>), bgrid, block, 0, s, a, n_blocks, table);    \
+      else hipLaunchKernelGGL((attn_bwd_kernel<DD, CC, DR>), bgrid, block, 0, s, a, n_blocks);                      \
     } else {                                                                                                        \
       if (qg == 2) OASES_ATTN_DQ(DD, 2, CC, DR);                                                                    \
       else if constexpr (DD == 64) OASES_ATTN_DQ(DD, 1, CC, DR);                                                    \

@@ -68,6 +68,14 @@ def test_attention_forward_registers(kernels):
             assert k[".vgpr_count"] + k[".agpr_count"] <= 128 and k[".group_segment_fixed_size"] <= 40960, (n, k[".vgpr_count"])
 
 
+def test_attention_backward_arguments(kernels):
+    """A backward that turns nothing back is not given the rotation's table (nor the order of stores that goes with it)."""
+    some = {n: k[".kernarg_segment_size"] for n, k in kernels.items() if n.startswith(("attn_bwd_", "attn_dkv", "wave_d"))}
+    assert len(some) == 36
+    for n, size in some.items():
+        assert size == (152 if n.startswith("attn_bwd_rope") else 140 if n.startswith("attn_bwd") else 136), n
+
+
 def test_gemm_arguments(kernels):
     """A GEMM kernel of one problem is given what it reads: 88 bytes, and 32 more where it adds up its own k slices or leaves row sums behind."""
     some = [n for n in kernels if n.startswith("gemm_") and "group" not in n]
