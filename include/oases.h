@@ -324,6 +324,9 @@ int oases_op_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace
  * result bit for bit), with counters that the pass keeps at zero in its workspace, while a tile's other slices come to no more than 208 KiB of
  * partial sums, and the counters and partial sums have room; a second launch adds up the others. */
 int oases_pass_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace_bytes);
+/* The kernel with which a handle's backward forms the gradient of the attention output (NT, K = hidden, bf16) and leaves delta = rowsum(dO * O) of
+ * the attention backward behind, W = 4 or 5 of the same encoding; 0 where delta is left to the attention backward.  Host only. */
+int oases_pass_delta_variant(const oases_handle *h);
 /* oases_op_gemm on the instantiation `variant` names (encoding above) instead of the one the library would choose:
  * for tests and tuning sweeps.  EINVAL if no such instantiation exists (block tiles 256x256, 128x256, 256x128,
  * 128x128; W = 1 only with the rectangular ones; W = 2, 3 only as x01256256, x01128256, x02128256 or x04128256 on shapes they fit, W = 4 as 4SS064064 or 4SS064128, W = 5 as 5SS128128; 1..8

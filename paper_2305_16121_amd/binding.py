@@ -75,6 +75,7 @@ _sig("oases_op_rope", _i, _P, _i, _i, _i64, _i, _i, _i, _P, _i, _P)
 _sig("oases_op_gemm", _i, _i, _i, _i, _i, _i, _P, _i, _P, _i, _P, _i, _P, _P, _i, _P, _sz, _P)
 _sig("oases_op_gemm_variant", _i, _i, _i, _i, _i, _i, _sz)
 _sig("oases_pass_gemm_variant", _i, _i, _i, _i, _i, _i, _sz)
+_sig("oases_pass_delta_variant", _i, _P)
 _sig("oases_op_gemm_tn_pair", _i, _i, _i, _i, _P, _i, _P, _i, _P, _i, _i, _i, _P, _i, _P, _i, _P, _i, _P)
 _sig("oases_op_gemm_tn_pair_wins", _i, _i, _i, _i, _i, _i)
 _sig("oases_op_gemm_tn_group", _i, _i, _i, _i, _i, _P, _i, _P, _i, _P, _i, _i, _i, _P, _i, _P, _i, _P, _i, _P, _sz, _P)
@@ -156,6 +157,10 @@ class Handle:
     @property
     def gemm_workspace_bytes(self) -> int:
         return lib.oases_gemm_workspace_bytes(self._h)
+
+    @property
+    def pass_delta_variant(self) -> int:
+        return lib.oases_pass_delta_variant(self._h)
 
     def schedule(self, backward: bool) -> str:
         n = lib.oases_schedule_dump(self._h, int(backward), None, 0)

@@ -1131,6 +1131,7 @@ int oases_pass_gemm_variant(int op, int epi, int M, int N, int K, size_t workspa
   if (op < 0 || op > 2 || M <= 0 || N <= 0 || K <= 0) { set_error("oases_pass_gemm_variant: bad argument"); return OASES_EINVAL; }
   return gemm_variant(op, epi, M, N, K, workspace_bytes, true);
 }
+int oases_pass_delta_variant(const oases_handle* h) { return h ? h->proj_delta : OASES_ENULL; }
 int oases_op_gemm_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0, void* C0, int ldc0, int M1, int N1,
                           const void* A1, int lda1, const void* B1, int ldb1, void* C1, int ldc1, void* stream) {
   return launch_gemm_tn_pair(K, M0, N0, A0, lda0, B0, ldb0, C0, ldc0, M1, N1, A1, lda1, B1, ldb1, C1, ldc1, (hipStream_t)stream);

@@ -15,6 +15,7 @@ CASES = [(32, 72, 8, 64, 1, 0.0),                   # 512 / 768: two groups, the
          (32, 72, 8, 128, 0, 0.0),
          (8, 200, 16, 128, 1, 0.0),                 # 512 / 896
          (8, 200, 16, 64, 1, 0.2),
+         (8, 200, 16, 128, 0, 0.2),
          (16, 96, 8, 128, 1, 0.3),                  # 256 / 384, short: two groups
          (2, 520, 8, 64, 1, 0.0),                   # 144 / 272: one group, two launches
          (2, 520, 8, 64, 0, 0.1),

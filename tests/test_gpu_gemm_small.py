@@ -66,21 +66,24 @@ def test_small_tiles_swiglu(B, ll, M, fp, K):
     g = gen(M + fp + K)
     a, wg, wu = bf16_round(randn(g, M, K)), bf16_round(randn(g, K, fp, scale=0.05)), bf16_round(randn(g, K, fp, scale=0.05))
     ad, wd = dev(a, torch.bfloat16), dev(interleave(wg, wu), torch.bfloat16)
-    f = torch.full((M, fp + 8), 7.0, dtype=torch.bfloat16, device="cuda")
-    gu = torch.full((M, 2 * fp + 8), 7.0, dtype=torch.bfloat16, device="cuda")
-    fwd = (B.GEMM_NN, B.EPI_SWIGLU, M, 2 * fp, K, ad.data_ptr(), K, wd.data_ptr(), 2 * fp, f.data_ptr(), fp + 8, None, gu.data_ptr(), 2 * fp + 8, None, 0, None)
-    assert B.lib.oases_op_gemm_forced(401064064, *fwd) == B.EINVAL     # gate and up columns must meet in one wave
-    B.check(B.lib.oases_op_gemm_forced(401064128, *fwd))
     gate, up = a.double() @ wg.double(), a.double() @ wu.double()
-    assert_bf16_close(gu[:, :2 * fp].float(), interleave(gate, up), 1e-5, 2e-6 * float(gate.abs().max()))
-    assert_bf16_close(f[:, :fp].float(), ll.silu(gate) * up, 1e-4, 1e-5)
-    assert bool((f[:, fp:] == 7.0).all()) and bool((gu[:, 2 * fp:] == 7.0).all())
+    for variant in (401064064, 401064128, 501128128):
+        f = torch.full((M, fp + 8), 7.0, dtype=torch.bfloat16, device="cuda")
+        gu = torch.full((M, 2 * fp + 8), 7.0, dtype=torch.bfloat16, device="cuda")
+        fwd = (B.GEMM_NN, B.EPI_SWIGLU, M, 2 * fp, K, ad.data_ptr(), K, wd.data_ptr(), 2 * fp, f.data_ptr(), fp + 8, None, gu.data_ptr(), 2 * fp + 8, None, 0, None)
+        if variant == 401064064:
+            assert B.lib.oases_op_gemm_forced(variant, *fwd) == B.EINVAL     # gate and up columns must meet in one wave
+            continue
+        B.check(B.lib.oases_op_gemm_forced(variant, *fwd))
+        assert_bf16_close(gu[:, :2 * fp].float(), interleave(gate, up), 1e-5, 2e-6 * float(gate.abs().max()))
+        assert_bf16_close(f[:, :fp].float(), ll.silu(gate) * up, 1e-4, 1e-5)
+        assert bool((f[:, fp:] == 7.0).all()) and bool((gu[:, 2 * fp:] == 7.0).all())
     w2 = bf16_round(randn(g, fp, K, scale=0.05))
     w2d = dev(w2, torch.bfloat16)
     dF = a.double() @ w2.double().t()
     gs = gu[:, :2 * fp].float().cpu().double().reshape(M, fp // 32, 2, 32)
     gst, ust = gs[:, :, 0].reshape(M, fp), gs[:, :, 1].reshape(M, fp)
-    for variant in (401064064, 401064128):
+    for variant in (401064064, 401064128, 501128128):
         dgu = torch.full((M, 2 * fp + 8), 7.0, dtype=torch.bfloat16, device="cuda")
         B.check(B.lib.oases_op_gemm_forced(variant, B.GEMM_NT, B.EPI_DSWIGLU, M, fp, K, ad.data_ptr(), K, w2d.data_ptr(), K, dgu.data_ptr(), 2 * fp + 8, None,
                                            gu.data_ptr(), 2 * fp + 8, None, 0, None))

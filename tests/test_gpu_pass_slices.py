@@ -80,18 +80,29 @@ def test_bias_gradients_that_come_with_the_weight_gradients(M, h):
     H.close()
 
 
-@pytest.mark.parametrize("h,d,seq,batch", [(512, 64, 72, 3), (512, 128, 200, 1), (1024, 64, 264, 2), (2048, 128, 40, 5), (2048, 64, 128, 1), (4096, 64, 136, 2)])
-def test_delta_that_comes_with_the_gradient_of_the_attention_output(h, d, seq, batch):
-    """delta = rowsum(dO * O) per head, which small tiles that hold whole heads leave behind with dO (64 or 128 columns, with and without k slices; last
-    tiles of rows that are not whole, sequences that end inside a tile), against the arrays of the pass in 64 bits."""
+# ..., kernel that leaves delta behind (0: none does, delta is the attention backward's own).  501128128 with 4608 and 1024 columns: the two
+# launches of the attention backward; the others its single launch
+@pytest.mark.parametrize("h,d,seq,batch,tp,causal,variant", [
+    (512, 64, 72, 3, 1, 1, 401064064), (512, 128, 200, 1, 1, 1, 401064128), (1024, 64, 264, 2, 1, 1, 0), (2048, 128, 40, 5, 1, 1, 404064128),
+    (2048, 64, 128, 1, 1, 1, 404064064), (4096, 64, 136, 2, 1, 1, 0),
+    (4608, 64, 72, 1, 1, 1, 402064128),       # two heads a tile
+    (5632, 64, 368, 1, 8, 1, 404064128),      # the same with an odd number of heads: the last tile holds one
+    (10240, 64, 72, 1, 2, 1, 505128128),
+    (1024, 128, 840, 3, 1, 0, 501128128),     # a last tile of 88 rows
+    (4608, 128, 1376, 2, 4, 1, 501128128),
+    (4608, 128, 200, 1, 1, 0, 503128128),     # a last tile of 72 rows
+])
+def test_delta_that_comes_with_the_gradient_of_the_attention_output(h, d, seq, batch, tp, causal, variant):
+    """delta = rowsum(dO * O) per head, which small tiles that hold whole heads leave behind with dO (with and without k slices; last tiles of rows
+    and of heads that are not whole, sequences that end inside a tile), against the arrays of the pass in 64 bits."""
     from paper_2305_16121_amd import binding as B
-    M = seq * batch
-    H = B.Handle(B.make_cfg(dict(hidden=h, n_heads=h // d, seq=seq, batch=batch, tp=1, n_sub=1, n_layers=1, causal=1, dropout_p=0.0), seed=1))
-    assert B.lib.oases_pass_gemm_variant(1, 1, M, h, h, H.gemm_workspace_bytes) >= 400000000
+    M, hp, fp = seq * batch, h // tp, 4 * h // tp
+    H = B.Handle(B.make_cfg(dict(hidden=h, n_heads=h // d, seq=seq, batch=batch, tp=tp, n_sub=1, n_layers=1, causal=causal, dropout_p=0.0), seed=1))
+    assert H.pass_delta_variant == variant
     g = torch.Generator(device="cuda").manual_seed(M)
     n = lambda *s: torch.randn(s, generator=g, device="cuda")
-    W = {k: (n(*s) / h ** 0.5).bfloat16() for k, s in dict(wqkv=(h, 3 * h), wo=(h, h), w1=(h, 4 * h), w2=(4 * h, h)).items()}
-    W.update(bqkv=n(3 * h), bo=n(h), b1=n(4 * h), b2=n(h), ln1_g=n(h), ln1_b=n(h), ln2_g=n(h), ln2_b=n(h))
+    W = {k: (n(*s) / h ** 0.5).bfloat16() for k, s in dict(wqkv=(h, 3 * hp), wo=(hp, h), w1=(h, fp), w2=(fp, h)).items()}
+    W.update(bqkv=n(3 * hp), bo=n(h), b1=n(fp), b2=n(h), ln1_g=n(h), ln1_b=n(h), ln2_g=n(h), ln2_b=n(h))
     G = {k: torch.zeros(v.shape, device="cuda") for k, v in W.items()}
     x, y, dx = n(M, h), torch.empty(M, h, device="cuda"), torch.empty(M, h, device="cuda")
     ws = torch.full((H.workspace_bytes,), 0xFF, dtype=torch.uint8, device="cuda")
@@ -102,8 +113,8 @@ def test_delta_that_comes_with_the_gradient_of_the_attention_output(h, d, seq, b
     def tensor(name, dtype):
         off, nb = H.tensor_span(name, 0)
         return ws[off:off + nb].view(dtype)
-    products = (tensor("da", torch.bfloat16).double() * tensor("attn", torch.bfloat16).double()).view(batch, seq, h // d, d)
-    got = tensor("delta", torch.float32).double().view(batch, h // d, seq)
+    products = (tensor("da", torch.bfloat16).double() * tensor("attn", torch.bfloat16).double()).view(batch, seq, hp // d, d)
+    got = tensor("delta", torch.float32).double().view(batch, hp // d, seq)
     err = (got - products.sum(dim=3).transpose(1, 2)).abs()
     bound = d * 2.0 ** -24 * products.abs().sum(dim=3).transpose(1, 2)  # d roundings at most of partial sums below the sum of the magnitudes
     assert bool((err <= bound + 1e-30).all()), float((err / (bound + 1e-30)).max())
