@@ -321,7 +321,7 @@ int oases_op_gemm(int op, int epi, int M, int N, int K, const void *A, int lda, 
  * Host only; used to group per-operator timings by kernel. */
 int oases_op_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace_bytes);
 /* The same for a GEMM of a pass.  There the launches of the W = 3, 4 and 5 kernels add up their k slices themselves, in slice order (the same
- * result bit for bit), with counters that the pass keeps at zero in its workspace, while a tile's other slices come to no more than 208 KiB of
+ * result bit for bit), with counters that the pass keeps at zero in its workspace, while a tile's other slices come to no more than 128 KiB of
  * partial sums, and the counters and partial sums have room; a second launch adds up the others. */
 int oases_pass_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace_bytes);
 /* The kernel with which a handle's backward forms the gradient of the attention output (NT, K = hidden, bf16) and leaves delta = rowsum(dO * O) of

@@ -1910,10 +1910,10 @@ int launch_one(const GemmArgs& g0, int ksplit, float* ws, hipStream_t s) {
 
 // Whether a launch of a pass adds up its own k slices, or a second launch does: the last workgroup of a tile reads the other slices' sums at some
 // 47 GB/s; a second launch costs 6 to 9 us inside a step.  us, own -> two launches: inside a step 400 x 2560 x 5120 over three of 128x128 25.3 -> 30,
-// 256 x 256 x 12600 TN over eight of 64x64 14 -> 17; over four of 128x256 two launches are the faster (forward pass of three layers with 400 x 4096 x
-// 8192 519 -> 508, of two with 304 x 3840 x 10240 and 304 x 5120 x 10240 468 -> 449, of one with 160 x 5632 x 11264 207 -> 198);
-// over two of 128x256 the two are within 1 % of a step (24 of them).
-inline bool own_slices(int slices, int bm, int bn) { return (slices - 1) * bm * bn * 4 <= 208 << 10; }
+// 256 x 256 x 12600 TN over eight of 64x64 14 -> 17; four of 128x128 128 x 6144 x 12288 56 -> 46 + 5.4, NT 75 -> 66 + 6.1 (19 steps 0 to 2 % shorter); over four
+// of 128x256 forward pass of three layers with 400 x 4096 x 8192 519 -> 508, of two with 304 x 3840 x 10240 and 304 x 5120 x 10240 468 -> 449, of
+// one with 160 x 5632 x 11264 207 -> 198; over two of 128x256 the two are within 1 % of a step (24 of them).
+inline bool own_slices(int slices, int bm, int bn) { return (slices - 1) * bm * bn * 4 <= 128 << 10; }
 inline int st_k_per(int K, int slices) { return ((K + slices - 1) / slices + BKS - 1) / BKS * BKS; }  // k of one slice
 
 template <int TM, int TN, int NS, bool A_KC, bool B_KC, int EPI>
@@ -2048,11 +2048,11 @@ TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, do
   const KindTable& kt = g_kinds[kind];
   const double out = (double)M * N * (epi == EPI_F32 ? 4.0 : kind == 2 ? 8.0 : epi == EPI_SWIGLU ? 3.0 : epi == EPI_DSWIGLU ? 8.0 : epi == EPI_BIAS_GELU || epi == EPI_DGELU ? 4.0 : 2.0);
   auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  // a second launch: 3.2 us by itself, up to 9 in a pass (see own_slices; at 6.5 400 x 4096 x 8192 goes to four slices of 128x256, 508 us for that
-  // pass, 490 on two of 128x128)
+  // a second launch: 3.2 us by itself; in a pass (see own_slices) 6.2, behind 128x256 tiles 9.  At 6.5 there 400 x 4096 x 8192 goes to four slices of
+  // 128x256, 508 us for that pass, 490 on two of 128x128; at 9 behind 128x128 tiles, too, six of 18 passes take 2 to 4 % more.
   auto slices = [&](int S, int bm, int bn) {
     const bool own = own_sum && (bn_min || own_slices(S, bm, bn));
-    return S <= 1 ? 0.0 : 2.0 * S * M * N * 4.0 / 6.0e12 + (own ? 2.0e-6 + (S - 1) * bm * bn * 4.0 / 47.0e9 : own_sum ? 9.0e-6 : 3.2e-6);
+    return S <= 1 ? 0.0 : 2.0 * S * M * N * 4.0 / 6.0e12 + (own ? 2.0e-6 + (S - 1) * bm * bn * 4.0 / 47.0e9 : own_sum ? (bm * bn > 128 * 128 ? 9.0e-6 : 6.2e-6) : 3.2e-6);
   };
   auto room = [&](int S, int bm, int bn) {  // partial sums and counters of slices that the launch adds up
     return S <= 1 || (tiles(bm, bn) <= kSliceCounters && (size_t)tiles(bm, bn) * S * bm * bn * 4 <= ws_bytes);
@@ -2399,11 +2399,12 @@ static double tn_single_seconds(int M, int N, int K, size_t ws_bytes) {
   t = pp_seconds(c.bm, (long)((M + c.bm - 1) / c.bm) * ((N + 255) / 256) * c.ksplit, K / c.ksplit, 8.0 * M * N);
   return c.ksplit > 1 ? t + 2.0e-6 + 2.7e-6 * (c.ksplit - 1) : t;
 }
-// Which kernel, how many slices, and whether one launch takes less time than two.  k slices cost 2 us and 2.7 us each: the last
-// workgroup of a tile reads the others' sums one after the other.  Both sides measured, us, two launches -> one: 8192 rows,
-// 2048x2048 twice 141 -> 116 (one round instead of two with slices), 512x2048 and 2048x1536 84 -> 68 (two slices; one 83, four 81), 1376x4096 and
-// 4096x2752 268 -> 290 (stays two launches: 176 tiles of 256x256 each fill one round); 4096 rows, 1024x1024 twice 35 -> 26; 2048
-// rows, 256x1024 and 1024x768 18 -> 12; 512 rows, 1024x512 twice 9.7 -> 7.
+// Which kernel, how many slices, and whether one launch takes less time than two.  k slices cost 2 us and 2.7 us each: the last workgroup of a tile
+// reads the others' sums one after the other.  Inside a step, us, two launches -> one (small tiles bring the bias gradient along, which is a launch of
+// its own beside two: + its time): 8192 rows, 2048x2048 twice 170 -> 125 (one round instead of two with slices), 512x2048 and 2048x1536 119 -> 85
+// (two slices); 4096 rows, 1024x1024 twice 34 to 48 + 5 -> 34 (64x128; four slices of 128x256 38 + 5, 64x64 36), 256x1024 and 1024x768 32 + 5 -> 23 (64x64; 64x128 33); 2048
+// rows, the same 21 + 4 -> 20 and 19 + 4 -> 13.5; 512 rows, 1024x512 twice 11.4 + 2.4 -> 7.3 (64x64; 64x128 9.4); 128 rows, 12288x6144 and 6144x12288
+// 282 + 5 -> 272.  8192 rows, 1376x4096 and 4096x2752 stay two (118 and 173; by themselves 268 together, one launch 290).
 int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes, bool* wins) {
   const double out = ((double)M0 * N0 + (double)M1 * N1) * 8.0;
   double best_t = 1e30;
