@@ -292,7 +292,8 @@ def main():
                       "frac_of_bf16_peak": round(tflops / PEAK_BF16_TFLOPS, 4)}}
 
     # HIP-event timers around every operator of the step.  A profiling handle executes its sub-batches one by one, so it is
-    # given as many as the timed handle works in parts: the same launches.  Serialised, so that a bracket holds one operator.
+    # given as many as the timed handle works in parts: the same operators, though a pass of short layers may launch fewer kernels (weight
+    # gradients of a block together, bias sums, delta and inverse rotation with other kernels).  Serialised, so that a bracket holds one operator.
     if not a.no_profile:
         HP = wl.handle(B.FLAG_SERIALISE | B.FLAG_PROFILE | (B.FLAG_RECOMPUTE if a.recompute else 0), n_sub=H.pass_parts)
         pcfg = dict(cfg, n_sub=H.pass_parts)

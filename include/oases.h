@@ -130,7 +130,8 @@ int oases_create(const oases_layer_cfg *cfg, oases_handle **out);
 void oases_destroy(oases_handle *h);
 
 /* Bytes of caller-allocated device workspace (activation stash of all layers + backward scratch).
- * The same workspace must be passed to oases_forward and to the oases_backward that follows it; every call that takes
+ * The same workspace must be passed to oases_forward and to the oases_backward that follows it (a caller that keeps its contents elsewhere in
+ * between keeps all of them: the counters of k slices that the forward pass leaves at zero are part of it); every call that takes
  * a workspace also takes its size in bytes and returns OASES_EWORKSPACE, before any launch, if that is less than this. */
 size_t oases_workspace_bytes(const oases_handle *h);
 /* Host only: into how many parts of consecutive sub-batches oases_forward / oases_backward and the segment-level calls divide the
@@ -191,8 +192,10 @@ int oases_backward_segment(oases_handle *h, int layer, int segment, const oases_
                            const void *dy, void *dx, const oases_grads *g, void *workspace, size_t workspace_bytes,
                            void *partial_out, const void *reduced_in, void *stream);
 
-/* The operator order of the schedule (what a handle with OASES_FLAG_PROFILE executes; any other one the same operators over
- * oases_pass_parts parts on one stream) as text, one operator per line
+/* The operator order of the schedule (what a handle with OASES_FLAG_PROFILE executes; any other one the same work over
+ * oases_pass_parts parts on one stream, where a pass of one part may take the two weight gradients of a block as one launch, bias sums with
+ * weight gradients, the attention backward's delta with the gradient of its input, and the inverse rotation with the attention backward: the
+ * rows of oases_profile_read describe this schedule, not the launches of such a pass) as text, one operator per line
  * ("<stream> <op> L<layer> sb<sub-batch>", "sb*" = all sub-batches at once), NUL-terminated into buf (at most n bytes).
  * Returns the number of bytes the full text needs (like snprintf).  Host only. */
 int oases_schedule_dump(const oases_handle *h, int backward, char *buf, size_t n);

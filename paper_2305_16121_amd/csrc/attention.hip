@@ -862,7 +862,7 @@ __device__ __forceinline__ void attn_dkv_block(const AttnArgs& a, int wg, char* 
 // next tile: the products S and dP of tile t+1 stand between the exponentials of tile t.  Three stages: tile t+1 is read for these
 // products, tile t for dV and dK, and tile t+2 written over tile t-1, whose last reads lie before the barrier that ended
 // iteration t-1.  Measured (both backward
-// passes, us): 4x2048x4x128 causal 148 -> 122, not causal 222 -> 173, 8x1024x8x128 174 -> 152, 8x512x4x128 42 -> 35.
+// passes by themselves, us; inside a step of h 4096 the first 151 -> 132): 4x2048x4x128 causal 148 -> 122, not causal 222 -> 173, 8x1024x8x128 174 -> 152, 8x512x4x128 42 -> 35.
 // =================================================================================================
 struct Dkv128Lds {
   static constexpr int kTile = SharedTile<128, 64>::bytes, kStage = 2 * kTile + 512;  // Q, dO, lse * log2(e) [64], delta [64]
