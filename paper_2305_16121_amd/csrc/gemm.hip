@@ -2037,11 +2037,11 @@ double pp_seconds(int bm, long wgs, int k_per, double out_bytes) {
 // us, large tile -> small: 4096 x 1536 x 2048 NN bias 31.6 -> 34.8 (stays large), 1024 x 3072 x 8192 56.2 -> 71.6 (stays
 // large), 4096 x 512 x 4096 NT 29.8 -> 22.9, 1024 x 1024 x 4096 TN 21.4 -> 16.9, 64 x 4608 x 12288 NN 53.5 -> 34.8,
 // 6144 x 12288 x 128 TN 195 -> 152.  Slices of 8192 k and more stay with the large tiles.
-// own_sum: the launch adds its slices up by itself (SliceSum): a call of a pass.  The last workgroup of a tile then reads the other slices'
-// sums, one after the other at some 47 GB/s, instead of a second launch (own_slices); 128x128 tiles on the same scheme are candidates, with any
+// own_sum: a call of a pass, whose launches add up a few slices by themselves (SliceSum, own_slices): the last workgroup of a tile then reads the other
+// slices' sums, one after the other at some 47 GB/s, instead of a second launch; 128x128 tiles on the same scheme are candidates, with any
 // number of slices (0.6 us a stage, 0.85 of that where 218 and fewer workgroups leave CUs idle and the others more of the power; what TN reads and writes moves at
-// 3.4 TB/s from the second round on, since a CU holds one workgroup: 10240 x 3840 x 208 92 us on 64x128, 118 on 128x128).  Measured, us, the choice without -> with: inside a step 128 x 4608 x 12288 NN 52 -> 48
-// (register-staged kernel over eight slices -> 128x128 over six), NT 128 x 6144 x 12288 78 -> 75; 512 x 8192 x 3072 NT 47 -> 36, 8192 x 512 x
+// 3.4 TB/s from the second round on, since a CU holds one workgroup: 10240 x 3840 x 208 92 us on 64x128, 118 on 128x128).  Measured, us, the choice without -> with, second launches
+// included: inside a step 128 x 4608 x 12288 NN 52 -> 45 (register-staged kernel over eight slices -> 128x128 over six), NT 128 x 6144 x 12288 79 -> 71 (over five); 512 x 8192 x 3072 NT 47 -> 36, 8192 x 512 x
 // 2048 NT 31 -> 26, 200 x 3072 x 8192 36 -> 27; 1488 x 3072 x 3072 NN stays on 144 tiles of 128x256 (40; 64x128 over two slices 72).
 TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, double* seconds = nullptr, bool own_sum = false, int bn_min = 0) {
   const TileChoice large = pick_large_tile(kind, epi, M, N, K, ws_bytes);
