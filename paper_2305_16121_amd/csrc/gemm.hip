@@ -359,6 +359,129 @@ __device__ __forceinline__ void epilogue_tile_swiglu(const GemmArgs& g, int row0
   }
 }
 
+// ---- accumulators of v_mfma_f32_16x16x32_bf16 (the eight-wave and small-tile kernels) -------------------------------------------------
+// A lane l holds row l%16, k = 8*(l/16)..+7; B the same with columns.  The B fragment comes first, so that element e of lane l is
+// C[l%16][4*(l/16) + e]: a lane owns four consecutive columns.  Two tiles of 16 columns side by side make 32 columns of a row: between them
+// v_permlane16_swap turns "columns 4 (l/16)..+3 of either tile" into eight columns of one tile (its own inverse), so that bf16 arrays are read
+// and written 16 bytes at a time.
+__device__ __forceinline__ void swap_rows16(u32x2& x, u32x2& y) {
+#pragma unroll
+  for (int k = 0; k < 2; k++) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x[k], y[k], false, false);
+    x[k] = r[0];
+    y[k] = r[1];
+  }
+}
+__device__ __forceinline__ int col16(int lane) { return 16 * ((lane >> 4) & 1) + 8 * (lane >> 5); }  // the lane's eight columns behind the swap
+// fp32 outputs (EPI_F32, EPI_ACC_F32): the A fragment first, element e of lane l is C[4*(l/16) + e][l%16]; the same swap between the two tiles makes x the
+// rows 8*(l/32) + e, columns l%32, and y the rows 4 further on: half a wave writes and reads whole lines of 128 bytes in the order of its lanes.
+constexpr bool epi_rows(int epi) { return epi == EPI_F32 || epi == EPI_ACC_F32; }
+__device__ __forceinline__ void swap_lines(f32x4& x, f32x4& y) {
+#pragma unroll
+  for (int e = 0; e < 4; e++) {
+    const float xe = x[e], ye = y[e];
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, xe), __builtin_bit_cast(uint32_t, ye), false, false);
+    const uint32_t r0 = r[0], r1 = r[1];
+    x[e] = __builtin_bit_cast(float, r0);
+    y[e] = __builtin_bit_cast(float, r1);
+  }
+}
+// requests ahead of the first store, as epi_request: 16 rows x 32 columns from (row0, col0)
+template <int EPI, bool FULL>
+__device__ __forceinline__ void epi_request16(const GemmArgs& g, int row0, int col0, int lane, EpiOperands (&o)[2]) {
+  if constexpr (EPI == EPI_ACC_F32) {
+    int col = col0 + (lane & 31);
+    if (!FULL) col = min(col, g.N - 1);
+#pragma unroll
+    for (int t = 0; t < 2; t++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        int row = row0 + 8 * (lane >> 5) + 4 * t + e;
+        if (!FULL) row = min(row, g.M - 1);
+        o[t].f[e] = reinterpret_cast<const float*>(g.C)[(size_t)row * g.ldc + col];
+      }
+    return;
+  }
+  int row = row0 + (lane & 15);
+  if (!FULL) row = min(row, g.M - 1);
+  if constexpr (EPI == EPI_DGELU || EPI == EPI_DSWIGLU) {
+    int col = col0 + col16(lane);
+    if (!FULL) col = min(col, g.N - 8);
+    const uint16_t* p = g.aux + (size_t)row * g.ldaux + col + (EPI == EPI_DSWIGLU ? (col & ~31) : 0);
+    load_quarters(p, o[0].a, o[1].a);
+    if constexpr (EPI == EPI_DSWIGLU) load_quarters(p + 32, o[0].b, o[1].b);
+  } else {
+#pragma unroll
+    for (int t = 0; t < 2; t++) {
+      int col = col0 + 16 * t + 4 * (lane >> 4);
+      if (!FULL) col = min(col, g.N - 4);
+      o[t] = epi_load<EPI>(g, row, col);
+    }
+  }
+}
+template <int EPI, bool FULL>
+__device__ __forceinline__ void epi_finish16(const GemmArgs& g, int row0, int col0, int lane, const f32x4& a0, const f32x4& a1, const EpiOperands (&o)[2]) {
+  if constexpr (EPI == EPI_F32 || EPI == EPI_ACC_F32) {
+    f32x4 v[2] = {a0, a1};
+    swap_lines(v[0], v[1]);
+    const int col = col0 + (lane & 31);
+    if (!FULL && col >= g.N) return;
+    float* cp = reinterpret_cast<float*>(g.C) + col;
+#pragma unroll
+    for (int t = 0; t < 2; t++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const int row = row0 + 8 * (lane >> 5) + 4 * t + e;
+        if (!FULL && row >= g.M) continue;
+        cp[(size_t)row * g.ldc] = EPI == EPI_ACC_F32 ? o[t].f[e] + v[t][e] : v[t][e];
+      }
+  } else {
+    const int row = row0 + (lane & 15);
+    if (!FULL && row >= g.M) return;
+    EpiOperands x = o[0], y = o[1];
+    if constexpr (EPI == EPI_DGELU || EPI == EPI_DSWIGLU) swap_rows16(x.a, y.a);
+    if constexpr (EPI == EPI_DSWIGLU) swap_rows16(x.b, y.b);
+    u32x2 out[2], also[2];
+    epi_bf16<EPI>(a0, x, out[0], also[0]);
+    epi_bf16<EPI>(a1, y, out[1], also[1]);
+    swap_rows16(out[0], out[1]);
+    if constexpr (EPI == EPI_DSWIGLU || EPI == EPI_BIAS_GELU) swap_rows16(also[0], also[1]);
+    const int col = col0 + col16(lane);
+    if (!FULL && col >= g.N) return;
+    uint16_t* cp = reinterpret_cast<uint16_t*>(g.C) + (size_t)row * g.ldc + col + (EPI == EPI_DSWIGLU ? (col & ~31) : 0);
+    *reinterpret_cast<u32x4_align8*>(cp) = u32x4{out[0][0], out[0][1], out[1][0], out[1][1]};
+    if constexpr (EPI == EPI_DSWIGLU) *reinterpret_cast<u32x4_align8*>(cp + 32) = u32x4{also[0][0], also[0][1], also[1][0], also[1][1]};
+    if constexpr (EPI == EPI_BIAS_GELU)
+      *reinterpret_cast<u32x4_align8*>(g.aux + (size_t)row * g.ldaux + col) = u32x4{also[0][0], also[0][1], also[1][0], also[1][1]};
+  }
+}
+// SwiGLU: gate columns col0 .. col0+31 of the interleaved layout in g0, g1, the up columns behind them in u0, u1
+template <bool FULL>
+__device__ __forceinline__ void epi_swiglu16(const GemmArgs& g, int row0, int col0, int lane, const f32x4& g0, const f32x4& g1, const f32x4& u0, const f32x4& u1) {
+  const int row = row0 + (lane & 15);
+  if (!FULL && row >= g.M) return;
+  u32x2 pg[2], pu[2], pf[2];
+#pragma unroll
+  for (int t = 0; t < 2; t++) {
+    const f32x4& ag = t ? g1 : g0;
+    const f32x4& au = t ? u1 : u0;
+    float f[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) f[e] = silu_f(ag[e]) * au[e];
+    pg[t] = u32x2{pack_bf16x2(ag[0], ag[1]), pack_bf16x2(ag[2], ag[3])};
+    pu[t] = u32x2{pack_bf16x2(au[0], au[1]), pack_bf16x2(au[2], au[3])};
+    pf[t] = u32x2{pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3])};
+  }
+  swap_rows16(pg[0], pg[1]);
+  swap_rows16(pu[0], pu[1]);
+  swap_rows16(pf[0], pf[1]);
+  const int c = col16(lane);
+  if (!FULL && col0 + c >= g.N) return;
+  uint16_t* ap = g.aux + (size_t)row * g.ldaux + col0 + c;
+  *reinterpret_cast<u32x4_align8*>(ap) = u32x4{pg[0][0], pg[0][1], pg[1][0], pg[1][1]};
+  *reinterpret_cast<u32x4_align8*>(ap + 32) = u32x4{pu[0][0], pu[0][1], pu[1][0], pu[1][1]};
+  *reinterpret_cast<u32x4_align8*>(reinterpret_cast<uint16_t*>(g.C) + (size_t)row * g.ldc + col0 / 2 + c) = u32x4{pf[0][0], pf[0][1], pf[1][0], pf[1][1]};
+}
 // Waves of a workgroup form a WGM x WGN x WGK grid: a wave owns a (BM/WGM) x (BN/WGN) part of the block tile and,
 // when WGK > 1, every WGK-th pair of the 16-wide k steps of each stage; the WGK partial accumulators of a part are
 // added through LDS after the k loop, in a fixed order.  Splitting k inside the workgroup instead of the tile keeps
@@ -1091,45 +1214,132 @@ __global__ __launch_bounds__(256) void gemm_dtl_rect_kernel(GemmArgs g) {  // g:
 // =================================================================================================
 // Eight-wave kernels: two waves on every SIMD, alternating between a memory phase and an MFMA phase.
 // A wave's part of the block tile is 128 x 64 (128 accumulator registers), so two waves fit the register file of a SIMD.
-// Waves 0-3 (one per SIMD) and waves 4-7 run the same loop one phase apart: group 1 passes one extra barrier before the
+// Waves 0-3 (group 0, one per SIMD) and waves 4-7 (group 1) run the same loop one phase apart: group 1 passes one extra barrier before the
 // loop and group 0 one behind it, so that every workgroup barrier ends a memory phase of one group and an MFMA phase of
-// the other.  Memory phase of k tile kt: the 12 operand fragments of the tile are read from LDS into registers, the
-// direct-to-LDS loads of tile kt+NS-1 are issued into the stage that held tile kt-1, and the wave waits until its own
-// loads of tile kt+1 have landed.  MFMA phase: 16 MFMAs, nothing else.  While one wave of a SIMD multiplies, the other
-// one's LDS reads, address arithmetic and waits cost the MFMA pipe nothing.
-//   Why this is safe.  Number the barriers B0 (before the loop, all waves), B(2k+1) = {group 0 ends its memory phase k, group
-//   1 ends its MFMA phase k-1 (k = 0: the extra barrier)}, B(2k+2) = {group 0 ends MFMA phase k, group 1 ends memory phase
-//   k}.  Group 0 reads tile k between B(2k) and B(2k+1), group 1 between B(2k+1) and B(2k+2); every wave's reads have
-//   returned (lgkmcnt(0)) before it reaches the barrier that ends the phase.  (a) Tile k is complete before it is read:
-//   each wave waits for its own loads of tile k in its memory phase k-1, i.e. before B(2k-1) (group 0) or B(2k) (group
-//   1); tile 0 before B0.  (b) A stage is refilled only after its last reader is done: tile k+NS-1 replaces tile k-1;
-//   group 0 issues it behind B(2k), group 1 behind B(2k+1); the last reads of tile k-1 are group 1's, complete before
-//   B(2k).
-// 256 x 256 tiles (variant 301256256): waves 2 x 4, LDS stages and layouts of the four-wave direct-to-LDS kernel (four
-// stages of 32 k).  128 x 256 tiles (301128256, over k slices 302128256 / 304128256): waves 1 x 4 x 2 -- the two groups
-// split the four k steps of a 64-wide stage and add their accumulators through LDS after the loop -- three stages,
-// layouts of the four-wave 128 x 256 kernel.  Shapes: as those kernels.
+// the other.  Memory phase of iteration k: the 12 operand fragments (32 k) are read from LDS into registers, and the wave waits until its
+// own direct-to-LDS loads of what is read next have landed.  MFMA phase: 32 v_mfma_f32_16x16x32_bf16, and between them the loads that refill LDS.
+//   Why 16x16x32 and not 32x32x16: the chip lowers its clock under MFMA load, and the smaller shape moves half the accumulator registers per
+// flop (registers only, random-normal operands 1865 -> 2115 TFLOP/s, zeros 2425 with either).  Its sums are those of the larger shape bit for bit.
+//   Why the loads stand between the MFMAs: a memory phase issues 24 reads at most, and an instruction that loads 1 KB holds its wave up for 16 cycles and
+// more; behind the reads they made the memory phase the longer of the two (TN 4096 x 2048 x 8192 with the MFMAs left out 115 of 131 us).
+//   Numbering: barriers B0 (before the loop, all waves), B(2k+1) = {group 0 ends its memory phase k, group 1 ends its MFMA phase k-1 (k = 0: the
+// extra barrier)}, B(2k+2) = {group 0 ends MFMA phase k, group 1 ends memory phase k}.  Group 0 reads for iteration k between B(2k) and
+// B(2k+1), group 1 between B(2k+1) and B(2k+2); every wave's reads have returned (lgkmcnt(0)) before it reaches the barrier that ends the phase.
+// So (a) what group 0 loads is there for both groups' iteration k+1 if its waves have waited before B(2k+1) (memory phase k), what group 1 loads if its
+// waves have waited before B(2k+2) (memory phase k); (b) in its MFMA phase k group 0 may refill what was read last in iteration k-1, group 1 what
+// was read last in iteration k.
+//   256 x 256 tiles (variant 301256256): waves 2 x 4, both groups read the same 32 k.  Group 0 loads A, group 1 B, each into a ring of its own; 160 KB in
+// all.  A k-major operand comes in units of 64 k, rows of 128 bytes: rows of 64 bytes take the L2 twice the requests and the loop was bound by them
+// (NT 4096 x 4096 x 8192 without MFMAs 196 -> 154 us).  us on cold operands, four stages of 32 k that both groups load in their memory phases with 32x32x16 ->
+// now: 8192 rows x 4096 NN 1536 bias 102 -> 95, NN 2048 x 4096 bias+GeLU 125 -> 107, NT 2048 x 4096 dGeLU 135 -> 115, NT 4096 x 2048 138 -> 122, NN
+// 4096 x 2048 130 -> 117, NN 4096 x 512 60 -> 54.5; TN 4096 x 4096 x 8192 224 -> 213.
+//   128 x 256 tiles (301128256, over k slices 302128256 / 304128256): waves 1 x 4 x 2 -- the two groups take the k halves of 64 k and add their
+// accumulators through LDS after the loop.  TN: the halves are stages of their own (six), group 0 loads those of group 1 and the other way round, so
+// that a load has two iterations to arrive (4096 x 2048 x 8192 129 -> 122 us).  With a k-major operand, whose 128-byte rows hold both halves: three stages of 64 k that
+// all waves load in their memory phases (NT 4096 x 2048 x 8192 121 -> 116).
+// A row-indexed operand may end inside its tile, and so may a k-major one (pp_src).  K: whole multiples of 32 resp. 64.
 // =================================================================================================
-// fragment I (of NF) of k step KK.  KC: off[KK] + I * FRAG bytes; MC: off[I] + KK * KSTEP bytes, second half HALF bytes on
-template <bool KC, int KK, int I, int FRAG, int KSTEP, int HALF>
-__device__ __forceinline__ u32x4 pp_read_frag(uint32_t base, const uint32_t* off) {
+// Chunk swizzles of the operand tiles that 16-row fragments are read from: 16-byte chunk c of a row lies at slot c ^ swizzle(row).
+//   Row-indexed, k rows of 256 bytes and more: one LDS cycle of the transpose read serves 32 lanes, 8 bytes each, here the k rows 0..3 and 8..11 of
+//   an eight-row pitch x 32 bytes, which then fall on 16 different chunk positions mod 16.
+//   k-major, rows of 128 bytes: one cycle of ds_read_b128 serves the lanes 0-3, 12-15, 20-27 (or 4-11, 16-19, 28-31) of a half wave, and lanes
+//   16-31 hold the next chunk of the rows of lanes 0-15.  (Rows of 64 bytes would do for a stage of 32 k, with 2 ((row/8)%2), but a load of half
+//   lines takes the L2 twice the requests: TCP_TCC_READ_REQ of NT 4096 x 4096 x 8192 33.5 against 16.8 million.)
+// SQ_LDS_BANK_CONFLICT is 0 with both.
+__device__ __forceinline__ int mc_swizzle(int kr) { return 4 * (kr & 3) ^ 2 * ((kr >> 3) & 1); }
+__device__ __forceinline__ int kc_swizzle(int row) { return (row >> 1) & 7; }
+// byte offset from the operand of the 16 bytes that a lane fetches in DMA instruction q of the first k tile (k-major: 64 k) of R rows (columns)
+// from r0.  Rows / columns beyond the operand's extent are fetched from its last row / first column: valid memory, and what they feed is never stored.
+template <bool KC, int R>
+__device__ __forceinline__ uint32_t pp_src(int ld, int r0, int q, int lane, int extent) {
+  if (KC) {
+    const int row = 8 * q + (lane >> 3), chunk = (lane & 7) ^ kc_swizzle(row);
+    return ((uint32_t)min(r0 + row, extent - 1) * ld + chunk * 8) * 2u;
+  }
+  constexpr int CPR = R / 8, KPI = 64 / CPR;
+  const int kr = KPI * q + lane / CPR, cc = (lane % CPR) ^ mc_swizzle(kr);
+  int col = r0 + cc * 8;
+  if (col >= extent) col = 0;
+  return ((uint32_t)kr * ld + col) * 2u;
+}
+// Fragments of 16 rows (columns) x 32 k from an operand tile in LDS.  k-major, PITCH bytes a row: one offset, fragment i adds 16 rows; row-indexed,
+// PITCH bytes a k row: an offset per fragment (the swizzle falls on the column), its second half lies four k rows on.
+template <bool KC, int N>
+struct FragOffsets {
+  uint32_t off[KC ? 1 : N];
+};
+template <bool KC, int PITCH, int N>
+__device__ __forceinline__ void read_frags16(u32x4 (&f)[N], uint32_t base, const FragOffsets<KC, N>& o) {
+  static_assert(N == 2 || N == 4 || N == 8, "fragments of a wave");
   if constexpr (KC) {
-    return lds_read_b128<I * FRAG>(base + off[KK]);
+    const uint32_t a = base + o.off[0];
+    f[0] = lds_read_b128<0>(a);
+    f[1] = lds_read_b128<16 * PITCH>(a);
+    if constexpr (N > 2) {
+      f[2] = lds_read_b128<32 * PITCH>(a);
+      f[3] = lds_read_b128<48 * PITCH>(a);
+    }
+    if constexpr (N > 4) {
+      f[4] = lds_read_b128<64 * PITCH>(a);
+      f[5] = lds_read_b128<80 * PITCH>(a);
+      f[6] = lds_read_b128<96 * PITCH>(a);
+      f[7] = lds_read_b128<112 * PITCH>(a);
+    }
   } else {
-    const u32x2 lo = lds_read_tr16_b64<KK * KSTEP>(base + off[I]);
-    const u32x2 hi = lds_read_tr16_b64<KK * KSTEP + HALF>(base + off[I]);
-    return u32x4{lo[0], lo[1], hi[0], hi[1]};
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+      const u32x2 lo = lds_read_tr16_b64<0>(base + o.off[i]);
+      const u32x2 hi = lds_read_tr16_b64<4 * PITCH>(base + o.off[i]);
+      f[i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+    }
   }
 }
-__device__ __forceinline__ void pp_wait_frags(u32x4 (&a)[2][4], u32x4 (&b)[2][2]) {
+
+// SWZ(row or k row): the chunk swizzle of the layout; R0: first row (column) of the wave's part; chunk0 / krow0: its k range in the tile
+template <int PITCH, int N, class SWZ>
+__device__ __forceinline__ FragOffsets<true, N> frag_offsets_kc(int R0, int chunk0, int lane, SWZ swz) {
+  const int row = R0 + (lane & 15);
+  FragOffsets<true, N> o;
+  o.off[0] = (uint32_t)(row * PITCH + (((chunk0 + (lane >> 4)) ^ swz(row)) << 4));
+  return o;
+}
+template <int PITCH, int N, class SWZ>
+__device__ __forceinline__ FragOffsets<false, N> frag_offsets_mc(int R0, int krow0, int lane, SWZ swz) {
+  const int krow = krow0 + 8 * (lane >> 4) + ((lane & 15) >> 2);
+  FragOffsets<false, N> o;
+#pragma unroll
+  for (int i = 0; i < N; i++) {
+    const int col = R0 + 16 * i + 4 * (lane & 3);
+    o.off[i] = (uint32_t)(krow * PITCH + (((col >> 3) ^ swz(krow)) << 4) + (col & 7) * 2);
+  }
+  return o;
+}
+// the fragments of a k step of 32 against each other, every second row of tiles backwards: neighbouring MFMAs share an operand
+// between(i): what goes behind row i
+template <bool ROWS, int NA, int NB, class F>
+__device__ __forceinline__ void mma16(f32x4 (&acc)[NA][NB], const u32x4 (&fa)[NA], const u32x4 (&fb)[NB], F between) {
+#pragma unroll
+  for (int i = 0; i < NA; i++) {
+#pragma unroll
+    for (int jj = 0; jj < NB; jj++) {
+      const int j = (i & 1) ? NB - 1 - jj : jj;
+      const bf16x8 a = __builtin_bit_cast(bf16x8, fa[i]), b = __builtin_bit_cast(bf16x8, fb[j]);
+      if constexpr (ROWS) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[i][j], 0, 0, 0);
+      else acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a, acc[i][j], 0, 0, 0);
+    }
+    between(i);
+  }
+}
+__device__ __forceinline__ void wait_frags16(u32x4 (&a)[8], u32x4 (&b)[4]) {
   asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(a[0][0]), "+v"(a[0][1]), "+v"(a[0][2]), "+v"(a[0][3]), "+v"(a[1][0]), "+v"(a[1][1]), "+v"(a[1][2]), "+v"(a[1][3]),
-                 "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
+               : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]),
+                 "+v"(b[3]));
 }
 
-constexpr int kPpLds256 = NSD * kDtlStage;                                  // 128 KB
+constexpr int kPpLds256 = 5 * (256 + 256) * 64;                             // 160 KB
 constexpr int kPpExchange = 8 * 2 * 2 * 4 * 64 * 16;                        // 128 x 256 tiles: half of every wave's accumulator
-constexpr int kPpLds128 = NSR * kRectStage > kPpExchange ? NSR * kRectStage : kPpExchange;  // 144 KB
+constexpr int kPpLds128 = 6 * (128 + 256) * 64;                  // 144 KB
+static_assert(kPpExchange + 16 <= kPpLds128, "exchange and flag");
 
 // k slices that are added up by the launch itself: every workgroup of a tile leaves its partial sums in `part`
 // ([tile][slice][wave][group of four][half][lane] x 2 floats, so that each access of a wave is whole lines) and counts itself in; whoever counts last
@@ -1192,239 +1402,299 @@ __device__ __forceinline__ bool sum_slices(const SliceSum& ss, f32x4 (&v)[N], ch
   return true;
 }
 
+template <int N>
+__device__ __forceinline__ void vm_wait() {  // vmcnt(N)
+  __builtin_amdgcn_s_waitcnt(((N >> 4) << 14) | (N & 15) | (7 << 4) | (15 << 8));
+}
 template <int BM, bool A_KC, bool B_KC, int EPI, bool FULL, bool SLICED = false>
 __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, const SliceSum& ss = SliceSum{}) {
   static_assert(BM == 256 || BM == 128, "block tiles 256 x 256 and 128 x 256");
   static_assert(!SLICED || BM == 128, "slices: 128 x 256 tiles");
   constexpr bool SQ = BM == 256;
-  constexpr int NS = SQ ? NSD : NSR;                 // LDS stages
-  constexpr int KT = SQ ? BKD : BKR;                 // k extent of a stage
-  constexpr int kOpA = SQ ? kDtlOperand : kRectA;    // bytes of the A tile of a stage (B behind it)
-  constexpr int kStage = SQ ? kDtlStage : kRectStage;
-  constexpr int PER_A = 2, PER_B = SQ ? 2 : 4, PER = PER_A + PER_B;  // direct-to-LDS instructions of a wave per stage
+  constexpr bool HALVES = !SQ && !A_KC && !B_KC;     // 128 x 256, each group's k half a stage of its own
+  // k extent of what an instruction fetches of a row, and with it of a stage: the row-indexed operands 32 (64 where both groups read one stage), the
+  // k-major ones 64, whole lines of 128 bytes
+  constexpr int TK_A = A_KC || (!SQ && !HALVES) ? 64 : 32, TK_B = B_KC || (!SQ && !HALVES) ? 64 : 32;
   int tile_m, tile_n;
   tile_of_workgroup(pid, g.tiles_m, g.tiles_n, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * 256;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave >> 2, wn = wave & 3;          // grp: phase group; 256 x 256: also the row half, 128 x 256: the k half
-  const int nk = g.K / KT;
 
-  f32x16 acc[4][2];
+  f32x4 acc[8][4];
 #pragma unroll
-  for (int i = 0; i < 4; i++)
+  for (int i = 0; i < 8; i++)
 #pragma unroll
-    for (int j = 0; j < 2; j++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+    for (int j = 0; j < 4; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const __amdgpu_buffer_rsrc_t rsA = operand_rsrc(g.A), rsB = operand_rsrc(g.B);
-  uint32_t srcA[PER_A], srcB[PER_B];
-#pragma unroll
-  for (int j = 0; j < PER_A; j++)
-    srcA[j] = lane_offset(SQ ? dtl_src<A_KC>(g.A, g.lda, m0, PER_A * wave + j, lane, g.M) : rect_src<A_KC, 128>(g.A, g.lda, m0, PER_A * wave + j, lane, g.M), g.A);
-#pragma unroll
-  for (int j = 0; j < PER_B; j++)
-    srcB[j] = lane_offset(SQ ? dtl_src<B_KC>(g.B, g.ldb, n0, PER_B * wave + j, lane, g.N) : rect_src<B_KC, 256>(g.B, g.ldb, n0, PER_B * wave + j, lane, g.N), g.B);
-#ifdef OASES_PP_SAMEK   // timing experiment: every k tile is tile 0 (all loads hit L2)
-  const uint32_t stepA_k = 0, stepB_k = 0;
-#else
-  const uint32_t stepA_k = A_KC ? (uint32_t)KT * 2 : (uint32_t)KT * g.lda * 2, stepB_k = B_KC ? (uint32_t)KT * 2 : (uint32_t)KT * g.ldb * 2;  // next k tile
-#endif
-  auto issue = [&](int t) {
-    char* st = lds + (t % NS) * kStage;
-#pragma unroll
-    for (int j = 0; j < PER_A; j++) dma16(rsA, srcA[j], (uint32_t)t * stepA_k, st + (PER_A * wave + j) * 1024);
-#pragma unroll
-    for (int j = 0; j < PER_B; j++) dma16(rsB, srcB[j], (uint32_t)t * stepB_k, st + kOpA + (PER_B * wave + j) * 1024);
-  };
+  const uint32_t stepA_k = 2u * TK_A * (A_KC ? 1u : g.lda), stepB_k = 2u * TK_B * (B_KC ? 1u : g.ldb);  // next k tile
 
-  uint32_t offA[4], offB[4];
-  if constexpr (SQ) {
-    dtl_frag_offsets<A_KC>(offA, grp * 128, lane);
-    dtl_frag_offsets<B_KC>(offB, wn * 64, lane);
-  } else {
-    rect_frag_offsets<A_KC, 128>(offA, 0, grp, lane);
-    rect_frag_offsets<B_KC, 256>(offB, wn * 64, grp, lane);
-  }
-  // strides of the LDS layouts: fragment to fragment (k-major operand), k step to k step and first to second half of a
-  // fragment (row-indexed operand)
-  constexpr int FRAG = SQ ? 2048 : 4096;
-  constexpr int KSTEP_A = SQ ? 8192 : 16 * 2 * 128, HALF_A = SQ ? 2048 : 4 * 2 * 128;
-  constexpr int KSTEP_B = SQ ? 8192 : 16 * 2 * 256, HALF_B = SQ ? 2048 : 4 * 2 * 256;
+  constexpr int PITCH_A = A_KC ? 2 * TK_A : 2 * BM, PITCH_B = B_KC ? 2 * TK_B : 2 * 256;  // row pitches of the two layouts
+  const int k32 = !SQ && !HALVES ? grp : 0;
+  FragOffsets<A_KC, 8> offA;
+  FragOffsets<B_KC, 4> offB;
+  const int ra = SQ ? grp * 128 : 0;
+  if constexpr (A_KC) offA = frag_offsets_kc<PITCH_A, 8>(ra, 4 * k32, lane, kc_swizzle);
+  else offA = frag_offsets_mc<PITCH_A, 8>(ra, 32 * k32, lane, mc_swizzle);
+  if constexpr (B_KC) offB = frag_offsets_kc<PITCH_B, 4>(wn * 64, 4 * k32, lane, kc_swizzle);
+  else offB = frag_offsets_mc<PITCH_B, 4>(wn * 64, 32 * k32, lane, mc_swizzle);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(OASES_LDS char*)lds;
-  u32x4 fa[2][4], fb[2][2];
-  auto read_stage = [&](uint32_t st) {
-#define OASES_PP_A(KK, I) fa[KK][I] = pp_read_frag<A_KC, KK, I, FRAG, KSTEP_A, HALF_A>(st, offA);
-#define OASES_PP_B(KK, I) fb[KK][I] = pp_read_frag<B_KC, KK, I, FRAG, KSTEP_B, HALF_B>(st + kOpA, offB);
-    OASES_PP_A(0, 0) OASES_PP_A(0, 1) OASES_PP_A(0, 2) OASES_PP_A(0, 3) OASES_PP_B(0, 0) OASES_PP_B(0, 1)
-    OASES_PP_A(1, 0) OASES_PP_A(1, 1) OASES_PP_A(1, 2) OASES_PP_A(1, 3) OASES_PP_B(1, 0) OASES_PP_B(1, 1)
-#undef OASES_PP_A
-#undef OASES_PP_B
+  u32x4 fa[8], fb[4];
+  // the end of a memory phase and the MFMA phase, with the loads that go between its MFMAs
+  auto multiply = [&](auto between) {
+    wait_frags16(fa, fb);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    mma16<epi_rows(EPI)>(acc, fa, fb, between);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
   };
-  auto mma = [&]() {
+  auto begin = [&]() {
+    __builtin_amdgcn_s_barrier();                 // B0
+    if (grp == 1) __builtin_amdgcn_s_barrier();   // group 1 runs one phase behind
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if constexpr (SQ) {
+    const int S = g.K / 32;  // iterations
+    // the two groups run code of their own: a branch between MFMAs, taken or not, costs the MFMA pipe more than what it jumps over
+    auto run = [&](auto grp_c) {
+      constexpr int GRP = decltype(grp_c)::value;
+      // a unit of a ring: 64 k (k-major: two k tiles, an instruction fetches 8 rows x 128 bytes) or one k tile of 32 (row-indexed)
+      constexpr int RING_A = A_KC ? 3 : 5, RING_B = B_KC ? 2 : A_KC ? 4 : 5;       // units
+      constexpr int UNIT_A = 256 * TK_A * 2, UNIT_B = 256 * TK_B * 2, kB = RING_A * UNIT_A;  // bytes; where the ring of B begins
+      static_assert(kB + RING_B * UNIT_B == kPpLds256, "rings");
+      // what this group loads
+      constexpr bool KC = GRP ? B_KC : A_KC;
+      constexpr int PER = KC ? 8 : 4, RING = GRP ? RING_B : RING_A, UNIT = GRP ? UNIT_B : UNIT_A;
+      const __amdgpu_buffer_rsrc_t rs = GRP ? rsB : rsA;
+      const uint32_t step = GRP ? stepB_k : stepA_k;
+      uint32_t src[PER];
 #pragma unroll
-    for (int kk = 0; kk < 2; kk++)
+      for (int j = 0; j < PER; j++) src[j] = pp_src<KC, 256>(GRP ? g.ldb : g.lda, GRP ? n0 : m0, PER * wn + j, lane, GRP ? g.N : g.M);
+      char* const dst = lds + (GRP ? kB : 0) + PER * wn * 1024;
+      auto issue1 = [&](int j, int u, uint32_t at) { dma16(rs, src[j], (uint32_t)u * step, dst + at + j * 1024); };
+      // all of unit u; K an odd number of k tiles: the second half of the last unit of a k-major operand lies beyond K and is fetched from the first half (not used)
+      auto issue_all = [&](int u, uint32_t at) {
+        const uint32_t back = KC && 2 * u + 1 == S ? 64 : 0;
 #pragma unroll
-      for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) {
-          const bf16x8 a = __builtin_bit_cast(bf16x8, fa[kk][i]), b = __builtin_bit_cast(bf16x8, fb[kk][j]);
-          if constexpr (EPI == EPI_F32) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[i][j], 0, 0, 0);
-          else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[i][j], 0, 0, 0);
+        for (int j = 0; j < PER; j++) {
+          const int chunk = (lane & 7) ^ ((4 * j + (lane >> 4)) & 7);  // of eight: instruction j of a k-major unit
+          dma16(rs, chunk >= 4 ? src[j] - back : src[j], (uint32_t)u * step, dst + at + j * 1024);
         }
-  };
-  constexpr int kYoung = PER * (NS - 2);  // direct-to-LDS instructions of the younger tiles that may still be in flight
-  constexpr int kVmSteady = ((kYoung >> 4) << 14) | (kYoung & 15) | (7 << 4) | (15 << 8), kVm0 = (7 << 4) | (15 << 8);
-
+      };
+      // before the loop: as many units as are there when the loop is in MFMA phase 0
+      constexpr int FIRST = GRP ? RING : KC ? 2 : 4, TILES = KC ? 2 : 1;
 #pragma unroll
-  for (int t = 0; t < NS - 1; t++)
-    if (t < nk) issue(t);
-  if (nk > NS - 2) __builtin_amdgcn_s_waitcnt(kVmSteady); else __builtin_amdgcn_s_waitcnt(kVm0);  // own part of tile 0
-  __builtin_amdgcn_s_barrier();                 // B0
-  if (grp == 1) __builtin_amdgcn_s_barrier();   // group 1 runs one phase behind
-  __builtin_amdgcn_sched_barrier(0);
-
-  uint32_t cur = lds0;
-  auto iteration = [&](auto steady_c, int kt) {
-    constexpr bool STEADY = decltype(steady_c)::value;  // tile kt+NS-1 exists and is requested now
-    // Timing experiments only (results are wrong with any bit set): -DOASES_PP_SKIP=bits switches parts of the loop off --
-    // 1 the direct-to-LDS loads, 2 the fragment reads (tile 0's stay), 4 the priority changes, 8 the MFMAs, 16 the two
-    // barriers (every wave still passes the same number of barriers); -DOASES_PP_SAMEK makes every k tile tile 0.
-#ifndef OASES_PP_SKIP
-#define OASES_PP_SKIP 0
-#endif
-    if (!(OASES_PP_SKIP & 2) || kt == 0) read_stage(cur);
-    if (STEADY) {
-      if (!(OASES_PP_SKIP & 1)) issue(kt + NS - 1);
-      __builtin_amdgcn_s_waitcnt(kVmSteady);
+      for (int u = 0; u < FIRST; u++)
+        if (u * TILES < S) issue_all(u, u * UNIT);
+      if (S < 5) vm_wait<0>(); else vm_wait<PER * (FIRST - 1)>();  // unit 0
+      begin();
+      uint32_t curA = 0, curB = kB, into = FIRST % RING * UNIT;
+      constexpr int YOUNG = KC ? (GRP ? 0 : 8) : 4 * ((GRP ? RING : 4) - 2);  // instructions behind those of what is read next
+      auto read = [&](uint32_t odd) {
+        FragOffsets<A_KC, 8> oa = offA;
+        FragOffsets<B_KC, 4> ob = offB;
+        if constexpr (A_KC) oa.off[0] ^= odd * 64;  // the other four chunks of a row
+        if constexpr (B_KC) ob.off[0] ^= odd * 64;
+        read_frags16<A_KC, PITCH_A>(fa, lds0 + curA, oa);
+        read_frags16<B_KC, PITCH_B>(fb, lds0 + curB, ob);
+      };
+      auto advance = [&](bool odd) {
+        if (!A_KC || odd) curA = curA + UNIT_A == RING_A * UNIT_A ? 0 : curA + UNIT_A;
+        if (!B_KC || odd) curB = curB + UNIT_B == kPpLds256 ? kB : curB + UNIT_B;
+      };
+      auto advance_into = [&]() { into = into + UNIT == RING * UNIT ? 0 : into + UNIT; };
+      auto unit_of = [&](int kt) { return KC ? (kt >> 1) + 2 : kt + (GRP ? RING : 4); };
+      // MFMA phase kt loads, if k-major, unit kt / 2 + 2 (A: even kt, B: odd), else unit kt + 4 (A) or kt + RING_B
+      auto iteration = [&](auto odd_c, int kt) {
+        constexpr bool ODD = decltype(odd_c)::value;
+        read(ODD);
+        constexpr bool ON = !KC || ODD == (GRP == 1);
+        if (!KC || ODD) vm_wait<YOUNG>();
+        multiply([&](int i) {
+          if (ON && i < PER) {
+            __builtin_amdgcn_sched_barrier(0);
+            issue1(i, unit_of(kt), into);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        });
+        advance(ODD);
+        if (ON) advance_into();
+      };
+      int kt = 0;
+      for (; kt + 1 + 5 < S; kt += 2) {
+        iteration(std::false_type{}, kt);
+        iteration(std::true_type{}, kt + 1);
+      }
+      for (; kt < S; kt++) {  // few k tiles left behind this one: what is still to be loaded goes behind the MFMA phase
+        const bool odd = kt & 1;
+        read(odd);
+        int young;  // as above, as far as it exists
+        if (KC) young = GRP ? (odd ? 0 : 8) : 2 * (kt >> 1) + 4 < S ? 8 : 0;
+        else young = 4 * (min(S, unit_of(kt)) - (kt + 2));
+        if (young >= 12) vm_wait<12>();
+        else if (young >= 8) vm_wait<8>();
+        else if (young >= 4) vm_wait<4>();
+        else vm_wait<0>();
+        multiply([](int) {});
+        const int u = unit_of(kt);
+        if ((!KC || odd == (GRP == 1)) && u * TILES < S) {
+          issue_all(u, into);
+          advance_into();
+        }
+        advance(odd);
+      }
+    };
+    if (grp == 0) run(std::integral_constant<int, 0>{}); else run(std::integral_constant<int, 1>{});
+  } else {
+    constexpr int TK = TK_A, NS = HALVES ? 6 : 3;                            // k of a stage, stages
+    constexpr int kOpA = BM * TK * 2, kStage = (BM + 256) * TK * 2;          // bytes of the A part of a stage (B behind it), of a stage
+    constexpr int PER_A = 2, PER_B = 4, PER = PER_A + PER_B;                 // direct-to-LDS instructions of a wave per k tile that it loads
+    const int S = g.K / TK, nk = HALVES ? S / 2 : S;                         // k tiles, iterations of a wave
+    uint32_t srcA[PER_A], srcB[PER_B];
+    const int lw = HALVES ? wn : wave;  // which of the waves that load a k tile
+#pragma unroll
+    for (int j = 0; j < PER_A; j++) srcA[j] = pp_src<A_KC, BM>(g.lda, m0, PER_A * lw + j, lane, g.M);
+#pragma unroll
+    for (int j = 0; j < PER_B; j++) srcB[j] = pp_src<B_KC, 256>(g.ldb, n0, PER_B * lw + j, lane, g.N);
+    auto issue1 = [&](int j, int t, uint32_t at) {  // instruction j of k tile t into the stage at byte `at`
+      if (j < PER_A) dma16(rsA, srcA[j], (uint32_t)t * stepA_k, lds + at + (PER_A * lw + j) * 1024);
+      else dma16(rsB, srcB[j - PER_A], (uint32_t)t * stepB_k, lds + at + kOpA + (PER_B * lw + j - PER_A) * 1024);
+    };
+    auto next = [](uint32_t at, int n) { return at + n * kStage >= NS * kStage ? at + (n - NS) * kStage : at + n * kStage; };
+    auto read = [&](uint32_t at) {
+      read_frags16<A_KC, PITCH_A>(fa, lds0 + at, offA);
+      read_frags16<B_KC, PITCH_B>(fb, lds0 + at + kOpA, offB);
+    };
+    if constexpr (HALVES) {
+      // before the loop: group 0 k tiles 1 and 3, group 1 k tiles 0, 2 and 4
+#pragma unroll
+      for (int q = 0; q < 3; q++) {
+        const int t = 1 - grp + 2 * q;
+        if (t < min(S, NS - 1))
+#pragma unroll
+          for (int j = 0; j < PER; j++) issue1(j, t, t * kStage);
+      }
+      if (grp == 1) {  // own part of tile 0
+        if (S >= NS - 1) vm_wait<2 * PER>(); else vm_wait<0>();
+      }
+      begin();
+      uint32_t cur = grp * kStage, into = grp ? 0 : (NS - 1) * kStage;  // stages that the iteration reads and refills,
+      const int ahead = grp ? NS : NS - 1;                              // the latter with k tile 2 kt + ahead
+      auto iteration = [&](auto steady_c, int kt) {
+        constexpr bool STEADY = decltype(steady_c)::value;  // that k tile exists
+        read(cur);
+        if (STEADY || nk - 1 - kt > grp) vm_wait<PER>(); else vm_wait<0>();  // the k tile of this wave's loads that is read next, and one behind it
+        multiply([&](int i) {
+          if (STEADY && i < PER) {
+            __builtin_amdgcn_sched_barrier(0);
+            issue1(i, 2 * kt + ahead, into);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        });
+        cur = next(cur, 2);
+        into = next(into, 2);
+      };
+      int kt = 0;
+      for (; 2 * kt + ahead < S; kt++) iteration(std::true_type{}, kt);
+      for (; kt < nk; kt++) iteration(std::false_type{}, kt);
     } else {
-      __builtin_amdgcn_s_waitcnt(kVm0);
+#pragma unroll
+      for (int t = 0; t < NS - 1; t++)
+        if (t < S)
+#pragma unroll
+          for (int j = 0; j < PER; j++) issue1(j, t, t * kStage);
+      if (S > 1) vm_wait<PER>(); else vm_wait<0>();  // own part of tile 0
+      begin();
+      uint32_t cur = 0, into = (NS - 1) * kStage;
+      auto iteration = [&](auto steady_c, int kt) {
+        constexpr bool STEADY = decltype(steady_c)::value;  // k tile kt + 2 exists
+        read(cur);
+        if (STEADY) {
+#pragma unroll
+          for (int j = 0; j < PER; j++) issue1(j, kt + NS - 1, into);
+          vm_wait<PER>();
+        } else {
+          vm_wait<0>();
+        }
+        multiply([](int) {});
+        cur = next(cur, 1);
+        into = next(into, 1);
+      };
+      int kt = 0;
+      for (; kt + NS - 1 < S; kt++) iteration(std::true_type{}, kt);
+      for (; kt < S; kt++) iteration(std::false_type{}, kt);
     }
-    pp_wait_frags(fa, fb);
-    __builtin_amdgcn_sched_barrier(0);
-    if (!(OASES_PP_SKIP & 16)) __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    if (!(OASES_PP_SKIP & 4)) __builtin_amdgcn_s_setprio(1);
-    if (!(OASES_PP_SKIP & 8)) mma();
-    if (!(OASES_PP_SKIP & 4)) __builtin_amdgcn_s_setprio(0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (!(OASES_PP_SKIP & 16)) __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    cur = cur + kStage == lds0 + NS * kStage ? lds0 : cur + kStage;
-  };
-  {
-    int kt = 0;
-    for (; kt + NS - 1 < nk; kt++) iteration(std::true_type{}, kt);
-    for (; kt < nk; kt++) iteration(std::false_type{}, kt);
   }
   if (grp == 0) __builtin_amdgcn_s_barrier();   // group 0 catches up: both groups have passed the same number of barriers
   __builtin_amdgcn_sched_barrier(0);
 
   // What the epilogue reads besides the accumulators is under way a tile row ahead (see epi_request; a bias once for all rows).
   constexpr bool BIAS = EPI == EPI_BIAS_BF16 || EPI == EPI_BIAS_GELU, READS = BIAS || EPI == EPI_ACC_F32 || EPI == EPI_DGELU || EPI == EPI_DSWIGLU;
-  EpiOperands eo[2][2][4];
-  auto request = [&](EpiOperands (&o)[2][4], int row0) {
+  EpiOperands eo[2][2][2][2];  // [buffer][16 rows][32 columns][16 columns]
+  auto request = [&](EpiOperands (&o)[2][2][2], int row0) {
 #pragma unroll
-    for (int j = 0; j < 2; j++) epi_request<EPI, FULL>(g, row0, n0 + wn * 64 + 32 * j, lane, o[j]);
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        if (!BIAS || h == 0) epi_request16<EPI, FULL>(g, row0 + 16 * h, n0 + wn * 64 + 32 * j, lane, o[h][j]);
+      }
+  };
+  // 16 rows of the wave's 64 columns
+  auto finish_rows = [&](int row, const f32x4& a0, const f32x4& a1, const f32x4& a2, const f32x4& a3, const EpiOperands (&o)[2][2]) {
+    if constexpr (EPI == EPI_SWIGLU) {  // the wave's 64 columns are one [gate 32 | up 32] block
+      epi_swiglu16<FULL>(g, row, n0 + wn * 64, lane, a0, a1, a2, a3);
+    } else {
+      epi_finish16<EPI, FULL>(g, row, n0 + wn * 64, lane, a0, a1, o[0]);
+      epi_finish16<EPI, FULL>(g, row, n0 + wn * 64 + 32, lane, a2, a3, o[1]);
+    }
   };
   if constexpr (SQ) {
     const int r0 = m0 + grp * 128;
     if constexpr (READS) request(eo[0], r0);
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-      if constexpr (READS) {
-        if (!BIAS && i < 3) request(eo[(i + 1) & 1], r0 + 32 * (i + 1));
+      if (READS && !BIAS && i < 3) request(eo[(i + 1) & 1], r0 + 32 * (i + 1));
 #pragma unroll
-        for (int j = 0; j < 2; j++) epi_finish<EPI, FULL>(g, r0 + 32 * i, n0 + wn * 64 + 32 * j, lane, acc[i][j], eo[BIAS ? 0 : i & 1][j]);
-      } else if constexpr (EPI == EPI_SWIGLU) {  // the wave's 64 columns are one [gate 32 | up 32] block
-        epilogue_tile_swiglu<FULL>(g, m0 + grp * 128 + i * 32, n0 + wn * 64, lane, acc[i][0], acc[i][1]);
-      } else {
-        epilogue_tile<EPI, FULL>(g, m0 + grp * 128 + i * 32, n0 + wn * 64, lane, acc[i][0]);
-        epilogue_tile<EPI, FULL>(g, m0 + grp * 128 + i * 32, n0 + wn * 64 + 32, lane, acc[i][1]);
-      }
+      for (int h = 0; h < 2; h++)
+        finish_rows(r0 + 32 * i + 16 * h, acc[2 * i + h][0], acc[2 * i + h][1], acc[2 * i + h][2], acc[2 * i + h][3], eo[BIAS ? 0 : i & 1][BIAS ? 0 : h]);
     }
   } else {
     // The two waves that hold the k halves of one 128 x 64 part each finish 64 of its rows: a wave hands the accumulator
     // tiles of the other 64 rows over through LDS (lane for lane) and adds what it receives to its own (two terms: the
     // order of the addition does not matter).
     f32x4* xch = reinterpret_cast<f32x4*>(lds);
-    const int mine = wave * 16, theirs = (wave ^ 4) * 16;  // 2 x 2 tiles x 4 quarters per wave
+    const int mine = wave * 16, theirs = (wave ^ 4) * 16;  // 4 x 4 tiles per wave
     __syncthreads();  // every wave has its last fragments in registers, and all direct-to-LDS loads have landed
     auto hand_over = [&](auto half_c) {
       constexpr int H = decltype(half_c)::value;
 #pragma unroll
-      for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-          for (int q = 0; q < 4; q++) {
-            const f32x16& a = acc[H * 2 + i][j];
-            xch[(mine + (i * 2 + j) * 4 + q) * 64 + lane] = f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
-          }
-    };
-    auto finish = [&](auto half_c) {
-      constexpr int H = decltype(half_c)::value;
-#pragma unroll
-      for (int i = 0; i < 2; i++) {
-        f32x16 a[2] = {acc[H * 2 + i][0], acc[H * 2 + i][1]};
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-          for (int q = 0; q < 4; q++) {
-            const f32x4 o = xch[(theirs + (i * 2 + j) * 4 + q) * 64 + lane];
-#pragma unroll
-            for (int e = 0; e < 4; e++) a[j][4 * q + e] += o[e];
-          }
-        if constexpr (READS) {
-#pragma unroll
-          for (int j = 0; j < 2; j++)
-            epi_finish<EPI, FULL>(g, m0 + (H * 2 + i) * 32, n0 + wn * 64 + 32 * j, lane, a[j], eo[BIAS ? 0 : i][j]);
-        } else if constexpr (EPI == EPI_SWIGLU) {
-          epilogue_tile_swiglu<FULL>(g, m0 + (H * 2 + i) * 32, n0 + wn * 64, lane, a[0], a[1]);
-        } else {
-          epilogue_tile<EPI, FULL>(g, m0 + (H * 2 + i) * 32, n0 + wn * 64, lane, a[0]);
-          epilogue_tile<EPI, FULL>(g, m0 + (H * 2 + i) * 32, n0 + wn * 64 + 32, lane, a[1]);
-        }
-      }
+      for (int q = 0; q < 16; q++) xch[(mine + q) * 64 + lane] = acc[H * 4 + (q >> 2)][q & 3];
     };
     if (grp == 0) hand_over(std::integral_constant<int, 1>{}); else hand_over(std::integral_constant<int, 0>{});
+    __syncthreads();
+    f32x4 v[16];  // this wave's 64 x 64 part of the tile, both k halves
+    auto gather = [&](auto half_c) {
+      constexpr int H = decltype(half_c)::value;
+#pragma unroll
+      for (int q = 0; q < 16; q++) v[q] = acc[H * 4 + (q >> 2)][q & 3] + xch[(theirs + q) * 64 + lane];
+    };
+    if (grp == 0) gather(std::integral_constant<int, 0>{}); else gather(std::integral_constant<int, 1>{});
     if constexpr (SLICED) {
-      __syncthreads();
-      // this wave's 64 x 64 part of the tile, both k halves
-      f32x4 v[16];
-      auto gather = [&](auto half_c) {
-        constexpr int H = decltype(half_c)::value;
-#pragma unroll
-        for (int q = 0; q < 16; q++) {
-          const f32x16& a = acc[H * 2 + (q >> 3)][(q >> 2) & 1];
-          v[q] = f32x4{a[4 * (q & 3)], a[4 * (q & 3) + 1], a[4 * (q & 3) + 2], a[4 * (q & 3) + 3]} + xch[(theirs + q) * 64 + lane];
-        }
-      };
-      if (grp == 0) gather(std::integral_constant<int, 0>{}); else gather(std::integral_constant<int, 1>{});
       if (!sum_slices<16>(ss, v, lds + kPpLds128 - 16)) return;
-      if constexpr (READS) {
-        request(eo[0], m0 + grp * 64);
-        if (!BIAS) request(eo[1], m0 + grp * 64 + 32);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) {
-          f32x16 a;
-#pragma unroll
-          for (int e = 0; e < 16; e++) a[e] = v[(i * 2 + j) * 4 + (e >> 2)][e & 3];
-          const int row = m0 + (grp * 2 + i) * 32, col = n0 + wn * 64 + 32 * j;
-          if constexpr (EPI == EPI_F32) epilogue_tile<EPI, FULL>(g, row, col, lane, a);
-          else epi_finish<EPI, FULL>(g, row, col, lane, a, eo[BIAS ? 0 : i][j]);
-        }
-      return;
     }
     if constexpr (READS) {
       request(eo[0], m0 + grp * 64);
       if (!BIAS) request(eo[1], m0 + grp * 64 + 32);
     }
-    __syncthreads();
-    if (grp == 0) finish(std::integral_constant<int, 0>{}); else finish(std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      finish_rows(m0 + grp * 64 + 16 * i, v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3], eo[BIAS ? 0 : i >> 1][BIAS ? 0 : i & 1]);
   }
 }
 
