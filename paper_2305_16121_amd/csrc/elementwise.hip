@@ -57,6 +57,23 @@ __global__ __launch_bounds__(NT) void dropout_mask_kernel(uint8_t* mask, DropCfg
 __device__ __forceinline__ f32x4 row_load4(const float* row, uint32_t off) {
   return *reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(row) + off);
 }
+// STREAM: fp32 rows go past the caches, loads and results.  Where they come to more than the caches hold between one use and the next, keeping them only
+// drives out what the products around hand over (bf16 rows, partial sums; the bf16 results, which the next product reads at once, are kept).  us a step,
+// cached -> past the caches: 4096 rows of 1024 623 -> 612, 8192 of 2048 1001 -> 973, 8192 of 4096 1790 -> 1728 (RMSNorm 1930 -> 1844), 4096 of 8192 2739
+// -> 2693, 2048 of 1024 451 -> 440 and 532 -> 529.  Below 8 MiB an array is still in a cache when the next kernel comes: 512 rows of 512 reduction
+// point 3.60 -> 3.80, backward 4.68 -> 4.96, 600 of 1024 4.44 -> 4.56.
+template <bool STREAM>
+__device__ __forceinline__ f32x4 stream_load4(const float* row, uint32_t off) {
+  const f32x4* p = reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(row) + off);
+  if constexpr (STREAM) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool STREAM>
+__device__ __forceinline__ void stream_store4(float* p, const f32x4& v) {
+  if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
+  else *reinterpret_cast<f32x4*>(p) = v;
+}
+bool streams(int rows, int h) { return (long)rows * h * 4 >= 8l << 20; }
 template <int T>
 __device__ __forceinline__ uint32_t chunk_off(int tid, int i, int nc) { return 16u * (uint32_t)min(tid + i * T, nc - 1); }
 // wave of the workgroup, uniform
@@ -76,7 +93,7 @@ __device__ __forceinline__ void row_sum2(float& a, float& b, float* red) {
 // without part, xo: kSliceCounters words that are set to zero, or nullptr (one argument more would cost every launch 0.3 us on the host)
 // ln_out = gamma * (xo - mu) * rstd + beta          (if ln_out != nullptr; bf16), the same in fp32 to ln_f32 if given
 // RMS: ln_out = gamma * xo * rstd with rstd = 1/sqrt(mean(xo^2) + eps) (RMSNorm: no mean, no beta, mu_out unused)
-template <int NC, int T, bool RMS>
+template <int NC, int T, bool RMS, bool STREAM>
 __global__ __launch_bounds__(T) void bdr_ln_kernel(const float* __restrict__ part, const float* __restrict__ peer,
                                                     const float* __restrict__ bias, const float* __restrict__ xin,
                                                     float* __restrict__ xo, const float* __restrict__ gamma,
@@ -91,13 +108,13 @@ __global__ __launch_bounds__(T) void bdr_ln_kernel(const float* __restrict__ par
   const size_t base = (size_t)row * h;
   f32x4 v[NC], z[NC];
 #pragma unroll
-  for (int i = 0; i < NC; i++) v[i] = row_load4(xin + base, chunk_off<T>(tid, i, nc));
+  for (int i = 0; i < NC; i++) v[i] = stream_load4<STREAM>(xin + base, chunk_off<T>(tid, i, nc));
   if (part) {
 #pragma unroll
-    for (int i = 0; i < NC; i++) z[i] = row_load4(part + base, chunk_off<T>(tid, i, nc));
+    for (int i = 0; i < NC; i++) z[i] = stream_load4<STREAM>(part + base, chunk_off<T>(tid, i, nc));
     if (peer)
 #pragma unroll
-      for (int i = 0; i < NC; i++) z[i] += row_load4(peer + base, chunk_off<T>(tid, i, nc));
+      for (int i = 0; i < NC; i++) z[i] += stream_load4<STREAM>(peer + base, chunk_off<T>(tid, i, nc));
     if (bias)
 #pragma unroll
       for (int i = 0; i < NC; i++) z[i] += row_load4(bias, chunk_off<T>(tid, i, nc));
@@ -108,7 +125,7 @@ __global__ __launch_bounds__(T) void bdr_ln_kernel(const float* __restrict__ par
       dropout_keep4(d, ((uint64_t)(row0 + row) * h >> 2) + c, k);
 #pragma unroll
       for (int j = 0; j < 4; j++) v[i][j] = k[j] ? v[i][j] + z[i][j] * d.scale : v[i][j];
-      if (c < nc) *reinterpret_cast<f32x4*>(xo + base + 4 * c) = v[i];
+      if (c < nc) stream_store4<STREAM>(xo + base + 4 * c, v[i]);
     }
   }
   if (!ln_out && !ln_f32) return;
@@ -181,7 +198,7 @@ constexpr int wg_max(int T) { return T == 64 ? 512 : T; }
 constexpr int colsum_lds(int NC, int T) { return T == 64 ? 8 * NC * 64 : 1; }
 
 // dz = keep * dyin * scale (bf16); partial column sums of the unrounded dz into scratch[group][h]
-template <int NC, int T>
+template <int NC, int T, bool STREAM>
 __global__ __launch_bounds__(wg_max(T)) void dropout_bwd_kernel(const float* __restrict__ dyin, uint16_t* __restrict__ dz,
                                                          float* __restrict__ scratch, int rows, int h, DropCfg d,
                                                          int64_t row0) {
@@ -195,7 +212,7 @@ __global__ __launch_bounds__(wg_max(T)) void dropout_bwd_kernel(const float* __r
     const size_t base = (size_t)row * h;
     f32x4 g[NC];
 #pragma unroll
-    for (int i = 0; i < NC; i++) g[i] = row_load4(dyin + base, chunk_off<T>(tid, i, nc));
+    for (int i = 0; i < NC; i++) g[i] = stream_load4<STREAM>(dyin + base, chunk_off<T>(tid, i, nc));
 #pragma unroll
     for (int i = 0; i < NC; i++) {
       const int c = tid + i * T;
@@ -258,7 +275,7 @@ __global__ __launch_bounds__(NT) void colsum_finalize_kernel(FinalizeArgs a) {
 // of a row, with one row per workgroup under way.  Measured with the second stage, us, 256 threads per row -> a wave per row:
 // 512 x 512 14.6 -> 10.7, 2048 x 1024 19.6 -> 15.6, 4096 x 1024 33.9 -> 22.8; all of a row's loads at once, 128 x 12288 (also one row
 // per workgroup instead of two) 29.6 -> 18.6, 2048 x 12288 138 -> 104, 8192 x 4096 133 -> 126.
-template <int NC, int T, bool RMS, bool POST>
+template <int NC, int T, bool RMS, bool POST, bool STREAM>
 __global__ __launch_bounds__(wg_max(T)) void layernorm_bwd_kernel(const float* __restrict__ part, const float* __restrict__ peer,
                                                            const float* __restrict__ dres, const float* __restrict__ x,
                                                            const float* __restrict__ mu, const float* __restrict__ rstd,
@@ -280,10 +297,10 @@ __global__ __launch_bounds__(wg_max(T)) void layernorm_bwd_kernel(const float* _
     float s1 = 0.f, s2 = 0.f;
     auto load = [&](int i) {
       const uint32_t c = chunk_off<T>(tid, i, nc);
-      gg[i] = row_load4(part + base, c);
-      xh[i] = row_load4(x + base, c);
-      if (!POST || dres) dr[i] = row_load4(dres + base, c);  // pre-LN: needed only after the reduction, fetched now
-      if (peer) gg[i] += row_load4(peer + base, c);
+      gg[i] = stream_load4<STREAM>(part + base, c);
+      xh[i] = stream_load4<STREAM>(x + base, c);
+      if (!POST || dres) dr[i] = stream_load4<STREAM>(dres + base, c);  // pre-LN: needed only after the reduction, fetched now
+      if (peer) gg[i] += stream_load4<STREAM>(peer + base, c);
     };
     auto keep = [&](int i) {
       if (!dz) return;
@@ -331,7 +348,7 @@ __global__ __launch_bounds__(wg_max(T)) void layernorm_bwd_kernel(const float* _
         f32x4 o = POST ? f32x4{0.f, 0.f, 0.f, 0.f} : dr[i];
 #pragma unroll
         for (int j = 0; j < 4; j++) o[j] += rs * (gg[i][j] - m1 - xh[i][j] * m2);
-        *reinterpret_cast<f32x4*>(dxo + base + 4 * c) = o;
+        stream_store4<STREAM>(dxo + base + 4 * c, o);
         if (dz) {
 #pragma unroll
           for (int j = 0; j < 4; j++) o[j] = ((kb[i] >> j) & 1u) ? o[j] * d.scale : 0.f;
@@ -531,10 +548,14 @@ int launch_bdr_ln(const float* part, const float* peer, const float* bias, const
     set_error("bias_dropout_residual_ln: NULL argument");
     return OASES_ENULL;
   }
-#define OASES_BDR_LN(RMS)                                                                                                       \
-  OASES_ROW_DISPATCH(h, hipLaunchKernelGGL((bdr_ln_kernel<NC, T, RMS>), dim3(rows), dim3(T), 0, s, part, peer, bias, xin, xo, gamma, \
+#define OASES_BDR_LN(RMS, STREAM)                                                                                               \
+  OASES_ROW_DISPATCH(h, hipLaunchKernelGGL((bdr_ln_kernel<NC, T, RMS, STREAM>), dim3(rows), dim3(T), 0, s, part, peer, bias, xin, xo, gamma, \
                                            beta, (uint16_t*)ln_out, mu, rstd, h, eps, d, row0, ln_f32))
-  if (rms) { OASES_BDR_LN(true); } else { OASES_BDR_LN(false); }
+  if (streams(rows, h)) {
+    if (rms) { OASES_BDR_LN(true, true); } else { OASES_BDR_LN(false, true); }
+  } else {
+    if (rms) { OASES_BDR_LN(true, false); } else { OASES_BDR_LN(false, false); }
+  }
 #undef OASES_BDR_LN
   OASES_LAUNCH_CHECK("bdr_ln_kernel");
   return 0;
@@ -579,8 +600,11 @@ int launch_dropout_bwd(const float* dyin, void* dz, float* dbias, int rows, int 
   if (!check_h(rows, h, "dropout_bwd")) return OASES_EINVAL;
   if (!dyin || !dz || (dbias && !scratch)) { set_error("dropout_bwd: NULL argument"); return OASES_ENULL; }
   const int groups = col_groups(rows);
-  OASES_BWD_DISPATCH(h, hipLaunchKernelGGL((dropout_bwd_kernel<NC, T>), dim3(groups), dim3(row_threads(T, rows, groups)), 0, s, dyin,
-                                           (uint16_t*)dz, dbias ? scratch : nullptr, rows, h, d, row0));
+#define OASES_DROPOUT_BWD(STREAM)                                                                                                       \
+  OASES_BWD_DISPATCH(h, hipLaunchKernelGGL((dropout_bwd_kernel<NC, T, STREAM>), dim3(groups), dim3(row_threads(T, rows, groups)), 0, s, dyin, \
+                                           (uint16_t*)dz, dbias ? scratch : nullptr, rows, h, d, row0))
+  if (streams(rows, h)) { OASES_DROPOUT_BWD(true); } else { OASES_DROPOUT_BWD(false); }
+#undef OASES_DROPOUT_BWD
   OASES_LAUNCH_CHECK("dropout_bwd_kernel");
   if (dbias) return finish_colsums(sink, scratch, 0, dbias, nullptr, nullptr, groups, h, s);
   return 0;
@@ -600,11 +624,15 @@ int launch_layernorm_bwd(const float* part, const float* peer, const float* dres
   const int want_dbias = dz && dbias;
   // distance between the three arrays of partial rows: behind one another for this call alone, or as the sink lays them out
   const size_t kstride = sink ? sink->kstride : (size_t)groups * h;
-#define OASES_LN_BWD(RMS, POST)                                                                                                       \
-  OASES_BWD_DISPATCH(h, hipLaunchKernelGGL((layernorm_bwd_kernel<NC, T, RMS, POST>), dim3(groups), dim3(row_threads(T, rows, groups)), \
+#define OASES_LN_BWD(RMS, POST, STREAM)                                                                                               \
+  OASES_BWD_DISPATCH(h, hipLaunchKernelGGL((layernorm_bwd_kernel<NC, T, RMS, POST, STREAM>), dim3(groups), dim3(row_threads(T, rows, groups)), \
                                            0, s, part, peer, dres, x, mu, rstd, gamma, dxo, (uint16_t*)dz, scratch, rows, h, d, row0,   \
                                            want_dbias, kstride))
-  if (rms) { OASES_LN_BWD(true, false); } else if (post) { OASES_LN_BWD(false, true); } else { OASES_LN_BWD(false, false); }
+  if (streams(rows, h)) {
+    if (rms) { OASES_LN_BWD(true, false, true); } else if (post) { OASES_LN_BWD(false, true, true); } else { OASES_LN_BWD(false, false, true); }
+  } else {
+    if (rms) { OASES_LN_BWD(true, false, false); } else if (post) { OASES_LN_BWD(false, true, false); } else { OASES_LN_BWD(false, false, false); }
+  }
 #undef OASES_LN_BWD
   OASES_LAUNCH_CHECK("layernorm_bwd_kernel");
   return finish_colsums(sink, scratch, kstride, dgamma, rms ? nullptr : dbeta, want_dbias ? dbias : nullptr, groups, h, s);

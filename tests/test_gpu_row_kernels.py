@@ -100,3 +100,30 @@ def test_column_sums_against_fp64(rows, cols):
     B.check(B.lib.oases_op_colsum_bf16(_ptr(a), cols + 16, rows, cols, _ptr(out), _ptr(scratch), None))
     torch.cuda.synchronize()
     assert rel_err(out, a[:, :cols].double().sum(0) + 1) < 2e-5
+
+
+@pytest.mark.parametrize("h", [1024, 4096, 8192])
+def test_rows_past_the_caches(h):
+    """From 8 MiB of fp32 rows on the row kernels load and store past the caches: one row fewer, which goes the other way, gives the same rows bit for bit."""
+    from paper_2305_16121_amd import binding as B
+    gen = torch.Generator(device="cuda").manual_seed(h)
+    most = (8 << 20) // (4 * h)
+    n = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    part, peer, dres, x = n(most, h), n(most, h), n(most, h), n(most, h)
+    gamma, beta, bias = n(h), n(h), n(h)
+    scratch = torch.empty(3 * 1024 * h, device="cuda")
+    outs = []
+    for rows in (most - 1, most):
+        xo, dxo = torch.full_like(x, float("nan")), torch.full_like(x, float("nan"))
+        ln, dz, dz2 = (torch.full((most, h), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3))
+        mu, rstd, sums = torch.empty(most, device="cuda"), torch.empty(most, device="cuda"), torch.zeros(4, h, device="cuda")
+        B.check(B.lib.oases_op_bias_dropout_residual_ln(_ptr(part), _ptr(peer), _ptr(bias), _ptr(x), _ptr(xo), _ptr(gamma), _ptr(beta),
+                                                        _ptr(ln), _ptr(mu), _ptr(rstd), rows, h, 1e-5, 9, 1, 0, 8, 0.25, None))
+        B.check(B.lib.oases_op_layernorm_bwd(_ptr(part), _ptr(peer), _ptr(dres), _ptr(x), _ptr(mu), _ptr(rstd), _ptr(gamma), _ptr(dxo),
+                                             _ptr(sums[0]), _ptr(sums[1]), _ptr(dz), _ptr(sums[2]), rows, h, 9, 1, 0, 8, 0.25, _ptr(scratch), None))
+        B.check(B.lib.oases_op_dropout_bwd(_ptr(part), _ptr(dz2), _ptr(sums[3]), rows, h, 9, 1, 0, 8, 0.25, _ptr(scratch), None))
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(xo[:rows]).all()) and bool(torch.isnan(xo[rows:]).all()) and bool(torch.isnan(dxo[rows:]).all())
+        outs.append([t[:most - 1] for t in (xo, ln, mu, rstd, dxo, dz, dz2)])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
