@@ -386,18 +386,36 @@ __device__ __forceinline__ void swap_lines(f32x4& x, f32x4& y) {
     y[e] = __builtin_bit_cast(float, r1);
   }
 }
+// the 16 rows x 32 columns of C from (row0, col0), in that order of the lanes: address arithmetic in scalar registers.  (Stores that go past the caches
+// shorten a launch of few rows, 4096 x 1024 x 1024 17.1 -> 16.0 us, whose L2s have less to write back at its end, but the kernel that reads the result then pays
+// for it: steps of h 4096 1767 -> 1795 us, h 2048 forward 309 -> 316, h 12288 with 128 rows 971 -> 983, h 1024 606 -> 601.)
+struct LinesOfC {
+  __amdgpu_buffer_rsrc_t rs;
+  int at, pitch;
+  __device__ __forceinline__ LinesOfC(const GemmArgs& g, int row0, int col0, int lane)
+      : rs(__builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<float*>(g.C) + (size_t)row0 * g.ldc + col0, 0, 0x7fffffff, 0x00020000)),
+        at((8 * (lane >> 5) * g.ldc + (lane & 31)) * 4), pitch(g.ldc * 4) {}
+  __device__ __forceinline__ float load(int row) const { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, at, row * pitch, 0)); }
+  __device__ __forceinline__ void store(int row, float v) const { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, at, row * pitch, 0); }
+};
 // requests ahead of the first store, as epi_request: 16 rows x 32 columns from (row0, col0)
 template <int EPI, bool FULL>
 __device__ __forceinline__ void epi_request16(const GemmArgs& g, int row0, int col0, int lane, EpiOperands (&o)[2]) {
   if constexpr (EPI == EPI_ACC_F32) {
-    int col = col0 + (lane & 31);
-    if (!FULL) col = min(col, g.N - 1);
+    if constexpr (FULL) {
+      const LinesOfC c(g, row0, col0, lane);
+#pragma unroll
+      for (int t = 0; t < 2; t++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) o[t].f[e] = c.load(4 * t + e);
+      return;
+    }
+    const int col = min(col0 + (lane & 31), g.N - 1);
 #pragma unroll
     for (int t = 0; t < 2; t++)
 #pragma unroll
       for (int e = 0; e < 4; e++) {
-        int row = row0 + 8 * (lane >> 5) + 4 * t + e;
-        if (!FULL) row = min(row, g.M - 1);
+        const int row = min(row0 + 8 * (lane >> 5) + 4 * t + e, g.M - 1);
         o[t].f[e] = reinterpret_cast<const float*>(g.C)[(size_t)row * g.ldc + col];
       }
     return;
@@ -424,15 +442,23 @@ __device__ __forceinline__ void epi_finish16(const GemmArgs& g, int row0, int co
   if constexpr (EPI == EPI_F32 || EPI == EPI_ACC_F32) {
     f32x4 v[2] = {a0, a1};
     swap_lines(v[0], v[1]);
+    if constexpr (FULL) {
+      const LinesOfC c(g, row0, col0, lane);
+#pragma unroll
+      for (int t = 0; t < 2; t++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) c.store(4 * t + e, EPI == EPI_ACC_F32 ? o[t].f[e] + v[t][e] : v[t][e]);
+      return;
+    }
     const int col = col0 + (lane & 31);
-    if (!FULL && col >= g.N) return;
+    if (col >= g.N) return;
     float* cp = reinterpret_cast<float*>(g.C) + col;
 #pragma unroll
     for (int t = 0; t < 2; t++)
 #pragma unroll
       for (int e = 0; e < 4; e++) {
         const int row = row0 + 8 * (lane >> 5) + 4 * t + e;
-        if (!FULL && row >= g.M) continue;
+        if (row >= g.M) continue;
         cp[(size_t)row * g.ldc] = EPI == EPI_ACC_F32 ? o[t].f[e] + v[t][e] : v[t][e];
       }
   } else {
@@ -1335,6 +1361,15 @@ __device__ __forceinline__ void wait_frags16(u32x4 (&a)[8], u32x4 (&b)[4]) {
                : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]),
                  "+v"(b[3]));
 }
+__device__ __forceinline__ void wait_frags16(u32x4 (&a)[2], u32x4 (&b)[2]) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(b[0]), "+v"(b[1]));
+}
+__device__ __forceinline__ void wait_frags16(u32x4 (&a)[2], u32x4 (&b)[4]) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]));
+}
+__device__ __forceinline__ void wait_frags16(u32x4 (&a)[4], u32x4 (&b)[4]) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]));
+}
 
 constexpr int kPpLds256 = 5 * (256 + 256) * 64;                             // 160 KB
 constexpr int kPpExchange = 8 * 2 * 2 * 4 * 64 * 16;                        // 128 x 256 tiles: half of every wave's accumulator
@@ -1754,7 +1789,7 @@ __global__ __launch_bounds__(512) void gemm_pp_group_kernel(GemmArgs g0, GemmArg
 // =================================================================================================
 // Small tiles: 64 x 64 (TN = 1) and 64 x 128 (TN = 2), for launches that the large tiles would leave short of workgroups or
 // that are a chain of memory latencies rather than MFMA work.  Eight waves: 2 x 2 parts of 32 x 32 TN elements, times two
-// k halves -- a wave multiplies two of the four 16-wide k steps of a 64-wide stage, and the two partial sums of a part
+// k halves -- a wave multiplies one of the two 32-wide k steps of a 64-wide stage (v_mfma_f32_16x16x32_bf16), and the two partial sums of a part
 // meet once, through LDS, after the loop (a k half has its own accumulator, so the order of the additions is the same for
 // every shape).  Tiles come by direct-to-LDS buffer loads into NS stages, so NS-1 tiles are in flight: with K of a few
 // hundred the whole k extent is requested before the first MFMA, and the launch pays one memory latency instead of one
@@ -1765,9 +1800,9 @@ __global__ __launch_bounds__(512) void gemm_pp_group_kernel(GemmArgs g0, GemmArg
 //   before its MFMAs), whose stage then takes tile kt+NS-1.
 // Any M, N, K that are multiples of 8: rows and columns beyond an operand are fetched from valid memory and never stored;
 // k beyond K in the last tile is fetched from k = 0 and replaced by zeros in the fragments.
-// Layouts of the operand tiles: k-major [R][64] as in the 128 x 256 kernel; row-indexed [64][R] with chunk c of k row kr at
-// slot c ^ 4 (kr%4) for R = 128 (256-byte k rows: four of them share all banks) and c ^ 4 ((kr/2)%2) for R = 64 (128-byte k
-// rows: every second one does).
+// Layouts of the operand tiles: k-major [R][64] as in the eight-wave kernels; row-indexed [64][R] with chunk c of k row kr at
+// slot c ^ st_swizzle(kr): for R = 128 (256-byte k rows share all banks) the swizzle of the eight-wave kernels, for R = 64 (every second 128-byte k row
+// does) the same of the k rows that meet, 4 ((kr/2)%2) ^ 2 ((kr/8)%2).
 //   What bounds it: LDS bandwidth when the chip is full (48 KB resp. 72 KB read and written per stage, 0.16 / 0.24 us at 128
 // bytes per clock; measured 0.22 / 0.33 us per stage and workgroup), one memory latency plus some 3 us of launch and drain
 // otherwise.  Measured in microseconds, register-staged kernels before -> this one: NN bias 256 x 768 x 512 9.5 -> 4.4,
@@ -1775,10 +1810,14 @@ __global__ __launch_bounds__(512) void gemm_pp_group_kernel(GemmArgs g0, GemmArg
 // NN bias+GeLU 2048 x 1024 x 1024 18.0 -> 11.2, TN 1024 x 512 x 512 10.0 -> 4.8, NT bf16 4096 x 512 x 2048 22.9 -> 13.9, NN fp32
 // 64 x 12288 x 1536 23.1 -> 9.2.  Five stages against three or nine for 64 x 64 and three against six for 64 x 128: within
 // 5 % of each other or better; 128 x 128 tiles on the same scheme (four stages): slower on every shape that these two win.
+// 16x16x32 MFMAs and a wave's half of the rows (whole lines of C, bf16 sixteen bytes a lane) against 32x32x16 and a half of the columns of every row, us:
+// 4096 x 1024 x 1024 NN bias+GeLU 20.8 -> 18.1, NT dGeLU 18.7 -> 17.6, fp32 16.5 -> 16.9; TN 12288 x 6144 x 128 150 -> 137; 512 x 768 x 512 bias 6.8 -> 6.6.  Steps:
+// h 1024 619 -> 608, h 12288 with 128 rows 998 -> 969, two recomputed layers of h 1024 536 -> 524, three of 600 rows 533 -> 526.  The fragments of a k step
+// requested ahead of the MFMAs of the one before it: within 1 % (the loop waits for its loads, not for LDS).
 // =================================================================================================
 constexpr int BKS = 64;
 template <int R>
-__device__ __forceinline__ int st_swizzle(int kr) { return R == 64 ? 4 * ((kr >> 1) & 1) : 4 * (kr & 3); }
+__device__ __forceinline__ int st_swizzle(int kr) { return R == 64 ? 4 * ((kr >> 1) & 1) ^ 2 * ((kr >> 3) & 1) : mc_swizzle(kr); }
 // byte offset from the operand of the 16 bytes that a lane fetches in DMA instruction q of a tile that starts at row r0
 // (k tile 0), and the lane's k within the tile
 template <bool KC, int R>
@@ -1795,49 +1834,6 @@ __device__ __forceinline__ uint32_t st_src(int ld, int r0, int q, int lane, int 
   *k = kr;
   return ((uint32_t)kr * ld + col) * 2u;
 }
-// fragments of k step KK (of the wave's two) of T 32-row parts
-template <bool KC, int R, int T, int KK>
-__device__ __forceinline__ void st_read_frags(u32x4 (&f)[T], uint32_t base, const uint32_t* off) {
-  if constexpr (KC) {
-    f[0] = lds_read_b128<0>(base + off[KK]);
-    if constexpr (T > 1) f[1] = lds_read_b128<4096>(base + off[KK]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < T; i++) {
-      const u32x2 lo = lds_read_tr16_b64<KK * 16 * 2 * R>(base + off[i]);
-      const u32x2 hi = lds_read_tr16_b64<KK * 16 * 2 * R + 4 * 2 * R>(base + off[i]);
-      f[i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-    }
-  }
-}
-template <bool KC, int R, int T>
-__device__ __forceinline__ void st_frag_offsets(uint32_t (&off)[2], int R0, int wk, int lane) {
-  if (KC) {  // off[kk]: k step kk of the wave's half (fragment i adds 32 rows = 4096 bytes)
-#pragma unroll
-    for (int kk = 0; kk < 2; kk++) {
-      const int row = R0 + (lane & 31), chunk = 4 * wk + 2 * kk + (lane >> 5);
-      off[kk] = (uint32_t)(row * 128 + 16 * (chunk ^ ((row >> 1) & 7)));
-    }
-  } else {  // off[i]: fragment i
-    const int krow = 32 * wk + 8 * (lane >> 5) + ((lane & 15) >> 2);
-#pragma unroll
-    for (int i = 0; i < T; i++) {
-      const int col = R0 + 32 * i + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-      off[i] = (uint32_t)(krow * (2 * R) + (((col >> 3) ^ st_swizzle<R>(krow)) << 4) + (col & 7) * 2);
-    }
-  }
-}
-__device__ __forceinline__ void st_wait_frags(u32x4 (&a)[2][1], u32x4 (&b)[2][1]) {
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0][0]), "+v"(a[1][0]), "+v"(b[0][0]), "+v"(b[1][0]));
-}
-__device__ __forceinline__ void st_wait_frags(u32x4 (&a)[2][2], u32x4 (&b)[2][2]) {
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(a[0][0]), "+v"(a[0][1]), "+v"(a[1][0]), "+v"(a[1][1]), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
-}
-__device__ __forceinline__ void st_wait_frags(u32x4 (&a)[2][1], u32x4 (&b)[2][2]) {
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0][0]), "+v"(a[1][0]), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
-}
-
 template <int TM, int TN, int NS>
 struct StLds {
   static constexpr int kStage = 64 * (TM + TN) * BKS * 2, kExchange = 8 * TM * TN * 2 * 64 * 16;  // exchange: half of every wave's accumulator
@@ -1872,17 +1868,13 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
   const int row0 = m0 + wm * 32 * TM, col0 = n0 + wn * 32 * TN;
   const int nk = (g.K + BKS - 1) / BKS, ktail = g.K % BKS;
 
-  // operands of the epilogue.  A wave finishes quarters 2 wk and 2 wk + 1 of its accumulator tiles (quarter q of a
-  // transposed accumulator: columns 8 q + 4 (lane/32) ..+3 of row lane%32)
+  // operands of the epilogue.  A wave finishes half wk of its rows
   EpiOperands pre[TM][TN][2];
   if constexpr (EPI != EPI_F32 && EPI != EPI_SWIGLU) {
 #pragma unroll
     for (int i = 0; i < TM; i++)
 #pragma unroll
-      for (int j = 0; j < TN; j++)
-#pragma unroll
-        for (int q = 0; q < 2; q++)
-          pre[i][j][q] = epi_load<EPI>(g, min(row0 + 32 * i + (lane & 31), g.M - 1), min(col0 + 32 * j + 8 * (2 * wk + q) + 4 * (lane >> 5), g.N - 4));
+      for (int j = 0; j < TN; j++) epi_request16<EPI, false>(g, row0 + 16 * (TM * wk + i), col0 + 32 * j, lane, pre[i][j]);
   }
 
   const __amdgpu_buffer_rsrc_t rsA = operand_rsrc(g.A), rsB = operand_rsrc(g.B);
@@ -1908,30 +1900,33 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
       for (int j = 0; j < PER_B; j++) dma16(rsB, srcB[j], tB, st + kOpA + (PER_B * wave + j) * 1024);
     }
   };
-  uint32_t offA[2], offB[2];
-  st_frag_offsets<A_KC, BM, TM>(offA, wm * 32 * TM, wk, lane);
-  st_frag_offsets<B_KC, BN, TN>(offB, wn * 32 * TN, wk, lane);
+  constexpr int PITCH_A = A_KC ? 2 * BKS : 2 * BM, PITCH_B = B_KC ? 2 * BKS : 2 * BN, RA = 2 * TM, CB = 2 * TN;
+  auto swz_kc = [](int row) { return (row >> 1) & 7; };
+  FragOffsets<A_KC, RA> offA;
+  FragOffsets<B_KC, CB> offB;
+  if constexpr (A_KC) offA = frag_offsets_kc<PITCH_A, RA>(wm * 32 * TM, 4 * wk, lane, swz_kc);
+  else offA = frag_offsets_mc<PITCH_A, RA>(wm * 32 * TM, 32 * wk, lane, st_swizzle<BM>);
+  if constexpr (B_KC) offB = frag_offsets_kc<PITCH_B, CB>(wn * 32 * TN, 4 * wk, lane, swz_kc);
+  else offB = frag_offsets_mc<PITCH_B, CB>(wn * 32 * TN, 32 * wk, lane, st_swizzle<BN>);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(OASES_LDS char*)lds;
 
-  f32x16 acc[TM][TN];
+  f32x4 acc[RA][CB];
 #pragma unroll
-  for (int i = 0; i < TM; i++)
+  for (int i = 0; i < RA; i++)
 #pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+    for (int j = 0; j < CB; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
 #pragma unroll
   for (int t = 0; t < NS - 1; t++)
     if (t < nk) issue(t, t);
 
-  u32x4 fa[2][TM], fb[2][TN];
+  u32x4 fa[RA], fb[CB];
   int stage = 0;
   bool sums = false;
   if constexpr (COLSUM) sums = g.sums && tile_m == 0 && wm == 0;
-  float csum[TN], part[TN];
+  float csum[CB], part[CB];
 #pragma unroll
-  for (int j = 0; j < TN; j++) csum[j] = part[j] = 0.f;
+  for (int j = 0; j < CB; j++) csum[j] = part[j] = 0.f;
   // one tile; YOUNG: tiles behind it that may still be in flight (compile-time, for the wait); steady: tile kt+NS-1 exists
   auto iteration = [&](auto young_c, auto steady_c, int kt) {
     constexpr int Y = PER * decltype(young_c)::value;
@@ -1942,42 +1937,29 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
     __builtin_amdgcn_sched_barrier(0);
     if (STEADY) issue(kt + NS - 1, stage == 0 ? NS - 1 : stage - 1);
     const uint32_t st = lds0 + (uint32_t)stage * kStage;
-    st_read_frags<A_KC, BM, TM, 0>(fa[0], st, offA);
-    st_read_frags<B_KC, BN, TN, 0>(fb[0], st + kOpA, offB);
-    st_read_frags<A_KC, BM, TM, 1>(fa[1], st, offA);
-    st_read_frags<B_KC, BN, TN, 1>(fb[1], st + kOpA, offB);
-    st_wait_frags(fa, fb);
+    read_frags16<A_KC, PITCH_A>(fa, st, offA);
+    read_frags16<B_KC, PITCH_B>(fb, st + kOpA, offB);
+    wait_frags16(fa, fb);
     __builtin_amdgcn_sched_barrier(0);
     if (!STEADY && decltype(young_c)::value == 0 && ktail) {  // last tile: k beyond K counts as zero in both operands
+      if (32 * wk + 8 * (lane >> 4) >= ktail) {
 #pragma unroll
-      for (int kk = 0; kk < 2; kk++)
-        if (32 * wk + 16 * kk + 8 * (lane >> 5) >= ktail) {
+        for (int i = 0; i < RA; i++) fa[i] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-          for (int i = 0; i < TM; i++) fa[kk][i] = u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-          for (int j = 0; j < TN; j++) fb[kk][j] = u32x4{0u, 0u, 0u, 0u};
-        }
+        for (int j = 0; j < CB; j++) fb[j] = u32x4{0u, 0u, 0u, 0u};
+      }
     }
     if (COLSUM && sums) {
 #pragma unroll
-      for (int j = 0; j < TN; j++) {
-        part[j] += frag_sum(fb[0][j]) + frag_sum(fb[1][j]);
+      for (int j = 0; j < CB; j++) {
+        part[j] += frag_sum(fb[j]);
         if ((kt & 7) == 7) {
           csum[j] += part[j];
           part[j] = 0.f;
         }
       }
     }
-#pragma unroll
-    for (int kk = 0; kk < 2; kk++)
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++) {
-          const bf16x8 a = __builtin_bit_cast(bf16x8, fa[kk][i]), b = __builtin_bit_cast(bf16x8, fb[kk][j]);
-          if constexpr (EPI == EPI_F32) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[i][j], 0, 0, 0);
-          else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[i][j], 0, 0, 0);
-        }
+    mma16<epi_rows(EPI)>(acc, fa, fb, [](int) {});
     stage = stage == NS - 1 ? 0 : stage + 1;
   };
   int kt = 0;
@@ -1990,129 +1972,102 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
   };
   drain(drain, std::integral_constant<int, NS - 2>{});
 
-  // The two k halves of a part: each wave hands the quarters that the other one finishes over through LDS and adds what it
+  // The two k halves of a part: each wave hands the rows that the other one finishes over through LDS and adds what it
   // receives to its own (two terms: the order of the addition does not matter)
   f32x4* xch = reinterpret_cast<f32x4*>(lds);
+  constexpr int NV = TM * CB;  // tiles of a wave's half
   __syncthreads();  // every wave has its last fragments in registers, and all direct-to-LDS loads have landed
   auto hand_over = [&](auto half_c) {
-    constexpr int E = 8 * decltype(half_c)::value;
+    constexpr int I = TM * decltype(half_c)::value;
 #pragma unroll
-    for (int t = 0; t < TM * TN; t++)
-#pragma unroll
-      for (int q = 0; q < 2; q++) {
-        const f32x16& a = acc[t / TN][t % TN];
-        xch[((wave * TM * TN + t) * 2 + q) * 64 + lane] = f32x4{a[E + 4 * q], a[E + 4 * q + 1], a[E + 4 * q + 2], a[E + 4 * q + 3]};
-      }
+    for (int q = 0; q < NV; q++) xch[(wave * NV + q) * 64 + lane] = acc[I + q / CB][q % CB];
   };
   if (wk == 0) hand_over(std::integral_constant<int, 1>{}); else hand_over(std::integral_constant<int, 0>{});
-  float* xsum = reinterpret_cast<float*>(lds + StLds<TM, TN, NS>::kExchange) + 64 * TN * wn;
+  float* xsum = reinterpret_cast<float*>(lds + StLds<TM, TN, NS>::kExchange) + 64 * CB * wn;
   if (COLSUM && sums) {
 #pragma unroll
-    for (int j = 0; j < TN; j++) {
+    for (int j = 0; j < CB; j++) {
       csum[j] += part[j];
       if (wk == 1) xsum[64 * j + lane] = csum[j];
     }
   }
   __syncthreads();
   if constexpr (COLSUM) if (sums && wk == 0) {
-    static_assert(StLds<TM, TN, NS>::kExchange + 512 * TN <= StLds<TM, TN, NS>::bytes, "column sums behind the exchange");
+    static_assert(StLds<TM, TN, NS>::kExchange + 512 * CB <= StLds<TM, TN, NS>::bytes, "column sums behind the exchange");
 #pragma unroll
-    for (int j = 0; j < TN; j++) {
+    for (int j = 0; j < CB; j++) {
       float t = csum[j] + xsum[64 * j + lane];
-      t += __shfl_xor(t, 32, 64);  // the other eight k of a step
-      const int col = col0 + 32 * j + (lane & 31);
-      if (lane < 32 && col < g.N) g.sums[col] += t;
+      t += __shfl_xor(t, 16, 64);  // the other k of a step
+      t += __shfl_xor(t, 32, 64);
+      const int col = col0 + 16 * j + (lane & 15);
+      if (lane < 16 && col < g.N) g.sums[col] += t;
     }
   }
-  f32x4 v[TM * TN * 2];  // [row part][column part][quarter]
+  f32x4 v[NV];  // [row part][column part]
   auto gather = [&](auto half_c) {
-    constexpr int E = 8 * decltype(half_c)::value;
+    constexpr int I = TM * decltype(half_c)::value;
 #pragma unroll
-    for (int t = 0; t < TM * TN; t++)
-#pragma unroll
-      for (int q = 0; q < 2; q++) {
-        const f32x16& a = acc[t / TN][t % TN];
-        v[2 * t + q] = xch[(((wave ^ 4) * TM * TN + t) * 2 + q) * 64 + lane];
-#pragma unroll
-        for (int e = 0; e < 4; e++) v[2 * t + q][e] += a[E + 4 * q + e];
-      }
+    for (int q = 0; q < NV; q++) v[q] = acc[I + q / CB][q % CB] + xch[((wave ^ 4) * NV + q) * 64 + lane];
   };
   float dsum[TM];  // EPI_BF16_DELTA: this lane's part of a row's sum over the wave's columns, which belong to one head
 #pragma unroll
   for (int i = 0; i < TM; i++) dsum[i] = 0.f;
-  auto finish = [&](auto half_c, auto full_c) {
-    constexpr int H = decltype(half_c)::value;
+  auto finish = [&](auto full_c) {
     constexpr bool FULL = decltype(full_c)::value;
 #pragma unroll
-    for (int i = 0; i < TM; i++)
+    for (int i = 0; i < TM; i++) {
+      const int row = row0 + 16 * (TM * wk + i);
+      if constexpr (EPI == EPI_SWIGLU) {
+        epi_swiglu16<FULL>(g, row, col0, lane, v[i * CB], v[i * CB + 1], v[i * CB + 2], v[i * CB + 3]);
+      } else if constexpr (EPI == EPI_BF16_DELTA) {
+        const int r = row + (lane & 15);
+        if (!FULL && r >= g.M) continue;
 #pragma unroll
-      for (int q = 0; q < 2; q++) {
-        const int c = 8 * (2 * H + q) + 4 * (lane >> 5);
-        if constexpr (EPI == EPI_F32) {  // plain accumulator: element e of the quarter is C[row0 + 32 i + c + e][column lane%32 of the tile]
+        for (int j = 0; j < CB; j++) {
+          const int col = col0 + 16 * j + 4 * (lane >> 4);
+          if (!FULL && col >= g.N) continue;
+          const f32x4& x = v[i * CB + j];
+          const u32x2 o = pre[i][j >> 1][j & 1].a, w = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])};
+          *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + (size_t)r * g.ldc + col) = w;
 #pragma unroll
-          for (int j = 0; j < TN; j++) {
-            const int col = col0 + 32 * j + (lane & 31), row = row0 + 32 * i + c;
-            if (!FULL && col >= g.N) continue;
-            float* p = reinterpret_cast<float*>(g.C) + (size_t)row * g.ldc + col;
-#pragma unroll
-            for (int e = 0; e < 4; e++)
-              if (FULL || row + e < g.M) p[(size_t)e * g.ldc] = v[(i * TN + j) * 2 + q][e];
-          }
-        } else {
-          const int row = row0 + 32 * i + (lane & 31);
-          if (!FULL && row >= g.M) continue;
-          if constexpr (EPI == EPI_SWIGLU) {
-            if (FULL || col0 + c < g.N) epi_swiglu(g, row, col0 + c, col0 / 2 + c, v[i * TN * 2 + q], v[(i * TN + 1) * 2 + q]);
-          } else if constexpr (EPI == EPI_BF16_DELTA) {
-#pragma unroll
-            for (int j = 0; j < TN; j++) {
-              if (!FULL && col0 + 32 * j + c >= g.N) continue;
-              const f32x4& x = v[(i * TN + j) * 2 + q];
-              const u32x2 o = pre[i][j][q].a, r = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])};
-              *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + (size_t)row * g.ldc + col0 + 32 * j + c) = r;
-#pragma unroll
-              for (int k = 0; k < 2; k++) {
-                dsum[i] += bf16_bits_to_f32(r[k] & 0xffffu) * bf16_bits_to_f32(o[k] & 0xffffu);
-                dsum[i] += bf16_bits_to_f32(r[k] >> 16) * bf16_bits_to_f32(o[k] >> 16);
-              }
-            }
-          } else {
-#pragma unroll
-            for (int j = 0; j < TN; j++)
-              if (FULL || col0 + 32 * j + c < g.N) epi_apply<EPI>(g, row, col0 + 32 * j + c, v[(i * TN + j) * 2 + q], pre[i][j][q]);
+          for (int k = 0; k < 2; k++) {
+            dsum[i] += bf16_bits_to_f32(w[k] & 0xffffu) * bf16_bits_to_f32(o[k] & 0xffffu);
+            dsum[i] += bf16_bits_to_f32(w[k] >> 16) * bf16_bits_to_f32(o[k] >> 16);
           }
         }
+      } else {
+#pragma unroll
+        for (int j = 0; j < TN; j++) epi_finish16<EPI, FULL>(g, row, col0 + 32 * j, lane, v[i * CB + 2 * j], v[i * CB + 2 * j + 1], pre[i][j]);
       }
+    }
   };
   using H0 = std::integral_constant<int, 0>;
   using H1 = std::integral_constant<int, 1>;
   if constexpr (SLICED) {
     static_assert(StLds<TM, TN, NS>::kExchange < StLds<TM, TN, NS>::bytes, "four bytes behind the exchange");
     if (wk == 0) gather(H0{}); else gather(H1{});
-    if (!sum_slices<TM * TN * 2>(ss, v, lds + StLds<TM, TN, NS>::kExchange)) return;
+    if (!sum_slices<NV>(ss, v, lds + StLds<TM, TN, NS>::kExchange)) return;
+  } else {
+    if (wk == 0) gather(H0{}); else gather(H1{});
   }
-  const bool full = m0 + BM <= g.M && n0 + BN <= g.N;
-  auto tail = [&](auto half_c) {
-    if constexpr (!SLICED) gather(half_c);
-    if (full) finish(half_c, std::true_type{}); else finish(half_c, std::false_type{});
-  };
-  if (wk == 0) tail(H0{}); else tail(H1{});
-  if constexpr (EPI == EPI_BF16_DELTA) {  // the four waves of a row (two k halves, two column parts) put their sums together in LDS
+  if (m0 + BM <= g.M && n0 + BN <= g.N) finish(std::true_type{}); else finish(std::false_type{});
+  if constexpr (EPI == EPI_BF16_DELTA) {  // the two waves of a row (its column parts) put their sums together in LDS
     constexpr int at = StLds<TM, TN, NS>::kExchange + 1024;
-    static_assert(at + BM * 16 <= StLds<TM, TN, NS>::bytes, "row sums behind the exchange");
+    static_assert(at + BM * 8 <= StLds<TM, TN, NS>::bytes, "row sums behind the exchange");
     float* red = reinterpret_cast<float*>(lds + at);
 #pragma unroll
     for (int i = 0; i < TM; i++) {
+      dsum[i] += __shfl_xor(dsum[i], 16, 64);
       dsum[i] += __shfl_xor(dsum[i], 32, 64);
-      if (lane < 32) red[4 * (wm * 32 * TM + 32 * i + lane) + 2 * wn + wk] = dsum[i];
+      if (lane < 16) red[2 * (wm * 32 * TM + 16 * (TM * wk + i) + lane) + wn] = dsum[i];
     }
     __syncthreads();
     const int r = tid % BM, part = tid / BM;  // a head is 64 columns (one column part of a 128-wide tile) or all columns of the tile
     const bool one = g.head_dim == BN;
     const int row = m0 + r, head = n0 / g.head_dim + part, heads = g.N / g.head_dim;
     if (part < (one ? 1 : 2) && row < g.M && head < heads) {
-      const float* p = red + 4 * r + 2 * part;
-      g.sums[((size_t)(row / g.seq) * heads + head) * g.seq + row % g.seq] = one ? (p[0] + p[1]) + (p[2] + p[3]) : p[0] + p[1];
+      const float* p = red + 2 * r + part;
+      g.sums[((size_t)(row / g.seq) * heads + head) * g.seq + row % g.seq] = one ? p[0] + p[1] : p[0];
     }
   }
 }
