@@ -314,7 +314,8 @@ int oases_op_gemm(int op, int epi, int M, int N, int K, const void *A, int lda, 
  * any M, N the GEMM accepts; no forward SwiGLU epilogue; also over 2 or 4 k slices of whole stages, 202128256 and
  * 204128256, K % (64 * slices) == 0); the 256x256 kernel takes one slice only.  W = 3 names the eight-wave forms of
  * the same tiles (two waves per SIMD that alternate between loading and multiplying): 301256256, 301128256, 302128256,
- * 304128256, on the shapes of their W = 2 counterparts; 301128256 gives bit for bit what 201128256 gives.  W = 4 names the
+ * 304128256, on the shapes of their W = 2 counterparts; 301128256 gives bit for bit what 201128256 gives.  (The library's own choice also
+ * sends them ragged rows of a k-major operand, K % 64 == 0, and TN over any K from 1024 on; forced by name they keep to those shapes.)  W = 4 names the
  * small-tile kernels 64x64 and 64x128 (401064064, 401064128; direct-to-LDS loads, waves split k, any shape the GEMM
  * accepts, up to 16 slices of whole 64-wide stages; the forward SwiGLU epilogue on 64x128 only), W = 5 the same with 128x128 tiles
  * (501128128; chosen in passes only, see below).  The W >= 2
@@ -351,7 +352,7 @@ int oases_op_gemm_tn_pair(int K, int M0, int N0, const void *A0, int lda0, const
                           int ldc0, int M1, int N1, const void *A1, int lda1, const void *B1, int ldb1, void *C1,
                           int ldc1, void *stream);
 /* The same for any two weight gradients over the same K rows, on the kernel that `variant` names (0: the library's choice): 30S128256 =
- * eight-wave 128x256 tiles over S = 1, 2, 4 or 8 k slices (K % 64 == 0; any M, N the GEMM accepts), 401064064 and 401064128
+ * eight-wave 128x256 tiles over S = 1, 2, 4 or 8 k slices (K % 64 == 0, other K by the library's choice only; any M, N the GEMM accepts), 401064064 and 401064128
  * = small tiles (any K).  k slices are added up, in slice order, by the launch itself: workspace holds 4096 bytes of counters (set to
  * zero by this call) and then the partial sums, slices x tiles x 128 KiB.  NULL: never split.  EINVAL, EALIGN, ENULL before
  * the product is launched.  A whole pass issues the two weight gradients of a block this way where that is expected to take less time than

@@ -1476,10 +1476,18 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
   else offB = frag_offsets_mc<PITCH_B, 4>(wn * 64, 32 * k32, lane, mc_swizzle);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(OASES_LDS char*)lds;
   u32x4 fa[8], fb[4];
-  // the end of a memory phase and the MFMA phase, with the loads that go between its MFMAs
-  auto multiply = [&](auto between) {
+  // the end of a memory phase and the MFMA phase, with the loads that go between its MFMAs.  left: k from the first of the fragments on (TAIL: weight
+  // gradients over a number of rows that is no whole number of k tiles; k beyond K counts as zero in both operands)
+  constexpr bool TAIL = !A_KC && !B_KC;
+  auto multiply = [&](auto between, int left = 32) {
     wait_frags16(fa, fb);
     __builtin_amdgcn_sched_barrier(0);
+    if (TAIL && left < 32 && 8 * (lane >> 4) >= left) {
+#pragma unroll
+      for (int i = 0; i < 8; i++) fa[i] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int j = 0; j < 4; j++) fb[j] = u32x4{0u, 0u, 0u, 0u};
+    }
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(1);
@@ -1495,7 +1503,7 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
     __builtin_amdgcn_sched_barrier(0);
   };
   if constexpr (SQ) {
-    const int S = g.K / 32;  // iterations
+    const int S = TAIL ? (g.K + 31) / 32 : g.K / 32, F = g.K / 32;  // iterations; k tiles that are whole
     // the two groups run code of their own: a branch between MFMAs, taken or not, costs the MFMA pipe more than what it jumps over
     auto run = [&](auto grp_c) {
       constexpr int GRP = decltype(grp_c)::value;
@@ -1513,13 +1521,22 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
       for (int j = 0; j < PER; j++) src[j] = pp_src<KC, 256>(GRP ? g.ldb : g.lda, GRP ? n0 : m0, PER * wn + j, lane, GRP ? g.N : g.M);
       char* const dst = lds + (GRP ? kB : 0) + PER * wn * 1024;
       auto issue1 = [&](int j, int u, uint32_t at) { dma16(rs, src[j], (uint32_t)u * step, dst + at + j * 1024); };
-      // all of unit u; K an odd number of k tiles: the second half of the last unit of a k-major operand lies beyond K and is fetched from the first half (not used)
+      // all of unit u.  What lies beyond K is fetched from valid memory: the second half of a k-major unit from the first one (and not used), k rows from k = 0
       auto issue_all = [&](int u, uint32_t at) {
-        const uint32_t back = KC && 2 * u + 1 == S ? 64 : 0;
+        if constexpr (KC) {
+          const uint32_t back = 2 * u + 1 == S ? 64 : 0;
 #pragma unroll
-        for (int j = 0; j < PER; j++) {
-          const int chunk = (lane & 7) ^ ((4 * j + (lane >> 4)) & 7);  // of eight: instruction j of a k-major unit
-          dma16(rs, chunk >= 4 ? src[j] - back : src[j], (uint32_t)u * step, dst + at + j * 1024);
+          for (int j = 0; j < PER; j++) {
+            const int chunk = (lane & 7) ^ ((4 * j + (lane >> 4)) & 7);  // of eight: instruction j of a k-major unit
+            dma16(rs, chunk >= 4 ? src[j] - back : src[j], (uint32_t)u * step, dst + at + j * 1024);
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < PER; j++) {
+            const int kr = 2 * (PER * wn + j) + (lane >> 5);
+            if (!TAIL || u < F) dma16(rs, src[j], (uint32_t)u * step, dst + at + j * 1024);
+            else dma16(rs, 32 * u + kr < g.K ? src[j] + (uint32_t)u * step : src[j] - kr * (step / 32), 0, dst + at + j * 1024);
+          }
         }
       };
       // before the loop: as many units as are there when the loop is in MFMA phase 0
@@ -1562,7 +1579,7 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
         if (ON) advance_into();
       };
       int kt = 0;
-      for (; kt + 1 + 5 < S; kt += 2) {
+      for (; kt + 1 + 5 < F; kt += 2) {
         iteration(std::false_type{}, kt);
         iteration(std::true_type{}, kt + 1);
       }
@@ -1576,7 +1593,7 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
         else if (young >= 8) vm_wait<8>();
         else if (young >= 4) vm_wait<4>();
         else vm_wait<0>();
-        multiply([](int) {});
+        multiply([](int) {}, g.K - 32 * kt);
         const int u = unit_of(kt);
         if ((!KC || odd == (GRP == 1)) && u * TILES < S) {
           issue_all(u, into);
@@ -1590,7 +1607,7 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
     constexpr int TK = TK_A, NS = HALVES ? 6 : 3;                            // k of a stage, stages
     constexpr int kOpA = BM * TK * 2, kStage = (BM + 256) * TK * 2;          // bytes of the A part of a stage (B behind it), of a stage
     constexpr int PER_A = 2, PER_B = 4, PER = PER_A + PER_B;                 // direct-to-LDS instructions of a wave per k tile that it loads
-    const int S = g.K / TK, nk = HALVES ? S / 2 : S;                         // k tiles, iterations of a wave
+    const int nk = HALVES ? (g.K + 63) / 64 : g.K / TK, S = HALVES ? 2 * nk : nk;  // iterations of a wave, k tiles
     uint32_t srcA[PER_A], srcB[PER_B];
     const int lw = HALVES ? wn : wave;  // which of the waves that load a k tile
 #pragma unroll
@@ -1600,6 +1617,20 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
     auto issue1 = [&](int j, int t, uint32_t at) {  // instruction j of k tile t into the stage at byte `at`
       if (j < PER_A) dma16(rsA, srcA[j], (uint32_t)t * stepA_k, lds + at + (PER_A * lw + j) * 1024);
       else dma16(rsB, srcB[j - PER_A], (uint32_t)t * stepB_k, lds + at + kOpA + (PER_B * lw + j - PER_A) * 1024);
+    };
+    auto issue_all = [&](int t, uint32_t at) {  // k rows beyond K from k = 0
+#pragma unroll
+      for (int j = 0; j < PER; j++) {
+        if (!HALVES || 32 * t + 32 <= g.K) {
+          issue1(j, t, at);
+        } else if (j < PER_A) {
+          const int kr = 4 * (PER_A * lw + j) + (lane >> 4);
+          dma16(rsA, 32 * t + kr < g.K ? srcA[j] + (uint32_t)t * stepA_k : srcA[j] - kr * (stepA_k / 32), 0, lds + at + (PER_A * lw + j) * 1024);
+        } else {
+          const int q = PER_B * lw + j - PER_A, kr = 2 * q + (lane >> 5);
+          dma16(rsB, 32 * t + kr < g.K ? srcB[j - PER_A] + (uint32_t)t * stepB_k : srcB[j - PER_A] - kr * (stepB_k / 32), 0, lds + at + kOpA + q * 1024);
+        }
+      }
     };
     auto next = [](uint32_t at, int n) { return at + n * kStage >= NS * kStage ? at + (n - NS) * kStage : at + n * kStage; };
     auto read = [&](uint32_t at) {
@@ -1611,9 +1642,7 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
 #pragma unroll
       for (int q = 0; q < 3; q++) {
         const int t = 1 - grp + 2 * q;
-        if (t < min(S, NS - 1))
-#pragma unroll
-          for (int j = 0; j < PER; j++) issue1(j, t, t * kStage);
+        if (t < min(S, NS - 1)) issue_all(t, t * kStage);
       }
       if (grp == 1) {  // own part of tile 0
         if (S >= NS - 1) vm_wait<2 * PER>(); else vm_wait<0>();
@@ -1622,7 +1651,7 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
       uint32_t cur = grp * kStage, into = grp ? 0 : (NS - 1) * kStage;  // stages that the iteration reads and refills,
       const int ahead = grp ? NS : NS - 1;                              // the latter with k tile 2 kt + ahead
       auto iteration = [&](auto steady_c, int kt) {
-        constexpr bool STEADY = decltype(steady_c)::value;  // that k tile exists
+        constexpr bool STEADY = decltype(steady_c)::value;  // that k tile exists and is whole
         read(cur);
         if (STEADY || nk - 1 - kt > grp) vm_wait<PER>(); else vm_wait<0>();  // the k tile of this wave's loads that is read next, and one behind it
         multiply([&](int i) {
@@ -1631,12 +1660,13 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
             issue1(i, 2 * kt + ahead, into);
             __builtin_amdgcn_sched_barrier(0);
           }
-        });
+        }, STEADY ? 32 : g.K - 32 * (2 * kt + grp));
+        if (!STEADY && 2 * kt + ahead < S) issue_all(2 * kt + ahead, into);
         cur = next(cur, 2);
         into = next(into, 2);
       };
       int kt = 0;
-      for (; 2 * kt + ahead < S; kt++) iteration(std::true_type{}, kt);
+      for (; 2 * kt + ahead < g.K / 32; kt++) iteration(std::true_type{}, kt);
       for (; kt < nk; kt++) iteration(std::false_type{}, kt);
     } else {
 #pragma unroll
@@ -2193,21 +2223,33 @@ struct TileChoice { int bm, bn, ksplit; bool wave_ksplit; bool dtl = false; bool
 bool dtl_fits(int kind, int M, int N, int K) {
   return (kind == 2 || M % 256 == 0) && (kind != 1 || N % 256 == 0) && M % 8 == 0 && N % 8 == 0 && K % BKD == 0 && K >= BKD;
 }
+// The eight-wave kernels take more: ragged rows of a k-major operand on 256 x 256 tiles where K is whole 64-wide units, and weight gradients over any number of
+// rows.  The library's choice uses that; a variant forced by a caller's name keeps to the bounds above.  us, the tiles taken before (64x128, 128x256, register-
+// staged) -> these: TN 6144 x 3072 x 7240 432 -> 265, NT 7040 x 3456 x 3456 232 -> 152, NN 7112 x 3456 x 4608 257 -> 194; steps of drawn sizes with 2928 rows of
+// 3072 1978 -> 1831.  Fewer than 1024 rows stay on small tiles: 2560 x 5120 x 808 60 us.
+bool pp256_fits(int kind, int M, int N, int K) {
+  return dtl_fits(kind, M, N, K) || (M % 8 == 0 && N % 8 == 0 && K % 8 == 0 && (kind == 2 ? K >= 1024 : K % 64 == 0));
+}
+bool pp128_fits(int kind, int M, int N, int K) { return M % 8 == 0 && N % 8 == 0 && ((K % BKR == 0 && K >= BKR) || (kind == 2 && K % 8 == 0 && K >= 1024)); }
 bool dtl_rect_fits(int kind, int M, int N, int K) {  // the 128 x 256 kernel redirects rows of a k-major operand too
   (void)kind;
   return M % 8 == 0 && N % 8 == 0 && K % BKR == 0 && K >= BKR;
 }
 bool dtl_rect_whole(int M, int N, int K) { return M % 128 == 0 && N % 256 == 0 && K % BKR == 0 && K >= BKR; }
+bool pp_slices_fit(int kind, int M, int N, int K, int S) {  // S k slices of whole stages; a weight gradient's last one may be shorter
+  if (kind == 2 && K >= 1024 * S) return M % 8 == 0 && N % 8 == 0 && K % 8 == 0;
+  return K % (S * BKR) == 0 && dtl_rect_fits(kind, M, N, K / S);
+}
 struct KindTable { bool wave_ksplit; float r256x256, r128x256, r256x128, r128x128; };
-const KindTable g_kinds[4] = {{true, 1200.f, 1080.f, 960.f, 740.f}, {true, 1200.f, 1080.f, 960.f, 740.f},
-                        {true, 1200.f, 1080.f, 960.f, 740.f}, {false, 1200.f, 1080.f, 900.f, 740.f}};
+const KindTable g_kinds[4] = {{true, 1330.f, 1150.f, 960.f, 740.f}, {true, 1330.f, 1150.f, 960.f, 740.f},
+                        {true, 1330.f, 1150.f, 960.f, 740.f}, {false, 1330.f, 1150.f, 900.f, 740.f}};
 TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes) {
   const KindTable& kt = g_kinds[kind];
   // Tiles that the direct-to-LDS kernels do not cover run on the register-staged kernels.  256x256: at three quarters of their rate (NT dSwiGLU 8192 x
   // 1376 x 4096: 138 us against 133 on 128x256 tiles, which may be ragged, 9984 x 2624 x 1600 153 against 138, NT 8656 x 1984 x 1344 76 against 60).  128x256
   // where k is no whole number of stages: at half (NN 9576 x 1536 x 1376: 81 us, 62 on 256x256); TN at 700 and 740 (2560 x 5120 x 808: 256x256 75 us,
   // 128x256 75, 64x128 60).
-  const bool rect = dtl_rect_fits(kind, M, N, K);
+  const bool rect = pp128_fits(kind, M, N, K);
   const float r128 = rect ? kt.r128x256 : kind == 2 ? 740.f : 650.f, r256x128 = rect ? kt.r256x128 : kind == 2 ? 740.f : 600.f;
   const struct { int bm, bn; float tflops; } cand[] = {{256, 256, kt.r256x256}, {128, 256, r128}, {256, 128, r256x128}, {128, 128, kt.r128x128}};
   TileChoice best{128, 128, 1, kt.wave_ksplit};
@@ -2216,10 +2258,13 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
     const long tm = (M + c.bm - 1) / c.bm, tn = (N + c.bn - 1) / c.bn;
     for (int S = 1; S <= 8; S *= 2) {
       if (S > 1 && ((size_t)S * M * N * 4 > ws_bytes || K / S < 512)) break;
-      const long wgs = tm * tn * S, rounds = (wgs + 255) / 256;
-      // time of one workgroup's tile slice at the tile's rate (one workgroup per CU), times the number of rounds
-      const double tflops = c.bm == 256 && c.bn == 256 && !(S == 1 && dtl_fits(kind, M, N, K)) ? (kind == 2 ? 700.f : 900.f) : c.tflops;
-      double t = (double)rounds * (2.0 * c.bm * c.bn * ((double)K / S) + 3.0e6) / (tflops * 1e12 / 256.0);
+      const long wgs = tm * tn * S;
+      // time of one workgroup's tile slice at the tile's rate (one workgroup per CU), times the number of rounds; a last round of few workgroups has the
+      // chip's power to itself (pp_seconds): 8160 x 5120 x 2560 NN, 2.5 rounds of 256x256 199 us, 5 of 128x256 227
+      const bool pp = c.bn == 256 && (c.bm == 256 ? S == 1 && pp256_fits(kind, M, N, K) : rect);
+      const double rounds = pp && wgs > 256 ? wgs / 256 + (wgs % 256 ? std::max(0.75, wgs % 256 / 256.0) : 0.0) : (double)((wgs + 255) / 256);
+      const double tflops = c.bm == 256 && c.bn == 256 && !(S == 1 && pp256_fits(kind, M, N, K)) ? (kind == 2 ? 700.f : 900.f) : c.tflops;
+      double t = rounds * (2.0 * c.bm * c.bn * ((double)K / S) + 3.0e6) / (tflops * 1e12 / 256.0);
       if (S > 1) t += ((double)(2 * S + 1) * M * N * 4.0) / 3.0e12 + 4e-6;
       if (t < best_t) { best_t = t; best = TileChoice{c.bm, c.bn, S, kt.wave_ksplit}; }
     }
@@ -2227,8 +2272,8 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
   // Whole tiles without k slices: the eight-wave direct-to-LDS kernels, which measure faster than the four-wave and the
   // register-staged kernels of the same tile on every shape of the two full-size workloads (cold operands, 3-15 %).
   if (best.ksplit == 1) {
-    if (best.bm == 256 && best.bn == 256 && dtl_fits(kind, M, N, K)) best.dtl = best.pp = true;
-    if (best.bm == 128 && best.bn == 256 && dtl_rect_fits(kind, M, N, K)) best = TileChoice{128, 256, 1, true, true, true};
+    if (best.bm == 256 && best.bn == 256 && pp256_fits(kind, M, N, K)) best.dtl = best.pp = true;
+    if (best.bm == 128 && best.bn == 256 && pp128_fits(kind, M, N, K)) best = TileChoice{128, 256, 1, true, true, true};
     // Few rows, long k (a sub-batch of 1024 rows against K = 8192): 128 x 128 tiles fill the chip but run at the small
     // tile's rate; the 128 x 256 direct-to-LDS kernel over two k slices fills it too, and is faster even with its second
     // pass (measured on cold operands: 87-93 us against 108-116 us).
@@ -2237,7 +2282,7 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
         K % (2 * BKR) == 0 && dtl_rect_fits(kind, M, N, K / 2) && (size_t)2 * M * N * 4 <= ws_bytes)
       best = TileChoice{128, 256, 2, true, true, true};
   } else if (best.bm == 128 && best.bn == 256 && (best.ksplit == 2 || best.ksplit == 4) && epi != EPI_SWIGLU && epi != EPI_DSWIGLU &&
-             K % (best.ksplit * BKR) == 0 && dtl_rect_fits(kind, M, N, K / best.ksplit)) {
+             pp_slices_fit(kind, M, N, K, best.ksplit)) {
     best = TileChoice{128, 256, best.ksplit, true, true, true};  // k slices of whole stages: the eight-wave kernel
   }
   return best;
@@ -2249,7 +2294,7 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
 double pp_seconds(int bm, long wgs, int k_per, double out_bytes) {
   double t = out_bytes / 4.0e12;
   for (; wgs > 0; wgs -= 256)
-    t += 4.0e-6 + k_per / 64 * (bm == 256 ? 1.75e-6 : 0.9e-6) * std::max(0.75, (double)std::min(wgs, 256L) / 256.0);
+    t += 4.0e-6 + k_per / 64 * (bm == 256 ? 1.4e-6 : 0.83e-6) * std::max(0.75, (double)std::min(wgs, 256L) / 256.0);
   return t;
 }
 
@@ -2264,7 +2309,7 @@ double pp_seconds(int bm, long wgs, int k_per, double out_bytes) {
 // 6144 x 12288 x 128 TN 195 -> 152.  Slices of 8192 k and more stay with the large tiles.
 // own_sum: a call of a pass, whose launches add up a few slices by themselves (SliceSum, own_slices): the last workgroup of a tile then reads the other
 // slices' sums, one after the other at some 47 GB/s, instead of a second launch; 128x128 tiles on the same scheme are candidates, with any
-// number of slices (0.6 us a stage, 0.85 of that where 218 and fewer workgroups leave CUs idle and the others more of the power; what TN reads and writes moves at
+// number of slices (0.57 us a stage, 0.87 of that where 218 and fewer workgroups leave CUs idle and the others more of the power; what TN reads and writes moves at
 // 3.4 TB/s from the second round on, since a CU holds one workgroup: 10240 x 3840 x 208 92 us on 64x128, 118 on 128x128).  Measured, us, the choice without -> with, second launches
 // included: inside a step 128 x 4608 x 12288 NN 52 -> 45 (register-staged kernel over eight slices -> 128x128 over six), NT 128 x 6144 x 12288 79 -> 71 (over five); 512 x 8192 x 3072 NT 47 -> 36, 8192 x 512 x
 // 2048 NT 31 -> 26, 200 x 3072 x 8192 36 -> 27; 1488 x 3072 x 3072 NN stays on 144 tiles of 128x256 (40; 64x128 over two slices 72).
@@ -2314,7 +2359,7 @@ TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, do
       const int k_per = st_k_per(K, S);
       if (S > 1 && (!room(S, 128, 128) || k_per < 2 * BKS || (long)(S - 1) * k_per >= K)) break;
       const long wgs = tiles(128, 128) * S;
-      const double t = 4.0e-6 + (double)((wgs + 255) / 256) * ((k_per + BKS - 1) / BKS) * 0.6e-6 * (wgs < 218 ? 0.85 : 1.0) + out / (kind == 2 && wgs > 256 ? 3.4e12 : 4.0e12) + slices(S, 128, 128);
+      const double t = 4.0e-6 + (double)((wgs + 255) / 256) * ((k_per + BKS - 1) / BKS) * 0.57e-6 * (wgs < 218 ? 0.87 : 1.0) + out / (kind == 2 && wgs > 256 ? 3.4e12 : 4.0e12) + slices(S, 128, 128);
       if (t < best_t) {
         best_t = t;
         best = TileChoice{128, 128, S, true};
@@ -2330,17 +2375,18 @@ int encode_variant(const TileChoice& t) {
   return (t.st ? (t.bm == 128 ? 500000000 : 400000000) : t.dtl ? (t.pp ? 300000000 : 200000000) : rect && t.wave_ksplit ? 100000000 : 0) + t.ksplit * 1000000 + t.bm * 1000 + t.bn;
 }
 // variant -> TileChoice; false if no such instantiation exists or the k slices do not fit the problem / workspace
-bool decode_variant(int variant, int kind, int M, int N, int K, size_t ws_bytes, TileChoice* t) {
+// pass: one that the library chose itself
+bool decode_variant(int variant, int kind, int M, int N, int K, size_t ws_bytes, TileChoice* t, bool pass = false) {
   if (variant <= 0) return false;
   const int wk = variant / 100000000, S = variant / 1000000 % 100, bm = variant / 1000 % 1000, bn = variant % 1000;
   const bool square = (bm == 256 && bn == 256) || (bm == 128 && bn == 128), rect = (bm == 256 && bn == 128) || (bm == 128 && bn == 256);
   if ((wk == 2 || wk == 3) && S == 1) {  // direct-to-LDS kernels (3: eight waves), one k slice
-    if (bm == 256 && bn == 256 && dtl_fits(kind, M, N, K)) { *t = TileChoice{256, 256, 1, false, true, wk == 3}; return true; }
-    if (bm == 128 && bn == 256 && dtl_rect_fits(kind, M, N, K)) { *t = TileChoice{128, 256, 1, true, true, wk == 3}; return true; }
+    if (bm == 256 && bn == 256 && (wk == 3 && pass ? pp256_fits(kind, M, N, K) : dtl_fits(kind, M, N, K))) { *t = TileChoice{256, 256, 1, false, true, wk == 3}; return true; }
+    if (bm == 128 && bn == 256 && (wk == 3 && pass ? pp128_fits(kind, M, N, K) : dtl_rect_fits(kind, M, N, K))) { *t = TileChoice{128, 256, 1, true, true, wk == 3}; return true; }
     return false;
   }
   if ((wk == 2 || wk == 3) && bm == 128 && bn == 256 && (S == 2 || S == 4)) {  // the 128 x 256 kernels over k slices of whole stages
-    if (K % (S * BKR) || !dtl_rect_fits(kind, M, N, K / S) || (size_t)S * M * N * 4 > ws_bytes) return false;
+    if (!(wk == 3 && pass ? pp_slices_fit(kind, M, N, K, S) : K % (S * BKR) == 0 && dtl_rect_fits(kind, M, N, K / S)) || (size_t)S * M * N * 4 > ws_bytes) return false;
     *t = TileChoice{128, 256, S, true, true, wk == 3};
     return true;
   }
@@ -2369,11 +2415,9 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
   if (forced_variant == 0) {
     // Pinned choice: the number of k slices and whether waves split k -- the two things that set the order in which the
     // fp32 terms of an output element are added -- come from (choice_rows, N, K, epilogue), so every launch over a part of
-    // those rows adds in the same order.  The 256 x 256 direct-to-LDS kernels need whole row tiles; a part that has none
-    // runs the staged kernel of the same tile, which adds in the same order.
+    // those rows adds in the same order.
     const bool pinned = kind != 2 && choice_rows > g.M;
     t = pick_tile(kind, EPI, pinned ? choice_rows : g.M, g.N, g.K, ws ? ws_bytes : 0, nullptr, g.counters != nullptr);
-    if (pinned && t.dtl && t.bm == 256 && !dtl_fits(kind, g.M, g.N, g.K)) t.dtl = t.pp = false;
     const int rows = pinned ? choice_rows : g.M;
     if ((t.dtl || t.st) && !(gemm_span_fits(A_KC ? rows : g.K, g.lda) && gemm_span_fits(B_KC ? g.N : g.K, g.ldb))) {
       if (t.st) t = pick_large_tile(kind, EPI, rows, g.N, g.K, ws ? ws_bytes : 0);
@@ -2391,7 +2435,7 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
       }
     }
 #endif
-  } else if (!decode_variant(forced_variant, kind, g.M, g.N, g.K, ws ? ws_bytes : 0, &t)) {
+  } else if (!decode_variant(forced_variant, kind, g.M, g.N, g.K, ws ? ws_bytes : 0, &t, g.counters != nullptr)) {
     set_error("gemm: variant %d does not exist or does not fit M=%d N=%d K=%d with %zu workspace bytes", forced_variant, g.M, g.N, g.K, ws ? ws_bytes : (size_t)0);
     return OASES_EINVAL;
   } else if ((t.dtl || t.st) && !(gemm_span_fits(A_KC ? g.M : g.K, g.lda) && gemm_span_fits(B_KC ? g.N : g.K, g.ldb))) {
@@ -2406,13 +2450,11 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
     return OASES_EINVAL;
   }
   if (t.dtl && t.pp) {
-    constexpr bool kCanBeRagged = !A_KC || !B_KC;
     const int bm = t.bm;
     GemmCall d = g;
     d.tiles_m = (g.M + bm - 1) / bm;
     d.tiles_n = (g.N + 255) / 256;
     const bool whole = g.M % bm == 0 && g.N % 256 == 0;
-    if (!whole && bm == 256 && !kCanBeRagged) { set_error("gemm: direct-to-LDS kernel on a shape it does not cover"); return OASES_EINVAL; }
     if (bm == 128 && t.ksplit > 1) {
       if constexpr (EPI == EPI_SWIGLU || EPI == EPI_DSWIGLU) {
         set_error("gemm: the SwiGLU epilogues do not run over k slices");
@@ -2421,7 +2463,7 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
         if (!ws) { set_error("gemm: split-K chosen without a workspace"); return OASES_ENULL; }
         GemmCall p = d;
         p.ksplit = t.ksplit;
-        p.k_per = g.K / t.ksplit;
+        p.k_per = st_k_per(g.K, t.ksplit);
         const dim3 sgrid(d.tiles_m * d.tiles_n * t.ksplit);
         if (g.counters && own_slices(t.ksplit, 128, 256) && d.tiles_m * d.tiles_n <= kSliceCounters && (size_t)d.tiles_m * d.tiles_n * t.ksplit * 128 * 256 * 4 <= ws_bytes) {
           p.part = ws;
@@ -2448,7 +2490,7 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
       else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, false, false, GemmArgs>), grid, dim3(512), 0, s, d);
     } else {
       if (whole) hipLaunchKernelGGL((gemm_pp_kernel<256, A_KC, B_KC, EPI, true, false, GemmArgs>), grid, dim3(512), 0, s, d);
-      else if constexpr (kCanBeRagged) hipLaunchKernelGGL((gemm_pp_kernel<256, A_KC, B_KC, EPI, false, false, GemmArgs>), grid, dim3(512), 0, s, d);
+      else hipLaunchKernelGGL((gemm_pp_kernel<256, A_KC, B_KC, EPI, false, false, GemmArgs>), grid, dim3(512), 0, s, d);
     }
     OASES_LAUNCH_CHECK("gemm_pp_kernel");
     return 0;
@@ -2613,7 +2655,7 @@ int launch_gemm_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const v
 static bool tn_group_fits(int variant, int K, int M0, int N0, int M1, int N1, size_t ws_bytes) {
   if (variant == 401064064 || variant == 401064128) return true;
   const int S = variant / 1000000 % 100;
-  if (variant != 300128256 + S * 1000000 || (S != 1 && S != 2 && S != 4 && S != 8) || K % BKR) return false;
+  if (variant != 300128256 + S * 1000000 || (S != 1 && S != 2 && S != 4 && S != 8) || !(K % BKR == 0 || K >= 1024)) return false;
   const long T = (long)((M0 + 127) / 128) * ((N0 + 255) / 256) + (long)((M1 + 127) / 128) * ((N1 + 255) / 256);
   return S == 1 || (T <= kSliceCounters && (long)(S - 1) * st_k_per(K, S) < K && (size_t)T * S * 128 * 256 * 4 <= ws_bytes);  // every slice has stages of its own
 }
@@ -2638,7 +2680,7 @@ int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes
   for (int S = 1; S <= 8; S *= 2) {
     const int v = 300128256 + S * 1000000;
     if (!tn_group_fits(v, K, M0, N0, M1, N1, ws_bytes)) continue;
-    const double t = pp_seconds(128, T * S, (K / BKR + S - 1) / S * BKR, out) + (S > 1 ? 2.0e-6 + 2.7e-6 * S : 0.0);
+    const double t = 4.0e-6 + pp_seconds(128, T * S, st_k_per(K, S), out) + (S > 1 ? 2.0e-6 + 2.7e-6 * S : 0.0);  // 4 us: the bias gradient's own launch
     if (t < best_t) { best_t = t; best = v; }
   }
   for (int bn = 64; bn <= 128; bn += 64) {

@@ -1,0 +1,66 @@
+"""Products whose rows are no whole tiles of the eight-wave kernels: k-major operands that end inside a 256-row tile, and weight gradients over a number of
+rows that is no whole number of k tiles (the last tile of a wave group partly or wholly beyond K, with and without k slices, alone and two in a
+launch).  The library's choice goes to those kernels here; memory behind the operands holds NaN."""
+import pytest
+import torch
+
+from tests.test_gpu_gemm_rings import padded
+from tests.test_gpu_ops import B, gen  # noqa: F401  (fixtures)
+from tests.util import assert_bf16_close, bf16_round, dev, randn, rel_err
+
+pytestmark = pytest.mark.gpu
+WS = 256 << 20
+
+
+@pytest.mark.parametrize("op,M,N,K,variant", [("NN", 6072, 4096, 448, 301256256), ("NT", 6072, 4096, 448, 301256256), ("NT", 4088, 4088, 256, 301256256),
+                                                               ("TN", 1032, 4104, 1064, 301128256), ("TN", 2048, 4096, 2056, 301128256), ("TN", 2048, 4096, 2040, 301128256),
+                                                               ("TN", 4096, 4096, 1048, 301256256), ("TN", 4096, 4088, 1080, 301256256), ("TN", 4088, 4096, 1992, 301256256)])
+def test_choice_of_ragged_rows(B, op, M, N, K, variant):
+    """Exact products of bf16 values and fp32 sums against fp64: 1e-5; half a bf16 ulp for the bf16 output."""
+    opc = {"NN": B.GEMM_NN, "NT": B.GEMM_NT, "TN": B.GEMM_TN}[op]
+    assert B.lib.oases_op_gemm_variant(opc, B.EPI_F32, M, N, K, WS) == variant
+    g = gen(M + N + K)
+    a, b = bf16_round(randn(g, M, K)), bf16_round(randn(g, K, N, scale=0.05))
+    ref = (a.cuda() @ b.cuda()).cpu()
+    ad = padded(a, 0, 64) if op != "TN" else padded(a.t(), 64, 0)
+    bd = padded(b.t(), 0, 64) if op == "NT" else padded(b, 64, 0)
+    ws = torch.empty(WS, dtype=torch.uint8, device="cuda")
+    run = lambda epi, c: B.check(B.lib.oases_op_gemm(opc, epi, M, N, K, ad.data_ptr(), ad.shape[1], bd.data_ptr(), bd.shape[1], c.data_ptr(), N, None, None, 0,
+                                                     ws.data_ptr(), ws.numel(), None))
+    c0 = randn(g, M, N).float()
+    c = dev(c0, torch.float32)
+    run(B.EPI_F32, c)
+    assert rel_err(c.cpu().double(), ref + (c0.double() if op == "TN" else 0.0)) < 1e-5
+    if op != "TN":
+        cb = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+        run(B.EPI_BF16, cb)
+        assert_bf16_close(cb.float(), ref, 1e-5, 2e-6 * float(ref.abs().max()), op)
+
+
+@pytest.mark.parametrize("seq,batch", [(1032, 1), (520, 3), (680, 3), (1064, 2), (1352, 3)])
+def test_step_of_ragged_rows(B, seq, batch):
+    """A training step of a layer of 2048 over such rows: weight gradients (in one launch or two, with k slices) against the products of the pass's own
+    operands in fp64."""
+    from paper_2305_16121_amd import binding as Bi
+    cfg = dict(hidden=2048, n_heads=16, seq=seq, batch=batch, tp=2, n_sub=1, n_layers=1, causal=1, dropout_p=0.0)
+    H = Bi.Handle(Bi.make_cfg(cfg, rank=1))
+    h, hp, fp, M = 2048, 1024, 4096, seq * batch
+    g = torch.Generator(device="cuda").manual_seed(seq)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    w = {k: (n(*s) * 0.02).bfloat16() for k, s in dict(wqkv=(h, 3 * hp), wo=(hp, h), w1=(h, fp), w2=(fp, h)).items()}
+    w.update({k: n(s) * 0.02 + (1.0 if k.endswith("_g") else 0.0) for k, s in dict(ln1_g=h, ln2_g=h, ln1_b=h, ln2_b=h, bqkv=3 * hp, bo=h, b1=fp, b2=h).items()})
+    x, dy = n(M, h), n(M, h)
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    grads = Bi.zero_grads_like(w)
+    ws = torch.empty(H.workspace_bytes, dtype=torch.uint8, device="cuda")
+    H.forward([w], x, y, ws)
+    H.backward([w], x, dy, dx, [grads], ws)
+    torch.cuda.synchronize()
+
+    def t(name, cols):
+        off, nb = H.tensor_span(name, 0)
+        return ws[off:off + nb].view(torch.bfloat16).view(M, cols).double()
+
+    for k, a, ca, b, cb in (("wqkv", "u", h, "dqkv", 3 * hp), ("wo", "attn", hp, "dz1", h), ("w1", "v2", h, "dg", fp), ("w2", "f", fp, "dz2", h)):
+        ref = t(a, ca).t().contiguous() @ t(b, cb)
+        assert rel_err(grads[k].double(), ref) < 2e-5, k
