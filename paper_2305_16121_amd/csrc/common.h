@@ -49,14 +49,36 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) {
 struct Philox4 {
   uint32_t v[4];
 };
+// SHORT: both halves of a product from one instruction and three operands in one exclusive or; the compiler takes two multiplications, each at
+// a quarter of the rate, and two exclusive ors.  The masks of 8192 x 4096 elements by themselves 18.7 -> 12.0 us (multiplications alone 14.8, exclusive ors
+// alone 15.7); dropout backward 8192 x 2048 24.9 -> 22.1, attention forward 2048 x 4 x 64 with dropout 9.3 -> 8.9.
+template <bool SHORT>
+__device__ __forceinline__ void mul_wide(uint32_t m, uint32_t c, uint32_t& hi, uint32_t& lo) {
+  if constexpr (SHORT) {
+    uint64_t r, carry;
+    asm("v_mad_u64_u32 %0, %1, %2, %3, 0" : "=v"(r), "=s"(carry) : "s"(m), "v"(c));
+    hi = (uint32_t)(r >> 32);
+    lo = (uint32_t)r;
+  } else {
+    hi = __umulhi(m, c);
+    lo = m * c;
+  }
+}
+template <bool SHORT>
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  if constexpr (SHORT) return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+  else return a ^ b ^ c;
+}
+template <bool SHORT = true>
 __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                  uint32_t k0, uint32_t k1) {
   const uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u, W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
 #pragma unroll
   for (int r = 0; r < 10; r++) {
-    uint32_t hi0 = __umulhi(M0, c0), lo0 = M0 * c0;
-    uint32_t hi1 = __umulhi(M1, c2), lo1 = M1 * c2;
-    uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+    uint32_t hi0, lo0, hi1, lo1;
+    mul_wide<SHORT>(M0, c0, hi0, lo0);
+    mul_wide<SHORT>(M1, c2, hi1, lo1);
+    uint32_t n0 = xor3<SHORT>(hi1, c1, k0), n2 = xor3<SHORT>(hi0, c3, k1);
     c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
     k0 += W0; k1 += W1;
   }
@@ -70,12 +92,13 @@ struct DropCfg {
   uint32_t thresh;      // drop iff (word >> 8) < thresh; 0 disables dropout
   float scale;          // 1/(1-p)
 };
+template <bool SHORT = true>
 __device__ __forceinline__ void dropout_keep4(const DropCfg& d, uint64_t q, bool keep[4]) {
   if (d.thresh == 0) {
     keep[0] = keep[1] = keep[2] = keep[3] = true;
     return;
   }
-  Philox4 w = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), d.site, d.layer, d.k0, d.k1);
+  Philox4 w = philox4x32_10<SHORT>((uint32_t)q, (uint32_t)(q >> 32), d.site, d.layer, d.k0, d.k1);
 #pragma unroll
   for (int j = 0; j < 4; j++) keep[j] = (w.v[j] >> 8) >= d.thresh;
 }
