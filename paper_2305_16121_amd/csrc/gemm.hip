@@ -7,7 +7,7 @@
 // 128 bytes then cover all 64 banks once) and read with ds_read_b128; an
 // operand stored with the contraction index as row is kept as [64 k][rows] (padded rows) and read
 // with the LDS transpose read ds_read_b64_tr_b16, which hands each lane 4 consecutive k of one row.
-// v_mfma_f32_32x32x16_bf16: A lane l holds row l%32, k = 8*(l/32)..+7; B the same with columns;
+// v_mfma_f32_32x32x16_bf16 (the register-staged and the four-wave kernels; the others: see the epilogues of 16x16x32): A lane l holds row l%32, k = 8*(l/32)..+7; B the same with columns;
 // accumulator element i of lane l is C[8*(i/4) + 4*(l/32) + i%4][l%32].
 #include <algorithm>
 #include <type_traits>
@@ -395,11 +395,21 @@ struct LinesOfC {
   __device__ __forceinline__ LinesOfC(const GemmArgs& g, int row0, int col0, int lane)
       : rs(__builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<float*>(g.C) + (size_t)row0 * g.ldc + col0, 0, 0x7fffffff, 0x00020000)),
         at((8 * (lane >> 5) * g.ldc + (lane & 31)) * 4), pitch(g.ldc * 4) {}
-  __device__ __forceinline__ float load(int row) const { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, at, row * pitch, 0)); }
-  __device__ __forceinline__ void store(int row, float v) const { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, at, row * pitch, 0); }
+  template <bool AROUND>
+  __device__ __forceinline__ float load(int row) const { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, at, row * pitch, AROUND ? 2 : 0)); }
+  template <bool AROUND>
+  __device__ __forceinline__ void store(int row, float v) const { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, at, row * pitch, AROUND ? 2 : 0); }
 };
 // requests ahead of the first store, as epi_request: 16 rows x 32 columns from (row0, col0)
-template <int EPI, bool FULL>
+template <bool AROUND>
+__device__ __forceinline__ void store16(uint16_t* p, const u32x2& x, const u32x2& y) {
+  const u32x4_align8 v = u32x4{x[0], x[1], y[0], y[1]};
+  if constexpr (AROUND) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_align8*>(p));
+  else *reinterpret_cast<u32x4_align8*>(p) = v;
+}
+// AROUND (eight-wave kernels): a gradient that is added to and the pre-activations that are kept for the backward pass go past the caches, where they would only
+// drive out what the next kernels read.  us a step: h 4096 1769 -> 1759, h 8192 2765 -> 2752, llama h 4096 1856 -> 1847.  Not on small tiles (h 12288 with 128 rows 968 -> 979).
+template <int EPI, bool FULL, bool AROUND = false>
 __device__ __forceinline__ void epi_request16(const GemmArgs& g, int row0, int col0, int lane, EpiOperands (&o)[2]) {
   if constexpr (EPI == EPI_ACC_F32) {
     if constexpr (FULL) {
@@ -407,7 +417,7 @@ __device__ __forceinline__ void epi_request16(const GemmArgs& g, int row0, int c
 #pragma unroll
       for (int t = 0; t < 2; t++)
 #pragma unroll
-        for (int e = 0; e < 4; e++) o[t].f[e] = c.load(4 * t + e);
+        for (int e = 0; e < 4; e++) o[t].f[e] = c.template load<AROUND>(4 * t + e);
       return;
     }
     const int col = min(col0 + (lane & 31), g.N - 1);
@@ -437,7 +447,7 @@ __device__ __forceinline__ void epi_request16(const GemmArgs& g, int row0, int c
     }
   }
 }
-template <int EPI, bool FULL>
+template <int EPI, bool FULL, bool AROUND = false>
 __device__ __forceinline__ void epi_finish16(const GemmArgs& g, int row0, int col0, int lane, const f32x4& a0, const f32x4& a1, const EpiOperands (&o)[2]) {
   if constexpr (EPI == EPI_F32 || EPI == EPI_ACC_F32) {
     f32x4 v[2] = {a0, a1};
@@ -447,7 +457,7 @@ __device__ __forceinline__ void epi_finish16(const GemmArgs& g, int row0, int co
 #pragma unroll
       for (int t = 0; t < 2; t++)
 #pragma unroll
-        for (int e = 0; e < 4; e++) c.store(4 * t + e, EPI == EPI_ACC_F32 ? o[t].f[e] + v[t][e] : v[t][e]);
+        for (int e = 0; e < 4; e++) c.template store<AROUND && EPI == EPI_ACC_F32>(4 * t + e, EPI == EPI_ACC_F32 ? o[t].f[e] + v[t][e] : v[t][e]);
       return;
     }
     const int col = col0 + (lane & 31);
@@ -477,12 +487,11 @@ __device__ __forceinline__ void epi_finish16(const GemmArgs& g, int row0, int co
     uint16_t* cp = reinterpret_cast<uint16_t*>(g.C) + (size_t)row * g.ldc + col + (EPI == EPI_DSWIGLU ? (col & ~31) : 0);
     *reinterpret_cast<u32x4_align8*>(cp) = u32x4{out[0][0], out[0][1], out[1][0], out[1][1]};
     if constexpr (EPI == EPI_DSWIGLU) *reinterpret_cast<u32x4_align8*>(cp + 32) = u32x4{also[0][0], also[0][1], also[1][0], also[1][1]};
-    if constexpr (EPI == EPI_BIAS_GELU)
-      *reinterpret_cast<u32x4_align8*>(g.aux + (size_t)row * g.ldaux + col) = u32x4{also[0][0], also[0][1], also[1][0], also[1][1]};
+    if constexpr (EPI == EPI_BIAS_GELU) store16<AROUND>(g.aux + (size_t)row * g.ldaux + col, also[0], also[1]);
   }
 }
 // SwiGLU: gate columns col0 .. col0+31 of the interleaved layout in g0, g1, the up columns behind them in u0, u1
-template <bool FULL>
+template <bool FULL, bool AROUND = false>
 __device__ __forceinline__ void epi_swiglu16(const GemmArgs& g, int row0, int col0, int lane, const f32x4& g0, const f32x4& g1, const f32x4& u0, const f32x4& u1) {
   const int row = row0 + (lane & 15);
   if (!FULL && row >= g.M) return;
@@ -504,9 +513,9 @@ __device__ __forceinline__ void epi_swiglu16(const GemmArgs& g, int row0, int co
   const int c = col16(lane);
   if (!FULL && col0 + c >= g.N) return;
   uint16_t* ap = g.aux + (size_t)row * g.ldaux + col0 + c;
-  *reinterpret_cast<u32x4_align8*>(ap) = u32x4{pg[0][0], pg[0][1], pg[1][0], pg[1][1]};
-  *reinterpret_cast<u32x4_align8*>(ap + 32) = u32x4{pu[0][0], pu[0][1], pu[1][0], pu[1][1]};
-  *reinterpret_cast<u32x4_align8*>(reinterpret_cast<uint16_t*>(g.C) + (size_t)row * g.ldc + col0 / 2 + c) = u32x4{pf[0][0], pf[0][1], pf[1][0], pf[1][1]};
+  store16<AROUND>(ap, pg[0], pg[1]);
+  store16<AROUND>(ap + 32, pu[0], pu[1]);
+  store16<false>(reinterpret_cast<uint16_t*>(g.C) + (size_t)row * g.ldc + col0 / 2 + c, pf[0], pf[1]);
 }
 // Waves of a workgroup form a WGM x WGN x WGK grid: a wave owns a (BM/WGM) x (BN/WGN) part of the block tile and,
 // when WGK > 1, every WGK-th pair of the 16-wide k steps of each stage; the WGK partial accumulators of a part are
@@ -1707,16 +1716,16 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
     for (int h = 0; h < 2; h++)
 #pragma unroll
       for (int j = 0; j < 2; j++) {
-        if (!BIAS || h == 0) epi_request16<EPI, FULL>(g, row0 + 16 * h, n0 + wn * 64 + 32 * j, lane, o[h][j]);
+        if (!BIAS || h == 0) epi_request16<EPI, FULL, true>(g, row0 + 16 * h, n0 + wn * 64 + 32 * j, lane, o[h][j]);
       }
   };
   // 16 rows of the wave's 64 columns
   auto finish_rows = [&](int row, const f32x4& a0, const f32x4& a1, const f32x4& a2, const f32x4& a3, const EpiOperands (&o)[2][2]) {
     if constexpr (EPI == EPI_SWIGLU) {  // the wave's 64 columns are one [gate 32 | up 32] block
-      epi_swiglu16<FULL>(g, row, n0 + wn * 64, lane, a0, a1, a2, a3);
+      epi_swiglu16<FULL, true>(g, row, n0 + wn * 64, lane, a0, a1, a2, a3);
     } else {
-      epi_finish16<EPI, FULL>(g, row, n0 + wn * 64, lane, a0, a1, o[0]);
-      epi_finish16<EPI, FULL>(g, row, n0 + wn * 64 + 32, lane, a2, a3, o[1]);
+      epi_finish16<EPI, FULL, true>(g, row, n0 + wn * 64, lane, a0, a1, o[0]);
+      epi_finish16<EPI, FULL, true>(g, row, n0 + wn * 64 + 32, lane, a2, a3, o[1]);
     }
   };
   if constexpr (SQ) {
@@ -2290,7 +2299,7 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
 
 // Time of an eight-wave launch over wgs workgroups, seconds.  What the MFMA loops are bound by is the power they draw together, so a
 // round that leaves CUs idle runs its stages faster, down to three quarters of the time of a full one (128x256 tiles, a 64-wide
-// stage: 256 workgroups 0.9 us, 144 or fewer 0.68); the output, read and written, moves at 4 TB/s.
+// stage: 256 workgroups 0.83 us, 144 or fewer three quarters; 256x256 1.4); the output, read and written, moves at 4 TB/s.
 double pp_seconds(int bm, long wgs, int k_per, double out_bytes) {
   double t = out_bytes / 4.0e12;
   for (; wgs > 0; wgs -= 256)
