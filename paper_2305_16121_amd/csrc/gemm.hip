@@ -1886,6 +1886,13 @@ __device__ __forceinline__ float frag_sum(const u32x4& f) {
   for (int i = 0; i < 4; i++) s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_, (uint32_t)f[i]), one, s, false);
   return s;
 }
+// the sums of two fragments of 16 columns each, of the k rows of lanes l and l + 32: lane l has column l%16 of the first, lane 32 + l of the second one
+__device__ __forceinline__ float frag_sum_pair(const u32x4& f0, const u32x4& f1) {
+  const float x = frag_sum(f0), y = frag_sum(f1);
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y), false, false);
+  const uint32_t lo = r[0], hi = r[1];
+  return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+}
 // EPI_BF16_DELTA (dO = dZ1 Wo^T): the tile holds whole heads of dO, so the row sums of dO * O come from the registers that store it, for one
 // more operand of the epilogue; the launch that read both arrays again is saved (a step of two recomputed layers, h 1024, 512 tokens:
 // 544.7 -> 538.2 us; three layers of h 1024, 600 tokens, 128 columns a head: 534.9 -> 533.0, on 64x128 instead of 64x64 tiles).
@@ -1963,9 +1970,9 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
   int stage = 0;
   bool sums = false;
   if constexpr (COLSUM) sums = g.sums && tile_m == 0 && wm == 0;
-  float csum[CB], part[CB];
+  float csum[TN], part[TN];  // lane l: column 32 j + 16 (l/32) + l%16, k = 8 ((l/16)%2)..+7 and the same 16 further on
 #pragma unroll
-  for (int j = 0; j < CB; j++) csum[j] = part[j] = 0.f;
+  for (int j = 0; j < TN; j++) csum[j] = part[j] = 0.f;
   // one tile; YOUNG: tiles behind it that may still be in flight (compile-time, for the wait); steady: tile kt+NS-1 exists
   auto iteration = [&](auto young_c, auto steady_c, int kt) {
     constexpr int Y = PER * decltype(young_c)::value;
@@ -1990,8 +1997,8 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
     }
     if (COLSUM && sums) {
 #pragma unroll
-      for (int j = 0; j < CB; j++) {
-        part[j] += frag_sum(fb[j]);
+      for (int j = 0; j < TN; j++) {
+        part[j] += frag_sum_pair(fb[2 * j], fb[2 * j + 1]);
         if ((kt & 7) == 7) {
           csum[j] += part[j];
           part[j] = 0.f;
@@ -2022,24 +2029,23 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
     for (int q = 0; q < NV; q++) xch[(wave * NV + q) * 64 + lane] = acc[I + q / CB][q % CB];
   };
   if (wk == 0) hand_over(std::integral_constant<int, 1>{}); else hand_over(std::integral_constant<int, 0>{});
-  float* xsum = reinterpret_cast<float*>(lds + StLds<TM, TN, NS>::kExchange) + 64 * CB * wn;
+  float* xsum = reinterpret_cast<float*>(lds + StLds<TM, TN, NS>::kExchange) + 64 * TN * wn;
   if (COLSUM && sums) {
 #pragma unroll
-    for (int j = 0; j < CB; j++) {
+    for (int j = 0; j < TN; j++) {
       csum[j] += part[j];
       if (wk == 1) xsum[64 * j + lane] = csum[j];
     }
   }
   __syncthreads();
   if constexpr (COLSUM) if (sums && wk == 0) {
-    static_assert(StLds<TM, TN, NS>::kExchange + 512 * CB <= StLds<TM, TN, NS>::bytes, "column sums behind the exchange");
+    static_assert(StLds<TM, TN, NS>::kExchange + 512 * TN <= StLds<TM, TN, NS>::bytes, "column sums behind the exchange");
 #pragma unroll
-    for (int j = 0; j < CB; j++) {
+    for (int j = 0; j < TN; j++) {
       float t = csum[j] + xsum[64 * j + lane];
       t += __shfl_xor(t, 16, 64);  // the other k of a step
-      t += __shfl_xor(t, 32, 64);
-      const int col = col0 + 16 * j + (lane & 15);
-      if (lane < 16 && col < g.N) g.sums[col] += t;
+      const int col = col0 + 32 * j + 16 * (lane >> 5) + (lane & 15);
+      if (!(lane & 16) && col < g.N) g.sums[col] += t;
     }
   }
   f32x4 v[NV];  // [row part][column part]
@@ -2048,9 +2054,7 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
 #pragma unroll
     for (int q = 0; q < NV; q++) v[q] = acc[I + q / CB][q % CB] + xch[((wave ^ 4) * NV + q) * 64 + lane];
   };
-  float dsum[TM];  // EPI_BF16_DELTA: this lane's part of a row's sum over the wave's columns, which belong to one head
-#pragma unroll
-  for (int i = 0; i < TM; i++) dsum[i] = 0.f;
+  u32x2 w[EPI == EPI_BF16_DELTA ? NV : 1] = {};  // EPI_BF16_DELTA: dO as it is stored
   auto finish = [&](auto full_c) {
     constexpr bool FULL = decltype(full_c)::value;
 #pragma unroll
@@ -2066,13 +2070,8 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
           const int col = col0 + 16 * j + 4 * (lane >> 4);
           if (!FULL && col >= g.N) continue;
           const f32x4& x = v[i * CB + j];
-          const u32x2 o = pre[i][j >> 1][j & 1].a, w = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])};
-          *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + (size_t)r * g.ldc + col) = w;
-#pragma unroll
-          for (int k = 0; k < 2; k++) {
-            dsum[i] += bf16_bits_to_f32(w[k] & 0xffffu) * bf16_bits_to_f32(o[k] & 0xffffu);
-            dsum[i] += bf16_bits_to_f32(w[k] >> 16) * bf16_bits_to_f32(o[k] >> 16);
-          }
+          w[i * CB + j] = u32x2{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])};
+          *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + (size_t)r * g.ldc + col) = w[i * CB + j];
         }
       } else {
 #pragma unroll
@@ -2090,23 +2089,40 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
     if (wk == 0) gather(H0{}); else gather(H1{});
   }
   if (m0 + BM <= g.M && n0 + BN <= g.N) finish(std::true_type{}); else finish(std::false_type{});
-  if constexpr (EPI == EPI_BF16_DELTA) {  // the two waves of a row (its column parts) put their sums together in LDS
+  // The sums of a row, in the order of 32x32 accumulators: in each of 32 columns the four chains of columns 16 H + 4 b ..+3, +8 (H, b = 0, 1), which run on
+  // through the wave's parts of 32; then both b, both H and both waves of a head (which hold its column parts, one each where a head is 64 columns of a
+  // 128-wide tile), these by way of LDS.  A lane of the upper half holds the +8 of the lane 32 below it, whose chain it goes on with.
+  if constexpr (EPI == EPI_BF16_DELTA) {
     constexpr int at = StLds<TM, TN, NS>::kExchange + 1024;
-    static_assert(at + BM * 8 <= StLds<TM, TN, NS>::bytes, "row sums behind the exchange");
+    static_assert(at + BM * 16 <= StLds<TM, TN, NS>::bytes, "row sums behind the exchange");
     float* red = reinterpret_cast<float*>(lds + at);
 #pragma unroll
-    for (int i = 0; i < TM; i++) {
-      dsum[i] += __shfl_xor(dsum[i], 16, 64);
-      dsum[i] += __shfl_xor(dsum[i], 32, 64);
-      if (lane < 16) red[2 * (wm * 32 * TM + 16 * (TM * wk + i) + lane) + wn] = dsum[i];
-    }
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int H = 0; H < 2; H++) {
+        auto chain = [&](float s) {
+#pragma unroll
+          for (int j = 0; j < TN; j++)
+#pragma unroll
+            for (int k = 0; k < 2; k++) {
+              const uint32_t x = w[i * CB + 2 * j + H][k], o = pre[i][j][H].a[k];
+              s += bf16_bits_to_f32(x & 0xffffu) * bf16_bits_to_f32(o & 0xffffu);
+              s += bf16_bits_to_f32(x >> 16) * bf16_bits_to_f32(o >> 16);
+            }
+          return s;
+        };
+        const float below = __shfl_xor(chain(0.f), 32, 64);
+        float s = chain(lane < 32 ? 0.f : below);
+        s += __shfl_xor(s, 16, 64);
+        if ((lane & 48) == 32) red[4 * (wm * 32 * TM + 16 * (TM * wk + i) + (lane & 15)) + 2 * wn + H] = s;
+      }
     __syncthreads();
     const int r = tid % BM, part = tid / BM;  // a head is 64 columns (one column part of a 128-wide tile) or all columns of the tile
     const bool one = g.head_dim == BN;
     const int row = m0 + r, head = n0 / g.head_dim + part, heads = g.N / g.head_dim;
     if (part < (one ? 1 : 2) && row < g.M && head < heads) {
-      const float* p = red + 2 * r + part;
-      g.sums[((size_t)(row / g.seq) * heads + head) * g.seq + row % g.seq] = one ? p[0] + p[1] : p[0];
+      const float* p = red + 4 * r + 2 * part;
+      g.sums[((size_t)(row / g.seq) * heads + head) * g.seq + row % g.seq] = one ? (p[0] + p[1]) + (p[2] + p[3]) : p[0] + p[1];
     }
   }
 }
