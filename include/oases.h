@@ -315,7 +315,7 @@ int oases_op_gemm(int op, int epi, int M, int N, int K, const void *A, int lda, 
  * 204128256, K % (64 * slices) == 0); the 256x256 kernel takes one slice only.  W = 3 names the eight-wave forms of
  * the same tiles (two waves per SIMD that alternate between loading and multiplying): 301256256, 301128256, 302128256,
  * 304128256, on the shapes of their W = 2 counterparts; 301128256 gives bit for bit what 201128256 gives.  (The library's own choice also
- * sends them ragged rows of a k-major operand, K % 64 == 0, and TN over any K from 1024 on; forced by name they keep to those shapes.)  W = 4 names the
+ * sends x01128256 the TN form over any K from 1024 on, and its slices TN with a shorter last one; forced by name they keep to those shapes.)  W = 4 names the
  * small-tile kernels 64x64 and 64x128 (401064064, 401064128; direct-to-LDS loads, waves split k, any shape the GEMM
  * accepts, up to 16 slices of whole 64-wide stages; the forward SwiGLU epilogue on 64x128 only), W = 5 the same with 128x128 tiles
  * (501128128; chosen in passes only, see below).  The W >= 2

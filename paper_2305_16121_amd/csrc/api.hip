@@ -335,9 +335,9 @@ static bool group_sums_bias(const oases_handle* H, int variant) { return !H->lla
 static void group_weight_gradients(oases_handle* H, std::vector<Op>& ops) {
   if (H->cfg.flags & (OASES_FLAG_PIN_GEMM | OASES_FLAG_PROFILE)) return;
   bool wins;
-  int v = gemm_tn_group_variant(H->M, H->fp, H->h, H->h, H->fw, H->gemm_ws_bytes, &wins);
+  int v = gemm_tn_group_variant(H->M, H->fp, H->h, H->h, H->fw, H->gemm_ws_bytes, !H->llama, &wins);
   if (wins) H->ff_group = v;
-  v = gemm_tn_group_variant(H->M, H->hp, H->h, H->h, 3 * H->hp, H->gemm_ws_bytes, &wins);
+  v = gemm_tn_group_variant(H->M, H->hp, H->h, H->h, 3 * H->hp, H->gemm_ws_bytes, !H->llama, &wins);
   for (const Op& op : ops) wins = wins && op.kind != B_PQ_WGRAD;
   if (wins) H->pq_group = v;
   std::vector<Op> out;

@@ -208,7 +208,7 @@ struct TnProblem {
 constexpr int kSliceCounters = 1024;
 int launch_gemm_tn_group(int variant, int K, const TnProblem& a, const TnProblem& b, float* ws, size_t ws_bytes, uint32_t* counters, hipStream_t s);
 // the library's choice; wins: whether one launch is expected to take less time than two
-int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes, bool* wins = nullptr);
+int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes, bool bias, bool* wins = nullptr);
 constexpr size_t kSplitKWorkspaceBytes = 256u << 20;
 // p_attn > 0: dropout on the probabilities (mask keyed by seed, layer, sequence, global head = head0 + local head, q, k)
 // pin: block shapes chosen as for all batch * seq rows, so that calls over parts of those rows add in one order whatever the part

@@ -1485,13 +1485,12 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
   else offB = frag_offsets_mc<PITCH_B, 4>(wn * 64, 32 * k32, lane, mc_swizzle);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(OASES_LDS char*)lds;
   u32x4 fa[8], fb[4];
-  // the end of a memory phase and the MFMA phase, with the loads that go between its MFMAs.  left: k from the first of the fragments on (TAIL: weight
-  // gradients over a number of rows that is no whole number of k tiles; k beyond K counts as zero in both operands)
-  constexpr bool TAIL = !A_KC && !B_KC;
+  // the end of a memory phase and the MFMA phase, with the loads that go between its MFMAs.  left: k from the first of the fragments on (HALVES:
+  // weight gradients over a number of rows that is no whole number of k tiles; k beyond K counts as zero in both operands)
   auto multiply = [&](auto between, int left = 32) {
     wait_frags16(fa, fb);
     __builtin_amdgcn_sched_barrier(0);
-    if (TAIL && left < 32 && 8 * (lane >> 4) >= left) {
+    if (HALVES && left < 32 && 8 * (lane >> 4) >= left) {
 #pragma unroll
       for (int i = 0; i < 8; i++) fa[i] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
@@ -1512,7 +1511,7 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
     __builtin_amdgcn_sched_barrier(0);
   };
   if constexpr (SQ) {
-    const int S = TAIL ? (g.K + 31) / 32 : g.K / 32, F = g.K / 32;  // iterations; k tiles that are whole
+    const int S = g.K / 32;  // iterations
     // the two groups run code of their own: a branch between MFMAs, taken or not, costs the MFMA pipe more than what it jumps over
     auto run = [&](auto grp_c) {
       constexpr int GRP = decltype(grp_c)::value;
@@ -1530,22 +1529,13 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
       for (int j = 0; j < PER; j++) src[j] = pp_src<KC, 256>(GRP ? g.ldb : g.lda, GRP ? n0 : m0, PER * wn + j, lane, GRP ? g.N : g.M);
       char* const dst = lds + (GRP ? kB : 0) + PER * wn * 1024;
       auto issue1 = [&](int j, int u, uint32_t at) { dma16(rs, src[j], (uint32_t)u * step, dst + at + j * 1024); };
-      // all of unit u.  What lies beyond K is fetched from valid memory: the second half of a k-major unit from the first one (and not used), k rows from k = 0
+      // all of unit u; K an odd number of k tiles: the second half of the last unit of a k-major operand lies beyond K and is fetched from the first half (not used)
       auto issue_all = [&](int u, uint32_t at) {
-        if constexpr (KC) {
-          const uint32_t back = 2 * u + 1 == S ? 64 : 0;
+        const uint32_t back = KC && 2 * u + 1 == S ? 64 : 0;
 #pragma unroll
-          for (int j = 0; j < PER; j++) {
-            const int chunk = (lane & 7) ^ ((4 * j + (lane >> 4)) & 7);  // of eight: instruction j of a k-major unit
-            dma16(rs, chunk >= 4 ? src[j] - back : src[j], (uint32_t)u * step, dst + at + j * 1024);
-          }
-        } else {
-#pragma unroll
-          for (int j = 0; j < PER; j++) {
-            const int kr = 2 * (PER * wn + j) + (lane >> 5);
-            if (!TAIL || u < F) dma16(rs, src[j], (uint32_t)u * step, dst + at + j * 1024);
-            else dma16(rs, 32 * u + kr < g.K ? src[j] + (uint32_t)u * step : src[j] - kr * (step / 32), 0, dst + at + j * 1024);
-          }
+        for (int j = 0; j < PER; j++) {
+          const int chunk = (lane & 7) ^ ((4 * j + (lane >> 4)) & 7);  // of eight: instruction j of a k-major unit
+          dma16(rs, chunk >= 4 ? src[j] - back : src[j], (uint32_t)u * step, dst + at + j * 1024);
         }
       };
       // before the loop: as many units as are there when the loop is in MFMA phase 0
@@ -1588,7 +1578,7 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
         if (ON) advance_into();
       };
       int kt = 0;
-      for (; kt + 1 + 5 < F; kt += 2) {
+      for (; kt + 1 + 5 < S; kt += 2) {
         iteration(std::false_type{}, kt);
         iteration(std::true_type{}, kt + 1);
       }
@@ -1602,7 +1592,7 @@ __device__ __forceinline__ void pp_tile(const GemmArgs& g, int pid, char* lds, c
         else if (young >= 8) vm_wait<8>();
         else if (young >= 4) vm_wait<4>();
         else vm_wait<0>();
-        multiply([](int) {}, g.K - 32 * kt);
+        multiply([](int) {});
         const int u = unit_of(kt);
         if ((!KC || odd == (GRP == 1)) && u * TILES < S) {
           issue_all(u, into);
@@ -2236,7 +2226,10 @@ int launch_small(const GemmCall& g0, int ksplit, float* ws, size_t ws_bytes, hip
   }
 }
 
-// Tile and split-K choice by a small time model.  Bigger tiles run closer to the MFMA rate (fewer LDS bytes per flop)
+// Tile and split-K choice by a small time model.  What it chooses settles the order in which the fp32 terms of an output element are added: a 256x256 tile
+// and the square register-staged one run through k in one chain, the others (the k halves of 64) in two, every k slice in one or two of its own, and fewer chains round worse
+// (rms against 64 bits over 8192 rows 5.7e-7 with one, 4.0e-7 with two).  So its rates stay the ones that the results were fixed with: another kernel for
+// a shape is taken where it adds in the same order (same_sums).  Bigger tiles run closer to the MFMA rate (fewer LDS bytes per flop)
 // but a launch only uses the chip well if its workgroup count is near a multiple of the 256 CUs; splitting K multiplies
 // the workgroup count at the price of a second pass over fp32 partial planes.  Rates measured on this part.
 struct TileChoice { int bm, bn, ksplit; bool wave_ksplit; bool dtl = false; bool pp = false; bool st = false; };  // st: the small-tile kernel; pp: the eight-wave kernel of a direct-to-LDS tile shape
@@ -2248,33 +2241,29 @@ struct TileChoice { int bm, bn, ksplit; bool wave_ksplit; bool dtl = false; bool
 bool dtl_fits(int kind, int M, int N, int K) {
   return (kind == 2 || M % 256 == 0) && (kind != 1 || N % 256 == 0) && M % 8 == 0 && N % 8 == 0 && K % BKD == 0 && K >= BKD;
 }
-// The eight-wave kernels take more: ragged rows of a k-major operand on 256 x 256 tiles where K is whole 64-wide units, and weight gradients over any number of
-// rows.  The library's choice uses that; a variant forced by a caller's name keeps to the bounds above.  us, the tiles taken before (64x128, 128x256, register-
-// staged) -> these: TN 6144 x 3072 x 7240 432 -> 265, NT 7040 x 3456 x 3456 232 -> 152, NN 7112 x 3456 x 4608 257 -> 194; steps of drawn sizes with 2928 rows of
-// 3072 1978 -> 1831.  Fewer than 1024 rows stay on small tiles: 2560 x 5120 x 808 60 us.
-bool pp256_fits(int kind, int M, int N, int K) {
-  return dtl_fits(kind, M, N, K) || (M % 8 == 0 && N % 8 == 0 && K % 8 == 0 && (kind == 2 ? K >= 1024 : K % 64 == 0));
-}
-bool pp128_fits(int kind, int M, int N, int K) { return M % 8 == 0 && N % 8 == 0 && ((K % BKR == 0 && K >= BKR) || (kind == 2 && K % 8 == 0 && K >= 1024)); }
 bool dtl_rect_fits(int kind, int M, int N, int K) {  // the 128 x 256 kernel redirects rows of a k-major operand too
   (void)kind;
   return M % 8 == 0 && N % 8 == 0 && K % BKR == 0 && K >= BKR;
 }
+// The eight-wave kernel also takes weight gradients over any number of rows from 1024 on: the library's choice uses that, a variant forced by a caller's name keeps
+// to the bounds above.  Fewer than 1024 rows stay on small tiles: 2560 x 5120 x 808 60 us.
+bool pp128_fits(int kind, int M, int N, int K) { return dtl_rect_fits(kind, M, N, K) || (kind == 2 && M % 8 == 0 && N % 8 == 0 && K % 8 == 0 && K >= 1024); }
 bool dtl_rect_whole(int M, int N, int K) { return M % 128 == 0 && N % 256 == 0 && K % BKR == 0 && K >= BKR; }
 bool pp_slices_fit(int kind, int M, int N, int K, int S) {  // S k slices of whole stages; a weight gradient's last one may be shorter
-  if (kind == 2 && K >= 1024 * S) return M % 8 == 0 && N % 8 == 0 && K % 8 == 0;
+  if (S == 1) return pp128_fits(kind, M, N, K);
+  if (kind == 2 && K >= 1024 * S) return dtl_rect_fits(kind, M, N, K);
   return K % (S * BKR) == 0 && dtl_rect_fits(kind, M, N, K / S);
 }
 struct KindTable { bool wave_ksplit; float r256x256, r128x256, r256x128, r128x128; };
-const KindTable g_kinds[4] = {{true, 1330.f, 1150.f, 960.f, 740.f}, {true, 1330.f, 1150.f, 960.f, 740.f},
-                        {true, 1330.f, 1150.f, 960.f, 740.f}, {false, 1330.f, 1150.f, 900.f, 740.f}};
+const KindTable g_kinds[4] = {{true, 1200.f, 1080.f, 960.f, 740.f}, {true, 1200.f, 1080.f, 960.f, 740.f},
+                        {true, 1200.f, 1080.f, 960.f, 740.f}, {false, 1200.f, 1080.f, 900.f, 740.f}};
 TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes) {
   const KindTable& kt = g_kinds[kind];
   // Tiles that the direct-to-LDS kernels do not cover run on the register-staged kernels.  256x256: at three quarters of their rate (NT dSwiGLU 8192 x
   // 1376 x 4096: 138 us against 133 on 128x256 tiles, which may be ragged, 9984 x 2624 x 1600 153 against 138, NT 8656 x 1984 x 1344 76 against 60).  128x256
   // where k is no whole number of stages: at half (NN 9576 x 1536 x 1376: 81 us, 62 on 256x256); TN at 700 and 740 (2560 x 5120 x 808: 256x256 75 us,
   // 128x256 75, 64x128 60).
-  const bool rect = pp128_fits(kind, M, N, K);
+  const bool rect = dtl_rect_fits(kind, M, N, K);
   const float r128 = rect ? kt.r128x256 : kind == 2 ? 740.f : 650.f, r256x128 = rect ? kt.r256x128 : kind == 2 ? 740.f : 600.f;
   const struct { int bm, bn; float tflops; } cand[] = {{256, 256, kt.r256x256}, {128, 256, r128}, {256, 128, r256x128}, {128, 128, kt.r128x128}};
   TileChoice best{128, 128, 1, kt.wave_ksplit};
@@ -2283,13 +2272,10 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
     const long tm = (M + c.bm - 1) / c.bm, tn = (N + c.bn - 1) / c.bn;
     for (int S = 1; S <= 8; S *= 2) {
       if (S > 1 && ((size_t)S * M * N * 4 > ws_bytes || K / S < 512)) break;
-      const long wgs = tm * tn * S;
-      // time of one workgroup's tile slice at the tile's rate (one workgroup per CU), times the number of rounds; a last round of few workgroups has the
-      // chip's power to itself (pp_seconds): 8160 x 5120 x 2560 NN, 2.5 rounds of 256x256 199 us, 5 of 128x256 227
-      const bool pp = c.bn == 256 && (c.bm == 256 ? S == 1 && pp256_fits(kind, M, N, K) : rect);
-      const double rounds = pp && wgs > 256 ? wgs / 256 + (wgs % 256 ? std::max(0.75, wgs % 256 / 256.0) : 0.0) : (double)((wgs + 255) / 256);
-      const double tflops = c.bm == 256 && c.bn == 256 && !(S == 1 && pp256_fits(kind, M, N, K)) ? (kind == 2 ? 700.f : 900.f) : c.tflops;
-      double t = rounds * (2.0 * c.bm * c.bn * ((double)K / S) + 3.0e6) / (tflops * 1e12 / 256.0);
+      const long wgs = tm * tn * S, rounds = (wgs + 255) / 256;
+      // time of one workgroup's tile slice at the tile's rate (one workgroup per CU), times the number of rounds
+      const double tflops = c.bm == 256 && c.bn == 256 && !(S == 1 && dtl_fits(kind, M, N, K)) ? (kind == 2 ? 700.f : 900.f) : c.tflops;
+      double t = (double)rounds * (2.0 * c.bm * c.bn * ((double)K / S) + 3.0e6) / (tflops * 1e12 / 256.0);
       if (S > 1) t += ((double)(2 * S + 1) * M * N * 4.0) / 3.0e12 + 4e-6;
       if (t < best_t) { best_t = t; best = TileChoice{c.bm, c.bn, S, kt.wave_ksplit}; }
     }
@@ -2297,8 +2283,8 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
   // Whole tiles without k slices: the eight-wave direct-to-LDS kernels, which measure faster than the four-wave and the
   // register-staged kernels of the same tile on every shape of the two full-size workloads (cold operands, 3-15 %).
   if (best.ksplit == 1) {
-    if (best.bm == 256 && best.bn == 256 && pp256_fits(kind, M, N, K)) best.dtl = best.pp = true;
-    if (best.bm == 128 && best.bn == 256 && pp128_fits(kind, M, N, K)) best = TileChoice{128, 256, 1, true, true, true};
+    if (best.bm == 256 && best.bn == 256 && dtl_fits(kind, M, N, K)) best.dtl = best.pp = true;
+    if (best.bm == 128 && best.bn == 256 && dtl_rect_fits(kind, M, N, K)) best = TileChoice{128, 256, 1, true, true, true};
     // Few rows, long k (a sub-batch of 1024 rows against K = 8192): 128 x 128 tiles fill the chip but run at the small
     // tile's rate; the 128 x 256 direct-to-LDS kernel over two k slices fills it too, and is faster even with its second
     // pass (measured on cold operands: 87-93 us against 108-116 us).
@@ -2307,7 +2293,7 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
         K % (2 * BKR) == 0 && dtl_rect_fits(kind, M, N, K / 2) && (size_t)2 * M * N * 4 <= ws_bytes)
       best = TileChoice{128, 256, 2, true, true, true};
   } else if (best.bm == 128 && best.bn == 256 && (best.ksplit == 2 || best.ksplit == 4) && epi != EPI_SWIGLU && epi != EPI_DSWIGLU &&
-             pp_slices_fit(kind, M, N, K, best.ksplit)) {
+             K % (best.ksplit * BKR) == 0 && dtl_rect_fits(kind, M, N, K / best.ksplit)) {
     best = TileChoice{128, 256, best.ksplit, true, true, true};  // k slices of whole stages: the eight-wave kernel
   }
   return best;
@@ -2315,13 +2301,16 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
 
 // Time of an eight-wave launch over wgs workgroups, seconds.  What the MFMA loops are bound by is the power they draw together, so a
 // round that leaves CUs idle runs its stages faster, down to three quarters of the time of a full one (128x256 tiles, a 64-wide
-// stage: 256 workgroups 0.83 us, 144 or fewer three quarters; 256x256 1.4); the output, read and written, moves at 4 TB/s.
-double pp_seconds(int bm, long wgs, int k_per, double out_bytes) {
+// stage: 256 workgroups 0.9 us, 144 or fewer 0.68); the output, read and written, moves at 4 TB/s.
+double pp_seconds(long wgs, int k_per, double out_bytes, double stage) {
   double t = out_bytes / 4.0e12;
-  for (; wgs > 0; wgs -= 256)
-    t += 4.0e-6 + k_per / 64 * (bm == 256 ? 1.4e-6 : 0.83e-6) * std::max(0.75, (double)std::min(wgs, 256L) / 256.0);
+  for (; wgs > 0; wgs -= 256) t += 4.0e-6 + k_per / 64 * stage * std::max(0.75, (double)std::min(wgs, 256L) / 256.0);
   return t;
 }
+constexpr double kStage256 = 1.75e-6, kStage128 = 0.9e-6;  // of the model
+double pp_seconds(int bm, long wgs, int k_per, double out_bytes) { return pp_seconds(wgs, k_per, out_bytes, bm == 256 ? kStage256 : kStage128); }
+// today's time of a weight gradient on 128x256 tiles without k slices
+double pp128_seconds(long tiles, int K, double out_bytes) { return pp_seconds(tiles, K, out_bytes, 0.83e-6); }
 
 // Small tiles against the choice above, by the same kind of model (measured on this part): a launch costs 2.9 us, a
 // workgroup 0.225 us (64 x 64) or 0.335 us (64 x 128) per 64-wide stage of its slice, two workgroups on a CU take turns at the
@@ -2334,7 +2323,7 @@ double pp_seconds(int bm, long wgs, int k_per, double out_bytes) {
 // 6144 x 12288 x 128 TN 195 -> 152.  Slices of 8192 k and more stay with the large tiles.
 // own_sum: a call of a pass, whose launches add up a few slices by themselves (SliceSum, own_slices): the last workgroup of a tile then reads the other
 // slices' sums, one after the other at some 47 GB/s, instead of a second launch; 128x128 tiles on the same scheme are candidates, with any
-// number of slices (0.57 us a stage, 0.87 of that where 218 and fewer workgroups leave CUs idle and the others more of the power; what TN reads and writes moves at
+// number of slices (0.6 us a stage, 0.85 of that where 218 and fewer workgroups leave CUs idle and the others more of the power; what TN reads and writes moves at
 // 3.4 TB/s from the second round on, since a CU holds one workgroup: 10240 x 3840 x 208 92 us on 64x128, 118 on 128x128).  Measured, us, the choice without -> with, second launches
 // included: inside a step 128 x 4608 x 12288 NN 52 -> 45 (register-staged kernel over eight slices -> 128x128 over six), NT 128 x 6144 x 12288 79 -> 71 (over five); 512 x 8192 x 3072 NT 47 -> 36, 8192 x 512 x
 // 2048 NT 31 -> 26, 200 x 3072 x 8192 36 -> 27; 1488 x 3072 x 3072 NN stays on 144 tiles of 128x256 (40; 64x128 over two slices 72).
@@ -2384,7 +2373,7 @@ TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, do
       const int k_per = st_k_per(K, S);
       if (S > 1 && (!room(S, 128, 128) || k_per < 2 * BKS || (long)(S - 1) * k_per >= K)) break;
       const long wgs = tiles(128, 128) * S;
-      const double t = 4.0e-6 + (double)((wgs + 255) / 256) * ((k_per + BKS - 1) / BKS) * 0.57e-6 * (wgs < 218 ? 0.87 : 1.0) + out / (kind == 2 && wgs > 256 ? 3.4e12 : 4.0e12) + slices(S, 128, 128);
+      const double t = 4.0e-6 + (double)((wgs + 255) / 256) * ((k_per + BKS - 1) / BKS) * 0.6e-6 * (wgs < 218 ? 0.85 : 1.0) + out / (kind == 2 && wgs > 256 ? 3.4e12 : 4.0e12) + slices(S, 128, 128);
       if (t < best_t) {
         best_t = t;
         best = TileChoice{128, 128, S, true};
@@ -2393,6 +2382,25 @@ TileChoice pick_tile(int kind, int epi, int M, int N, int K, size_t ws_bytes, do
     }
   if (seconds) *seconds = best_t;
   return best;
+}
+
+// The kernel for the sums that the model has chosen: the 128x256 eight-wave kernel adds as the register-staged ones of 128x256 and (waves that split k) 256x128
+// tiles and the small tiles do, and takes shapes that the model does not price it for.  seconds: the model's, of its choice.
+//   Weight gradients over any number of rows, us, cold operands: register-staged -> this one 12336 x 472 x 1064 54 -> 40, over two slices 11544 x 144 x 4928 88 -> 58,
+// four 5728 x 168 x 6720 65 -> 46; the better small tiles -> this one 6144 x 3072 x 7240 357 -> 309, 4096 x 4096 x 1992 108 -> 93, 3072 x 3072 x 2920 98 -> 87, 2560 x
+// 2560 x 2056 57 -> 47, with 184 tiles 11736 x 288 x 1112 38 -> 35; with fewer the chip is left too empty: 122 (15544 x 136 x 1248) 26 -> 32, 110 (6928 x 408 x 1240) 26 -> 36.
+//   256x128 tiles, which fill their last round better, at long k: NT 7040 x 3456 x 3456 251 -> 191, dGeLU 14544 x 2176 x 5120 435 -> 354, NN 8648 x 4736 x 4096 377 -> 313, TN
+// 14280 x 1600 x 5568 374 -> 328; TN 12984 x 576 x 1280 56 -> 56, NT dGeLU 8232 x 832 x 768 36 -> 43, NN bias 9056 x 896 x 384 21 -> 24.
+constexpr long kPpLeastTiles = 160;
+TileChoice same_sums(const TileChoice& t, double seconds, int kind, int M, int N, int K) {
+  if (t.pp) return t;
+  const TileChoice pp{128, 256, t.ksplit, true, true, true};
+  const long tiles = (long)((M + 127) / 128) * ((N + 255) / 256);
+  bool takes;
+  if (t.st) takes = kind == 2 && t.ksplit == 1 && K % BKR && pp128_fits(kind, M, N, K) && tiles >= kPpLeastTiles && pp128_seconds(tiles, K, 8.0 * M * N) < seconds;
+  else if (t.bm == 128 && t.bn == 256) takes = kind == 2 && (t.ksplit == 1 || t.ksplit == 2 || t.ksplit == 4) && pp_slices_fit(kind, M, N, K, t.ksplit);
+  else takes = t.bm == 256 && t.bn == 128 && t.wave_ksplit && t.ksplit == 1 && K >= 2048 && pp128_fits(kind, M, N, K);
+  return takes ? pp : t;
 }
 
 int encode_variant(const TileChoice& t) {
@@ -2406,7 +2414,7 @@ bool decode_variant(int variant, int kind, int M, int N, int K, size_t ws_bytes,
   const int wk = variant / 100000000, S = variant / 1000000 % 100, bm = variant / 1000 % 1000, bn = variant % 1000;
   const bool square = (bm == 256 && bn == 256) || (bm == 128 && bn == 128), rect = (bm == 256 && bn == 128) || (bm == 128 && bn == 256);
   if ((wk == 2 || wk == 3) && S == 1) {  // direct-to-LDS kernels (3: eight waves), one k slice
-    if (bm == 256 && bn == 256 && (wk == 3 && pass ? pp256_fits(kind, M, N, K) : dtl_fits(kind, M, N, K))) { *t = TileChoice{256, 256, 1, false, true, wk == 3}; return true; }
+    if (bm == 256 && bn == 256 && dtl_fits(kind, M, N, K)) { *t = TileChoice{256, 256, 1, false, true, wk == 3}; return true; }
     if (bm == 128 && bn == 256 && (wk == 3 && pass ? pp128_fits(kind, M, N, K) : dtl_rect_fits(kind, M, N, K))) { *t = TileChoice{128, 256, 1, true, true, wk == 3}; return true; }
     return false;
   }
@@ -2440,10 +2448,14 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
   if (forced_variant == 0) {
     // Pinned choice: the number of k slices and whether waves split k -- the two things that set the order in which the
     // fp32 terms of an output element are added -- come from (choice_rows, N, K, epilogue), so every launch over a part of
-    // those rows adds in the same order.
+    // those rows adds in the same order.  The 256 x 256 direct-to-LDS kernels need whole row tiles; a part that has none
+    // runs the staged kernel of the same tile, which adds in the same order.
     const bool pinned = kind != 2 && choice_rows > g.M;
-    t = pick_tile(kind, EPI, pinned ? choice_rows : g.M, g.N, g.K, ws ? ws_bytes : 0, nullptr, g.counters != nullptr);
     const int rows = pinned ? choice_rows : g.M;
+    double seconds;
+    t = pick_tile(kind, EPI, rows, g.N, g.K, ws ? ws_bytes : 0, &seconds, g.counters != nullptr);
+    if (gemm_span_fits(A_KC ? rows : g.K, g.lda) && gemm_span_fits(B_KC ? g.N : g.K, g.ldb)) t = same_sums(t, seconds, kind, rows, g.N, g.K);
+    if (pinned && t.dtl && t.bm == 256 && !dtl_fits(kind, g.M, g.N, g.K)) t.dtl = t.pp = false;
     if ((t.dtl || t.st) && !(gemm_span_fits(A_KC ? rows : g.K, g.lda) && gemm_span_fits(B_KC ? g.N : g.K, g.ldb))) {
       if (t.st) t = pick_large_tile(kind, EPI, rows, g.N, g.K, ws ? ws_bytes : 0);
       t.dtl = t.pp = false;
@@ -2475,11 +2487,13 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
     return OASES_EINVAL;
   }
   if (t.dtl && t.pp) {
+    constexpr bool kCanBeRagged = !A_KC || !B_KC;
     const int bm = t.bm;
     GemmCall d = g;
     d.tiles_m = (g.M + bm - 1) / bm;
     d.tiles_n = (g.N + 255) / 256;
     const bool whole = g.M % bm == 0 && g.N % 256 == 0;
+    if (!whole && bm == 256 && !kCanBeRagged) { set_error("gemm: direct-to-LDS kernel on a shape it does not cover"); return OASES_EINVAL; }
     if (bm == 128 && t.ksplit > 1) {
       if constexpr (EPI == EPI_SWIGLU || EPI == EPI_DSWIGLU) {
         set_error("gemm: the SwiGLU epilogues do not run over k slices");
@@ -2515,7 +2529,7 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
       else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI, false, false, GemmArgs>), grid, dim3(512), 0, s, d);
     } else {
       if (whole) hipLaunchKernelGGL((gemm_pp_kernel<256, A_KC, B_KC, EPI, true, false, GemmArgs>), grid, dim3(512), 0, s, d);
-      else hipLaunchKernelGGL((gemm_pp_kernel<256, A_KC, B_KC, EPI, false, false, GemmArgs>), grid, dim3(512), 0, s, d);
+      else if constexpr (kCanBeRagged) hipLaunchKernelGGL((gemm_pp_kernel<256, A_KC, B_KC, EPI, false, false, GemmArgs>), grid, dim3(512), 0, s, d);
     }
     OASES_LAUNCH_CHECK("gemm_pp_kernel");
     return 0;
@@ -2680,7 +2694,7 @@ int launch_gemm_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const v
 static bool tn_group_fits(int variant, int K, int M0, int N0, int M1, int N1, size_t ws_bytes) {
   if (variant == 401064064 || variant == 401064128) return true;
   const int S = variant / 1000000 % 100;
-  if (variant != 300128256 + S * 1000000 || (S != 1 && S != 2 && S != 4 && S != 8) || !(K % BKR == 0 || K >= 1024)) return false;
+  if (variant != 300128256 + S * 1000000 || (S != 1 && S != 2 && S != 4 && S != 8) || (K % BKR && (S > 1 || K < 1024))) return false;
   const long T = (long)((M0 + 127) / 128) * ((N0 + 255) / 256) + (long)((M1 + 127) / 128) * ((N1 + 255) / 256);
   return S == 1 || (T <= kSliceCounters && (long)(S - 1) * st_k_per(K, S) < K && (size_t)T * S * 128 * 256 * 4 <= ws_bytes);  // every slice has stages of its own
 }
@@ -2697,15 +2711,15 @@ static double tn_single_seconds(int M, int N, int K, size_t ws_bytes) {
 // (two slices); 4096 rows, 1024x1024 twice 34 to 48 + 5 -> 34 (64x128; four slices of 128x256 38 + 5, 64x64 36), 256x1024 and 1024x768 32 + 5 -> 23 (64x64; 64x128 33); 2048
 // rows, the same 21 + 4 -> 20 and 19 + 4 -> 13.5; 512 rows, 1024x512 twice 11.4 + 2.4 -> 7.3 (64x64; 64x128 9.4); 128 rows, 12288x6144 and 6144x12288
 // 282 + 5 -> 272.  8192 rows, 1376x4096 and 4096x2752 stay two (118 and 173; by themselves 268 together, one launch 290).
-int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes, bool* wins) {
+int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes, bool bias, bool* wins) {
   const double out = ((double)M0 * N0 + (double)M1 * N1) * 8.0;
   double best_t = 1e30;
   int best = 0;
   const long T = (long)((M0 + 127) / 128) * ((N0 + 255) / 256) + (long)((M1 + 127) / 128) * ((N1 + 255) / 256);
   for (int S = 1; S <= 8; S *= 2) {
     const int v = 300128256 + S * 1000000;
-    if (!tn_group_fits(v, K, M0, N0, M1, N1, ws_bytes)) continue;
-    const double t = 4.0e-6 + pp_seconds(128, T * S, st_k_per(K, S), out) + (S > 1 ? 2.0e-6 + 2.7e-6 * S : 0.0);  // 4 us: the bias gradient's own launch
+    if (K % BKR || !tn_group_fits(v, K, M0, N0, M1, N1, ws_bytes)) continue;
+    const double t = pp_seconds(128, T * S, st_k_per(K, S), out) + (S > 1 ? 2.0e-6 + 2.7e-6 * S : 0.0);
     if (t < best_t) { best_t = t; best = v; }
   }
   for (int bn = 64; bn <= 128; bn += 64) {
@@ -2714,6 +2728,9 @@ int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes
     if (t < best_t) { best_t = t; best = 401064000 + bn; }
   }
   if (wins) *wins = gemm_span_fits(K, std::max({M0, N0, M1, N1})) && best_t < tn_single_seconds(M0, N0, K, ws_bytes) + tn_single_seconds(M1, N1, K, ws_bytes);
+  // rows that are no whole number of stages: the same sums on the eight-wave kernel (same_sums).  Not where the small tiles bring a bias gradient: the launch that
+  // it would need instead rounds a fifth more (rms against 64 bits, 3960 rows 3.8e-8 and 4.6e-8)
+  if (!bias && best / 100000000 == 4 && K % BKR && T >= kPpLeastTiles && tn_group_fits(301128256, K, M0, N0, M1, N1, ws_bytes) && pp128_seconds(T, K, out) < best_t) best = 301128256;
   return best;
 }
 
@@ -2728,7 +2745,7 @@ int launch_gemm_tn_group(int variant, int K, const TnProblem& a, const TnProblem
     if (!p->A || !p->B || !p->C) { set_error("gemm_tn_group: NULL operand"); return OASES_ENULL; }
     if (!aligned16(p->A) || !aligned16(p->B) || !aligned16(p->C)) { set_error("gemm_tn_group: operand not 16-byte aligned"); return OASES_EALIGN; }
   }
-  if (!variant) variant = gemm_tn_group_variant(K, a.M, a.N, b.M, b.N, ws && counters ? ws_bytes : 0);
+  if (!variant) variant = gemm_tn_group_variant(K, a.M, a.N, b.M, b.N, ws && counters ? ws_bytes : 0, a.colsum || b.colsum);
   if (!tn_group_fits(variant, K, a.M, a.N, b.M, b.N, ws && counters ? ws_bytes : 0)) {
     set_error("gemm_tn_group: variant %d does not exist or does not fit K=%d, %dx%d and %dx%d with %zu workspace bytes", variant, K, a.M, a.N, b.M, b.N, ws_bytes);
     return OASES_EINVAL;
@@ -2764,7 +2781,10 @@ int launch_gemm_tn_group(int variant, int K, const TnProblem& a, const TnProblem
 int gemm_variant(int op, int epi, int M, int N, int K, size_t ws_bytes, bool pass) {
   const int kind = op == OASES_GEMM_TN ? 2 : op == OASES_GEMM_NT ? 1 : (epi == EPI_BIAS_GELU || epi == EPI_SWIGLU) ? 3 : 0;
   if (epi == EPI_SWIGLU || epi == EPI_DSWIGLU) ws_bytes = 0;
-  return encode_variant(pick_tile(kind, op == OASES_GEMM_TN ? EPI_ACC_F32 : epi, M, N, K, ws_bytes, nullptr, pass));
+  if (op == OASES_GEMM_TN) epi = EPI_ACC_F32;
+  double seconds;
+  const TileChoice t = pick_tile(kind, epi, M, N, K, ws_bytes, &seconds, pass);
+  return encode_variant(same_sums(t, seconds, kind, M, N, K));
 }
 
 int launch_gemm(int op, int epi, int M, int N, int K, const void* A, int lda, const void* B, int ldb, void* C,

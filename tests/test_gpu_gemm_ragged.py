@@ -1,6 +1,6 @@
-"""Products whose rows are no whole tiles of the eight-wave kernels: k-major operands that end inside a 256-row tile, and weight gradients over a number of
-rows that is no whole number of k tiles (the last tile of a wave group partly or wholly beyond K, with and without k slices, alone and two in a
-launch).  The library's choice goes to those kernels here; memory behind the operands holds NaN."""
+"""Products whose rows are no whole tiles of the eight-wave kernels: k-major operands that end inside a tile, and weight gradients over a number of
+rows that is no whole number of k tiles (the last tile of a wave group partly or wholly beyond K, alone and two in a launch) or of slices.
+The library's choice goes to those kernels here; memory behind the operands holds NaN."""
 import pytest
 import torch
 
@@ -12,9 +12,11 @@ pytestmark = pytest.mark.gpu
 WS = 256 << 20
 
 
-@pytest.mark.parametrize("op,M,N,K,variant", [("NN", 6072, 4096, 448, 301256256), ("NT", 6072, 4096, 448, 301256256), ("NT", 4088, 4088, 256, 301256256),
-                                                               ("TN", 1032, 4104, 1064, 301128256), ("TN", 2048, 4096, 2056, 301128256), ("TN", 2048, 4096, 2040, 301128256),
-                                                               ("TN", 4096, 4096, 1048, 301256256), ("TN", 4096, 4088, 1080, 301256256), ("TN", 4088, 4096, 1992, 301256256)])
+# the last two: k slices whose last one is shorter (2688 and 2624 rows; three times 1600 and 1408), added up by a second launch
+@pytest.mark.parametrize("op,M,N,K,variant", [("NN", 6072, 4096, 448, 301128256), ("NT", 6072, 4096, 448, 301128256), ("NT", 4088, 4088, 256, 301128256),
+                                                               ("TN", 1160, 4104, 1064, 301128256), ("TN", 2048, 4096, 2056, 301128256), ("TN", 2048, 4096, 2040, 301128256),
+                                                               ("TN", 4096, 4096, 1048, 301128256), ("TN", 4096, 4088, 1080, 301128256), ("TN", 4088, 4096, 1992, 301128256),
+                                                               ("TN", 11160, 136, 5312, 302128256), ("TN", 80, 8632, 6208, 304128256)])
 def test_choice_of_ragged_rows(B, op, M, N, K, variant):
     """Exact products of bf16 values and fp32 sums against fp64: 1e-5; half a bf16 ulp for the bf16 output."""
     opc = {"NN": B.GEMM_NN, "NT": B.GEMM_NT, "TN": B.GEMM_TN}[op]
