@@ -93,7 +93,7 @@ def gemm_kernel_label(line, cfg, B, ws_bytes):
     tile = B.lib.oases_pass_gemm_variant({"NN": 0, "NT": 1, "TN": 2}[form], epi_id, m, n, k, ws_bytes)
     slices = tile // 1000000 % 100
     split = f"_splitk{slices}" if slices >= 2 else ""
-    wk = {0: "", 1: "_wavek2", 2: "_dtl", 3: "_pp", 4: "_st", 5: "_st"}[tile // 100000000]
+    wk = {0: "", 1: "_wavek2", 2: "_dtl", 3: "_pp", 4: "_st", 5: "_st", 6: "_pp"}[tile // 100000000]
     return f"gemm_{form}_{epi}_{tile // 1000 % 1000}x{tile % 1000}{wk}{split}"
 
 

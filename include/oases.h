@@ -314,8 +314,9 @@ int oases_op_gemm(int op, int epi, int M, int N, int K, const void *A, int lda, 
  * any M, N the GEMM accepts; no forward SwiGLU epilogue; also over 2 or 4 k slices of whole stages, 202128256 and
  * 204128256, K % (64 * slices) == 0); the 256x256 kernel takes one slice only.  W = 3 names the eight-wave forms of
  * the same tiles (two waves per SIMD that alternate between loading and multiplying): 301256256, 301128256, 302128256,
- * 304128256, on the shapes of their W = 2 counterparts; 301128256 gives bit for bit what 201128256 gives.  (The library's own choice also
- * sends x01128256 the TN form over any K from 1024 on, and its slices TN with a shorter last one; forced by name they keep to those shapes.)  W = 4 names the
+ * 304128256, on the shapes of their W = 2 counterparts; 301128256 gives bit for bit what 201128256 gives.  W = 6 names
+ * 301128256 .. 304128256 for the TN form on shapes that those refuse: 601128256 over any K from 1024 on, 602128256 and 604128256 over slices of whole stages
+ * whose last one is shorter (K % 64 == 0, K >= 1024 * slices).  W = 4 names the
  * small-tile kernels 64x64 and 64x128 (401064064, 401064128; direct-to-LDS loads, waves split k, any shape the GEMM
  * accepts, up to 16 slices of whole 64-wide stages; the forward SwiGLU epilogue on 64x128 only), W = 5 the same with 128x128 tiles
  * (501128128; chosen in passes only, see below).  The W >= 2
@@ -324,7 +325,7 @@ int oases_op_gemm(int op, int epi, int M, int N, int K, const void *A, int lda, 
  * oases_op_gemm_forced returns EINVAL for them on larger operands.
  * Host only; used to group per-operator timings by kernel. */
 int oases_op_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace_bytes);
-/* The same for a GEMM of a pass.  There the launches of the W = 3, 4 and 5 kernels add up their k slices themselves, in slice order (the same
+/* The same for a GEMM of a pass.  There the launches of the W = 3, 4, 5 and 6 kernels add up their k slices themselves, in slice order (the same
  * result bit for bit), with counters that the pass keeps at zero in its workspace, while a tile's other slices come to no more than 128 KiB of
  * partial sums, and the counters and partial sums have room; a second launch adds up the others. */
 int oases_pass_gemm_variant(int op, int epi, int M, int N, int K, size_t workspace_bytes);
@@ -333,7 +334,7 @@ int oases_pass_gemm_variant(int op, int epi, int M, int N, int K, size_t workspa
 int oases_pass_delta_variant(const oases_handle *h);
 /* oases_op_gemm on the instantiation `variant` names (encoding above) instead of the one the library would choose:
  * for tests and tuning sweeps.  EINVAL if no such instantiation exists (block tiles 256x256, 128x256, 256x128,
- * 128x128; W = 1 only with the rectangular ones; W = 2, 3 only as x01256256, x01128256, x02128256 or x04128256 on shapes they fit, W = 4 as 4SS064064 or 4SS064128, W = 5 as 5SS128128; 1..8
+ * 128x128; W = 1 only with the rectangular ones; W = 2, 3 only as x01256256, x01128256, x02128256 or x04128256 on shapes they fit, W = 6 as the last three of these, W = 4 as 4SS064064 or 4SS064128, W = 5 as 5SS128128; 1..8
  * slices, W = 4, 5: 1..16), if the slices do not fit K (every slice needs at least
  * one k column) or if the workspace is smaller than slices*M*N*4 bytes.  Results of different variants differ only
  * by the fp32 summation order. */
@@ -352,7 +353,7 @@ int oases_op_gemm_tn_pair(int K, int M0, int N0, const void *A0, int lda0, const
                           int ldc0, int M1, int N1, const void *A1, int lda1, const void *B1, int ldb1, void *C1,
                           int ldc1, void *stream);
 /* The same for any two weight gradients over the same K rows, on the kernel that `variant` names (0: the library's choice): 30S128256 =
- * eight-wave 128x256 tiles over S = 1, 2, 4 or 8 k slices (K % 64 == 0, other K by the library's choice only; any M, N the GEMM accepts), 401064064 and 401064128
+ * eight-wave 128x256 tiles over S = 1, 2, 4 or 8 k slices (K % 64 == 0; any M, N the GEMM accepts), 601128256 = the same without slices over any K from 1024 on, 401064064 and 401064128
  * = small tiles (any K).  k slices are added up, in slice order, by the launch itself: workspace holds 4096 bytes of counters (set to
  * zero by this call) and then the partial sums, slices x tiles x 128 KiB.  NULL: never split.  EINVAL, EALIGN, ENULL before
  * the product is launched.  A whole pass issues the two weight gradients of a block this way where that is expected to take less time than

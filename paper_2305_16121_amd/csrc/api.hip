@@ -1144,7 +1144,6 @@ int oases_op_gemm_tn_group(int variant, int K, int M0, int N0, const void* A0, i
   const bool room = workspace && workspace_bytes > head;
   uint32_t* counters = room ? (uint32_t*)workspace : nullptr;
   if (variant < 0) { set_error("gemm_tn_group: negative variant"); return OASES_EINVAL; }
-  if (variant / 100000000 == 3 && K % 64) { set_error("gemm_tn_group: variant %d needs whole stages of 64 k (K=%d)", variant, K); return OASES_EINVAL; }
   if (room) {
     int rc = launch_zero_counters(counters, (hipStream_t)stream);
     if (rc) return rc;

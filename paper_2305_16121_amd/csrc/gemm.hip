@@ -2245,14 +2245,14 @@ bool dtl_rect_fits(int kind, int M, int N, int K) {  // the 128 x 256 kernel red
   (void)kind;
   return M % 8 == 0 && N % 8 == 0 && K % BKR == 0 && K >= BKR;
 }
-// The eight-wave kernel also takes weight gradients over any number of rows from 1024 on: the library's choice uses that, a variant forced by a caller's name keeps
-// to the bounds above.  Fewer than 1024 rows stay on small tiles: 2560 x 5120 x 808 60 us.
+// The eight-wave kernel also takes weight gradients over any number of rows from 1024 on, which have a name of their own (W = 6): the others keep to the
+// bounds above and refuse what lies outside.  Fewer than 1024 rows stay on small tiles: 2560 x 5120 x 808 60 us.
 bool pp128_fits(int kind, int M, int N, int K) { return dtl_rect_fits(kind, M, N, K) || (kind == 2 && M % 8 == 0 && N % 8 == 0 && K % 8 == 0 && K >= 1024); }
 bool dtl_rect_whole(int M, int N, int K) { return M % 128 == 0 && N % 256 == 0 && K % BKR == 0 && K >= BKR; }
+bool rect_slices_whole(int kind, int M, int N, int K, int S) { return K % (S * BKR) == 0 && dtl_rect_fits(kind, M, N, K / S); }
 bool pp_slices_fit(int kind, int M, int N, int K, int S) {  // S k slices of whole stages; a weight gradient's last one may be shorter
   if (S == 1) return pp128_fits(kind, M, N, K);
-  if (kind == 2 && K >= 1024 * S) return dtl_rect_fits(kind, M, N, K);
-  return K % (S * BKR) == 0 && dtl_rect_fits(kind, M, N, K / S);
+  return (kind == 2 && K >= 1024 * S && dtl_rect_fits(kind, M, N, K)) || rect_slices_whole(kind, M, N, K, S);
 }
 struct KindTable { bool wave_ksplit; float r256x256, r128x256, r256x128, r128x128; };
 const KindTable g_kinds[4] = {{true, 1200.f, 1080.f, 960.f, 740.f}, {true, 1200.f, 1080.f, 960.f, 740.f},
@@ -2293,7 +2293,7 @@ TileChoice pick_large_tile(int kind, int epi, int M, int N, int K, size_t ws_byt
         K % (2 * BKR) == 0 && dtl_rect_fits(kind, M, N, K / 2) && (size_t)2 * M * N * 4 <= ws_bytes)
       best = TileChoice{128, 256, 2, true, true, true};
   } else if (best.bm == 128 && best.bn == 256 && (best.ksplit == 2 || best.ksplit == 4) && epi != EPI_SWIGLU && epi != EPI_DSWIGLU &&
-             K % (best.ksplit * BKR) == 0 && dtl_rect_fits(kind, M, N, K / best.ksplit)) {
+             rect_slices_whole(kind, M, N, K, best.ksplit)) {
     best = TileChoice{128, 256, best.ksplit, true, true, true};  // k slices of whole stages: the eight-wave kernel
   }
   return best;
@@ -2403,24 +2403,29 @@ TileChoice same_sums(const TileChoice& t, double seconds, int kind, int M, int N
   return takes ? pp : t;
 }
 
-int encode_variant(const TileChoice& t) {
-  const bool rect = t.bm != t.bn;
-  return (t.st ? (t.bm == 128 ? 500000000 : 400000000) : t.dtl ? (t.pp ? 300000000 : 200000000) : rect && t.wave_ksplit ? 100000000 : 0) + t.ksplit * 1000000 + t.bm * 1000 + t.bn;
+int encode_variant(const TileChoice& t, int kind, int M, int N, int K) {
+  const bool rect = t.bm != t.bn, any_rows = t.pp && t.bm == 128 && !rect_slices_whole(kind, M, N, K, t.ksplit);
+  return (t.st ? (t.bm == 128 ? 500000000 : 400000000) : t.dtl ? (any_rows ? 600000000 : t.pp ? 300000000 : 200000000) : rect && t.wave_ksplit ? 100000000 : 0) +
+         t.ksplit * 1000000 + t.bm * 1000 + t.bn;
 }
 // variant -> TileChoice; false if no such instantiation exists or the k slices do not fit the problem / workspace
-// pass: one that the library chose itself
-bool decode_variant(int variant, int kind, int M, int N, int K, size_t ws_bytes, TileChoice* t, bool pass = false) {
+bool decode_variant(int variant, int kind, int M, int N, int K, size_t ws_bytes, TileChoice* t) {
   if (variant <= 0) return false;
   const int wk = variant / 100000000, S = variant / 1000000 % 100, bm = variant / 1000 % 1000, bn = variant % 1000;
   const bool square = (bm == 256 && bn == 256) || (bm == 128 && bn == 128), rect = (bm == 256 && bn == 128) || (bm == 128 && bn == 256);
   if ((wk == 2 || wk == 3) && S == 1) {  // direct-to-LDS kernels (3: eight waves), one k slice
     if (bm == 256 && bn == 256 && dtl_fits(kind, M, N, K)) { *t = TileChoice{256, 256, 1, false, true, wk == 3}; return true; }
-    if (bm == 128 && bn == 256 && (wk == 3 && pass ? pp128_fits(kind, M, N, K) : dtl_rect_fits(kind, M, N, K))) { *t = TileChoice{128, 256, 1, true, true, wk == 3}; return true; }
+    if (bm == 128 && bn == 256 && dtl_rect_fits(kind, M, N, K)) { *t = TileChoice{128, 256, 1, true, true, wk == 3}; return true; }
     return false;
   }
   if ((wk == 2 || wk == 3) && bm == 128 && bn == 256 && (S == 2 || S == 4)) {  // the 128 x 256 kernels over k slices of whole stages
-    if (!(wk == 3 && pass ? pp_slices_fit(kind, M, N, K, S) : K % (S * BKR) == 0 && dtl_rect_fits(kind, M, N, K / S)) || (size_t)S * M * N * 4 > ws_bytes) return false;
+    if (!rect_slices_whole(kind, M, N, K, S) || (size_t)S * M * N * 4 > ws_bytes) return false;
     *t = TileChoice{128, 256, S, true, true, wk == 3};
+    return true;
+  }
+  if (wk == 6) {  // the eight-wave 128 x 256 kernel on weight gradients over any number of rows
+    if (kind != 2 || bm != 128 || bn != 256 || (S != 1 && S != 2 && S != 4) || !pp_slices_fit(kind, M, N, K, S) || (S > 1 && (size_t)S * M * N * 4 > ws_bytes)) return false;
+    *t = TileChoice{128, 256, S, true, true, true};
     return true;
   }
   if (wk >= 4) {  // small tiles; k slices of whole stages that all start inside K
@@ -2472,7 +2477,7 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
       }
     }
 #endif
-  } else if (!decode_variant(forced_variant, kind, g.M, g.N, g.K, ws ? ws_bytes : 0, &t, g.counters != nullptr)) {
+  } else if (!decode_variant(forced_variant, kind, g.M, g.N, g.K, ws ? ws_bytes : 0, &t)) {
     set_error("gemm: variant %d does not exist or does not fit M=%d N=%d K=%d with %zu workspace bytes", forced_variant, g.M, g.N, g.K, ws ? ws_bytes : (size_t)0);
     return OASES_EINVAL;
   } else if ((t.dtl || t.st) && !(gemm_span_fits(A_KC ? g.M : g.K, g.lda) && gemm_span_fits(B_KC ? g.N : g.K, g.ldb))) {
@@ -2627,7 +2632,7 @@ int gemm_delta_variant(int M, int N, int K, int head_dim, size_t ws_bytes) {
   double alone, t;
   pick_tile(1, EPI_BF16, M, N, K, ws_bytes, &alone, true);
   const TileChoice c = pick_tile(1, EPI_BF16, M, N, K, ws_bytes, &t, true, head_dim);
-  return c.st && t < alone + 3.0e-6 ? encode_variant(c) : 0;
+  return c.st && t < alone + 3.0e-6 ? encode_variant(c, 1, M, N, K) : 0;
 }
 int launch_gemm_delta(int variant, int M, int N, int K, const void* A, const void* B, void* C, const void* out, float* delta, int seq, int head_dim,
                       float* ws, size_t ws_bytes, uint32_t* counters, hipStream_t s) {
@@ -2690,11 +2695,12 @@ int launch_gemm_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const v
 }
 
 // Two weight gradients of a block in one launch.  Variants as those of a single GEMM: 30S128256 (here S = 1, 2, 4 or 8 slices, summed by the launch
-// itself), 401064064, 401064128.
+// itself), 601128256, 401064064, 401064128.
 static bool tn_group_fits(int variant, int K, int M0, int N0, int M1, int N1, size_t ws_bytes) {
   if (variant == 401064064 || variant == 401064128) return true;
+  if (variant == 601128256) return K >= 1024;
   const int S = variant / 1000000 % 100;
-  if (variant != 300128256 + S * 1000000 || (S != 1 && S != 2 && S != 4 && S != 8) || (K % BKR && (S > 1 || K < 1024))) return false;
+  if (variant != 300128256 + S * 1000000 || (S != 1 && S != 2 && S != 4 && S != 8) || K % BKR) return false;
   const long T = (long)((M0 + 127) / 128) * ((N0 + 255) / 256) + (long)((M1 + 127) / 128) * ((N1 + 255) / 256);
   return S == 1 || (T <= kSliceCounters && (long)(S - 1) * st_k_per(K, S) < K && (size_t)T * S * 128 * 256 * 4 <= ws_bytes);  // every slice has stages of its own
 }
@@ -2718,7 +2724,7 @@ int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes
   const long T = (long)((M0 + 127) / 128) * ((N0 + 255) / 256) + (long)((M1 + 127) / 128) * ((N1 + 255) / 256);
   for (int S = 1; S <= 8; S *= 2) {
     const int v = 300128256 + S * 1000000;
-    if (K % BKR || !tn_group_fits(v, K, M0, N0, M1, N1, ws_bytes)) continue;
+    if (!tn_group_fits(v, K, M0, N0, M1, N1, ws_bytes)) continue;
     const double t = pp_seconds(128, T * S, st_k_per(K, S), out) + (S > 1 ? 2.0e-6 + 2.7e-6 * S : 0.0);
     if (t < best_t) { best_t = t; best = v; }
   }
@@ -2730,7 +2736,7 @@ int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes
   if (wins) *wins = gemm_span_fits(K, std::max({M0, N0, M1, N1})) && best_t < tn_single_seconds(M0, N0, K, ws_bytes) + tn_single_seconds(M1, N1, K, ws_bytes);
   // rows that are no whole number of stages: the same sums on the eight-wave kernel (same_sums).  Not where the small tiles bring a bias gradient: the launch that
   // it would need instead rounds a fifth more (rms against 64 bits, 3960 rows 3.8e-8 and 4.6e-8)
-  if (!bias && best / 100000000 == 4 && K % BKR && T >= kPpLeastTiles && tn_group_fits(301128256, K, M0, N0, M1, N1, ws_bytes) && pp128_seconds(T, K, out) < best_t) best = 301128256;
+  if (!bias && best / 100000000 == 4 && K % BKR && T >= kPpLeastTiles && tn_group_fits(601128256, K, M0, N0, M1, N1, ws_bytes) && pp128_seconds(T, K, out) < best_t) best = 601128256;
   return best;
 }
 
@@ -2784,7 +2790,7 @@ int gemm_variant(int op, int epi, int M, int N, int K, size_t ws_bytes, bool pas
   if (op == OASES_GEMM_TN) epi = EPI_ACC_F32;
   double seconds;
   const TileChoice t = pick_tile(kind, epi, M, N, K, ws_bytes, &seconds, pass);
-  return encode_variant(same_sums(t, seconds, kind, M, N, K));
+  return encode_variant(same_sums(t, seconds, kind, M, N, K), kind, M, N, K);
 }
 
 int launch_gemm(int op, int epi, int M, int N, int K, const void* A, int lda, const void* B, int ldb, void* C,

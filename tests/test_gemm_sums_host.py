@@ -12,7 +12,7 @@ OP, PASS = "oases_op_gemm_variant", "oases_pass_gemm_variant"
 def chains(variant):
     """Partial sums of an element, from the kernel's name (1e8 W + 1e6 slices + 1e3 BM + BN)."""
     w, slices, bm, bn = variant // 100000000, variant // 1000000 % 100, variant // 1000 % 1000, variant % 1000
-    assert w in (0, 1, 2, 3, 4, 5)
+    assert w in (0, 1, 2, 3, 4, 5, 6)
     return slices * (1 if w == 0 or (w in (2, 3) and (bm, bn) == (256, 256)) else 2)
 
 
@@ -31,7 +31,8 @@ def test_partial_sums(B, query, op, epi, M, N, K, least):
 
 
 @pytest.mark.parametrize("query,M,N,K,variant", [
-    (OP, 6144, 3072, 7240, 301128256), (PASS, 3072, 3072, 2920, 301128256), (OP, 12336, 472, 1064, 301128256), (OP, 11544, 144, 4928, 302128256), (OP, 5728, 168, 6720, 304128256),
+    (OP, 6144, 3072, 7240, 601128256), (PASS, 3072, 3072, 2920, 601128256), (OP, 12336, 472, 1064, 601128256), (OP, 11544, 144, 4928, 602128256), (OP, 5728, 168, 6720, 604128256),
+    (OP, 5728, 168, 6656, 304128256),      # whole slices
     (PASS, 15544, 136, 1248, 501128128),   # 122 tiles of 128x256 for 256 CUs
     (PASS, 6928, 408, 1240, 501128128),    # 110
     (PASS, 2560, 5120, 1016, 401064128),   # too few rows

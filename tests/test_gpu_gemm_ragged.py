@@ -14,9 +14,9 @@ WS = 256 << 20
 
 # the last two: k slices whose last one is shorter (2688 and 2624 rows; three times 1600 and 1408), added up by a second launch
 @pytest.mark.parametrize("op,M,N,K,variant", [("NN", 6072, 4096, 448, 301128256), ("NT", 6072, 4096, 448, 301128256), ("NT", 4088, 4088, 256, 301128256),
-                                                               ("TN", 1160, 4104, 1064, 301128256), ("TN", 2048, 4096, 2056, 301128256), ("TN", 2048, 4096, 2040, 301128256),
-                                                               ("TN", 4096, 4096, 1048, 301128256), ("TN", 4096, 4088, 1080, 301128256), ("TN", 4088, 4096, 1992, 301128256),
-                                                               ("TN", 11160, 136, 5312, 302128256), ("TN", 80, 8632, 6208, 304128256)])
+                                                               ("TN", 1160, 4104, 1064, 601128256), ("TN", 2048, 4096, 2056, 601128256), ("TN", 2048, 4096, 2040, 601128256),
+                                                               ("TN", 4096, 4096, 1048, 601128256), ("TN", 4096, 4088, 1080, 601128256), ("TN", 4088, 4096, 1992, 601128256),
+                                                               ("TN", 11160, 136, 5312, 602128256), ("TN", 80, 8632, 6208, 604128256)])
 def test_choice_of_ragged_rows(B, op, M, N, K, variant):
     """Exact products of bf16 values and fp32 sums against fp64: 1e-5; half a bf16 ulp for the bf16 output."""
     opc = {"NN": B.GEMM_NN, "NT": B.GEMM_NT, "TN": B.GEMM_TN}[op]
@@ -33,6 +33,14 @@ def test_choice_of_ragged_rows(B, op, M, N, K, variant):
     c = dev(c0, torch.float32)
     run(B.EPI_F32, c)
     assert rel_err(c.cpu().double(), ref + (c0.double() if op == "TN" else 0.0)) < 1e-5
+    # the kernel that the query names can be forced, and is the one that the library takes
+    cf = dev(c0, torch.float32)
+    forced = lambda v: B.lib.oases_op_gemm_forced(v, opc, B.EPI_F32, M, N, K, ad.data_ptr(), ad.shape[1], bd.data_ptr(), bd.shape[1], cf.data_ptr(), N, None, None, 0,
+                                                  ws.data_ptr(), ws.numel(), None)
+    if op == "TN":
+        assert forced(variant - 300000000) == B.EINVAL
+    B.check(forced(variant))
+    assert torch.equal(c, cf)
     if op != "TN":
         cb = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
         run(B.EPI_BF16, cb)
@@ -66,3 +74,26 @@ def test_step_of_ragged_rows(B, seq, batch):
     for k, a, ca, b, cb in (("wqkv", "u", h, "dqkv", 3 * hp), ("wo", "attn", hp, "dz1", h), ("w1", "v2", h, "dg", fp), ("w2", "f", fp, "dz2", h)):
         ref = t(a, ca).t().contiguous() @ t(b, cb)
         assert rel_err(grads[k].double(), ref) < 2e-5, k
+
+
+@pytest.mark.parametrize("K", [1032, 1064, 2040])
+@pytest.mark.parametrize("M0,N0,M1,N1", [(256, 512, 128, 256), (136, 264, 8, 1000)])
+def test_two_in_a_launch(B, K, M0, N0, M1, N1):
+    """601128256 on two weight gradients over such rows, against the products in fp64 (the bound of the whole-stage test) and, bit for bit, each by itself."""
+    ws = torch.full((64 << 20,), 0xFF, dtype=torch.uint8, device="cuda")
+    sizes, c, old = ((M0, N0), (M1, N1)), [], []
+    ab = [(padded(randn(gen(K + i), K, M).bfloat16(), 64, 0), padded(randn(gen(M + i), K, N).bfloat16(), 64, 0)) for i, (M, N) in enumerate(sizes)]
+    args = lambda v: [v, K] + [x for i, (M, N) in enumerate(sizes) for x in (M, N, ab[i][0].data_ptr(), ab[i][0].shape[1], ab[i][1].data_ptr(), ab[i][1].shape[1], c[i].data_ptr(), N)]
+    for i, (M, N) in enumerate(sizes):
+        old.append(torch.randn(M, N, device="cuda"))
+        c.append(old[i].clone())
+    assert B.lib.oases_op_gemm_tn_group(*args(301128256), ws.data_ptr(), ws.numel(), None) == B.EINVAL
+    B.check(B.lib.oases_op_gemm_tn_group(*args(601128256), ws.data_ptr(), ws.numel(), None))
+    for i, (M, N) in enumerate(sizes):
+        a, b = ab[i]
+        ref = old[i].double() + a[:K].double().T @ b[:K].double()
+        assert float((c[i].double() - ref).abs().max()) < K * 2.0 ** -24 * 4 * K ** 0.5
+        single = old[i].clone()
+        B.check(B.lib.oases_op_gemm_forced(601128256, B.GEMM_TN, B.EPI_F32, M, N, K, a.data_ptr(), a.shape[1], b.data_ptr(), b.shape[1], single.data_ptr(), N,
+                                           None, None, 0, ws.data_ptr(), ws.numel(), None))
+        assert torch.equal(single, c[i])
