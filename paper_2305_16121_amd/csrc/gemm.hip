@@ -389,6 +389,9 @@ __device__ __forceinline__ void swap_lines(f32x4& x, f32x4& y) {
 // the 16 rows x 32 columns of C from (row0, col0), in that order of the lanes: address arithmetic in scalar registers.  (Stores that go past the caches
 // shorten a launch of few rows, 4096 x 1024 x 1024 17.1 -> 16.0 us, whose L2s have less to write back at its end, but the kernel that reads the result then pays
 // for it: steps of h 4096 1767 -> 1795 us, h 2048 forward 309 -> 316, h 12288 with 128 rows 971 -> 983, h 1024 606 -> 601.)
+// 32-bit offsets within the 16 rows: leading dimensions up to kLdcOfLines; the forms that check their bounds (FULL false) take any.
+constexpr int kLdcOfLines = 32 << 20;
+static_assert(15ll * kLdcOfLines * 4 + 32 * 4 <= 0x7fffffff, "offsets of the 16 rows");
 struct LinesOfC {
   __amdgpu_buffer_rsrc_t rs;
   int at, pitch;
@@ -2078,7 +2081,7 @@ __device__ __forceinline__ void st_tile(const G& g, int pid, char* lds, const Sl
   } else {
     if (wk == 0) gather(H0{}); else gather(H1{});
   }
-  if (m0 + BM <= g.M && n0 + BN <= g.N) finish(std::true_type{}); else finish(std::false_type{});
+  if (m0 + BM <= g.M && n0 + BN <= g.N && (!epi_rows(EPI) || g.ldc <= kLdcOfLines)) finish(std::true_type{}); else finish(std::false_type{});
   // The sums of a row, in the order of 32x32 accumulators: in each of 32 columns the four chains of columns 16 H + 4 b ..+3, +8 (H, b = 0, 1), which run on
   // through the wave's parts of 32; then both b, both H and both waves of a head (which hold its column parts, one each where a head is 64 columns of a
   // 128-wide tile), these by way of LDS.  A lane of the upper half holds the +8 of the lane 32 below it, whose chain it goes on with.
@@ -2491,14 +2494,16 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
     set_error("gemm: the 64x64 kernel has no SwiGLU epilogue");
     return OASES_EINVAL;
   }
+  constexpr bool kLines = epi_rows(EPI);
+  if (kLines && t.pp && t.bm == 256 && A_KC && B_KC && g.ldc > kLdcOfLines) t.dtl = t.pp = false;  // no form that checks its bounds: the staged kernel of the same tile
   if (t.dtl && t.pp) {
     constexpr bool kCanBeRagged = !A_KC || !B_KC;
     const int bm = t.bm;
     GemmCall d = g;
     d.tiles_m = (g.M + bm - 1) / bm;
     d.tiles_n = (g.N + 255) / 256;
-    const bool whole = g.M % bm == 0 && g.N % 256 == 0;
-    if (!whole && bm == 256 && !kCanBeRagged) { set_error("gemm: direct-to-LDS kernel on a shape it does not cover"); return OASES_EINVAL; }
+    const bool tiles = g.M % bm == 0 && g.N % 256 == 0, whole = tiles && (!kLines || g.ldc <= kLdcOfLines);
+    if (!tiles && bm == 256 && !kCanBeRagged) { set_error("gemm: direct-to-LDS kernel on a shape it does not cover"); return OASES_EINVAL; }
     if (bm == 128 && t.ksplit > 1) {
       if constexpr (EPI == EPI_SWIGLU || EPI == EPI_DSWIGLU) {
         set_error("gemm: the SwiGLU epilogues do not run over k slices");
@@ -2519,7 +2524,7 @@ int launch_shape(const GemmCall& g, float* ws, size_t ws_bytes, int forced_varia
         p.counters = nullptr;
         p.C = ws;
         p.ldc = g.N;
-        if (whole) hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI_F32, true, false, GemmArgs>), sgrid, dim3(512), 0, s, p);
+        if (tiles && p.ldc <= kLdcOfLines) hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI_F32, true, false, GemmArgs>), sgrid, dim3(512), 0, s, p);
         else hipLaunchKernelGGL((gemm_pp_kernel<128, A_KC, B_KC, EPI_F32, false, false, GemmArgs>), sgrid, dim3(512), 0, s, p);
         OASES_LAUNCH_CHECK("gemm_pp_kernel (split-K)");
         const long n4 = (long)g.M * (g.N / 4);
@@ -2689,7 +2694,9 @@ int launch_gemm_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const v
   }
   GemmArgs g0{(const uint16_t*)A0, (const uint16_t*)B0, C0, nullptr, nullptr, M0, N0, K, lda0, ldb0, ldc0, 0, M0 / 128, N0 / 256, 1, K};
   GemmArgs g1{(const uint16_t*)A1, (const uint16_t*)B1, C1, nullptr, nullptr, M1, N1, K, lda1, ldb1, ldc1, 0, M1 / 128, N1 / 256, 1, K};
-  hipLaunchKernelGGL((gemm_pp_group_kernel<true, false>), dim3(g0.tiles_m * g0.tiles_n + g1.tiles_m * g1.tiles_n), dim3(512), 0, s, g0, g1, nullptr, nullptr);
+  const dim3 grid(g0.tiles_m * g0.tiles_n + g1.tiles_m * g1.tiles_n);
+  if (std::max(ldc0, ldc1) <= kLdcOfLines) hipLaunchKernelGGL((gemm_pp_group_kernel<true, false>), grid, dim3(512), 0, s, g0, g1, nullptr, nullptr);
+  else hipLaunchKernelGGL((gemm_pp_group_kernel<false, false>), grid, dim3(512), 0, s, g0, g1, nullptr, nullptr);
   OASES_LAUNCH_CHECK("gemm_pp_group_kernel");
   return 0;
 }
@@ -2770,7 +2777,7 @@ int launch_gemm_tn_group(int variant, int K, const TnProblem& a, const TnProblem
     OASES_LAUNCH_CHECK("gemm_st_group_kernel");
     return 0;
   }
-  const bool whole = a.M % 128 == 0 && a.N % 256 == 0 && b.M % 128 == 0 && b.N % 256 == 0;
+  const bool whole = a.M % 128 == 0 && a.N % 256 == 0 && b.M % 128 == 0 && b.N % 256 == 0 && std::max(a.ldc, b.ldc) <= kLdcOfLines;
   if (S > 1) {
     if (whole) hipLaunchKernelGGL((gemm_pp_group_kernel<true, true>), grid, dim3(512), 0, s, g0, g1, ws, counters);
     else hipLaunchKernelGGL((gemm_pp_group_kernel<false, true>), grid, dim3(512), 0, s, g0, g1, ws, counters);
