@@ -320,16 +320,6 @@ __device__ __forceinline__ void epilogue_tile(const GemmArgs& g, int row0, int c
 
 // SwiGLU: two neighbouring accumulator tiles, gate (first column col0 of the interleaved [gate 32 | up 32] layout) and up,
 // hold the same 32 columns of f, element for element
-// one lane's part: gate columns cg .. cg+3 of the interleaved [gate 32 | up 32] layout, columns cf .. cf+3 of f
-__device__ __forceinline__ void epi_swiglu(const GemmArgs& g, int row, int cg, int cf, const f32x4& gate, const f32x4& up) {
-  uint16_t* ap = g.aux + (size_t)row * g.ldaux + cg;
-  *reinterpret_cast<u32x2*>(ap) = u32x2{pack_bf16x2(gate[0], gate[1]), pack_bf16x2(gate[2], gate[3])};
-  *reinterpret_cast<u32x2*>(ap + 32) = u32x2{pack_bf16x2(up[0], up[1]), pack_bf16x2(up[2], up[3])};
-  float f[4];
-#pragma unroll
-  for (int e = 0; e < 4; e++) f[e] = silu_f(gate[e]) * up[e];
-  *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + (size_t)row * g.ldc + cf) = u32x2{pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3])};
-}
 template <bool FULL>
 __device__ __forceinline__ void epilogue_tile_swiglu(const GemmArgs& g, int row0, int col0, int lane, const f32x16& ag, const f32x16& au) {
   const int row = row0 + (lane & 31);
@@ -403,13 +393,13 @@ struct LinesOfC {
   template <bool AROUND>
   __device__ __forceinline__ void store(int row, float v) const { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, at, row * pitch, AROUND ? 2 : 0); }
 };
-// requests ahead of the first store, as epi_request: 16 rows x 32 columns from (row0, col0)
 template <bool AROUND>
 __device__ __forceinline__ void store16(uint16_t* p, const u32x2& x, const u32x2& y) {
   const u32x4_align8 v = u32x4{x[0], x[1], y[0], y[1]};
   if constexpr (AROUND) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_align8*>(p));
   else *reinterpret_cast<u32x4_align8*>(p) = v;
 }
+// requests ahead of the first store, as epi_request: 16 rows x 32 columns from (row0, col0)
 // AROUND (eight-wave kernels): a gradient that is added to and the pre-activations that are kept for the backward pass go past the caches, where they would only
 // drive out what the next kernels read.  us a step: h 4096 1769 -> 1759, h 8192 2765 -> 2752, llama h 4096 1856 -> 1847.  Not on small tiles (h 12288 with 128 rows 968 -> 979).
 template <int EPI, bool FULL, bool AROUND = false>
