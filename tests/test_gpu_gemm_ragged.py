@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from tests.test_gpu_gemm_rings import padded
-from tests.test_gpu_ops import B, gen  # noqa: F401  (fixtures)
+from tests.test_gpu_ops import B, gen, lo  # noqa: F401  (fixtures)
 from tests.util import assert_bf16_close, bf16_round, dev, randn, rel_err
 
 pytestmark = pytest.mark.gpu
@@ -48,9 +48,9 @@ def test_choice_of_ragged_rows(B, op, M, N, K, variant):
 
 
 @pytest.mark.parametrize("seq,batch", [(1032, 1), (520, 3), (680, 3), (1064, 2), (1352, 3)])
-def test_step_of_ragged_rows(B, seq, batch):
-    """A training step of a layer of 2048 over such rows: weight gradients (in one launch or two, with k slices) against the products of the pass's own
-    operands in fp64."""
+def test_step_of_ragged_rows(B, lo, seq, batch):
+    """A training step of a layer of 2048 over such rows: what the FFN products and their epilogues leave, and the weight gradients (in one launch or two), against
+    the products of the pass's own operands in fp64."""
     from paper_2305_16121_amd import binding as Bi
     cfg = dict(hidden=2048, n_heads=16, seq=seq, batch=batch, tp=2, n_sub=1, n_layers=1, causal=1, dropout_p=0.0)
     H = Bi.Handle(Bi.make_cfg(cfg, rank=1))
@@ -71,6 +71,11 @@ def test_step_of_ragged_rows(B, seq, batch):
         off, nb = H.tensor_span(name, 0)
         return ws[off:off + nb].view(torch.bfloat16).view(M, cols).double()
 
+    z = t("v2", h) @ w["w1"].double() + w["b1"].double()
+    assert_bf16_close(t("pre", fp).float(), z.cpu(), 1e-5, 2e-6 * float(z.abs().max()), "pre")
+    assert_bf16_close(t("f", fp).float(), lo.gelu_fwd(z.cpu()), 1e-4, 1e-5, "f")
+    df = t("dz2", h) @ w["w2"].double().t().contiguous()
+    assert_bf16_close(t("dg", fp).float(), (df.cpu() * lo.gelu_grad(t("pre", fp).cpu())), 1e-4, 1e-5, "dg")
     for k, a, ca, b, cb in (("wqkv", "u", h, "dqkv", 3 * hp), ("wo", "attn", hp, "dz1", h), ("w1", "v2", h, "dg", fp), ("w2", "f", fp, "dz2", h)):
         ref = t(a, ca).t().contiguous() @ t(b, cb)
         assert rel_err(grads[k].double(), ref) < 2e-5, k
