@@ -60,8 +60,11 @@ __device__ __forceinline__ f32x4 row_load4(const float* row, uint32_t off) {
 // STREAM: fp32 rows go past the caches, loads and results.  Where they come to more than the caches hold between one use and the next, keeping them only
 // drives out what the products around hand over (bf16 rows, partial sums; the bf16 results, which the next product reads at once, are kept).  us a step,
 // cached -> past the caches: 4096 rows of 1024 623 -> 612, 8192 of 2048 1001 -> 973, 8192 of 4096 1790 -> 1728 (RMSNorm 1930 -> 1844), 4096 of 8192 2739
-// -> 2693, 2048 of 1024 451 -> 440 and 532 -> 529.  Below 8 MiB an array is still in a cache when the next kernel comes: 512 rows of 512 reduction
-// point 3.60 -> 3.80, backward 4.68 -> 4.96, 600 of 1024 4.44 -> 4.56.
+// -> 2693, 2048 of 1024 451 -> 440 and 532 -> 529.  Small arrays are still in a cache when the next kernel comes: 512 rows of 512 reduction
+// point 3.60 -> 3.80, backward 4.68 -> 4.96, 600 of 1024 4.44 -> 4.56.  Where the line lies, steps of two layers, cached -> past the caches, in per cent (GPT, LLaMA, BERT; two runs of
+// one side differ by 0.1 to 1): rows of 1024, 2.3 MiB +0.2 +0.3 0.0, 4 MiB +0.5 +1.2 -0.4, 6 MiB +1.2 +2.0 -1.3, 7 MiB +1.8 +1.5 -1.2, 8 MiB +0.5 -2.6 -3.0, 10 MiB -0.3
+// -1.5 -3.3, 16 MiB -6.2 -6.8 -5.9; rows of 512, 8 MiB +0.5 +1.0 -2.5.  Wider layers, whose products take more of the caches, would gain below it too: rows of 2048,
+// 4 MiB -1.5 -2.2 -2.7, 6 MiB -2.7 -4.0 -5.8, 8 MiB -5.2 -5.2 -6.4; rows of 4096 -2.4 -3.1 -1.6, -6.1 -4.2 -6.0, -8.0 -6.6 -6.5.
 template <bool STREAM>
 __device__ __forceinline__ f32x4 stream_load4(const float* row, uint32_t off) {
   const f32x4* p = reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(row) + off);
