@@ -1265,7 +1265,7 @@ __global__ __launch_bounds__(256) void gemm_dtl_rect_kernel(GemmArgs g) {  // g:
 // accumulators through LDS after the loop.  TN: the halves are stages of their own (six), group 0 loads those of group 1 and the other way round, so
 // that a load has two iterations to arrive (4096 x 2048 x 8192 129 -> 122 us).  With a k-major operand, whose 128-byte rows hold both halves: three stages of 64 k that
 // all waves load in their memory phases (NT 4096 x 2048 x 8192 121 -> 116).
-// A row-indexed operand may end inside its tile, and so may a k-major one (pp_src).  K: whole multiples of 32 resp. 64.
+// A row-indexed operand may end inside its tile, and on 128 x 256 tiles so may a k-major one (pp_src).  K: whole multiples of 32 resp. 64, TN on 128 x 256 tiles any.
 // =================================================================================================
 // Chunk swizzles of the operand tiles that 16-row fragments are read from: 16-byte chunk c of a row lies at slot c ^ swizzle(row).
 //   Row-indexed, k rows of 256 bytes and more: one LDS cycle of the transpose read serves 32 lanes, 8 bytes each, here the k rows 0..3 and 8..11 of
@@ -2714,6 +2714,10 @@ static double tn_single_seconds(int M, int N, int K, size_t ws_bytes) {
 // (two slices); 4096 rows, 1024x1024 twice 34 to 48 + 5 -> 34 (64x128; four slices of 128x256 38 + 5, 64x64 36), 256x1024 and 1024x768 32 + 5 -> 23 (64x64; 64x128 33); 2048
 // rows, the same 21 + 4 -> 20 and 19 + 4 -> 13.5; 512 rows, 1024x512 twice 11.4 + 2.4 -> 7.3 (64x64; 64x128 9.4); 128 rows, 12288x6144 and 6144x12288
 // 282 + 5 -> 272.  8192 rows, 1376x4096 and 4096x2752 stay two (118 and 173; by themselves 268 together, one launch 290).
+// Those were taken with 32x32x16 MFMAs.  On the kernels as they are, by themselves on cold operands (with the launch that clears the counters), two launches -> one, the choice
+// first: 8192 rows, 2048x2048 twice 175 -> 149 (two slices 162, 64x128 227), 512x2048 and 2048x1536 130 -> 97 (one slice 133); 4096 rows, 1024x1024 twice 51 -> 42 (four slices
+// 42, 64x64 48), 256x1024 and 1024x768 38 -> 32 (four slices 37, 64x128 41); 2048 rows 29 -> 25 (64x64 28) and 24 -> 19 (64x128 24), 704x1024 and 1024x1408 35 -> 36 (64x128
+// 32, which adds up in half as many chains); 512 rows 10.8 -> 9.8 (64x128 11.6); 128 rows 288 -> 291 (128x256 257).  1376x4096 and 4096x2752 stay two: 332, one launch 324.
 int gemm_tn_group_variant(int K, int M0, int N0, int M1, int N1, size_t ws_bytes, bool bias, bool* wins) {
   const double out = ((double)M0 * N0 + (double)M1 * N1) * 8.0;
   double best_t = 1e30;
