@@ -102,3 +102,28 @@ def test_two_in_a_launch(B, K, M0, N0, M1, N1):
         B.check(B.lib.oases_op_gemm_forced(601128256, B.GEMM_TN, B.EPI_F32, M, N, K, a.data_ptr(), a.shape[1], b.data_ptr(), b.shape[1], single.data_ptr(), N,
                                            None, None, 0, ws.data_ptr(), ws.numel(), None))
         assert torch.equal(single, c[i])
+
+
+@pytest.mark.parametrize("op,epi,M,N,K,variants", [
+    ("NN", "EPI_F32", 520, 328, 2112, (101256128, 101128256, 401064128, 301128256)), ("NT", "EPI_F32", 264, 520, 2048, (101256128, 101128256, 401064064, 301128256)),
+    ("NN", "EPI_BIAS_BF16", 264, 264, 2048, (101256128, 301128256)), ("NT", "EPI_BF16", 136, 520, 2176, (101256128, 301128256)), ("NT", "EPI_DGELU", 520, 136, 2048, (101256128, 301128256)),
+    ("TN", "EPI_F32", 520, 328, 2048, (101256128, 301128256)), ("TN", "EPI_F32", 264, 520, 2056, (101256128, 101128256, 401064064, 401064128, 501128128, 601128256)),
+    ("TN", "EPI_F32", 136, 264, 1032, (101256128, 101128256, 401064128, 601128256)), ("TN", "EPI_F32", 136, 264, 1080, (101128256, 401064064, 601128256)),
+    ("TN", "EPI_F32", 136, 264, 2112, (102128256, 402064128, 602128256)), ("TN", "EPI_F32", 264, 136, 4224, (104128256, 404064064, 604128256))])
+def test_kernels_that_add_in_the_same_order(B, op, epi, M, N, K, variants):
+    """Kernels between which the choice may change for speed alone give the same bits (wide rows of C and aux, odd multiples of eight)."""
+    g = gen(M + N + K)
+    a, b = randn(g, M, K).bfloat16(), (randn(g, K, N) * 0.05).bfloat16()
+    ad, bd = padded(a if op != "TN" else a.t(), 0, 24), padded(b.t() if op == "NT" else b, 0, 8)
+    opc, epi = getattr(B, "GEMM_" + op), getattr(B, epi)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    bias, aux = torch.randn(N, device="cuda"), torch.randn(M, N + 4, device="cuda").bfloat16()
+    start, out = torch.randn(M, N + 4, device="cuda"), []
+    for v in variants:
+        c = start.clone() if epi == B.EPI_F32 else start.bfloat16()
+        B.check(B.lib.oases_op_gemm_forced(v, opc, epi, M, N, K, ad.data_ptr(), ad.shape[1], bd.data_ptr(), bd.shape[1], c.data_ptr(), N + 4, bias.data_ptr(),
+                                           aux.data_ptr(), N + 4, ws.data_ptr(), ws.numel(), None))
+        out.append(c)
+    for v, c in zip(variants[:-1], out):
+        assert torch.equal(c, out[-1]), v
+    assert torch.equal(out[-1][:, N:].float(), (start if epi == B.EPI_F32 else start.bfloat16())[:, N:].float()) and not torch.equal(out[-1].float(), start)
